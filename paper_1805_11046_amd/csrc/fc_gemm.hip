@@ -1,0 +1,733 @@
+// Fully connected products (Section 4: Y = X W, g_{l-1} = g_l W^T; Sections 1, 7: g_W = X^T g_l with the 16-bit copy
+// of g_l) on the int8 MFMAs, operands read where they lie: nothing is transposed or padded in memory first.
+//
+// Every product is rows x cols over a reduction:
+//   forward   rows m, cols n, reduction k:  A = X  [m][k], B = W   [k][n]
+//   dgrad     rows m, cols k, reduction n:  A = dY [m][n], B = W   [k][n]
+//   wgrad     rows k, cols n, reduction m:  A = X  [m][k], B = dY16[m][n] (two byte planes, s = 256*hi + lo + 128)
+// An operand whose reduction index is the fast one ("RF") gives a lane its 16 MFMA bytes with one 16-byte load.  An
+// operand whose reduction index is the slow one ("RS") is read as dwords, four neighbouring columns of one reduction
+// index each; 4x4 byte transposes (v_perm) turn 16 of them into the 16-byte pieces of four columns.  The columns
+// 4c .. 4c+3 of a lane group therefore go to four different MFMA tiles, and a lane ends up with four neighbouring
+// results of a row, which leave as one 16-byte store.
+//
+// Ragged sizes cost no padding and no access outside a tensor: a group of columns (rows) that would hang over the
+// edge starts at the last full group instead (its results are computed twice, with the same value), and a piece of
+// the reduction that would hang over the end starts earlier with the entries already counted masked to zero in
+// both operands.  With masked entries zero, sum (a-za)(b-zb) = sum ab - zb sum a - za sum b + red za zb holds
+// for the real reduction length.
+//
+// Two kernels (times: back to back on one MI355X, M x N x K, against the general kernel that served every FC call before):
+//   fc_direct  operands go from memory to registers, no LDS in the main loop; the wavefronts of a workgroup share a
+//              tile of 32x64 (wgrad 64x64) results and split its reduction, or own a tile each.  Bound by latency
+//              (launch, one or two dependent loads, the fold through LDS): 64x128x256 takes 3.5 / 3.5 / 8.0 us for
+//              forward / dgrad / wgrad (18.7 / 12.2 / 8.0 before), 256x1000x512 4.4 / 5.0 / 6.6 (23.9 / 15.8 / 19.7),
+//              512x2048x2048 10.5 / 14.7 / 19.
+//   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  Bound by
+//              the operand bytes a compute unit gets from L2 (about 17 per clock: 540 MB in 60 us for 2048x4096x4096,
+//              MFMA pipe 22% busy): 67 / 57 / 113 us at that size (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s.
+// Measured and dropped: prefetching the next K-step in fc_direct (more registers, fewer wavefronts: 7.5 -> 8.4 us at
+// 1024^3), RS operands through LDS and the transposing reads ds_read_b64_tr_b8 / _b16 with 32x32x32 MFMAs (half the
+// instructions, same time: neither kernel is bound by instruction issue).
+#include "q8t_common.h"
+#include "q8t_internal.h"
+#include "gemm_core.h"
+
+namespace {
+
+using q8t_gemm::swz;
+using q8t_gemm::v4i;
+
+enum { FWD = 0, DGRAD = 1, WGRAD = 2 };
+
+struct FcArgs {
+    const int8_t *a;
+    const void *b;
+    const q8t_qparams *qa, *qb;
+    int rows, cols, red;
+    int lda, ldb;        // elements between neighbours along the slow index
+    float *out;          // nullable
+    void *acc;           // nullable: int32 (forward, dgrad) or int64 (wgrad)
+    int vec;             // float results leave in 16-byte stores
+    int tn, tiles;       // column tiles, all tiles
+};
+
+__device__ __forceinline__ uint4 ld16(const void *p)
+{
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+__device__ __forceinline__ uint2 ld8(const void *p)
+{
+    uint2 v;
+    __builtin_memcpy(&v, p, 8);
+    return v;
+}
+__device__ __forceinline__ uint32_t ld4(const void *p)
+{
+    uint32_t v;
+    __builtin_memcpy(&v, p, 4);
+    return v;
+}
+__device__ __forceinline__ int dot4_ones(uint32_t v, int acc) { return __builtin_amdgcn_sdot4((int)v, 0x01010101, acc, false); }
+
+// in[i] = columns 0..3 of reduction index i; out[j] = reduction indices 0..3 of column j
+__device__ __forceinline__ void transpose4x4(uint32_t i0, uint32_t i1, uint32_t i2, uint32_t i3, uint32_t (&out)[4])
+{
+    const uint32_t t0 = __builtin_amdgcn_perm(i1, i0, 0x05010400);
+    const uint32_t t1 = __builtin_amdgcn_perm(i1, i0, 0x07030602);
+    const uint32_t t2 = __builtin_amdgcn_perm(i3, i2, 0x05010400);
+    const uint32_t t3 = __builtin_amdgcn_perm(i3, i2, 0x07030602);
+    out[0] = __builtin_amdgcn_perm(t2, t0, 0x05040100);
+    out[1] = __builtin_amdgcn_perm(t2, t0, 0x07060302);
+    out[2] = __builtin_amdgcn_perm(t3, t1, 0x05040100);
+    out[3] = __builtin_amdgcn_perm(t3, t1, 0x07060302);
+}
+// high / (re-centred) low bytes of four 16-bit codes
+__device__ __forceinline__ uint32_t hi_bytes(const uint2 &v) { return __builtin_amdgcn_perm(v.y, v.x, 0x07050301); }
+__device__ __forceinline__ uint32_t lo_bytes(const uint2 &v) { return __builtin_amdgcn_perm(v.y, v.x, 0x06040200) ^ 0x80808080u; }
+
+// bytes first .. first+3 of a piece whose first `skip` bytes are masked out
+__device__ __forceinline__ uint32_t keep_mask(int first, int skip)
+{
+    const int n = min(max(skip - first, 0), 4);
+    return n == 4 ? 0u : 0xFFFFFFFFu << (8 * n);
+}
+
+struct Zero {
+    int za, zb;
+    float sc;
+};
+__device__ __forceinline__ Zero zero_points(const FcArgs &p)
+{
+    Zero z;
+    z.za = p.qa->zero_point - (1 << (p.qa->bits - 1));
+    z.zb = p.qb->zero_point - (1 << (p.qb->bits - 1));
+    z.sc = p.qa->scale * p.qb->scale;
+    return z;
+}
+
+// four neighbouring results of one row; v[j] the accumulators, rs / cs the byte sums of the row and the columns
+// (wgrad: cs = 256 * sum hi + sum lo)
+template <int WHICH>
+__device__ __forceinline__ void finish4(const FcArgs &p, const Zero &z, int row, int col, const int (&hi)[4], const int (&lo)[4],
+                                        int rs, const int (&cs)[4], const int (&cs1)[4])
+{
+    const int64_t o = (int64_t)row * p.cols + col;
+    float f[4];
+    if (WHICH != WGRAD) {
+        const uint32_t kzz = (uint32_t)p.red * (uint32_t)z.za * (uint32_t)z.zb - (uint32_t)z.zb * (uint32_t)rs;
+        int c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c[j] = (int)((uint32_t)hi[j] + kzz - (uint32_t)z.za * (uint32_t)cs[j]);   // fits 32 bits by contract
+            f[j] = z.sc * (float)c[j];
+        }
+        if (p.acc) {
+            int32_t *d = (int32_t *)p.acc + o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = c[j];
+        }
+    } else {
+        const int64_t t = (int64_t)(128 - z.zb) * rs + (int64_t)p.red * z.za * (z.zb - 128);
+        int64_t c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c[j] = 256 * (int64_t)hi[j] + lo[j] + t - (int64_t)z.za * (256 * (int64_t)cs[j] + cs1[j]);
+            f[j] = (float)((double)c[j] * (double)z.sc);
+        }
+        if (p.acc) {
+            int64_t *d = (int64_t *)p.acc + o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = c[j];
+        }
+    }
+    if (p.out) {
+        float *d = p.out + o;
+        if (p.vec) {
+            *reinterpret_cast<float4 *>(d) = make_float4(f[0], f[1], f[2], f[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = f[j];
+        }
+    }
+}
+
+// ---- small products: no LDS in the main loop ---------------------------------------------------------------------
+// KS wavefronts share a tile's reduction (K-steps of 64, dealt out round-robin); WAVES / KS tiles per workgroup.
+template <int WHICH, int WAVES, int KS>
+__global__ __launch_bounds__(WAVES * 64) void fc_direct(const FcArgs p)
+{
+    constexpr bool RSA = WHICH == WGRAD, RSB = WHICH != DGRAD;
+    constexpr int PL = WHICH == WGRAD ? 2 : 1;
+    constexpr int MT = RSA ? 4 : 2, TR = MT * 16;     // rows of a tile
+    constexpr int UNITS = MT * 4;                     // (mt, j): a lane's groups of four results
+    constexpr int TPB = WAVES / KS;
+    __shared__ int s_rs[TPB][TR], s_cs[TPB][PL][64];
+    __shared__ __attribute__((aligned(16))) int s_acc[KS > 1 ? WAVES * UNITS * 256 : 4];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kb = lane >> 4;
+    const int sub = wave / KS, ks = wave % KS;
+    for (int i = tid; i < TPB * TR; i += WAVES * 64) (&s_rs[0][0])[i] = 0;
+    for (int i = tid; i < TPB * PL * 64; i += WAVES * 64) (&s_cs[0][0][0])[i] = 0;
+    __syncthreads();
+    const int tile = min((int)blockIdx.x * TPB + sub, p.tiles - 1);   // a surplus wavefront repeats the last tile
+    const int m0 = (tile / p.tn) * TR, n0 = (tile % p.tn) * 64;
+
+    // rows / columns of the lane's pieces
+    const int8_t *pa[MT];
+    if (RSA) {
+        pa[0] = p.a + min(m0 + 4 * l16, p.rows - 4);
+    } else {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) pa[i] = p.a + (int64_t)min(m0 + i * 16 + l16, p.rows - 1) * p.lda;
+    }
+    const int col0 = min(n0 + 4 * l16, p.cols - 4);   // the lane's four columns, RF and RS alike
+    const int8_t *pb8 = (const int8_t *)p.b;
+    const int16_t *pb16 = (const int16_t *)p.b;
+
+    v4i acc[PL][MT][4];
+    int sa[MT], sb[PL][4];
+#pragma unroll
+    for (int h = 0; h < PL; ++h)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sb[h][j] = 0;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[h][i][j] = (v4i){0, 0, 0, 0};
+        }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) sa[i] = 0;
+
+    const int steps = (p.red + 63) >> 6;
+    for (int s = ks; s < steps; s += KS) {
+        const int kk = s * 64 + kb * 16, k1 = min(kk, p.red - 16), skip = kk - k1;
+        uint4 af[MT], bf[PL][4];
+        uint32_t ra[RSA ? 16 : 1], rb[RSB && PL == 1 ? 16 : 1];
+        uint2 rb16[PL == 2 ? 16 : 1];
+        // all loads of the step first
+        if (RSA) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) ra[i] = ld4(pa[0] + (int64_t)(k1 + i) * p.lda);
+        } else {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) af[i] = ld16(pa[i] + k1);
+        }
+        if (PL == 2) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) rb16[i] = ld8(pb16 + (int64_t)(k1 + i) * p.ldb + col0);
+        } else if (RSB) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) rb[i] = ld4(pb8 + (int64_t)(k1 + i) * p.ldb + col0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bf[0][j] = ld16(pb8 + (int64_t)(col0 + j) * p.ldb + k1);
+        }
+        if (RSA) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t o[4];
+                transpose4x4(ra[4 * d], ra[4 * d + 1], ra[4 * d + 2], ra[4 * d + 3], o);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) (&af[i].x)[d] = o[i];
+            }
+        }
+        if (PL == 2) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t o[4];
+                transpose4x4(hi_bytes(rb16[4 * d]), hi_bytes(rb16[4 * d + 1]), hi_bytes(rb16[4 * d + 2]), hi_bytes(rb16[4 * d + 3]), o);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) (&bf[0][j].x)[d] = o[j];
+                transpose4x4(lo_bytes(rb16[4 * d]), lo_bytes(rb16[4 * d + 1]), lo_bytes(rb16[4 * d + 2]), lo_bytes(rb16[4 * d + 3]), o);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) (&bf[PL - 1][j].x)[d] = o[j];
+            }
+        } else if (RSB) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t o[4];
+                transpose4x4(rb[4 * d], rb[4 * d + 1], rb[4 * d + 2], rb[4 * d + 3], o);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) (&bf[0][j].x)[d] = o[j];
+            }
+        }
+        if (s == steps - 1) {   // the piece that reaches back over counted entries
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t m = keep_mask(4 * d, skip);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) (&af[i].x)[d] &= m;
+#pragma unroll
+                for (int h = 0; h < PL; ++h)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) (&bf[h][j].x)[d] &= m;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) sa[i] = dot4_ones((&af[i].x)[d], sa[i]);
+#pragma unroll
+            for (int h = 0; h < PL; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sb[h][j] = dot4_ones((&bf[h][j].x)[d], sb[h][j]);
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int h = 0; h < PL; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[h][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        (v4i){(int)af[i].x, (int)af[i].y, (int)af[i].z, (int)af[i].w},
+                        (v4i){(int)bf[h][j].x, (int)bf[h][j].y, (int)bf[h][j].z, (int)bf[h][j].w}, acc[h][i][j], 0, 0, 0);
+    }
+    // byte sums of the tile's rows and columns (index inside an MFMA tile, tile)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) atomicAdd(&s_rs[sub][i * 16 + l16], sa[i]);
+#pragma unroll
+    for (int h = 0; h < PL; ++h)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) atomicAdd(&s_cs[sub][h][j * 16 + l16], sb[h][j]);
+
+    const Zero z = zero_points(p);
+    const bool col_ok = n0 + 4 * l16 < p.cols;
+    // results of unit u = (i, r): row idx 4*kb + r of MFMA row tile i, the lane's four columns
+    auto row_of = [&](int i, int r, bool &ok) {
+        const int idx = kb * 4 + r;
+        if (RSA) {
+            ok = m0 + 4 * idx < p.rows;
+            return min(m0 + 4 * idx, p.rows - 4) + i;
+        }
+        ok = m0 + i * 16 + idx < p.rows;
+        return m0 + i * 16 + idx;
+    };
+    if (KS == 1) {
+        __syncthreads();
+        int cs[4], cs1[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            cs[j] = s_cs[sub][0][j * 16 + l16];
+            cs1[j] = s_cs[sub][PL - 1][j * 16 + l16];
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                bool ok;
+                const int row = row_of(i, r, ok);
+                int hi[4], lo[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    hi[j] = acc[0][i][j][r];
+                    lo[j] = acc[PL - 1][i][j][r];
+                }
+                if (ok && col_ok) finish4<WHICH>(p, z, row, col0, hi, lo, s_rs[sub][i * 16 + kb * 4 + r], cs, cs1);
+            }
+    } else {
+        // every wavefront leaves its partial tile in LDS and folds its share of the units
+        constexpr int SHARE = UNITS / KS;
+        int sum[PL][SHARE][4];
+#pragma unroll
+        for (int h = 0; h < PL; ++h) {
+            if (h) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    *reinterpret_cast<int4 *>(&s_acc[((wave * UNITS + i * 4 + r) * 64 + lane) * 4]) =
+                        make_int4(acc[h][i][0][r], acc[h][i][1][r], acc[h][i][2][r], acc[h][i][3][r]);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < SHARE; ++u) {
+                int4 t = make_int4(0, 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    const int4 v = *reinterpret_cast<const int4 *>(&s_acc[(((sub * KS + k) * UNITS + ks * SHARE + u) * 64 + lane) * 4]);
+                    t.x += v.x;
+                    t.y += v.y;
+                    t.z += v.z;
+                    t.w += v.w;
+                }
+                sum[h][u][0] = t.x;
+                sum[h][u][1] = t.y;
+                sum[h][u][2] = t.z;
+                sum[h][u][3] = t.w;
+            }
+        }
+        int cs[4], cs1[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            cs[j] = s_cs[sub][0][j * 16 + l16];
+            cs1[j] = s_cs[sub][PL - 1][j * 16 + l16];
+        }
+#pragma unroll
+        for (int u = 0; u < SHARE; ++u) {
+            const int unit = ks * SHARE + u, i = unit >> 2, r = unit & 3;
+            bool ok;
+            const int row = row_of(i, r, ok);
+            if (ok && col_ok) finish4<WHICH>(p, z, row, col0, sum[0][u], sum[PL - 1][u], s_rs[sub][i * 16 + kb * 4 + r], cs, cs1);
+        }
+    }
+}
+
+// ---- large products: 128x128 tiles through LDS --------------------------------------------------------------------
+constexpr int BM = 128, BN = 128, TT = 256;
+
+// A staged operand of 128 rows (its rows or columns) x 64 reduction indices.  LDS row of (group c of four, member j):
+// (c / 16) * 64 + j * 16 + c % 16, so that MFMA tile j of a 64-row block holds the j-th members of 16 groups.
+__device__ __forceinline__ int lds_row_member(int lr) { return ((lr >> 6) * 16 + (lr & 15)) * 4 + ((lr >> 4) & 3); }
+
+template <int KIND>   // 0: RF int8, 1: RS int8, 2: RS int16 (two planes)
+struct Stage;
+
+template <>
+struct Stage<0> {
+    const int8_t *p0, *p1;
+    uint4 v[2][2];   // [register set][row]
+    int s[2];
+    int q;
+    // grouped: the columns of dgrad, whose LDS rows follow the member order; plain: the rows of A
+    __device__ __forceinline__ void init(const void *base, int ld, int first, int count, bool grouped)
+    {
+        const int ar = threadIdx.x >> 2;
+        q = threadIdx.x & 3;
+        int r0 = first + ar, r1 = first + ar + 64;
+        if (grouped) {
+            const int g0 = lds_row_member(ar), g1 = lds_row_member(ar + 64);
+            r0 = min(first + (g0 & ~3), count - 4) + (g0 & 3);
+            r1 = min(first + (g1 & ~3), count - 4) + (g1 & 3);
+        } else {
+            r0 = min(r0, count - 1);
+            r1 = min(r1, count - 1);
+        }
+        p0 = (const int8_t *)base + (int64_t)r0 * ld + q * 16;
+        p1 = (const int8_t *)base + (int64_t)r1 * ld + q * 16;
+        s[0] = s[1] = 0;
+    }
+    template <int SET>
+    __device__ __forceinline__ void load(int k0)
+    {
+        v[SET][0] = ld16(p0 + k0);
+        v[SET][1] = ld16(p1 + k0);
+    }
+    template <int SET>
+    __device__ __forceinline__ void store(int8_t *lds, int skip)
+    {
+        const int ar = threadIdx.x >> 2;
+        uint4 t[2] = {v[SET][0], v[SET][1]};
+        if (skip > 0) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t m = keep_mask(q * 16 + 4 * d, skip);
+                (&t[0].x)[d] &= m;
+                (&t[1].x)[d] &= m;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            s[0] = dot4_ones((&t[0].x)[d], s[0]);
+            s[1] = dot4_ones((&t[1].x)[d], s[1]);
+        }
+        int8_t *o = lds + ar * 64 + ((q ^ swz(ar)) * 16);
+        *reinterpret_cast<uint4 *>(o) = t[0];
+        *reinterpret_cast<uint4 *>(o + 64 * 64) = t[1];
+    }
+    __device__ __forceinline__ void sums(int *out)
+    {
+        const int ar = threadIdx.x >> 2;
+        atomicAdd(&out[ar], s[0]);
+        atomicAdd(&out[ar + 64], s[1]);
+    }
+};
+
+// a thread holds 8 reduction indices of one group of four columns
+template <>
+struct Stage<1> {
+    const int8_t *base;
+    int ld;
+    uint32_t voff;
+    uint32_t v[2][8];
+    int s[4];
+    __device__ __forceinline__ void init(const void *b, int ld_, int first, int count, bool)
+    {
+        base = (const int8_t *)b;
+        ld = ld_;
+        const int c = threadIdx.x & 31, k8 = threadIdx.x >> 5;
+        voff = (uint32_t)(min(first + 4 * c, count - 4)) + (uint32_t)(k8 * 8) * (uint32_t)ld;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] = 0;
+    }
+    template <int SET>
+    __device__ __forceinline__ void load(int k0)
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[SET][i] = ld4(base + (int64_t)(k0 + i) * ld + voff);
+    }
+    __device__ __forceinline__ static void put(int8_t *lds, int c, int k8, int j, uint32_t lo, uint32_t hi)
+    {
+        const int r = (c >> 4) * 64 + j * 16 + (c & 15);
+        *reinterpret_cast<uint2 *>(lds + r * 64 + (((k8 >> 1) ^ swz(r)) * 16) + (k8 & 1) * 8) = make_uint2(lo, hi);
+    }
+    template <int SET>
+    __device__ __forceinline__ void store(int8_t *lds, int skip)
+    {
+        const int c = threadIdx.x & 31, k8 = threadIdx.x >> 5;
+        uint32_t a[4], b[4];
+        transpose4x4(v[SET][0], v[SET][1], v[SET][2], v[SET][3], a);
+        transpose4x4(v[SET][4], v[SET][5], v[SET][6], v[SET][7], b);
+        if (skip > 0) {
+            const uint32_t ma = keep_mask(k8 * 8, skip), mb = keep_mask(k8 * 8 + 4, skip);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                a[j] &= ma;
+                b[j] &= mb;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            s[j] = dot4_ones(a[j], dot4_ones(b[j], s[j]));
+            put(lds, c, k8, j, a[j], b[j]);
+        }
+    }
+    __device__ __forceinline__ void sums(int *out)
+    {
+        const int c = threadIdx.x & 31;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) atomicAdd(&out[(c >> 4) * 64 + j * 16 + (c & 15)], s[j]);
+    }
+};
+
+template <>
+struct Stage<2> {
+    const int16_t *base;
+    int ld;
+    uint32_t voff;   // elements
+    uint2 v[2][8];
+    int s[2][4];
+    __device__ __forceinline__ void init(const void *b, int ld_, int first, int count, bool)
+    {
+        base = (const int16_t *)b;
+        ld = ld_;
+        const int c = threadIdx.x & 31, k8 = threadIdx.x >> 5;
+        voff = (uint32_t)(min(first + 4 * c, count - 4)) + (uint32_t)(k8 * 8) * (uint32_t)ld;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[0][j] = s[1][j] = 0;
+    }
+    template <int SET>
+    __device__ __forceinline__ void load(int k0)
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[SET][i] = ld8(base + (int64_t)(k0 + i) * ld + voff);
+    }
+    template <int SET>
+    __device__ __forceinline__ void store(int8_t *lds, int skip)
+    {
+        const int c = threadIdx.x & 31, k8 = threadIdx.x >> 5;
+        const uint32_t ma = keep_mask(k8 * 8, skip), mb = keep_mask(k8 * 8 + 4, skip);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint32_t t[8], a[4], b[4];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = h ? lo_bytes(v[SET][i]) : hi_bytes(v[SET][i]);
+            transpose4x4(t[0], t[1], t[2], t[3], a);
+            transpose4x4(t[4], t[5], t[6], t[7], b);
+            if (skip > 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    a[j] &= ma;
+                    b[j] &= mb;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                s[h][j] = dot4_ones(a[j], dot4_ones(b[j], s[h][j]));
+                Stage<1>::put(lds + h * BN * 64, c, k8, j, a[j], b[j]);
+            }
+        }
+    }
+    __device__ __forceinline__ void sums(int *out)
+    {
+        const int c = threadIdx.x & 31;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) atomicAdd(&out[h * BN + (c >> 4) * 64 + j * 16 + (c & 15)], s[h][j]);
+    }
+};
+
+template <int WHICH>
+__global__ __launch_bounds__(TT, 2) void fc_tile(const FcArgs p)
+{
+    constexpr int PL = WHICH == WGRAD ? 2 : 1;
+    constexpr int KA = WHICH == WGRAD ? 1 : 0, KB = WHICH == FWD ? 1 : (WHICH == DGRAD ? 0 : 2);
+    constexpr int A_BYTES = BM * 64, B_BYTES = PL * BN * 64;
+    __shared__ __attribute__((aligned(16))) int8_t sA[2 * A_BYTES], sB[2 * B_BYTES];
+    __shared__ int s_rs[BM], s_cs[PL * BN];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kb = lane >> 4;
+    const int lg = q8t_gemm::xcd_logical(blockIdx.x, p.tiles);
+    if (lg >= p.tiles) return;
+    // tiles in blocks of 8 rows of tiles: the tiles an XCD works on at a time share both operands
+    const int tm = p.tiles / p.tn, per = 8 * p.tn, blk = lg / per, in = lg - blk * per;
+    const int bh = min(8, tm - blk * 8);
+    const int m0 = (blk * 8 + in % bh) * BM, n0 = (in / bh) * BN;
+    for (int i = tid; i < BM; i += TT) s_rs[i] = 0;
+    for (int i = tid; i < PL * BN; i += TT) s_cs[i] = 0;
+
+    Stage<KA> sta;
+    Stage<KB> stb;
+    sta.init(p.a, p.lda, m0, p.rows, false);
+    stb.init(p.b, p.ldb, n0, p.cols, true);
+
+    v4i acc[PL][4][4];
+#pragma unroll
+    for (int h = 0; h < PL; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[h][i][j] = (v4i){0, 0, 0, 0};
+
+    const int steps = (p.red + 63) >> 6;
+    const int last0 = p.red - 64, over = steps * 64 - p.red;   // the last step reaches back over `over` counted entries
+    auto k0_of = [&](int s) { return min(s * 64, last0); };
+    auto skip_of = [&](int s) { return s < steps - 1 ? 0 : (s == steps - 1 ? over : 64); };
+    const int ra = (wave & 1) * 64, rb = (wave >> 1) * 64;
+
+#define Q8T_FC_STEP(SET, S)                                                                                     \
+    {                                                                                                           \
+        const int8_t *a_ = sA + ((S)&1) * A_BYTES, *b_ = sB + ((S)&1) * B_BYTES;                                \
+        v4i af[4];                                                                                              \
+        _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                           \
+        {                                                                                                       \
+            const int r = ra + i * 16 + l16;                                                                    \
+            af[i] = *reinterpret_cast<const v4i *>(a_ + r * 64 + ((kb ^ swz(r)) * 16));                         \
+        }                                                                                                       \
+        _Pragma("unroll") for (int h = 0; h < PL; ++h) _Pragma("unroll") for (int j = 0; j < 4; ++j)            \
+        {                                                                                                       \
+            const int r = rb + j * 16 + l16;                                                                    \
+            const v4i bf = *reinterpret_cast<const v4i *>(b_ + h * BN * 64 + r * 64 + ((kb ^ swz(r)) * 16));    \
+            _Pragma("unroll") for (int i = 0; i < 4; ++i) acc[h][i][j] =                                        \
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(af[i], bf, acc[h][i][j], 0, 0, 0);                        \
+        }                                                                                                       \
+        sta.template store<SET>(sA + (((S) + 1) & 1) * A_BYTES, skip_of((S) + 1));                              \
+        stb.template store<SET>(sB + (((S) + 1) & 1) * B_BYTES, skip_of((S) + 1));                              \
+        sta.template load<SET>(k0_of((S) + 3));                                                                 \
+        stb.template load<SET>(k0_of((S) + 3));                                                                 \
+        q8t_lds_barrier();                                                                                      \
+    }
+    sta.template load<0>(k0_of(0));
+    stb.template load<0>(k0_of(0));
+    sta.template load<1>(k0_of(1));
+    stb.template load<1>(k0_of(1));
+    sta.template store<0>(sA, skip_of(0));
+    stb.template store<0>(sB, skip_of(0));
+    sta.template load<0>(k0_of(2));
+    stb.template load<0>(k0_of(2));
+    __syncthreads();
+    for (int s = 0; s < steps; s += 2) {
+        Q8T_FC_STEP(1, s)
+        Q8T_FC_STEP(0, s + 1)   // surplus step: staged zeros
+    }
+#undef Q8T_FC_STEP
+    sta.sums(s_rs);
+    stb.sums(s_cs);
+    __syncthreads();
+
+    const Zero z = zero_points(p);
+    const int cg = n0 + rb + 4 * l16;   // the lane's four columns: member order undone
+    const bool col_ok = cg < p.cols;
+    const int col0 = min(cg, p.cols - 4);
+    int cs[4], cs1[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        cs[j] = s_cs[rb + j * 16 + l16];
+        cs1[j] = s_cs[(PL - 1) * BN + rb + j * 16 + l16];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int idx = kb * 4 + r, lr = ra + i * 16 + idx;
+            int row = m0 + lr;
+            bool ok = row < p.rows;
+            if (KA == 1) {
+                const int g = m0 + ra + 4 * idx;
+                ok = g < p.rows;
+                row = min(g, p.rows - 4) + i;
+            }
+            int hi[4], lo[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                hi[j] = acc[0][i][j][r];
+                lo[j] = acc[PL - 1][i][j][r];
+            }
+            if (ok && col_ok) finish4<WHICH>(p, z, row, col0, hi, lo, s_rs[lr], cs, cs1);
+        }
+}
+
+constexpr int kMaxRed = 65536;   // |a*b| <= 2^14 per product of two signed bytes: partial sums stay below 2^31
+
+}  // namespace
+
+// sizes the kernels above take: whole groups of four columns (rows) and one 16-entry piece of the reduction exist
+bool q8t_fc_supported(int which, int M, int N, int K)
+{
+    if (which == 0) return K >= 16 && N >= 4;
+    if (which == 1) return N >= 16 && K >= 4;
+    return M >= 16 && M <= kMaxRed && N >= 4 && K >= 4;
+}
+
+int q8t_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb, int M, int N, int K,
+           float *out_f, void *out_acc, hipStream_t st)
+{
+    FcArgs p;
+    p.a = (const int8_t *)a;
+    p.b = b;
+    p.qa = qa;
+    p.qb = qb;
+    p.rows = which == 2 ? K : M;
+    p.cols = which == 1 ? K : N;
+    p.red = which == 0 ? K : (which == 1 ? N : M);
+    p.lda = which == 1 ? N : K;
+    p.ldb = N;
+    p.out = out_f;
+    p.acc = out_acc;
+    p.vec = p.cols % 4 == 0 && q8t_aligned(out_f, 16);
+    const int64_t t128 = (int64_t)((p.rows + 127) / 128) * ((p.cols + 127) / 128);
+    const int steps = (p.red + 63) / 64;
+    // 128x128 tiles from half a tile per compute unit on: 1500^3 (144 tiles) takes 22 / 18 / 32 us in tiles and 22 / 20 / 34
+    // in fc_direct, 2048x616x3680's forward (90 tiles) 40 against 31; the weight gradient splits its reduction eight
+    // ways there and changes over a little later (128 tiles: 38 against 26 us)
+    if (t128 >= (which == 2 ? 140 : 128) && p.red >= 64) {
+        p.tn = (p.cols + 127) / 128;
+        p.tiles = (int)t128;
+        const dim3 grid(q8t_gemm::xcd_grid(t128));
+        if (which == 0) hipLaunchKernelGGL(fc_tile<FWD>, grid, dim3(TT), 0, st, p);
+        else if (which == 1) hipLaunchKernelGGL(fc_tile<DGRAD>, grid, dim3(TT), 0, st, p);
+        else hipLaunchKernelGGL(fc_tile<WGRAD>, grid, dim3(TT), 0, st, p);
+        Q8T_LAUNCH_CHECK();
+        return Q8T_OK;
+    }
+    const int tr = which == 2 ? 64 : 32;
+    p.tn = (p.cols + 63) / 64;
+    const int64_t tiles = (int64_t)((p.rows + tr - 1) / tr) * p.tn;
+    p.tiles = (int)tiles;
+    // wavefronts per tile: enough of them to fill the chip (two per SIMD; limits of 512 .. 8192 wavefronts were swept, and
+    // fewer leave the 512x2048x2048 forward at 24 instead of 10.5 us), no more than there are K-steps
+    int ks = 1;
+    while (ks < 8 && 2 * ks <= steps && tiles * ks < 2048) ks *= 2;
+    if (ks == 2) ks = 4;
+#define Q8T_GO(W, WAVES, KS) \
+    hipLaunchKernelGGL((fc_direct<W, WAVES, KS>), dim3((unsigned)((tiles + (WAVES / KS) - 1) / (WAVES / KS))), dim3(WAVES * 64), 0, st, p)
+    if (which == 0) { if (ks == 8) Q8T_GO(FWD, 8, 8); else if (ks == 4) Q8T_GO(FWD, 4, 4); else Q8T_GO(FWD, 4, 1); }
+    else if (which == 1) { if (ks == 8) Q8T_GO(DGRAD, 8, 8); else if (ks == 4) Q8T_GO(DGRAD, 4, 4); else Q8T_GO(DGRAD, 4, 1); }
+    else { if (ks == 8) Q8T_GO(WGRAD, 8, 8); else if (ks == 4) Q8T_GO(WGRAD, 4, 4); else Q8T_GO(WGRAD, 4, 1); }
+#undef Q8T_GO
+    Q8T_LAUNCH_CHECK();
+    return Q8T_OK;
+}
