@@ -21,29 +21,33 @@ int fc_check(int M, int N, int K, const void *a, const void *qa, const void *b, 
     return Q8T_OK;
 }
 
-// the im2col + GEMM form of a forward with few input channels pays off once the product is not tiny
-bool smallc_wanted(int which, const q8t_conv_desc *d)
+double products(const q8t_conv_desc *d)
 {
-    if (!q8t_smallc_conv_supported(which, d)) return false;
     const int P = (d->H + 2 * d->pad - d->R) / d->stride + 1, Q = (d->W + 2 * d->pad - d->S) / d->stride + 1;
-    return (double)d->K * d->C * d->R * d->S * d->N * P * Q >= 4194304.0;
+    return (double)d->K * d->C * d->R * d->S * d->N * P * Q;
 }
+// these forms, with a pass over an operand ahead, pay off once the product is not tiny
+bool not_tiny(const q8t_conv_desc *d) { return products(d) >= 4194304.0; }
+bool smallc_wanted(int which, const q8t_conv_desc *d) { return q8t_smallc_conv_supported(which, d) && not_tiny(d); }
+bool wgrad_wants_gemm(const q8t_conv_desc *d) { return q8t_gemm_wgrad_supported(d) && not_tiny(d); }
 
-// the GEMM form of the weight gradient pays off once the product is not tiny
-bool wgrad_wants_gemm(const q8t_conv_desc *d)
+// The general MFMA path, except where the general kernel needs a single step of 64 for the reduction and the product is
+// small: there its one launch is faster than three (whole calls, 33->48 1x1 layer gradient @20 batch 32, 20 M products:
+// 11.5 against 13.7 us; 48->48 @28 batch 64, 115 M: 17.7 against 15.9).  From two steps on the gathered operands cost
+// more at any size but the very smallest (16->16 3x3 @7 batch 8, 0.9 M products: 24.5 against 16.2 us; 8->8 3x3 @5 batch 1,
+// 14 thousand: 11.1 against 12.9).
+bool nhwc_wanted(int which, const q8t_conv_desc *d)
 {
-    if (!q8t_gemm_wgrad_supported(d)) return false;
-    const int P = (d->H + 2 * d->pad - d->R) / d->stride + 1, Q = (d->W + 2 * d->pad - d->S) / d->stride + 1;
-    return (double)d->K * d->C * d->R * d->S * d->N * P * Q >= 4194304.0;
+    if (!q8t_nhwc_conv_supported(which, d)) return false;
+    const int64_t red = (int64_t)(which == 0 ? d->C : d->K) * d->R * d->S;
+    return (d->C % 64 == 0 && d->K % 64 == 0) || products(d) >= (red > 64 ? 262144.0 : 33554432.0);
 }
 
 // bytes of partial statistics that the forward kernel for this shape writes from its epilogue (0: none there)
 size_t stats_in_epilogue_ws(const q8t_conv_desc *d)
 {
-    if (q8t_nhwc_conv_supported(0, d)) return q8t_nhwc_conv_stats_ws(d);
-    size_t s = smallc_wanted(0, d) ? q8t_smallc_conv_stats_ws(d) : 0;
-    const size_t f = q8t_first_conv_stats_ws(d);   // which of the two runs also depends on the pointers
-    return f > s ? f : s;
+    if (q8t_first_conv_supported(d)) return q8t_first_conv_stats_ws(d);
+    return nhwc_wanted(0, d) ? q8t_nhwc_conv_stats_ws(d) : 0;
 }
 
 // A 1x1 convolution with a stride and no padding is the stride-1 layer on the positions it reads: where the
@@ -140,9 +144,11 @@ size_t q8t_qconv_workspace_size(const q8t_conv_desc *desc, int which)
         const size_t pw = q8t_planes_wgrad_ws(desc);
         if (pw > f) f = pw;
     }
-    size_t h = which < 2 ? q8t_nhwc_conv_ws(which, desc) : (wgrad_wants_gemm(desc) ? q8t_gemm_wgrad_ws(desc) : 0);
-    if (smallc_wanted(which, desc)) h = q8t_smallc_conv_ws(which, desc);
-    if (which == 0 && q8t_first_conv_ws(desc) > h) h = q8t_first_conv_ws(desc);
+    size_t h = 0;
+    if (which == 0 && q8t_first_conv_supported(desc)) h = q8t_first_conv_ws(desc);
+    else if (which < 2) h = nhwc_wanted(which, desc) ? q8t_nhwc_conv_ws(which, desc) : 0;
+    else h = wgrad_wants_gemm(desc) ? q8t_gemm_wgrad_ws(desc) : 0;
+    if (h == 0 && smallc_wanted(which, desc)) h = q8t_smallc_conv_ws(which, desc);
     q8t_conv_desc sub;
     if (which == 0 && lattice_forward(desc, &sub)) {
         const size_t l = lattice_codes_bytes(&sub) + q8t_fast_conv_ws(0, &sub);
@@ -174,11 +180,11 @@ static int qconv_fwd_impl(const q8t_conv_desc *desc, const int8_t *qx, const q8t
     if (q8t_fast_conv_supported(0, desc, qx, qw, y, acc_out))
         return q8t_fast_conv(0, desc, qx, px, qw, pw, y, acc_out, nullptr, ws, (hipStream_t)stream, nullptr,
                              packed_tile64(packed, desc, 0));
-    if (q8t_nhwc_conv_supported(0, desc))
-        return q8t_nhwc_conv(0, desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
-    if (q8t_first_conv_supported(desc, qx, y, acc_out))
+    if (q8t_first_conv_supported(desc))
         return q8t_first_conv(desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
-    if (smallc_wanted(0, desc)) return q8t_smallc_conv(desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
+    if (nhwc_wanted(0, desc))
+        return q8t_nhwc_conv(0, desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
+    if (smallc_wanted(0, desc)) return q8t_smallc_conv(desc, qx, px, qw, pw, y, acc_out, ws, (hipStream_t)stream);
     return q8t_generic_conv(0, desc, qx, px, qw, pw, y, acc_out, ws, (hipStream_t)stream);
 }
 
@@ -228,12 +234,10 @@ static int qconv_fwd_bn_stats_impl(const q8t_conv_desc *desc, const int8_t *qx, 
         return q8t_fast_conv(0, desc, qx, px, qw, pw, y, acc_out, stats_out, ws, (hipStream_t)stream, nullptr,
                              packed_tile64(packed, desc, 0));
     void *sws = (char *)ws + ((q8t_qconv_workspace_size(desc, 0) + 255) & ~(size_t)255);
-    if (q8t_nhwc_conv_supported(0, desc))
-        return q8t_nhwc_conv(0, desc, qx, px, qw, pw, y, acc_out, stats_out, sws, ws, (hipStream_t)stream);
-    if (q8t_first_conv_supported(desc, qx, y, acc_out))
+    if (q8t_first_conv_supported(desc))
         return q8t_first_conv(desc, qx, px, qw, pw, y, acc_out, stats_out, sws, ws, (hipStream_t)stream);
-    if (smallc_wanted(0, desc) && q8t_smallc_conv_stats_ws(desc))
-        return q8t_smallc_conv(desc, qx, px, qw, pw, y, acc_out, stats_out, sws, ws, (hipStream_t)stream);
+    if (nhwc_wanted(0, desc))
+        return q8t_nhwc_conv(0, desc, qx, px, qw, pw, y, acc_out, stats_out, sws, ws, (hipStream_t)stream);
     const int rc2 = qconv_fwd_impl(desc, qx, px, qw, pw, y, acc_out, ws, stream, packed);
     if (rc2) return rc2;
     const int P = (desc->H + 2 * desc->pad - desc->R) / desc->stride + 1, Q = (desc->W + 2 * desc->pad - desc->S) / desc->stride + 1;
@@ -258,7 +262,7 @@ static int qconv_dgrad_impl(const q8t_conv_desc *desc, const int8_t *qdy, const 
     if (q8t_fast_conv_supported(1, desc, qdy, qw, dx, acc_out))
         return q8t_fast_conv(1, desc, qdy, pg, qw, pw, dx, acc_out, nullptr, ws, (hipStream_t)stream, nullptr,
                              packed_tile64(packed, desc, 1));
-    if (q8t_nhwc_conv_supported(1, desc))
+    if (nhwc_wanted(1, desc))
         return q8t_nhwc_conv(1, desc, qdy, pg, qw, pw, dx, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
     return q8t_generic_conv(1, desc, qdy, pg, qw, pw, dx, acc_out, ws, (hipStream_t)stream);
 }

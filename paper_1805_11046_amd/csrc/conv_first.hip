@@ -1,14 +1,14 @@
-// Forward convolution of a layer with very few input channels and 64 output channels (the first layer of a
-// ResNet: 3 -> 64, 7x7, stride 2), 8-bit operands with 32-bit accumulation (Section 4).
+// Forward convolution of a layer with very few input channels and a multiple of 64 output channels (the first layer of
+// a ResNet: 3 -> 64, 7x7, stride 2), 8-bit operands with 32-bit accumulation (Section 4).
 //
-// GEMM view: rows = output positions, columns = the 64 output channels, reduction = (channel, filter row) groups of
+// GEMM view: rows = output positions, columns = a block of 64 output channels, reduction = (channel, filter row) groups of
 // 8 columns each: the S <= 8 taps of one filter row, the surplus columns meeting filter entries that hold the
 // filter's zero code, so whatever input byte sits under them contributes nothing once the zero points are taken out:
 //    sum (a - za)(b - zb) = sum ab - zb * sum a - za * sum b + Kc * za * zb       (all sums over the Kc columns).
 // The operand rows are never built.  A workgroup stages the band of input rows under RPB output rows once (every
 // channel, zero code in the padding); the 8 bytes of a group for output column q are then 8 consecutive bytes of a
 // staged row, starting at q * stride, and a lane reads its MFMA fragment (16 bytes = two groups) straight from the
-// band with two unaligned 8-byte LDS reads.  The whole [64][Kc] filter lives in registers (v_mfma_i32_16x16x64_i8
+// band with two unaligned 8-byte LDS reads.  The block's [64][Kc] filter lives in registers (v_mfma_i32_16x16x64_i8
 // fragments, loaded once per workgroup).  Row sums: v_dot4 on the fragments, folded over the four lanes that share
 // a position.  HBM sees the int8 input once (plus the overlap of neighbouring bands) and the fp32 result once.
 #include "q8t_common.h"
@@ -25,6 +25,7 @@ constexpr int kTP = 36;       // ints per channel row of a wavefront's result ti
 
 struct FirstGeom {
     int N, C, H, W, R, S, stride, pad, P, Q;
+    int KB;        // blocks of 64 output channels
     int CR;        // (channel, filter row) groups
     int NR;        // staged input rows per channel: (kRPB - 1) * stride + R
     int L, Wp;     // left margin and pitch of a staged row (multiples of 4)
@@ -33,7 +34,7 @@ struct FirstGeom {
     int vec;       // 16-byte stores allowed
 };
 
-// filter [64][C*R*S] -> [64][Kc], column g * 8 + s = entry (g, s) of group g, the filter's zero code elsewhere;
+// filter [K][C*R*S] -> [K][Kc], column g * 8 + s = entry (g, s) of group g, the filter's zero code elsewhere;
 // sums per output channel over all Kc columns
 __global__ __launch_bounds__(64) void repack_first(const int8_t *__restrict__ w, int CRS, int CR, int S, int Kc,
                                                    const q8t_qparams *__restrict__ qpw, int8_t *__restrict__ wt,
@@ -64,7 +65,11 @@ __global__ __launch_bounds__(kThreads) void first_conv(const int8_t *__restrict_
     constexpr int Kc = 64 * KS;
     const int n = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kb = lane >> 4;
-    const int pbeg = blockIdx.x * kRPB, nrows = min(kRPB, g.P - pbeg);
+    // blocks of 64 output channels of one band are neighbours: the band's codes are fetched from memory once
+    const int kblk = blockIdx.x % g.KB, bandno = blockIdx.x / g.KB;
+    wt += (size_t)kblk * 64 * Kc;
+    colsum += kblk * 64;
+    const int pbeg = bandno * kRPB, nrows = min(kRPB, g.P - pbeg);
     const int za = qpx->zero_point - (1 << (qpx->bits - 1)), zb = qpw->zero_point - (1 << (qpw->bits - 1));
     const float sc = qpx->scale * qpw->scale;
     const uint32_t zfill = (uint32_t)(za & 255) * 0x01010101u;
@@ -88,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void first_conv(const int8_t *__restrict_
                 v[u] = 0;
                 if (cr < nstaged && (unsigned)h < (unsigned)g.H && w4 < W4) {
                     dst[u] = cr * g.Wp + g.L + 4 * w4;
-                    v[u] = *reinterpret_cast<const uint32_t *>(x + (((size_t)n * g.C + c) * g.H + h) * g.W + 4 * w4);
+                    __builtin_memcpy(&v[u], x + (((size_t)n * g.C + c) * g.H + h) * g.W + 4 * w4, 4);   // any alignment
                 }
             }
             if (r0 == 0 && w0 == 0) {
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(kThreads) void first_conv(const int8_t *__restrict_
         // lane -> piece lane % 8 (4 positions) of channels lane / 8 + 8 * it
         const int piece = lane & 7, pos = mp * 32 + piece * 4;
         const bool live = pos < g.Q;
-        const size_t obase = (((size_t)n * 64 + (lane >> 3)) * g.P + p) * g.Q + pos;
+        const size_t obase = ((((size_t)n * g.KB + kblk) * 64 + (lane >> 3)) * g.P + p) * g.Q + pos;
         const size_t ostep = (size_t)8 * g.P * g.Q;
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
@@ -238,7 +243,8 @@ __global__ __launch_bounds__(kThreads) void first_conv(const int8_t *__restrict_
             r.sum = (long long)slot_s[tid];
             r.mn = slot_mn[tid];
             r.mx = slot_mx[tid];
-            bnpart[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 64 + tid] = r;
+            const int bands = gridDim.x / g.KB;
+            bnpart[((size_t)(kblk * gridDim.y + blockIdx.y) * bands + bandno) * 64 + tid] = r;
         }
     }
 }
@@ -255,13 +261,14 @@ size_t lds_bytes(const FirstGeom &g) { return (size_t)band_bytes(g) + (kThreads 
 
 bool make_geom(const q8t_conv_desc *d, FirstGeom *g)
 {
-    if (d->N <= 0 || d->N > 65535 || d->C <= 0 || d->C >= 64 || d->K != 64 || d->H <= 0 || d->W <= 0) return false;
+    if (d->N <= 0 || d->N > 65535 || d->C <= 0 || d->C >= 64 || d->K <= 0 || d->K % 64 || d->K > 4096 || d->H <= 0 || d->W <= 0) return false;
     if (d->R <= 0 || d->R > 32 || d->S <= 0 || d->S > 8 || d->stride < 1 || d->stride > 4 || d->pad < 0 || d->pad > 16) return false;
     if (d->H + 2 * d->pad < d->R || d->W + 2 * d->pad < d->S || d->W % 4) return false;
     g->N = d->N; g->C = d->C; g->H = d->H; g->W = d->W; g->R = d->R; g->S = d->S; g->stride = d->stride; g->pad = d->pad;
     g->P = (d->H + 2 * d->pad - d->R) / d->stride + 1;
     g->Q = (d->W + 2 * d->pad - d->S) / d->stride + 1;
     g->CR = d->C * d->R;
+    g->KB = d->K / 64;
     if (g->CR > 32) return false;
     g->NR = (kRPB - 1) * d->stride + d->R;
     g->L = (d->pad + 3) & ~3;
@@ -269,7 +276,8 @@ bool make_geom(const q8t_conv_desc *d, FirstGeom *g)
     g->mtiles = (g->Q + 15) / 16;
     if ((int64_t)g->C * g->NR * g->Wp > 60 * 1024) return false;
     g->band_bytes = band_bytes(*g);
-    if ((int64_t)d->N * 64 * g->P * g->Q >= ((int64_t)1 << 40) || (int64_t)d->N * d->C * d->H * d->W >= ((int64_t)1 << 40)) return false;
+    if (lds_bytes(*g) > 64 * 1024) return false;
+    if ((int64_t)d->N * d->K * g->P * g->Q >= ((int64_t)1 << 40) || (int64_t)d->N * d->C * d->H * d->W >= ((int64_t)1 << 40)) return false;
     return true;
 }
 
@@ -277,26 +285,24 @@ int ksteps(const FirstGeom &g) { return (g.CR + 7) / 8; }
 
 }  // namespace
 
-bool q8t_first_conv_supported(const q8t_conv_desc *d, const void *a, const void *out_f, const void *out_acc)
+bool q8t_first_conv_supported(const q8t_conv_desc *d)
 {
     FirstGeom g;
-    if (!make_geom(d, &g)) return false;
-    if (lds_bytes(g) > 64 * 1024) return false;
-    return q8t_aligned(a, 4) && q8t_aligned(out_f, 4) && q8t_aligned(out_acc, 4);
+    return make_geom(d, &g);
 }
 
 size_t q8t_first_conv_ws(const q8t_conv_desc *d)
 {
     FirstGeom g;
     if (!make_geom(d, &g)) return 0;
-    return (size_t)64 * 64 * ksteps(g) + 256 + 64 * sizeof(int);
+    return (size_t)d->K * 64 * ksteps(g) + 256 + d->K * sizeof(int);
 }
 
 size_t q8t_first_conv_stats_ws(const q8t_conv_desc *d)
 {
     FirstGeom g;
     if (!make_geom(d, &g)) return 0;
-    return (size_t)((g.P + kRPB - 1) / kRPB) * d->N * 64 * sizeof(Q8tConvStat);
+    return (size_t)((g.P + kRPB - 1) / kRPB) * d->N * d->K * sizeof(Q8tConvStat);
 }
 
 int q8t_first_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb,
@@ -308,13 +314,14 @@ int q8t_first_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa,
     if (bn_stats && (!stats_ws || !q8t_aligned(stats_ws, 16))) return Q8T_ERR_WORKSPACE;
     const int KS = ksteps(g), Kc = 64 * KS;
     int8_t *wt = (int8_t *)ws;
-    int *colsum = (int *)((char *)ws + (((size_t)64 * Kc + 255) & ~(size_t)255));
+    int *colsum = (int *)((char *)ws + (((size_t)d->K * Kc + 255) & ~(size_t)255));
     Q8tConvStat *bnp = bn_stats ? (Q8tConvStat *)stats_ws : (Q8tConvStat *)nullptr;
     g.vec = g.Q % 4 == 0 && q8t_aligned(out_f, 16) && q8t_aligned(out_acc, 16);
-    hipLaunchKernelGGL(repack_first, dim3(64), dim3(64), 0, st, (const int8_t *)b, d->C * d->R * d->S, g.CR, d->S, Kc, qb, wt,
+    hipLaunchKernelGGL(repack_first, dim3((unsigned)d->K), dim3(64), 0, st, (const int8_t *)b, d->C * d->R * d->S, g.CR, d->S, Kc, qb, wt,
                        colsum);
     Q8T_LAUNCH_CHECK();
-    const dim3 grid((unsigned)((g.P + kRPB - 1) / kRPB), (unsigned)d->N);
+    const int bands = (g.P + kRPB - 1) / kRPB;
+    const dim3 grid((unsigned)(bands * g.KB), (unsigned)d->N);
     const size_t lds = lds_bytes(g);
 #define Q8T_FIRST(KSV)                                                                                                    \
     {                                                                                                                     \
@@ -332,8 +339,8 @@ int q8t_first_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa,
 #undef Q8T_FIRST
     Q8T_LAUNCH_CHECK();
     if (bnp) {
-        const int nwg = (int)(grid.x * grid.y);
-        return q8t_conv_stats_finalize(bnp, 64, nwg, nwg, (double)d->N * g.P * g.Q, qa, qb, bn_stats, st);
+        const int nwg = bands * d->N;
+        return q8t_conv_stats_finalize(bnp, d->K, nwg, nwg, (double)d->N * g.P * g.Q, qa, qb, bn_stats, st);
     }
     return Q8T_OK;
 }

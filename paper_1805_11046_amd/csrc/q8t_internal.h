@@ -58,8 +58,8 @@ int q8t_wide_conv_pack_layout(int which, const q8t_conv_desc *d);
 // Range BN statistics of an NCHW tensor alone (range_bn.hip); ws as for q8t_range_bn_fwd
 int q8t_range_bn_stats(const float *x, int N, int C, int H, int W, float *stats_out, void *ws, hipStream_t st);
 
-// general MFMA path over a channel-contiguous copy of the operand (conv_nhwc.hip): forward and
-// layer gradient, channel counts that are multiples of 64
+// general MFMA path over a channel-contiguous copy of the operand (conv_nhwc.hip): forward and layer gradient, any
+// channel counts, up to 49 taps, strides up to 4
 bool q8t_nhwc_conv_supported(int which, const q8t_conv_desc *d);
 size_t q8t_nhwc_conv_ws(int which, const q8t_conv_desc *d);
 // bn_stats (nullable, forward only): [3][K] mean / min / max of the float result, gathered in the epilogue
@@ -69,17 +69,16 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
                   hipStream_t st);
 size_t q8t_nhwc_conv_stats_ws(const q8t_conv_desc *d);
 
-// forward with fewer than 64 input channels (first layer): explicit im2col rows + the same GEMM
+// forward with fewer than 64 input channels where that path does not reach (more taps, larger strides), output channels
+// a multiple of 64: explicit im2col rows + the same GEMM
 bool q8t_smallc_conv_supported(int which, const q8t_conv_desc *d);
 size_t q8t_smallc_conv_ws(int which, const q8t_conv_desc *d);
-// bn_stats as for q8t_nhwc_conv; only where q8t_smallc_conv_stats_ws(d) != 0 (one block of 64 output channels, fused kernel)
 int q8t_smallc_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb,
-                    float *out_f, void *out_acc, float *bn_stats, void *stats_ws, void *ws, hipStream_t st);
-size_t q8t_smallc_conv_stats_ws(const q8t_conv_desc *d);
+                    float *out_f, void *out_acc, void *ws, hipStream_t st);
 
-// forward with very few input channels and 64 output channels, filter rows of at most 8 taps: operand fragments read
-// straight from a staged band of input rows, filter in registers (conv_first.hip).  Contract of q8t_smallc_conv.
-bool q8t_first_conv_supported(const q8t_conv_desc *d, const void *a, const void *out_f, const void *out_acc);
+// forward with very few input channels and blocks of 64 output channels, filter rows of at most 8 taps: operand fragments read
+// straight from a staged band of input rows, filter in registers (conv_first.hip).  Contract of q8t_nhwc_conv.
+bool q8t_first_conv_supported(const q8t_conv_desc *d);
 size_t q8t_first_conv_ws(const q8t_conv_desc *d);
 size_t q8t_first_conv_stats_ws(const q8t_conv_desc *d);
 int q8t_first_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb,

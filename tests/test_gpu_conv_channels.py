@@ -1,0 +1,73 @@
+"""GPU parity of the forward and layer-gradient convolutions for channel counts that are no multiples of 64: pieces of 16
+channels with a remainder, several taps in one step of 64, tiles of output channels with a remainder, stride classes with
+and without taps.  Accumulators and float results bit-exact (one rounding of an exact integer)."""
+import pytest
+
+import oracle
+import synth
+from gpu_util import close, dev, host, qp_dev_from, require_gpu, same_ints
+from test_gpu_products import _conv_operands
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # N, C, H, W, K, R, S, stride, pad
+    (40, 16, 32, 32, 16, 3, 3, 1, 1),     # four taps per step, the last step with three surplus pieces
+    (9, 17, 33, 31, 47, 3, 3, 1, 1),      # 2 and 3 pieces per tap, one channel in the last; odd plane
+    (6, 96, 27, 27, 200, 3, 3, 1, 1),     # 6 and 13 pieces, a last tile of 8 channels
+    (5, 65, 15, 14, 129, 3, 3, 1, 1),     # one channel behind a tile of 64 / 128
+    (300, 48, 5, 5, 63, 3, 3, 1, 1),      # tiny planes, 128-row tiles over many images
+    (4, 64, 28, 28, 100, 3, 3, 1, 1),     # whole tiles on one side only
+    (3, 200, 13, 17, 64, 1, 1, 1, 0),     # a single tap
+    (8, 1, 65, 64, 33, 5, 5, 1, 2),       # one channel
+    (4, 24, 40, 36, 40, 7, 7, 1, 3),      # 49 taps, pieces of two taps in a step
+    (4, 24, 36, 36, 72, 3, 3, 2, 1),      # stride 2, even width: class pairs
+    (4, 40, 35, 33, 72, 3, 3, 2, 1),      # ... odd sizes: classes of their own
+    (6, 80, 30, 28, 48, 1, 1, 2, 0),      # ... three classes without taps, zeros written by the fourth
+    (6, 80, 29, 28, 48, 1, 1, 2, 0),
+    (3, 36, 40, 40, 50, 5, 4, 3, 2),      # stride 3, filter not square
+    (2, 300, 14, 14, 260, 3, 3, 1, 1),    # 256-column tiles have to be declined or cut
+    (200, 130, 12, 12, 250, 3, 3, 1, 1),  # many rows: 256x256 tiles with a remainder of 6 channels
+    (3, 3, 40, 44, 192, 7, 7, 2, 3),      # few input channels: three blocks of 64 output channels on one band of rows
+    (2, 5, 27, 24, 128, 5, 3, 1, 1),      # ... two, ragged band
+    (3, 3, 64, 64, 64, 9, 9, 2, 4),       # more than 49 taps
+    (2, 3, 96, 96, 64, 16, 16, 16, 0),    # patches
+    (2, 20, 21, 21, 24, 3, 3, 5, 1),      # stride beyond 4: general kernel
+]
+
+
+@pytest.mark.parametrize("case", SHAPES)
+def test_conv_channel_counts(case):
+    q8t = require_gpu()
+    g = synth.rng(sum(case))
+    od, (sx, px), (sw, pw), (sg, pg), _ = _conv_operands(g, case)
+    d = q8t.conv_desc(*case)
+    dpx, dpw, dpg = (qp_dev_from(p) for p in (px, pw, pg))
+    oy, oacc = oracle.qconv_fwd(od, sx, px, sw, pw)
+    y, acc = q8t.qconv_fwd(d, dev(sx), dpx, dev(sw), dpw, want_acc=True)
+    same_ints(host(acc), oacc)
+    same_ints(host(y), oy)
+    y, acc, stats = q8t.qconv_fwd_bn_stats(d, dev(sx), dpx, dev(sw), dpw, want_acc=True)
+    same_ints(host(acc), oacc)
+    yk = oy.astype("float64").transpose(1, 0, 2, 3).reshape(oy.shape[1], -1)
+    close(host(stats)[0], yk.mean(axis=1))
+    same_ints(host(stats)[1:], [yk.min(axis=1), yk.max(axis=1)])
+    odx, oacc = oracle.qconv_dgrad(od, sg, pg, sw, pw)
+    dx, acc = q8t.qconv_dgrad(d, dev(sg), dpg, dev(sw), dpw, want_acc=True)
+    same_ints(host(acc), oacc)
+    same_ints(host(dx), odx)
+
+
+@pytest.mark.parametrize("case", [(7, 40, 19, 21, 72, 3, 3, 1, 1), (2, 3, 20, 24, 64, 3, 3, 1, 1)])
+def test_conv_operand_at_any_address(case):
+    # the relayout / the staged band of rows reads four codes at a time wherever the operand starts
+    q8t = require_gpu()
+    od, (sx, px), (sw, pw), _, _ = _conv_operands(synth.rng(3), case)
+    _, oacc = oracle.qconv_fwd(od, sx, px, sw, pw)
+    d = q8t.conv_desc(*case)
+    for off in (1, 2, 3):
+        flat = dev(sx.ravel())
+        buf = flat.new_empty(flat.numel() + off)
+        buf[off:] = flat
+        _, acc = q8t.qconv_fwd(d, buf[off:].view(sx.shape), qp_dev_from(px), dev(sw), qp_dev_from(pw), want_acc=True)
+        same_ints(host(acc), oacc)
