@@ -206,6 +206,13 @@ int q8t_qconv_dgrad_relu_sum(const q8t_conv_desc *desc /* host */, const int8_t 
                              const int8_t *qw, const q8t_qparams *pw, const float *other, const float *act,
                              float *dx, void *ws, void *stream);
 
+/* The same with nothing to mask: dx[i] = dgrad[i] + other[i], for a block whose input is no rectified tensor of the
+ * network (the start of a chain).  other: not NULL.  packed: the filter packed ahead (below) or NULL.  Bit-identical
+ * to q8t_qconv_dgrad followed by one fp32 addition; 8 instead of 16 bytes per element where the epilogue takes it. */
+int q8t_qconv_dgrad_sum(const q8t_conv_desc *desc /* host */, const int8_t *qdy, const q8t_qparams *pg,
+                        const int8_t *qw, const q8t_qparams *pw, const void *packed, const float *other,
+                        float *dx, void *ws, void *stream);
+
 /* Filters packed ahead of the products.  The forward and the layer-gradient product (Section 4, eqs. (forward),
  * (grad_layer)) of most layer shapes read the 8-bit filter in a kernel-specific order and need the sum of every
  * output channel's codes for the zero-point correction; by default each product call makes both in a small launch of
@@ -384,6 +391,8 @@ int q8t_tern_wgrad_multi(const float *g, const int8_t *a_codes, int M, int N, in
  *   (a shortcut that is itself convolution + Range BN); 8-bit codes as for q8t_add_relu_quantize.  x, other, out:
  *   [N,C,H,W]; stats, other_stats: [3][C]; gamma / beta pointers nullable.  The normalized tensors are never
  *   written: 12 (+5 for the codes) bytes per element instead of 20 (+5).  ws: q8t_add_relu_quantize_workspace_size.
+ * q8t_range_bn_add_relu: the same out = relu(bn(x) + other) for a block whose result is not quantized here: no codes,
+ *   no workspace; a NaN in the sum stays a NaN.
  * q8t_relu_bwd_add: res = (out > 0 ? g : 0) + other (other nullable: nothing added).
  * q8t_relu_bwd_sum: the gradient that reaches a rectified tensor `out` from its two consumers (a residual
  *   block's convolutions and its shortcut): res = out > 0 ? g1 + g2 : 0 in one pass, instead of a sum and a
@@ -404,6 +413,8 @@ int q8t_range_bn_add_relu_quantize(const float *x, const float *stats, const flo
                                    const float *other, const float *other_stats, const float *other_gamma,
                                    const float *other_beta, int N, int C, int H, int W, float eps, float *out, int8_t *q_out,
                                    q8t_qparams *qp_out, void *ws, void *stream);
+int q8t_range_bn_add_relu(const float *x, const float *stats, const float *gamma, const float *beta, const float *other, int N,
+                          int C, int H, int W, float eps, float *out, void *stream);
 int q8t_relu_bwd_add(const float *g, const float *out, const float *other, int64_t n, float *res, void *stream);
 int q8t_relu_bwd_sum(const float *g1, const float *g2, const float *out, int64_t n, float *res, void *stream);
 int q8t_relu_bwd_sum_lattice(const float *g1, const float *g2s, const float *out, int N, int C, int H, int W, int stride,

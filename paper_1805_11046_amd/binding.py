@@ -87,6 +87,7 @@ _SIGS = {
                                         _vp, _vp, _vp, _vp]),
     "q8t_probe_stream": (_i, [_i, _vp, _vp, _i64, _vp]),
     "q8t_range_bn_relu_maxpool_fwd": (_i, [_vp, _i, _i, _i, _i, _vp, _vp, _f, _vp, _vp, _vp, _vp]),
+    "q8t_qconv_dgrad_sum": (_i, [C.POINTER(ConvDesc), _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "q8t_maxpool_relu_bwd": (_i, [_vp, _vp, _i, _i, _i, _i, _vp, _vp]),
     "q8t_maxpool_range_bn_bwd_bifurcate_workspace_size": (_sz, [_i, _i, _i, _i]),
     "q8t_maxpool_range_bn_bwd_bifurcate": (_i, [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _f, _vp, _vp, _u64, _u64, _vp, _vp,
@@ -94,6 +95,7 @@ _SIGS = {
     "q8t_add_relu_quantize_workspace_size": (_sz, [_i64]),
     "q8t_add_relu_quantize": (_i, [_vp, _vp, _i64, _vp, _vp, _vp, _vp, _vp]),
     "q8t_range_bn_add_relu_quantize": (_i, [_vp] * 8 + [_i, _i, _i, _i, _f, _vp, _vp, _vp, _vp, _vp]),
+    "q8t_range_bn_add_relu": (_i, [_vp] * 5 + [_i, _i, _i, _i, _f, _vp, _vp]),
     "q8t_relu_bwd_add": (_i, [_vp, _vp, _vp, _i64, _vp, _vp]),
     "q8t_relu_bwd_sum": (_i, [_vp, _vp, _vp, _i64, _vp, _vp]),
     "q8t_relu_bwd_sum_lattice": (_i, [_vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp]),
@@ -439,6 +441,20 @@ def qconv_dgrad_relu_sum(d, qdy, pg, qw, pw, other, act, out=None, ws=None, pack
     return dx
 
 
+def qconv_dgrad_sum(d, qdy, pg, qw, pw, other, out=None, ws=None, packed=None):
+    """dgrad + other: the layer gradient of a residual block's first convolution with the gradient of the shortcut
+    added in its epilogue.  Returns dx."""
+    _dev(qdy), _dev(qw), _dev(other)
+    shape = (d.N, d.C, d.H, d.W)
+    assert tuple(qdy.shape) == (d.N, d.K, d.P, d.Q) and tuple(qw.shape) == (d.K, d.C, d.R, d.S)
+    assert tuple(other.shape) == shape and other.dtype == torch.float32 and other.is_contiguous()
+    dx = out if out is not None else torch.empty(shape, dtype=torch.float32, device=qdy.device)
+    ws = ws if ws is not None else workspace(_lib.q8t_qconv_workspace_size(C.byref(d), 1), qdy.device)
+    _check(_lib.q8t_qconv_dgrad_sum(C.byref(d), _ptr(qdy), _ptr(pg), _ptr(qw), _ptr(pw), _ptr(packed), _ptr(other), _ptr(dx),
+                                    _ptr(ws), _stream()), "q8t_qconv_dgrad_sum")
+    return dx
+
+
 def qconv_wgrad(d, qx, px, qdy16, pg16, want_acc=False, out=None, ws=None):
     _dev(qx), _dev(qdy16)
     assert tuple(qx.shape) == (d.N, d.C, d.H, d.W) and tuple(qdy16.shape) == (d.N, d.K, d.P, d.Q)
@@ -681,6 +697,17 @@ def range_bn_add_relu_quantize(x, stats, other, gamma=None, beta=None, other_sta
                                                _ptr(other_gamma), _ptr(other_beta), N, Cc, H, W, float(eps), _ptr(out),
                                                _ptr(q), _ptr(qp), _ptr(ws), _stream()), "q8t_range_bn_add_relu_quantize")
     return out, q, qp
+
+
+def range_bn_add_relu(x, stats, other, gamma=None, beta=None, eps=0.0):
+    """relu(bn(x) + other) in one pass, without codes; a NaN stays a NaN.  Returns out."""
+    _dev(x), _dev(stats), _dev(other)
+    N, Cc, H, W = x.shape
+    assert x.dtype == torch.float32 and other.dtype == torch.float32 and other.shape == x.shape
+    out = torch.empty_like(x)
+    _check(_lib.q8t_range_bn_add_relu(_ptr(x), _ptr(stats), _ptr(gamma), _ptr(beta), _ptr(other), N, Cc, H, W, eps, _ptr(out),
+                                      _stream()), "q8t_range_bn_add_relu")
+    return out
 
 
 def relu_bwd_sum(g1, g2=None, out=None):

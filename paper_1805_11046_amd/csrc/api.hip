@@ -277,7 +277,7 @@ static int qconv_dgrad_relu_sum_impl(const q8t_conv_desc *desc, const int8_t *qd
                                      const q8t_qparams *pw, const float *other, const float *act, float *dx, void *ws,
                                      void *stream, const void *packed)
 {
-    if (!desc || !qdy || !pg || !qw || !pw || !act || !dx) return Q8T_ERR_NULL;
+    if (!desc || !qdy || !pg || !qw || !pw || (!act && !other) || !dx) return Q8T_ERR_NULL;
     const int rc = q8t_conv_reduction_check(1, desc);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
@@ -297,6 +297,7 @@ static int qconv_dgrad_relu_sum_impl(const q8t_conv_desc *desc, const int8_t *qd
 int q8t_qconv_dgrad_relu_sum(const q8t_conv_desc *desc, const int8_t *qdy, const q8t_qparams *pg, const int8_t *qw,
                              const q8t_qparams *pw, const float *other, const float *act, float *dx, void *ws, void *stream)
 {
+    if (!act) return Q8T_ERR_NULL;
     return qconv_dgrad_relu_sum_impl(desc, qdy, pg, qw, pw, other, act, dx, ws, stream, nullptr);
 }
 
@@ -350,7 +351,15 @@ int q8t_qconv_dgrad_relu_sum_packed(const q8t_conv_desc *desc, const int8_t *qdy
                                     const q8t_qparams *pw, const void *packed, const float *other, const float *act, float *dx,
                                     void *ws, void *stream)
 {
+    if (!act) return Q8T_ERR_NULL;
     return qconv_dgrad_relu_sum_impl(desc, qdy, pg, qw, pw, other, act, dx, ws, stream, packed);
+}
+
+int q8t_qconv_dgrad_sum(const q8t_conv_desc *desc, const int8_t *qdy, const q8t_qparams *pg, const int8_t *qw,
+                        const q8t_qparams *pw, const void *packed, const float *other, float *dx, void *ws, void *stream)
+{
+    if (!other) return Q8T_ERR_NULL;
+    return qconv_dgrad_relu_sum_impl(desc, qdy, pg, qw, pw, other, nullptr, dx, ws, stream, packed);
 }
 
 int q8t_qconv_wgrad(const q8t_conv_desc *desc, const int8_t *qx, const q8t_qparams *px, const int16_t *qdy16,

@@ -437,7 +437,7 @@ __global__ __launch_bounds__(kThreads, 4) void conv_s1_kernel(const int8_t *__re
             }
             float4 nx_o = make_float4(0.0f, 0.0f, 0.0f, 0.0f), nx_a = nx_o;
             auto fetch = [&](size_t o) {
-                nx_a = *reinterpret_cast<const float4 *>(fuse.act + o);
+                if (fuse.act) nx_a = *reinterpret_cast<const float4 *>(fuse.act + o);
                 if (fuse.other) nx_o = *reinterpret_cast<const float4 *>(fuse.other + o);
             };
             if (live[0]) fetch(ob[0]);
@@ -464,10 +464,12 @@ __global__ __launch_bounds__(kThreads, 4) void conv_s1_kernel(const int8_t *__re
                         f.z = f.z + cu_o.z;
                         f.w = f.w + cu_o.w;
                     }
-                    f.x = cu_a.x > 0.0f ? f.x : 0.0f;
-                    f.y = cu_a.y > 0.0f ? f.y : 0.0f;
-                    f.z = cu_a.z > 0.0f ? f.z : 0.0f;
-                    f.w = cu_a.w > 0.0f ? f.w : 0.0f;
+                    if (fuse.act) {
+                        f.x = cu_a.x > 0.0f ? f.x : 0.0f;
+                        f.y = cu_a.y > 0.0f ? f.y : 0.0f;
+                        f.z = cu_a.z > 0.0f ? f.z : 0.0f;
+                        f.w = cu_a.w > 0.0f ? f.w : 0.0f;
+                    }
                     *reinterpret_cast<float4 *>(y + o) = f;
                 }
             }
@@ -666,8 +668,8 @@ int q8t_fast_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
     int32_t *pacc = (int32_t *)out_acc;
     const bool sq = d->H == d->W;
 #define Q8T_CONV(T, WCV, V)                                                                                        \
-    (bnpart ? launch_conv<T, WCV, V, true, false>(grid, st, pa, wpk, colsum, qa, qb, g, sch, out_f, pacc, bnpart, fuse)      \
-            : (fuse.act ? launch_conv<T, WCV, V, false, true>(grid, st, pa, wpk, colsum, qa, qb, g, sch, out_f, pacc, bnpart, fuse) \
+    (bnpart ? launch_conv<T, WCV, V, true, false>(grid, st, pa, wpk, colsum, qa, qb, g, sch, out_f, pacc, bnpart, fuse)                     \
+            : (fuse.act || fuse.other ? launch_conv<T, WCV, V, false, true>(grid, st, pa, wpk, colsum, qa, qb, g, sch, out_f, pacc, bnpart, fuse)     \
                         : launch_conv<T, WCV, V, false, false>(grid, st, pa, wpk, colsum, qa, qb, g, sch, out_f, pacc, bnpart, fuse)))
     if (taps == 9) {
         if (sq && d->W == 56 && v16) rc = Q8T_CONV(9, 56, true);

@@ -285,7 +285,8 @@ def _chain_fwd(a, specs, ws, apply_last=True):
 def _chain_bwd(saved, g, need_dx, block_end=None):
     """backward of _chain_fwd: the ReLU mask is recomputed inside the Range BN backward.  block_end = (other, act):
     the chain is the main branch of a residual block; the layer gradient of its first convolution then also adds
-    the other branch's gradient and applies the mask of the block's input (act > 0) in its epilogue."""
+    the other branch's gradient and applies the mask of the block's input (act > 0; None: nothing to mask) in its
+    epilogue."""
     g = g.contiguous()
     dws = [None] * len(saved)
     for i in range(len(saved) - 1, -1, -1):
@@ -300,8 +301,12 @@ def _chain_bwd(saved, g, need_dx, block_end=None):
         g = None
         if i == 0 and block_end is not None:
             other, act = block_end
-            g = _call("qconv_dgrad", ops, ny + (12 if other is not None else 8) * nx, q8t.qconv_dgrad_relu_sum, d, g8, pg8,
-                      qw, pw, other, act, tag=_tag(d), packed=_packed(qw, 1))
+            if act is None:
+                g = _call("qconv_dgrad", ops, ny + 8 * nx, q8t.qconv_dgrad_sum, d, g8, pg8, qw, pw, other, tag=_tag(d),
+                          packed=_packed(qw, 1))
+            else:
+                g = _call("qconv_dgrad", ops, ny + (12 if other is not None else 8) * nx, q8t.qconv_dgrad_relu_sum, d, g8,
+                          pg8, qw, pw, other, act, tag=_tag(d), packed=_packed(qw, 1))
         elif i > 0 or need_dx:
             g, _ = _call("qconv_dgrad", ops, ny + 4 * nx, q8t.qconv_dgrad, d, g8, pg8, qw, pw, tag=_tag(d), packed=_packed(qw, 1))
         dws[i] = _wgrad(d, qa, pa, g16, pg16, ops, nx, ny)
@@ -371,6 +376,26 @@ class ResBlock(torch.autograd.Function):
             gc, (dw1, dw2) = _chain_bwd(chain, gm, True)
             ga = _call("relu_bwd_sum", 0, 12 * gc.numel(), q8t.relu_bwd_sum, gc, gs, None)
         return ga, None, None, None, None, dw1, dw2, dwsc
+
+
+class Bottleneck(torch.autograd.Function):
+    """relu(chain(x) + x) as one node: the chain's last Range BN, the identity shortcut and the rectifier are one pass,
+    and the shortcut's gradient is added in the epilogue of the chain's last layer gradient."""
+
+    @staticmethod
+    def forward(ctx, x, specs, *ws):
+        x = x.contiguous()
+        (y, stats), ctx.chain = _chain_fwd(x, specs, ws, apply_last=False)
+        out = _call("range_bn_add_relu", 0, 12 * y.numel(), q8t.range_bn_add_relu, y, stats, x, eps=1e-5)
+        ctx.save_for_backward(out)
+        return out
+
+    @staticmethod
+    def backward(ctx, g):
+        out, = ctx.saved_tensors
+        gm = torch.ops.aten.threshold_backward(g.contiguous(), out, 0)
+        gx, dws = _chain_bwd(ctx.chain, gm, True, (gm, None))
+        return (gx, None, *dws)
 
 
 class Linear(torch.autograd.Function):
@@ -493,6 +518,10 @@ def step(x, labels, ws):
 
 def bottleneck_step(x, gy, ws):
     _layer[0] = 0
+    if _fuse and x.dtype == torch.float32 and ws[2].shape[0] == x.shape[1]:
+        out = Bottleneck.apply(x, ((1, 0), (1, 1), (1, 0)), *ws)
+        out.backward(gy)
+        return out
     if _fuse:
         h = ConvChain.apply(x, True, ((1, 0), (1, 1), (1, 0)), *ws)
     else:
