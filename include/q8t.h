@@ -291,6 +291,13 @@ int q8t_range_bn_bwd_bifurcate(const float *x, const float *dy, const float *sta
                                const float *gamma, float eps, float *dx, float *dgamma, float *dbeta,
                                uint64_t seed8, uint64_t seed16, int8_t *q8_out, q8t_qparams *qp8_out,
                                int16_t *q16_out, q8t_qparams *qp16_out, void *ws, void *stream);
+/* The same for the last Range BN of a residual block, whose sum runs through a rectifier with result act: the upstream
+ * gradient is dy where act is not <= 0 and 0 elsewhere; it is also left in dy_masked (for the shortcut; not dy itself nor
+ * any other operand).  No dx.  Bit-identical to masking dy in a pass of its own. */
+int q8t_range_bn_bwd_bifurcate_masked(const float *x, const float *dy, const float *act, const float *stats, int N, int C, int H,
+                                      int W, const float *gamma, float eps, float *dy_masked, float *dgamma, float *dbeta,
+                                      uint64_t seed8, uint64_t seed16, int8_t *q8_out, q8t_qparams *qp8_out, int16_t *q16_out,
+                                      q8t_qparams *qp16_out, void *ws, void *stream);
 
 /* Range BN followed by ReLU in one pass (eq. (range) of Section 3, then max(., 0); the 8-bit
  * output follows Section 4's remark that the normalizer already knows the extrema: the range of

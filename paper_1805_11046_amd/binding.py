@@ -89,6 +89,7 @@ _SIGS = {
     "q8t_range_bn_relu_maxpool_fwd": (_i, [_vp, _i, _i, _i, _i, _vp, _vp, _f, _vp, _vp, _vp, _vp]),
     "q8t_qconv_dgrad_sum": (_i, [C.POINTER(ConvDesc), _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "q8t_maxpool_relu_bwd": (_i, [_vp, _vp, _i, _i, _i, _i, _vp, _vp]),
+    "q8t_range_bn_bwd_bifurcate_masked": (_i, [_vp] * 4 + [_i, _i, _i, _i, _vp, _f, _vp, _vp, _vp, _u64, _u64] + [_vp] * 6),
     "q8t_maxpool_range_bn_bwd_bifurcate_workspace_size": (_sz, [_i, _i, _i, _i]),
     "q8t_maxpool_range_bn_bwd_bifurcate": (_i, [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _f, _vp, _vp, _u64, _u64, _vp, _vp,
                                                 _vp, _vp, _vp, _vp]),
@@ -575,6 +576,21 @@ def range_bn_bwd_bifurcate(x, dy, stats, gamma=None, eps=0.0, seed8=0, seed16=1,
                                            int(seed16) & (2 ** 64 - 1), _ptr(q8), _ptr(qp8), _ptr(q16), _ptr(qp16),
                                            _ptr(ws), _stream()), "q8t_range_bn_bwd_bifurcate")
     return dx, dgamma, dbeta, q8, qp8, q16, qp16
+
+
+def range_bn_bwd_bifurcate_masked(x, dy, act, stats, gamma=None, eps=0.0, seed8=0, seed16=1):
+    """range_bn_bwd_bifurcate with the gradient dy masked by the rectifier whose result is act.
+    Returns (masked dy, dgamma, dbeta, q8, qp8, q16, qp16)."""
+    _dev(x), _dev(dy), _dev(act), _dev(stats)
+    N, Cc, H, W = x.shape
+    assert dy.shape == x.shape and act.shape == x.shape and dy.dtype == torch.float32 and act.dtype == torch.float32
+    gm = torch.empty_like(x)
+    _, dgamma, dbeta, q8, qp8, q16, qp16, ws = _bn_bwd_bifurcate_buffers(x, None, None, None, None, None, None, False)
+    _check(_lib.q8t_range_bn_bwd_bifurcate_masked(_ptr(x), _ptr(dy), _ptr(act), _ptr(stats), N, Cc, H, W, _ptr(gamma), float(eps),
+                                                  _ptr(gm), _ptr(dgamma), _ptr(dbeta), int(seed8) & (2 ** 64 - 1),
+                                                  int(seed16) & (2 ** 64 - 1), _ptr(q8), _ptr(qp8), _ptr(q16), _ptr(qp16),
+                                                  _ptr(ws), _stream()), "q8t_range_bn_bwd_bifurcate_masked")
+    return gm, dgamma, dbeta, q8, qp8, q16, qp16
 
 
 # ------------------------------------------------------------------ ternarized back-propagation

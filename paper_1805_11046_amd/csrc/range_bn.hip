@@ -566,13 +566,31 @@ __device__ __forceinline__ float4 pool_grad4(const PoolSrc &ps, const uint8_t *l
                                  ps.Q);
 }
 
-template <bool VEC, bool POOL = false>
+// The rectifier behind the block's sum, seen from below: the gradient passes where its result `act` is not <= 0 (a NaN
+// passes, as in a rectifier's own backward); `gm` receives the masked gradient for pass 2 and the shortcut.
+struct MaskSrc {
+    const float *act;
+    float *gm;
+};
+__device__ __forceinline__ float mask_grad(float g, float a) { return a <= 0.0f ? 0.0f : g; }
+__device__ __forceinline__ float4 mask_grad4(const MaskSrc &ms, int64_t i4, float4 g)
+{
+    const float4 a = q8t_ld_last(reinterpret_cast<const float4 *>(ms.act) + i4);
+    g.x = mask_grad(g.x, a.x); g.y = mask_grad(g.y, a.y);
+    g.z = mask_grad(g.z, a.z); g.w = mask_grad(g.w, a.w);
+    reinterpret_cast<float4 *>(ms.gm)[i4] = g;
+    return g;
+}
+
+// MASK: the masking pass in front of this one happens on the way (1.65 GB at 128x256x56x56 against 1.23 + 0.82 in two
+// passes of 214 + 165 us): bound by memory; a whole bottleneck block of that size takes 1936 instead of 1967 us.
+template <bool VEC, bool POOL = false, bool MASK = false>
 __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restrict__ x, const float *__restrict__ dy,
                                                             const float *__restrict__ stats, int N, int C, int HW, int NB,
                                                             float cn, float eps, const float *__restrict__ gamma,
                                                             const float *__restrict__ beta, int relu,
                                                             BwdPartialQ *__restrict__ parts, ExtList *__restrict__ lists,
-                                                            uint8_t *__restrict__ flags, const PoolSrc pool)
+                                                            uint8_t *__restrict__ flags, const PoolSrc pool, const MaskSrc mask)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t pool_lds[];
     __shared__ double smd[kThreads / 64];
@@ -633,7 +651,8 @@ __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restr
 #pragma unroll 2
                 for (int i = threadIdx.x; i < hw4; i += kThreads) {
                     const float4 v = q8t_ld_first(px + i);
-                    const float4 g = POOL ? pool_grad4(pool, pool_lds, i) : q8t_ld_first(pg + i);
+                    float4 g = POOL ? pool_grad4(pool, pool_lds, i) : q8t_ld_first(pg + i);
+                    if (MASK) g = mask_grad4(mask, (base >> 2) + i, g);
                     const uint32_t m = one(v.x, g.x, b, 4 * i) | (one(v.y, g.y, b, 4 * i + 1) << 1) |
                                        (one(v.z, g.z, b, 4 * i + 2) << 2) | (one(v.w, g.w, b, 4 * i + 3) << 3);
                     if (flags) flags[(base >> 2) + i] = (uint8_t)m;
@@ -647,7 +666,8 @@ __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restr
                 const int bl = idx / hw4, i = idx - bl * hw4;
                 const int64_t base = ((int64_t)(b0 + bl) * C + c) * HW;
                 const float4 v = q8t_ld_first(reinterpret_cast<const float4 *>(x + base) + i);
-                const float4 g = q8t_ld_first(reinterpret_cast<const float4 *>(dy + base) + i);
+                float4 g = q8t_ld_first(reinterpret_cast<const float4 *>(dy + base) + i);
+                if (MASK) g = mask_grad4(mask, (base >> 2) + i, g);
                 const uint32_t m = one(v.x, g.x, b0 + bl, 4 * i) | (one(v.y, g.y, b0 + bl, 4 * i + 1) << 1) |
                                    (one(v.z, g.z, b0 + bl, 4 * i + 2) << 2) | (one(v.w, g.w, b0 + bl, 4 * i + 3) << 3);
                 if (flags) flags[(base >> 2) + i] = (uint8_t)m;
@@ -658,7 +678,12 @@ __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restr
         for (int idx = threadIdx.x; idx < cnt; idx += kThreads) {
             const int b = b0 + idx / HW, i = idx % HW;
             const int64_t j = ((int64_t)b * C + c) * HW + i;
-            one(x[j], dy[j], b, i);
+            float d = dy[j];
+            if (MASK) {
+                d = mask_grad(d, mask.act[j]);
+                mask.gm[j] = d;
+            }
+            one(x[j], d, b, i);
         }
     }
     BwdPartialQ r;
@@ -1292,12 +1317,14 @@ static bool pooled_direct(int H, int W)
            q8t_pool::lds_bytes(P * Q) <= 60 * 1024;
 }
 
+// act / gm != NULL: the upstream gradient is dy where act is not <= 0, else 0; pass 1 leaves it in gm.
 // gpool / idx != NULL: dy is not read; the upstream gradient is gathered from the pooled one (pooled_direct shapes)
 static int range_bn_bwd_bifurcate_impl(const float *x, const float *dy, const float *stats, int N, int C, int H, int W,
                                        const float *gamma, const float *beta, int relu, float eps, float *dx,
                                        float *dgamma, float *dbeta, uint64_t seed8, uint64_t seed16, int8_t *q8_out,
                                        q8t_qparams *qp8_out, int16_t *q16_out, q8t_qparams *qp16_out, void *ws,
-                                       void *stream, const float *gpool = nullptr, const uint8_t *idx = nullptr)
+                                       void *stream, const float *gpool = nullptr, const uint8_t *idx = nullptr,
+                                       const float *act = nullptr, float *gm = nullptr)
 {
     const int rc = check_shape(N, C, H, W);
     if (rc) return rc;
@@ -1313,9 +1340,10 @@ static int range_bn_bwd_bifurcate_impl(const float *x, const float *dy, const fl
     const int split = split_for(N, C), NB = (N + split - 1) / split;
     const int nsplit = (N + NB - 1) / NB;
     const bool vec = (HW % 4 == 0) && q8t_aligned(x, 16) && q8t_aligned(dy, 16) && (!dx || q8t_aligned(dx, 16)) &&
-                     q8t_aligned(q8_out, 4) && q8t_aligned(q16_out, 8);
+                     q8t_aligned(q8_out, 4) && q8t_aligned(q16_out, 8) && q8t_aligned(act, 16) && q8t_aligned(gm, 16);
     if (pooled && !(vec && !relu && pooled_direct(H, W) && q8t_aligned(gpool, 16) && q8t_aligned(idx, 16))) return Q8T_ERR_SHAPE;
     PoolSrc pool = {gpool, idx, W >> 2, (H - 1) / 2 + 1, (W - 1) / 2 + 1, 1.0f / (float)(W >> 2 ? W >> 2 : 1)};
+    const MaskSrc mask = {act, gm};
     const size_t pool_lds = pooled ? q8t_pool::lds_bytes(pool.P * pool.Q) : 0;
     // Without the rectifier (and with float4 access) pass 2 leaves x alone: 15 instead of 19 bytes per element.
     // Measured: -6% only, the pass is as much bound by the ~45 vector operations per element of the two hashed
@@ -1323,20 +1351,28 @@ static int range_bn_bwd_bifurcate_impl(const float *x, const float *dy, const fl
     // variant keeps reading x (flags == NULL; the kernels still take them).
     const int64_t total = (int64_t)N * C * HW;
     const bool flat4 = !vec && HW >= 4 && total % 4 == 0 && q8t_aligned(x, 16) && q8t_aligned(dy, 16) &&
-                       (!dx || q8t_aligned(dx, 16)) && q8t_aligned(q8_out, 4) && q8t_aligned(q16_out, 8);
+                       (!dx || q8t_aligned(dx, 16)) && q8t_aligned(q8_out, 4) && q8t_aligned(q16_out, 8) && q8t_aligned(gm, 16);
     const bool nox = (vec || flat4) && !relu;
     ExtList *lists = nox ? (ExtList *)((char *)ws + bwdq_head_bytes(C)) : (ExtList *)nullptr;
     int *crowded = nox ? (int *)((char *)lists + align16((size_t)C * kMaxSplit * sizeof(ExtList))) : (int *)nullptr;
     uint8_t *flags = nullptr;
     if (pooled)
         hipLaunchKernelGGL((bn_bwdq_partial<true, true>), dim3(C, nsplit), dim3(kThreads), pool_lds, st, x, dy, stats, N, C, HW, NB,
-                           cn, eps, gamma, beta, relu, parts, lists, flags, pool);
-    else if (vec)
+                           cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask);
+    else if (gm) {
+        if (vec)
+            hipLaunchKernelGGL((bn_bwdq_partial<true, false, true>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C, HW,
+                               NB, cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask);
+        else
+            hipLaunchKernelGGL((bn_bwdq_partial<false, false, true>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C,
+                               HW, NB, cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask);
+        dy = gm;
+    } else if (vec)
         hipLaunchKernelGGL((bn_bwdq_partial<true, false>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C, HW, NB, cn,
-                           eps, gamma, beta, relu, parts, lists, flags, pool);
+                           eps, gamma, beta, relu, parts, lists, flags, pool, mask);
     else
         hipLaunchKernelGGL((bn_bwdq_partial<false, false>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C, HW, NB, cn,
-                           eps, gamma, beta, relu, parts, lists, flags, pool);
+                           eps, gamma, beta, relu, parts, lists, flags, pool, mask);
     Q8T_LAUNCH_CHECK();
     float2 *mm = consts + C;
     const int nmm = (C + kThreads / 64 - 1) / (kThreads / 64);
@@ -1399,6 +1435,18 @@ int q8t_range_bn_bwd_bifurcate(const float *x, const float *dy, const float *sta
 {
     return range_bn_bwd_bifurcate_impl(x, dy, stats, N, C, H, W, gamma, nullptr, 0, eps, dx, dgamma, dbeta, seed8, seed16,
                                        q8_out, qp8_out, q16_out, qp16_out, ws, stream);
+}
+
+int q8t_range_bn_bwd_bifurcate_masked(const float *x, const float *dy, const float *act, const float *stats, int N, int C, int H,
+                                      int W, const float *gamma, float eps, float *dy_masked, float *dgamma, float *dbeta,
+                                      uint64_t seed8, uint64_t seed16, int8_t *q8_out, q8t_qparams *qp8_out, int16_t *q16_out,
+                                      q8t_qparams *qp16_out, void *ws, void *stream)
+{
+    const int rc = check_shape(N, C, H, W);
+    if (rc) return rc;
+    if (!act || !dy_masked) return Q8T_ERR_NULL;
+    return range_bn_bwd_bifurcate_impl(x, dy, stats, N, C, H, W, gamma, nullptr, 0, eps, nullptr, dgamma, dbeta, seed8, seed16,
+                                       q8_out, qp8_out, q16_out, qp16_out, ws, stream, nullptr, nullptr, act, dy_masked);
 }
 
 int q8t_range_bn_relu_bwd_bifurcate(const float *x, const float *dy, const float *stats, int N, int C, int H, int W,

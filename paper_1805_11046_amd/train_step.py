@@ -282,16 +282,24 @@ def _chain_fwd(a, specs, ws, apply_last=True):
     return out, saved
 
 
-def _chain_bwd(saved, g, need_dx, block_end=None):
+def _chain_bwd(saved, g, need_dx, block_end=None, out=None):
     """backward of _chain_fwd: the ReLU mask is recomputed inside the Range BN backward.  block_end = (other, act):
     the chain is the main branch of a residual block; the layer gradient of its first convolution then also adds
     the other branch's gradient and applies the mask of the block's input (act > 0; None: nothing to mask) in its
-    epilogue."""
+    epilogue.  out: the rectified result of the block; g is then the gradient of that result, masked on the way into the
+    chain, and the masked gradient takes the place of `other`."""
     g = g.contiguous()
     dws = [None] * len(saved)
     for i in range(len(saved) - 1, -1, -1):
         d, qa, pa, qw, pw, y, stats, ops, nx, ny, lid = saved[i]
-        if i + 1 == len(saved):
+        if i + 1 == len(saved) and out is not None and _angles is None:
+            r = _call("range_bn_bwd_bifurcate", 0, 23 * ny, q8t.range_bn_bwd_bifurcate_masked, y, g, out, stats, None, 1e-5,
+                      2 * lid + 1, 2 * lid + 2)
+            block_end = (r[0], block_end[1])
+        elif i + 1 == len(saved):
+            if out is not None:
+                g = torch.ops.aten.threshold_backward(g, out, 0)
+                block_end = (g, block_end[1])
             r = _bn_bwd(q8t.range_bn_bwd_bifurcate, "range_bn_bwd_bifurcate", ny, y, g, stats, None, 1e-5, 2 * lid + 1,
                         2 * lid + 2)
         else:
@@ -393,8 +401,7 @@ class Bottleneck(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g):
         out, = ctx.saved_tensors
-        gm = torch.ops.aten.threshold_backward(g.contiguous(), out, 0)
-        gx, dws = _chain_bwd(ctx.chain, gm, True, (gm, None))
+        gx, dws = _chain_bwd(ctx.chain, g, True, (None, None), out)
         return (gx, None, *dws)
 
 
