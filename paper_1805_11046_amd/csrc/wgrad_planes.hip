@@ -516,61 +516,85 @@ __global__ __launch_bounds__(kThreads) void wgrad_planes(const int16_t *__restri
 // a = 256*hi + lo + (128 - zg) the gradient level minus its zero point and b = x - zx:
 //   sum a*b = 256*sum(hi*x) + sum(lo*x) + (128 - zg)*colsum(x) - zx*(256*rowsum(hi) + rowsum(lo) + (128 - zg)*Kp)
 // over the Kp padded positions of the range (pads contribute a = 0 and b = 0).
-// A thread owns four neighbouring accumulator entries (four input channels of one output channel and tap) and walks
-// its share of the image ranges with 16-byte loads, several ranges in flight; the wavefronts of a workgroup take
-// interleaved subsets of the ranges and fold through LDS.  (One entry per thread and one range per wavefront, the
-// first form of this kernel, spent most of its time starting workgroups: 31 -> 18 us for 256 -> 256 @14 at batch 256.)
-constexpr int kFinishMaxQ = 16;
-template <class SH>
-__global__ __launch_bounds__(64 * kFinishMaxQ) void wgrad_planes_finish(const int *__restrict__ partial, PGeom g,
-                                                                       const q8t_qparams *__restrict__ qpg,
-                                                                       const q8t_qparams *__restrict__ qpx,
-                                                                       float *__restrict__ dw, int64_t *__restrict__ acc_out)
+// A workgroup owns every tap of a few accumulator registers, so that its results are whole runs of dW (32 channels x 9 taps
+// = 1152 bytes) and leave through LDS in full lines.  (One tap per workgroup, the form before this one, wrote every ninth
+// float of lines that eight other workgroups, on other XCDs, wrote to as well.)  A wavefront reads one tap; a thread holds
+// four neighbouring entries (channels) and LG groups of lanes take every LG-th image range, QW wavefronts more of them
+// where there is one tap only.  The loop only adds; the zero points are applied to the sums.
+// Bound by the read of the partial sums, 75 MB at batch 256 whatever the layer (before -> now): 512 -> 512 @7, 4 ranges
+// 27.8 -> 18.3 us; 256 -> 256 @14, 16 ranges 17.5 -> 14.2; 128 -> 256 @28/2, 32 ranges 21.1 -> 14.6; 64 -> 128 @56/2, 128
+// ranges 23.5 -> 18.2, its 1x1 projection 10.2 -> 4.4.
+template <class SH, int LG>
+struct Finish {
+    static constexpr int QW = SH::TAPS == 1 ? 8 : 1, WAVES = SH::TAPS * QW;
+    static constexpr int REGS = 4 / LG;                      // accumulator registers of a workgroup
+    static constexpr int RUN = 32 * SH::TAPS, ROWS = 2 * REGS;   // floats of a run, runs of a workgroup
+    static constexpr int BLOCKS = SH::HALF_INTS / (REGS * 64 * SH::TAPS);
+};
+template <class SH, int LG>
+__global__ __launch_bounds__(64 * (SH::TAPS == 1 ? 8 : SH::TAPS)) void wgrad_planes_finish(
+    const int *__restrict__ partial, PGeom g, const q8t_qparams *__restrict__ qpg, const q8t_qparams *__restrict__ qpx,
+    float *__restrict__ dw, int64_t *__restrict__ acc_out)
 {
-    __shared__ int64_t fold[kFinishMaxQ][4][64];
+    using F = Finish<SH, LG>;
     constexpr int TAPS = SH::TAPS, NBV = SH::NBV;
-    const int sub = blockIdx.y;
-    const int cg = sub % g.ncg, rg = sub / g.ncg;
-    const int ln = threadIdx.x & 63, quarter = threadIdx.x >> 6, nq = blockDim.x >> 6;
-    const int idx = (blockIdx.x * 64 + ln) * 4;   // ((((kt*2 + ch)*TAPS + tap)*16 + reg)*64 + lane; HALF_INTS is a multiple of 256
-    const int lane = idx & 63, reg = (idx >> 6) & 15, rest = idx >> 10;
-    const int tap = rest % TAPS, ch = (rest / TAPS) & 1, kt = rest / (2 * TAPS);
+    __shared__ int64_t fold[F::QW][F::ROWS][F::RUN];
+    const int cg = (int)blockIdx.y % g.ncg, rg = (int)blockIdx.y / g.ncg;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), ln = threadIdx.x & 63;
+    const int tap = wave % TAPS, qw = wave / TAPS;
+    constexpr int GL = 64 / LG;                               // lanes of a group
+    const int grp = ln / GL, e = (ln % GL) * 4;               // entry within the workgroup's REGS * 64
+    const int half = blockIdx.x / (16 / F::REGS), reg = (blockIdx.x % (16 / F::REGS)) * F::REGS + (e >> 6), lane = e & 63;
+    const int kt = half >> 1, ch = half & 1;
+    const int idx = ((half * TAPS + tap) * 16 + reg) * 64 + lane;
     // 32x32 accumulator tile: lane = column + 32 * ((row / 4) % 2), register = 4 * (row / 8) + row % 4
     const int row_l = kt * 32 + 8 * (reg >> 2) + 4 * (lane >> 5) + (reg & 3), ch_l = ch * 32 + (lane & 31);
     const int bv = SH::bvar(tap);
 
-    const int zsg = qpg->zero_point - (1 << (qpg->bits - 1)), zsx = qpx->zero_point - (1 << (qpx->bits - 1));
-    const int64_t ca = 128 - zsg;
-    int64_t v[4] = {0, 0, 0, 0};
+    int64_t v[4] = {0, 0, 0, 0}, cs[4] = {0, 0, 0, 0}, rs = 0;
+    const int64_t pitch = (int64_t)g.nrg * g.ncg * SH::PART_INTS;
+    const int *base = partial + ((int64_t)rg * g.ncg + cg) * SH::PART_INTS;
 #pragma unroll 4
-    for (int kr = quarter; kr < g.S; kr += nq) {
-        const int *p = partial + ((int64_t)(kr * g.nrg + rg) * g.ncg + cg) * SH::PART_INTS;
-        const int nimg = min(g.N, (kr + 1) * g.ipr) - kr * g.ipr;
-        const int64_t Kp = (int64_t)((nimg + SH::NIMG - 1) / SH::NIMG) * SH::NBAND * KC;
+    for (int kr = qw * LG + grp; kr < g.S; kr += F::QW * LG) {
+        const int *p = base + kr * pitch;
         const v4i hi = *reinterpret_cast<const v4i *>(p + idx), lo = *reinterpret_cast<const v4i *>(p + SH::HALF_INTS + idx);
-        const v4i csv = *reinterpret_cast<const v4i *>(p + SH::TILE_INTS + bv * CT + ch_l);
-        const int64_t rsh = p[SH::TILE_INTS + NBV * CT + row_l], rsl = p[SH::TILE_INTS + NBV * CT + KT + row_l];
-        const int64_t common = (int64_t)zsx * (256 * rsh + rsl + ca * Kp);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] += 256 * (int64_t)hi[j] + (int64_t)lo[j] + ca * (int64_t)csv[j] - common;
-    }
-    if (nq > 1) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) fold[quarter][j][ln] = v[j];
-        __syncthreads();
-        if (quarter != 0) return;
+        const v4i c = *reinterpret_cast<const v4i *>(p + SH::TILE_INTS + bv * CT + ch_l);
+        rs += 256 * (int64_t)p[SH::TILE_INTS + NBV * CT + row_l] + p[SH::TILE_INTS + NBV * CT + KT + row_l];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            v[j] = 0;
-            for (int q = 0; q < nq; ++q) v[j] += fold[q][j][ln];
+            v[j] += 256 * (int64_t)hi[j] + lo[j];
+            cs[j] += c[j];
         }
     }
-    const double sc = (double)(qpg->scale * qpx->scale);
+    const int zsg = qpg->zero_point - (1 << (qpg->bits - 1)), zsx = qpx->zero_point - (1 << (qpx->bits - 1));
+    const int64_t ca = 128 - zsg;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int64_t o = ((int64_t)(rg * KT + row_l) * g.C + cg * CT + ch_l + j) * TAPS + tap;
-        if (acc_out) acc_out[o] = v[j];
-        if (dw) dw[o] = (float)((double)v[j] * sc);
+    for (int j = 0; j < 4; ++j) v[j] += ca * cs[j] - (int64_t)zsx * rs;
+#pragma unroll
+    for (int m = GL; m < 64; m *= 2)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] += __shfl_xor((long long)v[j], m, 64);
+    const int run = 2 * (e >> 6) + (lane >> 5);
+    if (grp == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fold[qw][run][((lane & 31) + j) * TAPS + tap] = v[j];
+    }
+    __syncthreads();
+    // padded positions of all ranges together (every range but the last is whole chunks)
+    const int full = g.S - 1, rest = g.N - full * g.ipr;
+    const int64_t Kp = ((int64_t)full * (g.ipr / SH::NIMG) + (rest + SH::NIMG - 1) / SH::NIMG) * SH::NBAND * KC;
+    const int64_t pads = (int64_t)zsx * ca * Kp;
+    const double sc = (double)(qpg->scale * qpx->scale);
+    for (int i = threadIdx.x; i < F::ROWS * F::RUN; i += 64 * F::WAVES) {
+        const int rw = i / F::RUN, k = i - rw * F::RUN;
+        int64_t t = -pads;
+#pragma unroll
+        for (int q = 0; q < F::QW; ++q) t += fold[q][rw][k];
+        const int r = (blockIdx.x % (16 / F::REGS)) * F::REGS + (rw >> 1);
+        const int row = rg * KT + kt * 32 + 8 * (r >> 2) + 4 * (rw & 1) + (r & 3);
+        const int64_t o = ((int64_t)row * g.C + cg * CT + ch * 32) * TAPS + k;
+        if (acc_out) acc_out[o] = t;
+        if (dw) dw[o] = (float)((double)t * sc);
     }
 }
 
@@ -615,11 +639,15 @@ int launch_planes(const q8t_conv_desc *d, const int16_t *g16, const q8t_qparams 
     if (q8t_allow_lds(optin, (const void *)wgrad_planes<SH>, SH::SMEM) != Q8T_OK) return Q8T_ERR_HIP;
     hipLaunchKernelGGL(wgrad_planes<SH>, dim3(blocks), dim3(kThreads), SH::SMEM, st, g16, x, qg, qx, g, (int *)ws);
     Q8T_LAUNCH_CHECK();
-    // wavefronts per workgroup: each walks two ranges or more (measured best: 16 wavefronts of one range each spend their time starting up)
-    int nq = 1;
-    while (nq < kFinishMaxQ && g.S >= 4 * nq) nq *= 2;
-    hipLaunchKernelGGL(wgrad_planes_finish<SH>, dim3(SH::HALF_INTS / 256, per), dim3(64 * nq), 0, st, (const int *)ws, g, qg, qx,
-                       dw, acc_out);
+    // Lane groups: enough of them for about 4000 wavefronts, no more than there are ranges.  With four groups everywhere
+    // 512 -> 512 @7 (64 tiles) took 116 us for the whole call against 105 with one, 256 -> 256 @14 (16 tiles) 95 against 91.
+#define Q8T_FINISH(LG)                                                                                                  \
+    hipLaunchKernelGGL((wgrad_planes_finish<SH, LG>), dim3(Finish<SH, LG>::BLOCKS, per), dim3(64 * Finish<SH, LG>::WAVES), 0, st, \
+                       (const int *)ws, g, qg, qx, dw, acc_out)
+    if (per < 16 && g.S >= 4) Q8T_FINISH(4);
+    else if (per < 32 && g.S >= 2) Q8T_FINISH(2);
+    else Q8T_FINISH(1);
+#undef Q8T_FINISH
     Q8T_LAUNCH_CHECK();
     return Q8T_OK;
 }
