@@ -119,7 +119,8 @@ EXPORTED = tuple(sorted(_SIGS))
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    # a plain address: the declared argument types convert it, an object made here would only be converted once more
+    return None if t is None else t.data_ptr()
 
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -131,8 +132,8 @@ def _stream():
     ~0.2 ms of host time per call (it re-checks the environment), which starves the GPU when a step makes
     hundreds of library calls; the raw accessor is a plain C call."""
     if _raw_stream is not None:
-        return C.c_void_p(_raw_stream(_raw_device()))
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return _raw_stream(_raw_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(rc, where):
