@@ -23,12 +23,13 @@
 //              (launch, one or two dependent loads, the fold through LDS): 64x128x256 takes 3.5 / 3.5 / 8.0 us for
 //              forward / dgrad / wgrad (18.7 / 12.2 / 8.0 before), 256x1000x512 4.4 / 5.0 / 6.6 (23.9 / 15.8 / 19.7),
 //              512x2048x2048 10.5 / 14.7 / 19.
-//   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  Bound by
-//              the operand bytes a compute unit gets from L2 (about 17 per clock: 540 MB in 60 us for 2048x4096x4096,
-//              MFMA pipe 22% busy): 67 / 57 / 113 us at that size (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s.
+//   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  67 / 57 / 113 us
+//              at 2048x4096x4096 (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s.  The wavefronts wait for issue (44% of their
+//              cycles) more than for data: MFMA pipe 22% busy, L2 hits 92% at 304 clocks a read, LDS active a third of the time.
 // Measured and dropped: prefetching the next K-step in fc_direct (more registers, fewer wavefronts: 7.5 -> 8.4 us at
 // 1024^3), RS operands through LDS and the transposing reads ds_read_b64_tr_b8 / _b16 with 32x32x32 MFMAs (half the
-// instructions, same time: neither kernel is bound by instruction issue).
+// instructions, same time), K-steps of 128 in fc_tile with one or two register sets (whole 128-byte lines per row: 68 / 61 and
+// 68 / 65 us against 70 / 64 on the same box, 3000x333x2777 30 -> 38).
 #include "q8t_common.h"
 #include "q8t_internal.h"
 #include "gemm_core.h"
