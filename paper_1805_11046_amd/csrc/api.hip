@@ -98,7 +98,7 @@ const char *q8t_version(void) { return "q8t 0.1 (gfx950)"; }
 size_t q8t_qgemm_workspace_size(int M, int N, int K, int which)
 {
     if (M <= 0 || N <= 0 || K <= 0 || which < 0 || which > 2) return 0;
-    return q8t_fc_supported(which, M, N, K) ? 0 : q8t_generic_fc_ws(which, M, N, K);
+    return q8t_fc_supported(which, M, N, K) ? q8t_fc_ws(which, M, N, K) : q8t_generic_fc_ws(which, M, N, K);
 }
 
 int q8t_qgemm_fwd(const int8_t *qx, const q8t_qparams *px, const int8_t *qw, const q8t_qparams *pw, int M, int N,
@@ -107,7 +107,7 @@ int q8t_qgemm_fwd(const int8_t *qx, const q8t_qparams *px, const int8_t *qw, con
     const int rc = fc_check(M, N, K, qx, px, qw, pw, y, acc_out);
     if (rc) return rc;
     if (K > kMaxRed32) return Q8T_ERR_OVERFLOW;
-    if (q8t_fc_supported(0, M, N, K)) return q8t_fc(0, qx, px, qw, pw, M, N, K, y, acc_out, (hipStream_t)stream);
+    if (q8t_fc_supported(0, M, N, K)) return q8t_fc(0, qx, px, qw, pw, M, N, K, y, acc_out, ws, (hipStream_t)stream);
     return q8t_generic_fc(0, qx, px, qw, pw, M, N, K, y, acc_out, ws, (hipStream_t)stream);
 }
 
@@ -117,7 +117,7 @@ int q8t_qgemm_dgrad(const int8_t *qdy, const q8t_qparams *pg, const int8_t *qw, 
     const int rc = fc_check(M, N, K, qdy, pg, qw, pw, dx, acc_out);
     if (rc) return rc;
     if (N > kMaxRed32) return Q8T_ERR_OVERFLOW;
-    if (q8t_fc_supported(1, M, N, K)) return q8t_fc(1, qdy, pg, qw, pw, M, N, K, dx, acc_out, (hipStream_t)stream);
+    if (q8t_fc_supported(1, M, N, K)) return q8t_fc(1, qdy, pg, qw, pw, M, N, K, dx, acc_out, ws, (hipStream_t)stream);
     return q8t_generic_fc(1, qdy, pg, qw, pw, M, N, K, dx, acc_out, ws, (hipStream_t)stream);
 }
 
@@ -126,7 +126,7 @@ int q8t_qgemm_wgrad(const int8_t *qx, const q8t_qparams *px, const int16_t *qdy1
 {
     const int rc = fc_check(M, N, K, qx, px, qdy16, pg16, dw, acc_out);
     if (rc) return rc;
-    if (q8t_fc_supported(2, M, N, K)) return q8t_fc(2, qx, px, qdy16, pg16, M, N, K, dw, acc_out, (hipStream_t)stream);
+    if (q8t_fc_supported(2, M, N, K)) return q8t_fc(2, qx, px, qdy16, pg16, M, N, K, dw, acc_out, ws, (hipStream_t)stream);
     return q8t_generic_fc(2, qdy16, pg16, qx, px, M, N, K, dw, acc_out, ws, (hipStream_t)stream);
 }
 

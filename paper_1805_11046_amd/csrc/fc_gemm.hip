@@ -22,7 +22,8 @@
 //              tile of 32x64 (wgrad 64x64) results and split its reduction, or own a tile each.  Bound by latency
 //              (launch, one or two dependent loads, the fold through LDS): 64x128x256 takes 3.5 / 3.5 / 8.0 us for
 //              forward / dgrad / wgrad (18.7 / 12.2 / 8.0 before), 256x1000x512 4.4 / 5.0 / 6.6 (23.9 / 15.8 / 19.7),
-//              512x2048x2048 10.5 / 14.7 / 19.
+//              512x2048x2048 10.5 / 14.7 / 19.  Few results and a long reduction: slices of it in workgroups of their own and
+//              fc_fold behind them.
 //   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  67 / 57 / 113 us
 //              at 2048x4096x4096 (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s.  The wavefronts wait for issue (44% of their
 //              cycles) more than for data: MFMA pipe 22% busy, L2 hits 92% at 304 clocks a read, LDS active a third of the time.
@@ -49,6 +50,8 @@ struct FcArgs {
     int lda, ldb;        // elements between neighbours along the slow index
     float *out;          // nullable
     void *acc;           // nullable: int32 (forward, dgrad) or int64 (wgrad)
+    int64_t *partial;    // not NULL: a slice of the reduction leaves its share of the results here, [slice][rows][cols]
+    int slice;           // K-steps per slice
     int vec;             // float results leave in 16-byte stores
     int tn, tiles;       // column tiles, all tiles
 };
@@ -110,20 +113,26 @@ __device__ __forceinline__ Zero zero_points(const FcArgs &p)
 }
 
 // four neighbouring results of one row; v[j] the accumulators, rs / cs the byte sums of the row and the columns
-// (wgrad: cs = 256 * sum hi + sum lo)
+// (wgrad: cs = 256 * sum hi + sum lo), red the entries of the reduction in them
 template <int WHICH>
-__device__ __forceinline__ void finish4(const FcArgs &p, const Zero &z, int row, int col, const int (&hi)[4], const int (&lo)[4],
-                                        int rs, const int (&cs)[4], const int (&cs1)[4])
+__device__ __forceinline__ void finish4(const FcArgs &p, const Zero &z, int red, int row, int col, const int (&hi)[4],
+                                        const int (&lo)[4], int rs, const int (&cs)[4], const int (&cs1)[4])
 {
     const int64_t o = (int64_t)row * p.cols + col;
     float f[4];
     if (WHICH != WGRAD) {
-        const uint32_t kzz = (uint32_t)p.red * (uint32_t)z.za * (uint32_t)z.zb - (uint32_t)z.zb * (uint32_t)rs;
+        const uint32_t kzz = (uint32_t)red * (uint32_t)z.za * (uint32_t)z.zb - (uint32_t)z.zb * (uint32_t)rs;
         int c[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             c[j] = (int)((uint32_t)hi[j] + kzz - (uint32_t)z.za * (uint32_t)cs[j]);   // fits 32 bits by contract
             f[j] = z.sc * (float)c[j];
+        }
+        if (p.partial) {
+            int64_t *d = p.partial + (int64_t)blockIdx.y * p.rows * p.cols + o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = c[j];
+            return;
         }
         if (p.acc) {
             int32_t *d = (int32_t *)p.acc + o;
@@ -131,12 +140,18 @@ __device__ __forceinline__ void finish4(const FcArgs &p, const Zero &z, int row,
             for (int j = 0; j < 4; ++j) d[j] = c[j];
         }
     } else {
-        const int64_t t = (int64_t)(128 - z.zb) * rs + (int64_t)p.red * z.za * (z.zb - 128);
+        const int64_t t = (int64_t)(128 - z.zb) * rs + (int64_t)red * z.za * (z.zb - 128);
         int64_t c[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             c[j] = 256 * (int64_t)hi[j] + lo[j] + t - (int64_t)z.za * (256 * (int64_t)cs[j] + cs1[j]);
             f[j] = (float)((double)c[j] * (double)z.sc);
+        }
+        if (p.partial) {
+            int64_t *d = p.partial + (int64_t)blockIdx.y * p.rows * p.cols + o;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = c[j];
+            return;
         }
         if (p.acc) {
             int64_t *d = (int64_t *)p.acc + o;
@@ -156,7 +171,8 @@ __device__ __forceinline__ void finish4(const FcArgs &p, const Zero &z, int row,
 }
 
 // ---- small products: no LDS in the main loop ---------------------------------------------------------------------
-// KS wavefronts share a tile's reduction (K-steps of 64, dealt out round-robin); WAVES / KS tiles per workgroup.
+// KS wavefronts share a tile's reduction (K-steps of 64, dealt out round-robin); WAVES / KS tiles per workgroup.  Where the
+// tiles are few and the reduction is long, blockIdx.y takes slices of it, and fc_fold adds them up.
 template <int WHICH, int WAVES, int KS>
 __global__ __launch_bounds__(WAVES * 64) void fc_direct(const FcArgs p)
 {
@@ -203,7 +219,8 @@ __global__ __launch_bounds__(WAVES * 64) void fc_direct(const FcArgs p)
     for (int i = 0; i < MT; ++i) sa[i] = 0;
 
     const int steps = (p.red + 63) >> 6;
-    for (int s = ks; s < steps; s += KS) {
+    const int s0 = blockIdx.y * p.slice, s1 = min(steps, s0 + p.slice), red = min(s1 * 64, p.red) - s0 * 64;
+    for (int s = s0 + ks; s < s1; s += KS) {
         const int kk = s * 64 + kb * 16, k1 = min(kk, p.red - 16), skip = kk - k1;
         uint4 af[MT], bf[PL][4];
         uint32_t ra[RSA ? 16 : 1], rb[RSB && PL == 1 ? 16 : 1];
@@ -326,7 +343,7 @@ __global__ __launch_bounds__(WAVES * 64) void fc_direct(const FcArgs p)
                     hi[j] = acc[0][i][j][r];
                     lo[j] = acc[PL - 1][i][j][r];
                 }
-                if (ok && col_ok) finish4<WHICH>(p, z, row, col0, hi, lo, s_rs[sub][i * 16 + kb * 4 + r], cs, cs1);
+                if (ok && col_ok) finish4<WHICH>(p, z, red, row, col0, hi, lo, s_rs[sub][i * 16 + kb * 4 + r], cs, cs1);
             }
     } else {
         // every wavefront leaves its partial tile in LDS and folds its share of the units
@@ -370,8 +387,40 @@ __global__ __launch_bounds__(WAVES * 64) void fc_direct(const FcArgs p)
             const int unit = ks * SHARE + u, i = unit >> 2, r = unit & 3;
             bool ok;
             const int row = row_of(i, r, ok);
-            if (ok && col_ok) finish4<WHICH>(p, z, row, col0, sum[0][u], sum[PL - 1][u], s_rs[sub][i * 16 + kb * 4 + r], cs, cs1);
+            if (ok && col_ok) finish4<WHICH>(p, z, red, row, col0, sum[0][u], sum[PL - 1][u], s_rs[sub][i * 16 + kb * 4 + r], cs, cs1);
         }
+    }
+}
+
+// adds up the slices of a split reduction: 32 neighbouring results per workgroup, eight threads share the slices of a
+// result.  Few results and up to 64 slices: the loads of a thread have to be in flight together.
+constexpr int kFoldResults = 32, kFoldGroups = 8;
+template <bool WIDE>   // int64 results (wgrad)
+__global__ __launch_bounds__(kFoldResults * kFoldGroups) void fc_fold(const int64_t *__restrict__ partial, int slices, int64_t count,
+                                                                     const q8t_qparams *__restrict__ qa,
+                                                                     const q8t_qparams *__restrict__ qb, float *__restrict__ out,
+                                                                     void *__restrict__ acc)
+{
+    __shared__ int64_t part[kFoldGroups][kFoldResults];
+    const int e = threadIdx.x % kFoldResults, g = threadIdx.x / kFoldResults;
+    const int64_t i = (int64_t)blockIdx.x * kFoldResults + e;
+    const float sc = qa->scale * qb->scale;
+    int64_t v = 0;
+    if (i < count) {
+#pragma unroll 8
+        for (int z = g; z < slices; z += kFoldGroups) v += partial[z * count + i];
+    }
+    part[g][e] = v;
+    __syncthreads();
+    if (g != 0 || i >= count) return;
+#pragma unroll
+    for (int k = 1; k < kFoldGroups; ++k) v += part[k][e];
+    if (WIDE) {
+        if (acc) ((int64_t *)acc)[i] = v;
+        if (out) out[i] = (float)((double)v * (double)sc);
+    } else {
+        if (acc) ((int32_t *)acc)[i] = (int32_t)v;
+        if (out) out[i] = sc * (float)(int32_t)v;
     }
 }
 
@@ -667,68 +716,128 @@ __global__ __launch_bounds__(TT, 2) void fc_tile(const FcArgs p)
                 hi[j] = acc[0][i][j][r];
                 lo[j] = acc[PL - 1][i][j][r];
             }
-            if (ok && col_ok) finish4<WHICH>(p, z, row, col0, hi, lo, s_rs[lr], cs, cs1);
+            if (ok && col_ok) finish4<WHICH>(p, z, p.red, row, col0, hi, lo, s_rs[lr], cs, cs1);
         }
 }
 
 constexpr int kMaxRed = 65536;   // |a*b| <= 2^14 per product of two signed bytes: partial sums stay below 2^31
+
+struct Plan {
+    int rows, cols, red;
+    int tile;               // fc_tile instead of fc_direct
+    int tn;                 // column tiles
+    int64_t tiles;
+    int ks, slice, slices;  // fc_direct: wavefronts per tile, K-steps per slice of the reduction, slices
+};
+
+Plan plan_for(int which, int M, int N, int K)
+{
+    Plan p;
+    p.rows = which == 2 ? K : M;
+    p.cols = which == 1 ? K : N;
+    p.red = which == 0 ? K : (which == 1 ? N : M);
+    const int64_t t128 = (int64_t)((p.rows + 127) / 128) * ((p.cols + 127) / 128);
+    const int steps = (p.red + 63) / 64;
+    p.ks = p.slices = 1;
+    p.slice = steps;
+    // 128x128 tiles from half a tile per compute unit on: 1500^3 (144 tiles) takes 22 / 18 / 32 us in tiles and 22 / 20 / 34
+    // in fc_direct, 2048x616x3680's forward (90 tiles) 40 against 31; the weight gradient splits its reduction eight
+    // ways there and changes over a little later (128 tiles: 38 against 26 us).  With a single K-step a result narrower
+    // than a tile pays for the padding (weight gradient 65536x16x64 13.5 against 8.6 us).
+    p.tile = t128 >= (which == 2 ? 140 : 128) && (p.red > 64 || (p.red == 64 && p.rows > 64 && p.cols > 64));
+    p.tn = p.tile ? (p.cols + 127) / 128 : (p.cols + 63) / 64;
+    const int tr = which == 2 ? 64 : 32;
+    p.tiles = p.tile ? t128 : (int64_t)((p.rows + tr - 1) / tr) * p.tn;
+    if (p.tile) return p;
+    // wavefronts per tile: enough of them to fill the chip (two per SIMD; limits of 512 .. 8192 wavefronts were swept, and
+    // fewer leave the 512x2048x2048 forward at 24 instead of 10.5 us), no more than there are K-steps
+    while (p.ks < 8 && 2 * p.ks <= steps && p.tiles * p.ks < 2048) p.ks *= 2;
+    // A tile is shared by four wavefronts even where they outnumber the K-steps: they share its results, too (64-bit
+    // arithmetic in the weight gradient).  One K-step, 64x64x256: 4.9 / 5.2 / 8.4 -> 3.8 / 3.8 / 6.1 us; with 460 tiles
+    // the weight gradient is back to 8.6 with a wavefront a tile against 10.9.
+    if (p.ks == 2 || (p.ks == 1 && p.tiles <= 256)) p.ks = 4;
+    // Few tiles: slices of the reduction, two K-steps per wavefront or more, as many as give every compute unit a
+    // workgroup.  Unsplit -> split: weight gradient 16x16x65536 198 -> 11 us, 64x64x4096 18.1 -> 10.8, 12x237x2065 14.2 ->
+    // 12.1, 1000x256x4096 (64 tiles) 19.6 -> 18.3; forward 64x64x16384 24.4 -> 7.0, 64x64x4096 8.7 -> 6.7; layer gradient
+    // 16x64x4096 12.0 -> 7.2.  Two or three slices over more tiles cost what they gain until the reduction is longer (128
+    // tiles: 64 K-steps 9.5 -> 13.3, 79 30.6 -> 21.9).
+    if (p.ks == 8 && steps >= 32 && (p.tiles <= 64 || steps >= 128)) {
+        const int n = min((int)min((int64_t)64, 256 / p.tiles), steps / 16);
+        if (n > 1) {
+            p.slice = (steps + n - 1) / n;
+            p.slices = (steps + p.slice - 1) / p.slice;
+        }
+    }
+    return p;
+}
 
 }  // namespace
 
 // sizes the kernels above take: whole groups of four columns (rows) and one 16-entry piece of the reduction exist
 bool q8t_fc_supported(int which, int M, int N, int K)
 {
+    // A reduction of less than one K-step under many results is bound by their stores.  Up to about the size of the last
+    // cache the general kernel's leave faster (16384x1000x16 25 against 30 us, 65536x1000x16 79 against 104), beyond it not
+    // (16384x16384x16 401 against 340), and below 4 M results neither (2280x1571x18 10.8 both).
+    const int64_t results = (int64_t)M * (which == 0 ? N : K);
+    if (which < 2 && (which == 0 ? K : N) < 64 && results >= 4000000 && results <= (1 << 27)) return false;
     if (which == 0) return K >= 16 && N >= 4;
     if (which == 1) return N >= 16 && K >= 4;
     return M >= 16 && M <= kMaxRed && N >= 4 && K >= 4;
 }
 
-int q8t_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb, int M, int N, int K,
-           float *out_f, void *out_acc, hipStream_t st)
+size_t q8t_fc_ws(int which, int M, int N, int K)
 {
+    const Plan pl = plan_for(which, M, N, K);
+    return pl.slices > 1 ? (size_t)pl.slices * pl.rows * pl.cols * sizeof(int64_t) : 0;
+}
+
+int q8t_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb, int M, int N, int K,
+           float *out_f, void *out_acc, void *ws, hipStream_t st)
+{
+    const Plan pl = plan_for(which, M, N, K);
+    if (pl.slices > 1 && (!ws || !q8t_aligned(ws, 8))) return Q8T_ERR_WORKSPACE;
     FcArgs p;
     p.a = (const int8_t *)a;
     p.b = b;
     p.qa = qa;
     p.qb = qb;
-    p.rows = which == 2 ? K : M;
-    p.cols = which == 1 ? K : N;
-    p.red = which == 0 ? K : (which == 1 ? N : M);
+    p.rows = pl.rows;
+    p.cols = pl.cols;
+    p.red = pl.red;
     p.lda = which == 1 ? N : K;
     p.ldb = N;
     p.out = out_f;
     p.acc = out_acc;
+    p.partial = pl.slices > 1 ? (int64_t *)ws : nullptr;
+    p.slice = pl.slice;
     p.vec = p.cols % 4 == 0 && q8t_aligned(out_f, 16);
-    const int64_t t128 = (int64_t)((p.rows + 127) / 128) * ((p.cols + 127) / 128);
-    const int steps = (p.red + 63) / 64;
-    // 128x128 tiles from half a tile per compute unit on: 1500^3 (144 tiles) takes 22 / 18 / 32 us in tiles and 22 / 20 / 34
-    // in fc_direct, 2048x616x3680's forward (90 tiles) 40 against 31; the weight gradient splits its reduction eight
-    // ways there and changes over a little later (128 tiles: 38 against 26 us)
-    if (t128 >= (which == 2 ? 140 : 128) && p.red >= 64) {
-        p.tn = (p.cols + 127) / 128;
-        p.tiles = (int)t128;
-        const dim3 grid(q8t_gemm::xcd_grid(t128));
+    p.tn = pl.tn;
+    p.tiles = (int)pl.tiles;
+    if (pl.tile) {
+        const dim3 grid(q8t_gemm::xcd_grid(pl.tiles));
         if (which == 0) hipLaunchKernelGGL(fc_tile<FWD>, grid, dim3(TT), 0, st, p);
         else if (which == 1) hipLaunchKernelGGL(fc_tile<DGRAD>, grid, dim3(TT), 0, st, p);
         else hipLaunchKernelGGL(fc_tile<WGRAD>, grid, dim3(TT), 0, st, p);
         Q8T_LAUNCH_CHECK();
         return Q8T_OK;
     }
-    const int tr = which == 2 ? 64 : 32;
-    p.tn = (p.cols + 63) / 64;
-    const int64_t tiles = (int64_t)((p.rows + tr - 1) / tr) * p.tn;
-    p.tiles = (int)tiles;
-    // wavefronts per tile: enough of them to fill the chip (two per SIMD; limits of 512 .. 8192 wavefronts were swept, and
-    // fewer leave the 512x2048x2048 forward at 24 instead of 10.5 us), no more than there are K-steps
-    int ks = 1;
-    while (ks < 8 && 2 * ks <= steps && tiles * ks < 2048) ks *= 2;
-    if (ks == 2) ks = 4;
-#define Q8T_GO(W, WAVES, KS) \
-    hipLaunchKernelGGL((fc_direct<W, WAVES, KS>), dim3((unsigned)((tiles + (WAVES / KS) - 1) / (WAVES / KS))), dim3(WAVES * 64), 0, st, p)
-    if (which == 0) { if (ks == 8) Q8T_GO(FWD, 8, 8); else if (ks == 4) Q8T_GO(FWD, 4, 4); else Q8T_GO(FWD, 4, 1); }
-    else if (which == 1) { if (ks == 8) Q8T_GO(DGRAD, 8, 8); else if (ks == 4) Q8T_GO(DGRAD, 4, 4); else Q8T_GO(DGRAD, 4, 1); }
-    else { if (ks == 8) Q8T_GO(WGRAD, 8, 8); else if (ks == 4) Q8T_GO(WGRAD, 4, 4); else Q8T_GO(WGRAD, 4, 1); }
+#define Q8T_GO(W, WAVES, KS)                                                                                                  \
+    hipLaunchKernelGGL((fc_direct<W, WAVES, KS>), dim3((unsigned)((pl.tiles + (WAVES / KS) - 1) / (WAVES / KS)), (unsigned)pl.slices), \
+                       dim3(WAVES * 64), 0, st, p)
+    if (which == 0) { if (pl.ks == 8) Q8T_GO(FWD, 8, 8); else if (pl.ks == 4) Q8T_GO(FWD, 4, 4); else Q8T_GO(FWD, 4, 1); }
+    else if (which == 1) { if (pl.ks == 8) Q8T_GO(DGRAD, 8, 8); else if (pl.ks == 4) Q8T_GO(DGRAD, 4, 4); else Q8T_GO(DGRAD, 4, 1); }
+    else { if (pl.ks == 8) Q8T_GO(WGRAD, 8, 8); else if (pl.ks == 4) Q8T_GO(WGRAD, 4, 4); else Q8T_GO(WGRAD, 4, 1); }
 #undef Q8T_GO
     Q8T_LAUNCH_CHECK();
+    if (pl.slices > 1) {
+        const int64_t count = (int64_t)pl.rows * pl.cols;
+        const dim3 grid((unsigned)((count + kFoldResults - 1) / kFoldResults)), block(kFoldResults * kFoldGroups);
+        if (which == 2)
+            hipLaunchKernelGGL(fc_fold<true>, grid, block, 0, st, (const int64_t *)ws, pl.slices, count, qa, qb, out_f, out_acc);
+        else
+            hipLaunchKernelGGL(fc_fold<false>, grid, block, 0, st, (const int64_t *)ws, pl.slices, count, qa, qb, out_f, out_acc);
+        Q8T_LAUNCH_CHECK();
+    }
     return Q8T_OK;
 }

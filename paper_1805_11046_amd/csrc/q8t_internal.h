@@ -10,11 +10,12 @@
 int q8t_generic_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb, int M,
                    int N, int K, float *out_f, void *out_acc, void *ws, hipStream_t st);
 size_t q8t_generic_fc_ws(int which, int M, int N, int K);
-// FC products on operands read in place (fc_gemm.hip), no workspace; operand order as in the calls of q8t.h: a = X or dY,
+// FC products on operands read in place (fc_gemm.hip); workspace only where the reduction is split; operand order as in the calls of q8t.h: a = X or dY,
 // b = W, or for wgrad a = X (8 bit), b = dY16.  false: sizes that stay with the general kernel
 bool q8t_fc_supported(int which, int M, int N, int K);
+size_t q8t_fc_ws(int which, int M, int N, int K);
 int q8t_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb, int M, int N, int K,
-           float *out_f, void *out_acc, hipStream_t st);
+           float *out_f, void *out_acc, void *ws, hipStream_t st);
 int q8t_generic_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b,
                      const q8t_qparams *qb, float *out_f, void *out_acc, void *ws, hipStream_t st);
 size_t q8t_generic_conv_ws(int which, const q8t_conv_desc *d);

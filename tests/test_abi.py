@@ -97,3 +97,13 @@ def test_packed_filter_sizes_follow_the_kernel_that_serves_the_shape():
     L = binding._lib
     assert L.q8t_qconv_pack_multi(1, None, None, None, None, None) == -1
     assert L.q8t_qconv_pack_multi(0, None, None, None, None, None) == 0
+
+
+def test_long_reductions_under_few_results_are_split():
+    # slices of the reduction in workgroups of their own leave their partial results in the workspace
+    _lib_path()
+    from paper_1805_11046_amd import binding
+    size = binding._lib.q8t_qgemm_workspace_size
+    for M, N, K, which in ((65536, 64, 64, 2), (64, 64, 16384, 0), (61, 29390, 29, 1)):
+        assert size(M, N, K, which) >= 2 * 8 * {0: M * N, 1: M * K, 2: K * N}[which]
+    assert size(256, 1000, 512, 0) == 0

@@ -51,3 +51,31 @@ def test_fc_edges(M, N, K, off):
     odw, oacc = oracle.qgemm_wgrad(sx, px, sg16, pg16)
     same_ints(host(acc), oacc)
     same_ints(host(dw), odw)
+
+
+# few results under a long reduction: slices of it in workgroups of their own, the last one shorter, pieces that reach back
+# into the slice before, results that hang over the edge of a tile
+@pytest.mark.parametrize("M,N,K", [
+    (7, 5, 2047), (7, 5, 2048), (6, 5, 27421), (33, 70, 4097), (16, 4096, 4100), (65, 66, 16400), (480, 260, 9000),   # forward
+    (5, 2049, 6), (61, 29390, 29), (96, 5000, 130), (1607, 8229, 14),                                                 # layer gradient
+    (2047, 9, 34), (2065, 12, 237), (65535, 4, 5), (65536, 70, 19), (4101, 600, 195), (8300, 70, 515),                # weight gradient
+])
+def test_fc_split_reduction(M, N, K):
+    test_fc_edges(M, N, K, 0)
+
+
+# one K-step: tiles shared by more wavefronts than it has steps, narrow results, and the general kernel's range
+@pytest.mark.parametrize("M,N,K", [(16, 16, 16), (64, 1000, 1000), (64, 1025, 1030), (64, 9000, 70), (4001, 1000, 40), (1000, 40, 4000), (64, 16, 17000)])
+def test_fc_single_step(M, N, K):
+    test_fc_edges(M, N, K, 0)
+
+
+def test_fc_split_needs_its_workspace():
+    q8t = require_gpu()
+    import torch
+    x, w = torch.zeros((8, 8192), dtype=torch.int8, device="cuda:0"), torch.zeros((8192, 8), dtype=torch.int8, device="cuda:0")
+    _, px = q8t.quantize(torch.zeros(4, device="cuda:0"), 8)
+    with pytest.raises(q8t.Q8TError) as e:
+        q8t.binding._check(q8t.binding._lib.q8t_qgemm_fwd(x.data_ptr(), px.data_ptr(), w.data_ptr(), px.data_ptr(), 8, 8, 8192,
+                                                          x.data_ptr(), None, None, 0), "q8t_qgemm_fwd")
+    assert e.value.code == -5
