@@ -2,7 +2,7 @@
 // take 8-bit operands and accumulate in 32 bits): any filter size, stride, padding and channel count.
 // Three launches per call:
 //
-//  1. to_nhwc      the NCHW int8 operand is rewritten channel-contiguous ([N][H][W][Cp], Cp = reduction
+//  1. to_nhwc      (many small planes: to_nhwc_small) the NCHW int8 operand is rewritten channel-contiguous ([N][H][W][Cp], Cp = reduction
 //                  channels rounded up to 16) into the workspace, so that 16 reduction channels of one
 //                  filter tap are one aligned 16-byte piece; the same pass emits the per-position channel
 //                  sum that the zero-point correction needs.
@@ -144,6 +144,51 @@ __global__ __launch_bounds__(kThreads * G) void to_nhwc(const int8_t *__restrict
             chansum[(size_t)n * HW + p0 + threadIdx.x] = s;
         }
     }
+}
+
+// Planes of fewer than 64 positions: the channels of a few neighbouring images are one stretch of the NCHW tensor, and
+// their positions one stretch of the copy.  A workgroup takes the images' bytes to LDS as they lie (16-byte loads, any
+// alignment) and picks the 16 channels of a position out of it.  With the kernel above a plane costs a workgroup of 64
+// positions however small it is: whole 1x1 products over 65536 planes of one position, 48 -> 80 channels 74 -> 23 us,
+// 256 -> 512 190 -> 63, of four positions, 64 -> 64 95 -> 40; 4096 planes of 49, 64 -> 64 49 both.
+constexpr int kSmallBytes = 32 * 1024;
+__global__ __launch_bounds__(kThreads) void to_nhwc_small(const int8_t *__restrict__ src, int N, int C, int Cp, int HW, int ipw,
+                                                         int8_t *__restrict__ dst, int *__restrict__ chansum)
+{
+    extern __shared__ __align__(16) int8_t flat[];   // [images][C][HW], then the sums of the positions
+    const int n0 = blockIdx.x * ipw, images = min(ipw, N - n0), CC = Cp >> 4;
+    const int bytes = images * C * HW, positions = images * HW;
+    int *sum = reinterpret_cast<int *>(flat + ((ipw * C * HW + 15) & ~15));
+    const int8_t *in = src + (size_t)n0 * C * HW;
+    for (int i = threadIdx.x * 16; i < bytes; i += kThreads * 16) {
+        if (i + 16 <= bytes) {
+            uint4 v;
+            __builtin_memcpy(&v, in + i, 16);
+            *reinterpret_cast<uint4 *>(flat + i) = v;
+        } else {
+            for (int k = i; k < bytes; ++k) flat[k] = in[k];
+        }
+    }
+    for (int i = threadIdx.x; i < positions; i += kThreads) sum[i] = 0;
+    __syncthreads();
+    int8_t *out = dst + (size_t)n0 * HW * Cp;
+    for (int i = threadIdx.x; i < positions * CC; i += kThreads) {
+        const int pos = i / CC, q = i - pos * CC, img = pos / HW, p = pos - img * HW;
+        const int8_t *b = flat + (img * C + q * 16) * HW + p;
+        const int left = C - q * 16;   // channels from here on
+        uint32_t w[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            w[d] = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (4 * d + e < left) w[d] |= (uint32_t)(uint8_t)b[(4 * d + e) * HW] << (8 * e);
+        }
+        *reinterpret_cast<uint4 *>(out + (size_t)i * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+        atomicAdd(&sum[pos], bytesum4(w[0]) + bytesum4(w[1]) + bytesum4(w[2]) + bytesum4(w[3]));
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < positions; i += kThreads) chansum[(size_t)n0 * HW + i] = sum[i];
 }
 
 // ---- 2. filter -> [class][output channel][tap][reduction channel], sums per output channel ------
@@ -877,6 +922,15 @@ struct Plan {
     size_t o_chansum, o_wt, o_colsum, o_tapoff, o_cls, total;
 };
 
+// Operand planes for to_nhwc_small: from half the images on that fill the chip with workgroups of to_nhwc.  Fewer leave
+// the latter the shorter chain (512 channels of 49 positions, 64 images: 19.4 against 24.4 us a call), and so do planes of
+// many bytes (512 channels of 25 positions, 4096 images: 86 against 91).
+bool small_planes(const Plan &p, int N)
+{
+    const int64_t HW = (int64_t)p.IH * p.IW;
+    return HW < 64 && HW * p.red <= 6144 && N >= 1024;
+}
+
 bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
 {
     if (which < 0 || which > 1) return false;
@@ -897,6 +951,9 @@ bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
     const int64_t ipos = (int64_t)d->N * p->IH * p->IW, opos = (int64_t)d->N * p->OHf * p->OWf;
     if (ipos >= ((int64_t)1 << 31) || opos >= ((int64_t)1 << 31)) return false;
     if ((int64_t)d->N * (which == 0 ? d->C : d->K) >= ((int64_t)1 << 31)) return false;
+    // a launch holds fewer than 2^32 threads: 256 for 64 positions of a plane (to_nhwc), 256 for 128 result positions
+    if (!small_planes(*p, d->N) && (int64_t)d->N * (((int64_t)p->IH * p->IW + 63) / 64) >= (1 << 24)) return false;
+    if (opos >= ((int64_t)1 << 30)) return false;
     const size_t xn = up256((size_t)ipos * p->Cp);
     p->o_chansum = xn;
     p->o_wt = p->o_chansum + up256((size_t)ipos * sizeof(int));
@@ -1052,7 +1109,17 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
         const dim3 grid((unsigned)(ptiles * d->N));   // below 2^31: so is the number of positions
         // four channel groups per position tile where single ones would leave wavefront slots empty (256 compute
         // units hold 2048 workgroups of 256 threads)
-        if (p.Cp > 64 && grid.x < 1024)
+        if (small_planes(p, d->N)) {
+            // images per workgroup: a piece of 16 bytes for every thread, more of them while the launch stays large
+            const int plane = p.red * HW, pieces = HW * (p.Cp >> 4);
+            int64_t ipw = (kThreads + pieces - 1) / pieces;
+            while (d->N / ipw > 2048) ipw *= 2;
+            if (ipw > kSmallBytes / plane) ipw = kSmallBytes / plane;   // LDS
+            if (ipw > 2048 / HW) ipw = 2048 / HW;
+            const size_t lds = ((size_t)(ipw * plane + 15) & ~(size_t)15) + (size_t)ipw * HW * sizeof(int);
+            hipLaunchKernelGGL(to_nhwc_small, dim3((unsigned)((d->N + ipw - 1) / ipw)), dim3(kThreads), lds, st, (const int8_t *)a,
+                               d->N, p.red, p.Cp, HW, (int)ipw, xn, chansum);
+        } else if (p.Cp > 64 && grid.x < 1024)
             hipLaunchKernelGGL(to_nhwc<4>, grid, dim3(kThreads * 4), 0, st, (const int8_t *)a, p.red, p.Cp, HW, ptiles, xn,
                                chansum);
         else

@@ -71,3 +71,27 @@ def test_conv_operand_at_any_address(case):
         buf[off:] = flat
         _, acc = q8t.qconv_fwd(d, buf[off:].view(sx.shape), qp_dev_from(px), dev(sw), qp_dev_from(pw), want_acc=True)
         same_ints(host(acc), oacc)
+
+
+@pytest.mark.parametrize("case", [
+    (1024, 48, 1, 1, 80, 1, 1, 1, 0),     # planes of one position: several images per workgroup of the relayout, both ways
+    (1030, 17, 2, 2, 33, 3, 3, 2, 1),     # ... the last workgroup short, odd numbers of bytes
+    (1500, 16, 1, 3, 16, 3, 3, 1, 1),
+    (1025, 97, 7, 9, 66, 1, 1, 1, 0),     # the most bytes of a plane that go this way, 63 positions
+    (1026, 64, 8, 8, 24, 3, 3, 1, 1),     # 64 positions: one workgroup per plane again
+    (1023, 48, 1, 2, 80, 1, 1, 1, 0),     # one image too few
+    (2049, 320, 2, 2, 70, 2, 2, 1, 0),    # 4 positions on one side, 1 on the other
+    (70001, 5, 1, 1, 130, 1, 1, 1, 0),    # many images per workgroup
+])
+def test_conv_tiny_planes(case):
+    test_conv_channel_counts(case)
+
+
+def test_conv_more_images_than_workgroups_of_a_launch():
+    # 256 threads per image would be more than the 2^32 of a launch
+    q8t = require_gpu()
+    case = ((1 << 24) + 5, 4, 1, 1, 1, 1, 1, 1, 0)
+    od, (sx, px), (sw, pw), _, _ = _conv_operands(synth.rng(5), case)
+    _, oacc = oracle.qconv_fwd(od, sx, px, sw, pw)
+    _, acc = q8t.qconv_fwd(q8t.conv_desc(*case), dev(sx), qp_dev_from(px), dev(sw), qp_dev_from(pw), want_acc=True)
+    same_ints(host(acc), oacc)
