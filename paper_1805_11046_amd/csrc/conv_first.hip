@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kThreads) void first_conv(const int8_t *__restrict_
     const int h0 = pbeg * g.stride - g.pad;
     const int band_dwords = (g.C * g.NR * g.Wp + 16 * g.stride + 32) >> 2;
     for (int r0 = 0; r0 < nstaged; r0 += (kThreads / 64) * kStageU) {
-        for (int w0 = 0; w0 < W4; w0 += 64) {
+        for (int w0 = 0; w0 < max(W4, 1); w0 += 64) {
             uint32_t v[kStageU];
             int dst[kStageU];
             const int w4 = w0 + lane;
@@ -104,6 +104,14 @@ __global__ __launch_bounds__(kThreads) void first_conv(const int8_t *__restrict_
 #pragma unroll
             for (int u = 0; u < kStageU; ++u)
                 if (dst[u] >= 0) *reinterpret_cast<uint32_t *>(band + dst[u]) = v[u];
+        }
+    }
+
+    if (g.W & 3) {   // the codes behind the last whole dword of a row, one by one (the zero codes are in place)
+        const int rem = g.W & 3;
+        for (int i = tid; i < nstaged * rem; i += kThreads) {
+            const int cr = i / rem, w = 4 * W4 + i - cr * rem, c = cr / g.NR, h = h0 + cr - c * g.NR;
+            if ((unsigned)h < (unsigned)g.H) band[cr * g.Wp + g.L + w] = x[(((size_t)n * g.C + c) * g.H + h) * g.W + w];
         }
     }
 
@@ -263,7 +271,7 @@ bool make_geom(const q8t_conv_desc *d, FirstGeom *g)
 {
     if (d->N <= 0 || d->N > 65535 || d->C <= 0 || d->C >= 64 || d->K <= 0 || d->K % 64 || d->K > 4096 || d->H <= 0 || d->W <= 0) return false;
     if (d->R <= 0 || d->R > 32 || d->S <= 0 || d->S > 8 || d->stride < 1 || d->stride > 4 || d->pad < 0 || d->pad > 16) return false;
-    if (d->H + 2 * d->pad < d->R || d->W + 2 * d->pad < d->S || d->W % 4) return false;
+    if (d->H + 2 * d->pad < d->R || d->W + 2 * d->pad < d->S) return false;
     g->N = d->N; g->C = d->C; g->H = d->H; g->W = d->W; g->R = d->R; g->S = d->S; g->stride = d->stride; g->pad = d->pad;
     g->P = (d->H + 2 * d->pad - d->R) / d->stride + 1;
     g->Q = (d->W + 2 * d->pad - d->S) / d->stride + 1;

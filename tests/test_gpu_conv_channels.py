@@ -95,3 +95,15 @@ def test_conv_more_images_than_workgroups_of_a_launch():
     _, oacc = oracle.qconv_fwd(od, sx, px, sw, pw)
     _, acc = q8t.qconv_fwd(q8t.conv_desc(*case), dev(sx), qp_dev_from(px), dev(sw), qp_dev_from(pw), want_acc=True)
     same_ints(host(acc), oacc)
+
+
+@pytest.mark.parametrize("case", [
+    (2, 3, 41, 45, 64, 7, 7, 2, 3),       # row ends with 1, 2 and 3 codes in the last dword, odd planes
+    (16, 1, 30, 58, 128, 5, 5, 1, 2),
+    (16, 4, 19, 27, 64, 3, 3, 1, 1),
+    (128, 3, 9, 259, 128, 7, 8, 2, 3),    # rows of more than 64 dwords, the last one ragged
+    (4, 2, 7, 2, 64, 3, 3, 1, 1),         # a single, ragged dword
+    (2, 2, 30, 3, 64, 7, 7, 1, 3),
+])
+def test_conv_few_channels_ragged_rows(case):
+    test_conv_channel_counts(case)
