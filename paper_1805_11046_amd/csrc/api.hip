@@ -26,28 +26,45 @@ double products(const q8t_conv_desc *d)
     const int P = (d->H + 2 * d->pad - d->R) / d->stride + 1, Q = (d->W + 2 * d->pad - d->S) / d->stride + 1;
     return (double)d->K * d->C * d->R * d->S * d->N * P * Q;
 }
-// these forms, with a pass over an operand ahead, pay off once the product is not tiny
+// forms with a pass over an operand ahead pay off once the product is not tiny
 bool not_tiny(const q8t_conv_desc *d) { return products(d) >= 4194304.0; }
 bool smallc_wanted(int which, const q8t_conv_desc *d) { return q8t_smallc_conv_supported(which, d) && not_tiny(d); }
 bool wgrad_wants_gemm(const q8t_conv_desc *d) { return q8t_gemm_wgrad_supported(d) && not_tiny(d); }
 
-// The general MFMA path, except where the general kernel needs a single step of 64 for the reduction and the product is
-// small: there its one launch is faster than three (whole calls, 33->48 1x1 layer gradient @20 batch 32, 20 M products:
-// 11.5 against 13.7 us; 48->48 @28 batch 64, 115 M: 17.7 against 15.9).  From two steps on the gathered operands cost
-// more at any size but the very smallest (16->16 3x3 @7 batch 8, 0.9 M products: 24.5 against 16.2 us; 8->8 3x3 @5 batch 1,
-// 14 thousand: 11.1 against 12.9).
-bool nhwc_wanted(int which, const q8t_conv_desc *d)
+// The form of a forward (which = 0) or layer-gradient (1) product that no specialised kernel takes.  Channel counts that are
+// multiples of 64 run on the channel-contiguous path; elsewhere the estimates of the three forms decide.  No simple line
+// separates them: the general kernel gathers bytes but splits a long reduction over the chip and needs one launch where
+// that is short, the channel-contiguous path copies its operand and pads it to 16 channels, the first-layer kernel pads
+// a filter row to eight taps.  Measured, us a call, general / channel-contiguous / first-layer form:
+//   472 -> 1 7x7 @7x4 batch 5   46 / 202 / -       16 -> 64 3x3 @32 batch 128 54 / 24 / -       4 -> 32 3x3 @27 batch 64 12.5 / 17.2 / -
+//   32 -> 512 1x1 @27 batch 64 65 / 59 / 104       3 -> 64 7x7/2 @27 batch 64 21 / 29 / 14       3 -> 64 1x1 @7 batch 56 8 / 14 / 12
+// Over 3700 calls (channels 1 .. 600, filters up to 7x7, strides 1 .. 3, planes 1 .. 224, batches 1 .. 65536, with and without
+// statistics) the form taken is 0.5% slower than the best of the three in the mean, more than 7% in 140 of them, 1.6 times at
+// most.
+enum Form { FIRST, NHWC, SMALLC, GENERAL };
+Form conv_form(int which, const q8t_conv_desc *d, bool stats)
 {
-    if (!q8t_nhwc_conv_supported(which, d)) return false;
-    const int64_t red = (int64_t)(which == 0 ? d->C : d->K) * d->R * d->S;
-    return (d->C % 64 == 0 && d->K % 64 == 0) || products(d) >= (red > 64 ? 262144.0 : 33554432.0);
+    const bool first = which == 0 && q8t_first_conv_supported(d), nhwc = q8t_nhwc_conv_supported(which, d);
+    if (nhwc && d->C % 64 == 0 && d->K % 64 == 0) return NHWC;
+    Form f = GENERAL;
+    double best = q8t_generic_conv_us(which, d, stats);
+    const double us = nhwc ? q8t_nhwc_conv_us(which, d, stats) : best;
+    if (us < best) {
+        f = NHWC;
+        best = us;
+    }
+    if (first && q8t_first_conv_us(d, stats) < best) f = FIRST;
+    return f == GENERAL && smallc_wanted(which, d) ? SMALLC : f;
 }
 
-// bytes of partial statistics that the forward kernel for this shape writes from its epilogue (0: none there)
-size_t stats_in_epilogue_ws(const q8t_conv_desc *d)
+size_t form_ws(int which, const q8t_conv_desc *d, bool stats)
 {
-    if (q8t_first_conv_supported(d)) return q8t_first_conv_stats_ws(d);
-    return nhwc_wanted(0, d) ? q8t_nhwc_conv_stats_ws(d) : 0;
+    switch (conv_form(which, d, stats)) {
+    case FIRST: return q8t_first_conv_ws(d);
+    case NHWC: return q8t_nhwc_conv_ws(which, d);
+    case SMALLC: return q8t_smallc_conv_ws(which, d);
+    default: return q8t_generic_conv_ws(which, d);
+    }
 }
 
 // A 1x1 convolution with a stride and no padding is the stride-1 layer on the positions it reads: where the
@@ -130,10 +147,10 @@ int q8t_qgemm_wgrad(const int8_t *qx, const q8t_qparams *px, const int16_t *qdy1
     return q8t_generic_fc(2, qdy16, pg16, qx, px, M, N, K, dw, acc_out, ws, (hipStream_t)stream);
 }
 
-size_t q8t_qconv_workspace_size(const q8t_conv_desc *desc, int which)
+static size_t conv_ws(const q8t_conv_desc *desc, int which, bool stats)
 {
     if (!desc || which < 0 || which > 2) return 0;
-    size_t g = q8t_generic_conv_ws(which, desc);
+    size_t g = which < 2 ? 0 : q8t_generic_conv_ws(which, desc);
     size_t f = q8t_fast_conv_ws(which, desc);
     if (which < 2) {
         const size_t wd = q8t_wide_conv_ws(which, desc);
@@ -145,10 +162,8 @@ size_t q8t_qconv_workspace_size(const q8t_conv_desc *desc, int which)
         if (pw > f) f = pw;
     }
     size_t h = 0;
-    if (which == 0 && q8t_first_conv_supported(desc)) h = q8t_first_conv_ws(desc);
-    else if (which < 2) h = nhwc_wanted(which, desc) ? q8t_nhwc_conv_ws(which, desc) : 0;
+    if (which < 2) h = q8t_conv_reduction_check(which, desc) == Q8T_OK ? form_ws(which, desc, stats) : 0;
     else h = wgrad_wants_gemm(desc) ? q8t_gemm_wgrad_ws(desc) : 0;
-    if (h == 0 && smallc_wanted(which, desc)) h = q8t_smallc_conv_ws(which, desc);
     q8t_conv_desc sub;
     if (which == 0 && lattice_forward(desc, &sub)) {
         const size_t l = lattice_codes_bytes(&sub) + q8t_fast_conv_ws(0, &sub);
@@ -156,6 +171,20 @@ size_t q8t_qconv_workspace_size(const q8t_conv_desc *desc, int which)
     }
     if (h > g) g = h;
     return g > f ? g : f;
+}
+
+size_t q8t_qconv_workspace_size(const q8t_conv_desc *desc, int which) { return conv_ws(desc, which, false); }
+
+// the product in the form taken, no specialised kernel's; stats (nullable, FIRST and NHWC only): see q8t_nhwc_conv
+static int run_form(Form f, int which, const q8t_conv_desc *desc, const int8_t *a, const q8t_qparams *pa, const int8_t *qw,
+                    const q8t_qparams *pw, float *y, int32_t *acc_out, float *stats, void *sws, void *ws, hipStream_t st)
+{
+    switch (f) {
+    case FIRST: return q8t_first_conv(desc, a, pa, qw, pw, y, acc_out, stats, sws, ws, st);
+    case NHWC: return q8t_nhwc_conv(which, desc, a, pa, qw, pw, y, acc_out, stats, sws, ws, st);
+    case SMALLC: return q8t_smallc_conv(desc, a, pa, qw, pw, y, acc_out, ws, st);
+    default: return q8t_generic_conv(which, desc, a, pa, qw, pw, y, acc_out, ws, st);
+    }
 }
 
 static int qconv_fwd_impl(const q8t_conv_desc *desc, const int8_t *qx, const q8t_qparams *px, const int8_t *qw,
@@ -180,12 +209,7 @@ static int qconv_fwd_impl(const q8t_conv_desc *desc, const int8_t *qx, const q8t
     if (q8t_fast_conv_supported(0, desc, qx, qw, y, acc_out))
         return q8t_fast_conv(0, desc, qx, px, qw, pw, y, acc_out, nullptr, ws, (hipStream_t)stream, nullptr,
                              packed_tile64(packed, desc, 0));
-    if (q8t_first_conv_supported(desc))
-        return q8t_first_conv(desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
-    if (nhwc_wanted(0, desc))
-        return q8t_nhwc_conv(0, desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
-    if (smallc_wanted(0, desc)) return q8t_smallc_conv(desc, qx, px, qw, pw, y, acc_out, ws, (hipStream_t)stream);
-    return q8t_generic_conv(0, desc, qx, px, qw, pw, y, acc_out, ws, (hipStream_t)stream);
+    return run_form(conv_form(0, desc, false), 0, desc, qx, px, qw, pw, y, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
 }
 
 int q8t_qconv_fwd(const q8t_conv_desc *desc, const int8_t *qx, const q8t_qparams *px, const int8_t *qw,
@@ -198,12 +222,15 @@ size_t q8t_qconv_fwd_bn_stats_workspace_size(const q8t_conv_desc *desc)
 {
     if (!desc || desc->stride < 1) return 0;
     const int P = (desc->H + 2 * desc->pad - desc->R) / desc->stride + 1, Q = (desc->W + 2 * desc->pad - desc->S) / desc->stride + 1;
-    const size_t c = (q8t_qconv_workspace_size(desc, 0) + 255) & ~(size_t)255;
+    const size_t c = (conv_ws(desc, 0, true) + 255) & ~(size_t)255;
     // behind the product's own workspace: the partial statistics of its epilogue, or the workspace of a
     // statistics pass over the result where the kernel for this shape gathers none
     size_t s = q8t_range_bn_workspace_size(desc->N, desc->K, P, Q);
-    const size_t e = stats_in_epilogue_ws(desc);
-    if (e > s) s = e;
+    if (q8t_conv_reduction_check(0, desc) == Q8T_OK) {
+        const Form f = conv_form(0, desc, true);
+        const size_t e = f == FIRST ? q8t_first_conv_stats_ws(desc) : (f == NHWC ? q8t_nhwc_conv_stats_ws(desc) : 0);
+        if (e > s) s = e;
+    }
     return c + s;
 }
 
@@ -233,16 +260,14 @@ static int qconv_fwd_bn_stats_impl(const q8t_conv_desc *desc, const int8_t *qx, 
     if (q8t_fast_conv_supported(0, desc, qx, qw, y, acc_out))
         return q8t_fast_conv(0, desc, qx, px, qw, pw, y, acc_out, stats_out, ws, (hipStream_t)stream, nullptr,
                              packed_tile64(packed, desc, 0));
-    void *sws = (char *)ws + ((q8t_qconv_workspace_size(desc, 0) + 255) & ~(size_t)255);
-    if (q8t_first_conv_supported(desc))
-        return q8t_first_conv(desc, qx, px, qw, pw, y, acc_out, stats_out, sws, ws, (hipStream_t)stream);
-    if (nhwc_wanted(0, desc))
-        return q8t_nhwc_conv(0, desc, qx, px, qw, pw, y, acc_out, stats_out, sws, ws, (hipStream_t)stream);
-    const int rc2 = qconv_fwd_impl(desc, qx, px, qw, pw, y, acc_out, ws, stream, packed);
-    if (rc2) return rc2;
+    void *sws = (char *)ws + ((conv_ws(desc, 0, true) + 255) & ~(size_t)255);
+    const Form f = conv_form(0, desc, true);
+    const bool inside = f == FIRST || f == NHWC;   // the statistics come from the epilogue
+    const int rc2 = run_form(f, 0, desc, qx, px, qw, pw, y, acc_out, inside ? stats_out : nullptr, inside ? sws : nullptr, ws,
+                             (hipStream_t)stream);
+    if (rc2 || inside) return rc2;
     const int P = (desc->H + 2 * desc->pad - desc->R) / desc->stride + 1, Q = (desc->W + 2 * desc->pad - desc->S) / desc->stride + 1;
-    void *bnws = (char *)ws + ((q8t_qconv_workspace_size(desc, 0) + 255) & ~(size_t)255);
-    return q8t_range_bn_stats(y, desc->N, desc->K, P, Q, stats_out, bnws, (hipStream_t)stream);
+    return q8t_range_bn_stats(y, desc->N, desc->K, P, Q, stats_out, sws, (hipStream_t)stream);
 }
 
 int q8t_qconv_fwd_bn_stats(const q8t_conv_desc *desc, const int8_t *qx, const q8t_qparams *px, const int8_t *qw,
@@ -262,9 +287,7 @@ static int qconv_dgrad_impl(const q8t_conv_desc *desc, const int8_t *qdy, const 
     if (q8t_fast_conv_supported(1, desc, qdy, qw, dx, acc_out))
         return q8t_fast_conv(1, desc, qdy, pg, qw, pw, dx, acc_out, nullptr, ws, (hipStream_t)stream, nullptr,
                              packed_tile64(packed, desc, 1));
-    if (nhwc_wanted(1, desc))
-        return q8t_nhwc_conv(1, desc, qdy, pg, qw, pw, dx, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
-    return q8t_generic_conv(1, desc, qdy, pg, qw, pw, dx, acc_out, ws, (hipStream_t)stream);
+    return run_form(conv_form(1, desc, false), 1, desc, qdy, pg, qw, pw, dx, acc_out, nullptr, nullptr, ws, (hipStream_t)stream);
 }
 
 int q8t_qconv_dgrad(const q8t_conv_desc *desc, const int8_t *qdy, const q8t_qparams *pg, const int8_t *qw,

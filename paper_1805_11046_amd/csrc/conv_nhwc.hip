@@ -967,6 +967,25 @@ bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
     return true;
 }
 
+// Tile: the one whose tiles, dealt out over 256 compute units, take the fewest rounds of work.  A unit is what a
+// 128x64 tile takes; a 128x128 tile does twice its products in about 1.6 times its time and a 256x256 tile eight
+// times in 6 (operand bytes read from LDS per product fall as 12 : 8 : 6).  Whole calls measured with 128x64 / 128x128
+// / 256x256 tiles: 128->256 3x3/2 @28 batch 256 68 / 70 / 61 us, 256->512 3x3/2 @14 batch 256 62 / 59 / 75,
+// 256->256 3x3/2 @14 batch 32 34 / 40 / 63, 240->240 3x3 @20 batch 200 125 / 104 / 113, 96->200 3x3 @27 batch 50
+// 49 / 46 / 48 us: the rule takes the fastest in each.
+struct Rounds {
+    double small, mid, big;
+};
+Rounds rounds_for(int64_t M, int ncls, int OCp)
+{
+    const int64_t r128 = (M + 127) / 128 * ncls, r256 = (M + 255) / 256 * ncls;
+    Rounds r;
+    r.small = (double)((r128 * (OCp / 64) + 255) / 256);
+    r.mid = OCp % 128 == 0 ? 1.6 * (double)((r128 * (OCp / 128) + 255) / 256) : 1e30;
+    r.big = OCp % 256 == 0 ? 6.0 * (double)((r256 * (OCp / 256) + 255) / 256) : 1e30;
+    return r;
+}
+
 struct SmallPlan {
     int P, Q, Kc;
     size_t lds, o_rowsum, o_wt, o_colsum, o_tapoff, total;
@@ -1076,6 +1095,23 @@ size_t q8t_nhwc_conv_ws(int which, const q8t_conv_desc *d)
 {
     Plan p;
     return make_plan(which, d, &p) ? p.total : 0;
+}
+
+// As q8t_generic_conv_us, for the product here (the shape is supported): three launches, the copy, the filter, then the longest
+// class's K-steps, the first round of them at the price of its latency.  Isolated results of strides beyond 2 cost their
+// lines several times.  0.8 .. 1.3 in 96% of the calls.
+double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats)
+{
+    Plan p;
+    if (!make_plan(which, d, &p)) return 0.0;
+    const int st = which == 0 ? 1 : d->stride;
+    const int64_t opos = (int64_t)d->N * p.OHf * p.OWf;
+    const Rounds rd = rounds_for((opos + p.ncls - 1) / p.ncls, p.ncls, p.OCp);
+    const double t = fmin(rd.small, fmin(rd.mid, rd.big)), results = 1e-6 * opos * p.oc;
+    const int taps = d->R * d->S, steps = (((d->R + st - 1) / st) * ((d->S + st - 1) / st) * p.Cp + 63) / 64;
+    double us = 10.3 + 0.44 * steps + 0.19 * steps * (t - 1.0) + t + 0.23 * taps + 0.67e-6 * d->N * p.IH * p.IW * p.Cp +
+                3.7e-6 * taps * p.OCp * p.Cp + (st > 2 ? 4.6 : (st == 2 && taps > 3 ? 1.3 : 0.8)) * results;
+    return us + (stats ? 3.2 + 0.4 * results : 0.0);
 }
 
 size_t q8t_nhwc_conv_stats_ws(const q8t_conv_desc *d)
@@ -1228,16 +1264,7 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
         Q8T_LAUNCH_CHECK();
         return Q8T_OK;
     }
-    // Tile: the one whose tiles, dealt out over 256 compute units, take the fewest rounds of work.  A unit is what a
-    // 128x64 tile takes; a 128x128 tile does twice its products in about 1.6 times its time and a 256x256 tile eight
-    // times in 6 (operand bytes read from LDS per product fall as 12 : 8 : 6).  Whole calls measured with 128x64 / 128x128
-    // / 256x256 tiles: 128->256 3x3/2 @28 batch 256 68 / 70 / 61 us, 256->512 3x3/2 @14 batch 256 62 / 59 / 75,
-    // 256->256 3x3/2 @14 batch 32 34 / 40 / 63, 240->240 3x3 @20 batch 200 125 / 104 / 113, 96->200 3x3 @27 batch 50
-    // 49 / 46 / 48 us: the rule takes the fastest in each.
-    const int64_t r128 = (maxM + 127) / 128 * ncls, r256 = (maxM + 255) / 256 * ncls;
-    const double t_small = (double)((r128 * (p.OCp / 64) + 255) / 256);
-    const double t_mid = p.OCp % 128 == 0 ? 1.6 * (double)((r128 * (p.OCp / 128) + 255) / 256) : 1e30;
-    const double t_big = p.OCp % 256 == 0 ? 6.0 * (double)((r256 * (p.OCp / 256) + 255) / 256) : 1e30;
+    const Rounds rd = rounds_for(maxM, ncls, p.OCp);
 #define Q8T_GO(CFG)                                                                                                  \
     {                                                                                                                \
         static Q8tLdsOptIn optin;                                                                                    \
@@ -1250,8 +1277,8 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
                                conv_lds_bytes<CFG>(), st, xn, chansum, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
                                (int32_t *)out_acc, bnp);                                                             \
     }
-    if (t_big <= t_mid && t_big <= t_small) Q8T_GO(q8t_gemm::Big)
-    else if (t_mid <= t_small) Q8T_GO(q8t_gemm::Mid)
+    if (rd.big <= rd.mid && rd.big <= rd.small) Q8T_GO(q8t_gemm::Big)
+    else if (rd.mid <= rd.small) Q8T_GO(q8t_gemm::Mid)
     else Q8T_GO(q8t_gemm::Small)
 #undef Q8T_GO
     Q8T_LAUNCH_CHECK();

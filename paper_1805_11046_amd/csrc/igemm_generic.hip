@@ -532,6 +532,25 @@ size_t q8t_generic_conv_ws(int which, const q8t_conv_desc *d)
     return ws_for(g.K, (int64_t)g.C * g.R * g.S, (int64_t)g.N * g.P * g.Q);
 }
 
+// Microseconds that a forward (which = 0) or layer-gradient (1) product takes here, back to back on one MI355X, for the
+// choice between the forms of api.hip: a K-step of a workgroup costs what gathering its operands byte by byte does, 1024
+// workgroups run side by side, slices are written, read and added up behind.  The constants are fitted to the 3700 calls
+// described there; measured over estimated 0.7 .. 1.4 in 96% of them.
+double q8t_generic_conv_us(int which, const q8t_conv_desc *d, bool stats)
+{
+    ConvGeom g;
+    if (!geom_ok(d, g)) return 0.0;
+    const int64_t rows = (int64_t)g.N * (which == 0 ? (int64_t)g.P * g.Q : (int64_t)g.H * g.W), cols = which == 0 ? g.K : g.C;
+    const int64_t red = (int64_t)(which == 0 ? g.C : g.K) * g.R * g.S;
+    const Plan p = plan_for(rows, cols, red);
+    if ((cols + BN - 1) / BN > 65535 || p.splits > 65535) return 1e30;   // refused here
+    const double steps = (double)(((red < p.slice_k ? red : p.slice_k) + BK - 1) / BK);
+    const double wgs = (double)((rows + BM - 1) / BM) * (double)((cols + BN - 1) / BN) * p.splits, results = 1e-6 * rows * cols;
+    double us = 3.0 + (which == 0 ? 5.4 : 7.7) * steps * (wgs > 1024 ? wgs / 1024 : 1.0) + 1.4 * results;
+    if (p.splits > 1) us += p.splits * (0.23 + 5.7 * results);
+    return us + (stats ? q8t_range_bn_stats_us(g.N, g.K, (int64_t)g.P * g.Q) : 0.0);
+}
+
 int q8t_conv_reduction_check(int which, const q8t_conv_desc *d)
 {
     ConvGeom g;

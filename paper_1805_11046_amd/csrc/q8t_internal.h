@@ -19,6 +19,10 @@ int q8t_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const
 int q8t_generic_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b,
                      const q8t_qparams *qb, float *out_f, void *out_acc, void *ws, hipStream_t st);
 size_t q8t_generic_conv_ws(int which, const q8t_conv_desc *d);
+// estimated microseconds of a forward (0) / layer-gradient (1) product, with the Range BN statistics of its result or without
+double q8t_generic_conv_us(int which, const q8t_conv_desc *d, bool stats);
+double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats);
+double q8t_first_conv_us(const q8t_conv_desc *d, bool stats);
 int q8t_conv_reduction_check(int which, const q8t_conv_desc *d);
 
 // Per-workgroup statistics of the corrected integer outputs of one output channel, gathered in a
@@ -57,6 +61,8 @@ int q8t_wide_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
 int q8t_wide_conv_pack_layout(int which, const q8t_conv_desc *d);
 
 // Range BN statistics of an NCHW tensor alone (range_bn.hip); ws as for q8t_range_bn_fwd
+// ... and the microseconds that takes (planes of HW positions)
+double q8t_range_bn_stats_us(int N, int C, int64_t HW);
 int q8t_range_bn_stats(const float *x, int N, int C, int H, int W, float *stats_out, void *ws, hipStream_t st);
 
 // general MFMA path over a channel-contiguous copy of the operand (conv_nhwc.hip): forward and layer gradient, any

@@ -1620,6 +1620,16 @@ int q8t_maxpool_range_bn_bwd_bifurcate(const float *x, const float *gpool, const
 
 }  // extern "C"
 
+// fitted with the estimates of the products (igemm_generic.hip); a plane that is a multiple of four positions is a turn of a
+// workgroup, or several, however small it is
+double q8t_range_bn_stats_us(int N, int C, int64_t HW)
+{
+    if (HW == 1 && row_shape(N, C)) return 4.1;
+    const int split = split_for(N, C), NB = (N + split - 1) / split;
+    const double plane_turns = HW % 4 == 0 ? (double)NB * ((HW + 1023) / 1024) : 0.0;
+    return 4.1 + 0.25 * ((N + NB - 1) / NB) + (HW == 1 ? 5.5e-6 : 0.78e-6) * N * C * HW + 0.78 * plane_turns;
+}
+
 int q8t_range_bn_stats(const float *x, int N, int C, int H, int W, float *stats_out, void *ws, hipStream_t st)
 {
     return q8t_range_bn_fwd(x, N, C, H, W, nullptr, nullptr, 0.0f, nullptr, stats_out, nullptr, nullptr, ws, (void *)st);

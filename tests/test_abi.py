@@ -107,3 +107,19 @@ def test_long_reductions_under_few_results_are_split():
     for M, N, K, which in ((65536, 64, 64, 2), (64, 64, 16384, 0), (61, 29390, 29, 1)):
         assert size(M, N, K, which) >= 2 * 8 * {0: M * N, 1: M * K, 2: K * N}[which]
     assert size(256, 1000, 512, 0) == 0
+
+
+def test_form_of_a_product_follows_its_size():
+    # the workspace shows which form serves a shape that no specialised kernel takes
+    _lib_path()
+    from paper_1805_11046_amd import binding
+
+    def size(*case):
+        return binding.qconv_workspace_size(binding.conv_desc(*case), 0)
+
+    assert size(56, 3, 7, 7, 64, 1, 1, 1, 0) == 0                             # general kernel: one launch, no workspace
+    rows = 5 * 7 * 4
+    assert size(5, 472, 7, 4, 1, 7, 7, 1, 3) % (8 * rows) == 0                # general kernel, slices of int64 results
+    assert size(40, 16, 32, 32, 16, 3, 3, 1, 1) >= 40 * 32 * 32 * (16 + 4)    # copy of the operand and its channel sums
+    assert 0 < size(64, 32, 27, 27, 512, 1, 1, 1, 0) - 64 * 27 * 27 * (32 + 4) < 1 << 20
+    assert 64 * 192 <= size(64, 3, 27, 27, 64, 7, 7, 2, 3) < 1 << 16          # first-layer kernel: the packed filter

@@ -107,3 +107,17 @@ def test_conv_more_images_than_workgroups_of_a_launch():
 ])
 def test_conv_few_channels_ragged_rows(case):
     test_conv_channel_counts(case)
+
+
+@pytest.mark.parametrize("case", [
+    (6, 80, 30, 28, 200, 1, 1, 2, 0),     # channel-contiguous layer gradient, three classes without taps
+    (6, 80, 29, 28, 200, 1, 1, 2, 0),
+    (3, 200, 13, 17, 300, 1, 1, 1, 0),    # ... a single tap, both ways
+    (8, 24, 40, 36, 40, 7, 7, 1, 3),      # ... 49 taps
+    (4, 300, 14, 14, 260, 3, 3, 1, 1),
+    (5, 472, 7, 4, 1, 7, 7, 1, 3),        # few results, long reduction: general kernel, split
+    (2, 5, 27, 24, 128, 5, 3, 1, 1),      # general product, first-layer kernel with statistics
+    (4, 1, 11, 18, 80, 1, 1, 1, 0),       # general product, statistics in a pass of their own
+])
+def test_conv_forms(case):
+    test_conv_channel_counts(case)
