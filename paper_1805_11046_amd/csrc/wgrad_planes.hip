@@ -524,27 +524,29 @@ __global__ __launch_bounds__(kThreads) void wgrad_planes(const int16_t *__restri
 // Bound by the read of the partial sums, 75 MB at batch 256 whatever the layer (before -> now): 512 -> 512 @7, 4 ranges
 // 27.8 -> 18.3 us; 256 -> 256 @14, 16 ranges 17.5 -> 14.2; 128 -> 256 @28/2, 32 ranges 21.1 -> 14.6; 64 -> 128 @56/2, 128
 // ranges 23.5 -> 18.2, its 1x1 projection 10.2 -> 4.4.
-template <class SH, int LG>
+template <class SH, int LG, int QW>
 struct Finish {
-    static constexpr int QW = SH::TAPS == 1 ? 8 : 1, WAVES = SH::TAPS * QW;
-    static constexpr int REGS = 4 / LG;                      // accumulator registers of a workgroup
-    static constexpr int RUN = 32 * SH::TAPS, ROWS = 2 * REGS;   // floats of a run, runs of a workgroup
-    static constexpr int BLOCKS = SH::HALF_INTS / (REGS * 64 * SH::TAPS);
+    static constexpr int WAVES = SH::TAPS * QW;
+    static constexpr int ENT = 256 / LG;                          // accumulator entries of a workgroup and tap
+    static constexpr int CH = ENT < 32 ? ENT : 32, ROWS = ENT / CH;   // channels of a run, runs of a workgroup
+    static constexpr int RUN = CH * SH::TAPS;                     // floats of a run
+    static constexpr int BLOCKS = SH::HALF_INTS / (ENT * SH::TAPS);
 };
-template <class SH, int LG>
-__global__ __launch_bounds__(64 * (SH::TAPS == 1 ? 8 : SH::TAPS)) void wgrad_planes_finish(
+template <class SH, int LG, int QW>
+__global__ __launch_bounds__(64 * SH::TAPS * QW) void wgrad_planes_finish(
     const int *__restrict__ partial, PGeom g, const q8t_qparams *__restrict__ qpg, const q8t_qparams *__restrict__ qpx,
     float *__restrict__ dw, int64_t *__restrict__ acc_out)
 {
-    using F = Finish<SH, LG>;
+    using F = Finish<SH, LG, QW>;
     constexpr int TAPS = SH::TAPS, NBV = SH::NBV;
-    __shared__ int64_t fold[F::QW][F::ROWS][F::RUN];
+    __shared__ int64_t fold[QW][F::ROWS][F::RUN];
     const int cg = (int)blockIdx.y % g.ncg, rg = (int)blockIdx.y / g.ncg;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), ln = threadIdx.x & 63;
     const int tap = wave % TAPS, qw = wave / TAPS;
     constexpr int GL = 64 / LG;                               // lanes of a group
-    const int grp = ln / GL, e = (ln % GL) * 4;               // entry within the workgroup's REGS * 64
-    const int half = blockIdx.x / (16 / F::REGS), reg = (blockIdx.x % (16 / F::REGS)) * F::REGS + (e >> 6), lane = e & 63;
+    const int grp = ln / GL, e = (ln % GL) * 4;               // entry of the workgroup
+    constexpr int PER = 16 * 64 / F::ENT;                     // workgroups of 16 registers
+    const int half = blockIdx.x / PER, first = (blockIdx.x % PER) * F::ENT, reg = (first + e) >> 6, lane = (first + e) & 63;
     const int kt = half >> 1, ch = half & 1;
     const int idx = ((half * TAPS + tap) * 16 + reg) * 64 + lane;
     // 32x32 accumulator tile: lane = column + 32 * ((row / 4) % 2), register = 4 * (row / 8) + row % 4
@@ -554,8 +556,8 @@ __global__ __launch_bounds__(64 * (SH::TAPS == 1 ? 8 : SH::TAPS)) void wgrad_pla
     int64_t v[4] = {0, 0, 0, 0}, cs[4] = {0, 0, 0, 0}, rs = 0;
     const int64_t pitch = (int64_t)g.nrg * g.ncg * SH::PART_INTS;
     const int *base = partial + ((int64_t)rg * g.ncg + cg) * SH::PART_INTS;
-#pragma unroll 4
-    for (int kr = qw * LG + grp; kr < g.S; kr += F::QW * LG) {
+#pragma unroll (LG >= 8 ? 8 : 4)
+    for (int kr = qw * LG + grp; kr < g.S; kr += QW * LG) {
         const int *p = base + kr * pitch;
         const v4i hi = *reinterpret_cast<const v4i *>(p + idx), lo = *reinterpret_cast<const v4i *>(p + SH::HALF_INTS + idx);
         const v4i c = *reinterpret_cast<const v4i *>(p + SH::TILE_INTS + bv * CT + ch_l);
@@ -574,10 +576,9 @@ __global__ __launch_bounds__(64 * (SH::TAPS == 1 ? 8 : SH::TAPS)) void wgrad_pla
     for (int m = GL; m < 64; m *= 2)
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] += __shfl_xor((long long)v[j], m, 64);
-    const int run = 2 * (e >> 6) + (lane >> 5);
     if (grp == 0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) fold[qw][run][((lane & 31) + j) * TAPS + tap] = v[j];
+        for (int j = 0; j < 4; ++j) fold[qw][e / F::CH][(e % F::CH + j) * TAPS + tap] = v[j];
     }
     __syncthreads();
     // padded positions of all ranges together (every range but the last is whole chunks)
@@ -589,10 +590,10 @@ __global__ __launch_bounds__(64 * (SH::TAPS == 1 ? 8 : SH::TAPS)) void wgrad_pla
         const int rw = i / F::RUN, k = i - rw * F::RUN;
         int64_t t = -pads;
 #pragma unroll
-        for (int q = 0; q < F::QW; ++q) t += fold[q][rw][k];
-        const int r = (blockIdx.x % (16 / F::REGS)) * F::REGS + (rw >> 1);
-        const int row = rg * KT + kt * 32 + 8 * (r >> 2) + 4 * (rw & 1) + (r & 3);
-        const int64_t o = ((int64_t)row * g.C + cg * CT + ch * 32) * TAPS + k;
+        for (int q = 0; q < QW; ++q) t += fold[q][rw][k];
+        const int r = (first + rw * F::CH) >> 6, l = (first + rw * F::CH) & 63;
+        const int row = rg * KT + kt * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+        const int64_t o = ((int64_t)row * g.C + cg * CT + ch * 32 + (l & 31)) * TAPS + k;
         if (acc_out) acc_out[o] = t;
         if (dw) dw[o] = (float)((double)t * sc);
     }
@@ -641,12 +642,18 @@ int launch_planes(const q8t_conv_desc *d, const int16_t *g16, const q8t_qparams 
     Q8T_LAUNCH_CHECK();
     // Lane groups: enough of them for about 4000 wavefronts, no more than there are ranges.  With four groups everywhere
     // 512 -> 512 @7 (64 tiles) took 116 us for the whole call against 105 with one, 256 -> 256 @14 (16 tiles) 95 against 91.
-#define Q8T_FINISH(LG)                                                                                                  \
-    hipLaunchKernelGGL((wgrad_planes_finish<SH, LG>), dim3(Finish<SH, LG>::BLOCKS, per), dim3(64 * Finish<SH, LG>::WAVES), 0, st, \
-                       (const int *)ws, g, qg, qx, dw, acc_out)
-    if (per < 16 && g.S >= 4) Q8T_FINISH(4);
-    else if (per < 32 && g.S >= 2) Q8T_FINISH(2);
-    else Q8T_FINISH(1);
+    // A single tile has up to 256 ranges and four groups leave most of the chip idle: eight of them (64 -> 64 @14 at batch 256,
+    // whole call 53 -> 40 us; sixteen, which read runs of 64 bytes, 46); with two tiles eight are no better than four.
+    // A single range needs one wavefront per tap (512 -> 512 1x1/2 @14 at batch 1: 10.6 -> 9.6 us).
+#define Q8T_FINISH(LG, QW)                                                                                              \
+    hipLaunchKernelGGL((wgrad_planes_finish<SH, LG, QW>), dim3(Finish<SH, LG, QW>::BLOCKS, per),                        \
+                       dim3(64 * Finish<SH, LG, QW>::WAVES), 0, st, (const int *)ws, g, qg, qx, dw, acc_out)
+    constexpr int QWS = SH::TAPS == 1 ? 8 : 1;
+    if (SH::TAPS > 1 && per == 1 && g.S >= 16) Q8T_FINISH(8, 1);
+    else if (per < 16 && g.S >= 4) Q8T_FINISH(4, QWS);
+    else if (per < 32 && g.S >= 2) Q8T_FINISH(2, QWS);
+    else if (g.S == 1) Q8T_FINISH(1, 1);
+    else Q8T_FINISH(1, QWS);
 #undef Q8T_FINISH
     Q8T_LAUNCH_CHECK();
     return Q8T_OK;

@@ -1,5 +1,5 @@
 """GPU parity of the weight gradient on padded planes where its last step (partial sums of the image ranges -> dW) changes
-its split: one, two or four groups of lanes, filters of one and of nine taps, one range up to many.  Bit-exact."""
+its split: one, two, four or eight groups of lanes, filters of one and of nine taps, one range up to many.  Bit-exact."""
 import pytest
 
 import oracle
@@ -19,7 +19,11 @@ pytestmark = pytest.mark.gpu
     (4, 64, 7, 7, 64, 3, 3, 1, 1),        # nine taps, one range
     (5, 64, 7, 7, 64, 3, 3, 1, 1),        # ... two
     (2, 64, 56, 56, 128, 3, 3, 2, 1),     # ... planes in bands
-    (9, 256, 14, 14, 512, 3, 3, 2, 1),    # ... 32 tiles, three ranges, the last chunk incomplete
+    (16, 64, 14, 14, 64, 3, 3, 1, 1),     # ... one tile, sixteen ranges: eight groups
+    (83, 64, 14, 14, 64, 3, 3, 2, 1),     # ... 21 ranges, no multiple of the groups
+    (70, 64, 28, 28, 64, 3, 3, 2, 1),     # ... 70 ranges
+    (1, 512, 14, 14, 512, 1, 1, 2, 0),    # one tap, one range, 64 tiles
+    (9, 256, 14, 14, 512, 3, 3, 2, 1),    # nine taps, 32 tiles, three ranges, the last chunk incomplete
 ])
 def test_weight_gradient_finish(case):
     q8t = require_gpu()
