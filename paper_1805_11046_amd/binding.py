@@ -150,15 +150,25 @@ def _dev(t):
 
 
 _ws_cache = {}
+_WS_STREAMS = 16     # buffers kept at most
+_capturing = getattr(torch._C, "_cuda_isCurrentStreamCapturing", None) or torch.cuda.is_current_stream_capturing
 
 
 def workspace(nbytes, device):
-    """A reusable device scratch buffer of at least nbytes (grown on demand, one per device)."""
-    key = (device.type, device.index)
+    """Device scratch memory of at least nbytes for one call on the current stream.  A buffer is kept per device and
+    stream and grown on demand: calls on one stream follow each other, calls on two must not share memory.  A buffer that
+    is replaced or, with many streams, dropped goes back to the allocator, which hands it to work on its own stream only.
+    A call that is being captured gets memory of its own from the graph's pool: replays use it later, on any stream and
+    whatever has become of the kept buffers by then."""
+    stream = _stream()
+    if stream and _capturing():      # the null stream cannot be captured
+        return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+    key = (device, stream)
     buf = _ws_cache.get(key)
-    need = max(int(nbytes), 256)
-    if buf is None or buf.numel() < need:
-        buf = torch.empty(need, dtype=torch.uint8, device=device)
+    if buf is None or buf.numel() < nbytes:
+        buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        if key not in _ws_cache and len(_ws_cache) >= _WS_STREAMS:
+            _ws_cache.pop(next(iter(_ws_cache)), None)
         _ws_cache[key] = buf
     return buf
 
@@ -272,7 +282,9 @@ def _fc(fn, name, a, pa, b, pb, M, N, K, out_shape, which, acc_dtype, want_acc, 
     dev = a.device
     y = out if out is not None else torch.empty(out_shape, dtype=torch.float32, device=dev)
     acc = torch.empty(out_shape, dtype=acc_dtype, device=dev) if want_acc else None
-    ws = ws if ws is not None else workspace(_lib.q8t_qgemm_workspace_size(M, N, K, which), dev)
+    if ws is None:
+        need = _lib.q8t_qgemm_workspace_size(M, N, K, which)
+        ws = workspace(need, dev) if need else None
     _check(fn(_ptr(a), _ptr(pa), _ptr(b), _ptr(pb), M, N, K, _ptr(y), _ptr(acc), _ptr(ws), _stream()), name)
     return y, acc
 
