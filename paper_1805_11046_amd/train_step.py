@@ -493,6 +493,13 @@ def _pack_filters(x, ws):
 
 
 def step(x, labels, ws):
+    try:
+        return _step(x, labels, ws)
+    finally:
+        _qcache.clear()   # codes are found by address: they must not outlive the step whose tensors these addresses are
+
+
+def _step(x, labels, ws):
     _qcache.clear()
     _pcache.clear()
     _layer[0] = 0
@@ -524,6 +531,8 @@ def step(x, labels, ws):
 
 
 def bottleneck_step(x, gy, ws):
+    _qcache.clear()
+    _pcache.clear()
     _layer[0] = 0
     # one node where the chain's result has the shape of its input (nothing for the sum to broadcast)
     plain = ws[2].shape[0] == x.shape[1] and [tuple(w.shape[2:]) for w in ws] == [(1, 1), (3, 3), (1, 1)]

@@ -124,3 +124,22 @@ def test_filters_packed_in_one_launch_change_nothing():
         assert lo == results[0][0]
         for i, (a, b) in enumerate(zip(results[0][1], go)):
             assert torch.equal(a, b), "gradient of parameter %d differs" % i
+
+
+def test_a_step_leaves_no_codes_behind():
+    # a weight that changes in place after a step keeps its address: the next use has to quantize it again
+    q8t = require_gpu()
+    import torch
+    from paper_1805_11046_amd import train_step as ts
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(7)
+    ws = ts.make_weights(dev, gen)
+    x = torch.randn((2, 3, 64, 64), device=dev, generator=gen)
+    ts.step(x, torch.randint(0, 1000, (2,), device=dev, generator=gen), ws)
+    a = torch.randn((8, 512), device=dev, generator=gen)
+    with torch.no_grad():
+        ws["fc"].mul_(-3.0)
+        y = ts.Linear.apply(a, ws["fc"])
+    (qa, pa), (qw, pw) = q8t.quantize(a, 8), q8t.quantize(ws["fc"].detach(), 8)
+    assert torch.equal(y, q8t.qgemm_fwd(qa, pa, qw, pw)[0])
