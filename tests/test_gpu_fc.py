@@ -24,8 +24,6 @@ SHAPES = [
 @pytest.mark.parametrize("off", [0, 1])
 def test_fc_edges(M, N, K, off):
     q8t = require_gpu()
-    if off and M * N * K > 20000000:
-        pytest.skip("misaligned operands are covered at the small sizes")
     g = synth.rng(M * 7 + N * 3 + K)
     sx, px = _rand_q(g, (M, K))
     sw, pw = _rand_q(g, (K, N))
@@ -51,6 +49,30 @@ def test_fc_edges(M, N, K, off):
     odw, oacc = oracle.qgemm_wgrad(sx, px, sg16, pg16)
     same_ints(host(acc), oacc)
     same_ints(host(dw), odw)
+
+
+# 128x128 tiles whose reduction is longer than the two steps of prefetch: odd and even numbers of steps, with a last piece
+# that reaches back and without, operands at odd addresses and of odd pitch
+@pytest.mark.parametrize("which", ["fwd", "dgrad", "wgrad"])
+@pytest.mark.parametrize("red,off", [(129, 0), (192, 0), (300, 0), (320, 1), (333, 0), (333, 1), (384, 0), (1025, 0)])
+def test_fc_tile_pipeline(which, red, off):
+    q8t = require_gpu()
+    R, Cc = 1409, 1411
+    g = synth.rng(red)
+
+    def put(a):
+        flat = dev(a.ravel())
+        buf = flat.new_empty(flat.numel() + off)
+        buf[off:] = flat
+        return buf[off:].view(a.shape)
+
+    shapes = {"fwd": ((R, red), (red, Cc)), "dgrad": ((R, red), (Cc, red)), "wgrad": ((red, R), (red, Cc))}[which]
+    a, pa = _rand_q(g, shapes[0])
+    b, pb = _rand_q(g, shapes[1], **({"bits": 16} if which == "wgrad" else {}))
+    out, acc = getattr(q8t, "qgemm_" + which)(put(a), qp_dev_from(pa), put(b), qp_dev_from(pb), want_acc=True)
+    oout, oacc = getattr(oracle, "qgemm_" + which)(a, pa, b, pb)
+    same_ints(host(acc), oacc)
+    same_ints(host(out), oout)
 
 
 # few results under a long reduction: slices of it in workgroups of their own, the last one shorter, pieces that reach back
