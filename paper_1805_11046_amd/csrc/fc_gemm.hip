@@ -20,13 +20,14 @@
 // Two kernels (times: back to back on one MI355X, M x N x K, against the general kernel that served every FC call before):
 //   fc_direct  operands go from memory to registers, no LDS in the main loop; the wavefronts of a workgroup share a
 //              tile of 32x64 (wgrad 64x64) results and split its reduction, or own a tile each.  Bound by latency
-//              (launch, one or two dependent loads, the fold through LDS): 64x128x256 takes 3.5 / 3.5 / 8.0 us for
-//              forward / dgrad / wgrad (18.7 / 12.2 / 8.0 before), 256x1000x512 4.4 / 5.0 / 6.6 (23.9 / 15.8 / 19.7),
-//              512x2048x2048 10.5 / 14.7 / 19.  Few results and a long reduction: slices of it in workgroups of their own and
-//              fc_fold behind them.
-//   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  67 / 57 / 113 us
-//              at 2048x4096x4096 (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s.  The wavefronts wait for issue (44% of their
-//              cycles) more than for data: MFMA pipe 22% busy, L2 hits 92% at 304 clocks a read, LDS active a third of the time.
+//              (launch, one or two dependent loads, the fold through LDS): 64x128x256 takes 3.9 / 3.9 / 6.0 us for
+//              forward / dgrad / wgrad (18.7 / 12.2 / 8.0 before), 256x1000x512 4.7 / 5.2 / 6.8 (23.9 / 15.8 / 19.7), the
+//              forward and dgrad of 512x2048x2048 10.7 and 15.0.  Few results and a long reduction: slices of it in
+//              workgroups of their own and fc_fold behind them.
+//   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  65 / 59 / 112 us
+//              at 2048x4096x4096 (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s; 512x2048x2048's wgrad 19.  The wavefronts wait
+//              for issue (37 - 43% of their cycles) more than for data (23 - 28%): 4 - 6 vector instructions per MFMA, MFMA pipe
+//              20 - 26% busy, L2 hits 88 - 92% at 170 - 305 clocks a read, LDS active a quarter of the time.
 // Measured and dropped: prefetching the next K-step in fc_direct (more registers, fewer wavefronts: 7.5 -> 8.4 us at
 // 1024^3), RS operands through LDS and the transposing reads ds_read_b64_tr_b8 / _b16 with 32x32x32 MFMAs (half the
 // instructions, same time), K-steps of 128 in fc_tile with one or two register sets (whole 128-byte lines per row: 68 / 61 and
@@ -740,10 +741,12 @@ Plan plan_for(int which, int M, int N, int K)
     const int steps = (p.red + 63) / 64;
     p.ks = p.slices = 1;
     p.slice = steps;
-    // 128x128 tiles from half a tile per compute unit on: 1500^3 (144 tiles) takes 22 / 18 / 32 us in tiles and 22 / 20 / 34
-    // in fc_direct, 2048x616x3680's forward (90 tiles) 40 against 31; the weight gradient splits its reduction eight
-    // ways there and changes over a little later (128 tiles: 38 against 26 us).  With a single K-step a result narrower
-    // than a tile pays for the padding (weight gradient 65536x16x64 13.5 against 8.6 us).
+    // 128x128 tiles from half a tile per compute unit on (tiles / fc_direct, us): 1500x1500x1500, 144 tiles, 22.6 / 22.1 forward,
+    // 18.5 / 20.2 dgrad; 2048x1024 results, 128 tiles, over 2048: 25.7 / 20.7, 20.5 / 26.6; the forward of 2048x616x3680, 80
+    // tiles, 39.7 / 30.1.  The weight gradient's fc_direct holds 64 KB of LDS per tile of 64x64, so 512 of those, 128 of these,
+    // are one round of workgroups and more are two: 128 tiles over 128 and 2048 10.9 / 12.2 and 39.2 / 29.0, 144 11.1 / 17.3 and
+    // 39.4 / 41.8.  With a single K-step a result narrower than a tile pays for the padding (weight gradient 65536x16x64 13.5
+    // against 8.6).
     p.tile = t128 >= (which == 2 ? 140 : 128) && (p.red > 64 || (p.red == 64 && p.rows > 64 && p.cols > 64));
     p.tn = p.tile ? (p.cols + 127) / 128 : (p.cols + 63) / 64;
     const int tr = which == 2 ? 64 : 32;
