@@ -2,10 +2,10 @@
 // take 8-bit operands and accumulate in 32 bits): any filter size, stride, padding and channel count.
 // Three launches per call:
 //
-//  1. to_nhwc      (many small planes: to_nhwc_small) the NCHW int8 operand is rewritten channel-contiguous ([N][H][W][Cp], Cp = reduction
+//  1. to_nhwc      the NCHW int8 operand is rewritten channel-contiguous ([N][H][W][Cp], Cp = reduction
 //                  channels rounded up to 16) into the workspace, so that 16 reduction channels of one
 //                  filter tap are one aligned 16-byte piece; the same pass emits the per-position channel
-//                  sum that the zero-point correction needs.
+//                  sum that the zero-point correction needs.  (to_nhwc_small for many small planes.)
 //  2. repack_taps  filter -> [class][output channel][tap][Cp], each row filled up with zeros to a multiple
 //                  of 64 and the output channels to a multiple of 64, and the per-output-channel sums
 //                  (per stride class).
