@@ -32,15 +32,16 @@ bool smallc_wanted(int which, const q8t_conv_desc *d) { return q8t_smallc_conv_s
 bool wgrad_wants_gemm(const q8t_conv_desc *d) { return q8t_gemm_wgrad_supported(d) && not_tiny(d); }
 
 // The form of a forward (which = 0) or layer-gradient (1) product that no specialised kernel takes.  Channel counts that are
-// multiples of 64 run on the channel-contiguous path; elsewhere the estimates of the three forms decide.  No simple line
+// multiples of 64 run on the channel-contiguous path; elsewhere the estimates of the forms decide.  No simple line
 // separates them: the general kernel gathers bytes but splits a long reduction over the chip and needs one launch where
 // that is short, the channel-contiguous path copies its operand and pads it to 16 channels, the first-layer kernel pads
-// a filter row to eight taps.  Measured, us a call, general / channel-contiguous / first-layer form:
+// a filter row to eight taps, im2col rows pad nothing but multiply the operand.  Measured, us a call, general / channel-contiguous / first-layer form:
 //   472 -> 1 7x7 @7x4 batch 5   46 / 202 / -       16 -> 64 3x3 @32 batch 128 54 / 24 / -       4 -> 32 3x3 @27 batch 64 12.5 / 17.2 / -
 //   32 -> 512 1x1 @27 batch 64 65 / 59 / 104       3 -> 64 7x7/2 @27 batch 64 21 / 29 / 14       3 -> 64 1x1 @7 batch 56 8 / 14 / 12
 // Over 3700 calls (channels 1 .. 600, filters up to 7x7, strides 1 .. 3, planes 1 .. 224, batches 1 .. 65536, with and without
-// statistics) the form taken is 0.5% slower than the best of the three in the mean, more than 7% in 140 of them, 1.6 times at
-// most.
+// statistics) the form taken is 0.5% slower than the best of the first three in the mean, more than 7% in 140 of them, 1.6 times
+// at most; over the 1646 calls with few channels that the estimate of im2col rows was fitted to 0.7%, 61 and 1.5 times
+// (without them 4.1%, 247 and 1.9).  Under 1x1 filters they are only a second copy: 32 -> 512 @27 batch 64 63 us, 59 without.
 enum Form { FIRST, NHWC, SMALLC, GENERAL };
 Form conv_form(int which, const q8t_conv_desc *d, bool stats)
 {
@@ -48,13 +49,16 @@ Form conv_form(int which, const q8t_conv_desc *d, bool stats)
     if (nhwc && d->C % 64 == 0 && d->K % 64 == 0) return NHWC;
     Form f = GENERAL;
     double best = q8t_generic_conv_us(which, d, stats);
-    const double us = nhwc ? q8t_nhwc_conv_us(which, d, stats) : best;
-    if (us < best) {
-        f = NHWC;
-        best = us;
-    }
-    if (first && q8t_first_conv_us(d, stats) < best) f = FIRST;
-    return f == GENERAL && smallc_wanted(which, d) ? SMALLC : f;
+    auto consider = [&](Form g, double us) {
+        if (us < best) {
+            f = g;
+            best = us;
+        }
+    };
+    if (nhwc) consider(NHWC, q8t_nhwc_conv_us(which, d, stats));
+    if (nhwc && d->R * d->S > 1 && q8t_smallc_conv_supported(which, d)) consider(SMALLC, q8t_smallc_conv_us(d, stats));
+    if (first) consider(FIRST, q8t_first_conv_us(d, stats));
+    return !nhwc && f == GENERAL && smallc_wanted(which, d) ? SMALLC : f;   // beyond 49 taps or strides of 4
 }
 
 size_t form_ws(int which, const q8t_conv_desc *d, bool stats)

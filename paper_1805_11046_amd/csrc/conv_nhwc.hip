@@ -824,10 +824,11 @@ __device__ __forceinline__ void stage_rows(const int8_t *__restrict__ x, int n, 
 }
 
 // ---- forward with few input channels and many taps ------------------------------------------------
-// Where the channel-contiguous path above does not take the shape (filters of more than 49 taps, strides beyond 4): the reduction (c, r, s) of an output position is laid out explicitly: xn[m][Kc] with
-// Kc = C*R*S rounded up to a multiple of 64, entry c*R*S + r*S + s = the input code under that tap
-// (zero code in the padding and in the surplus columns), plus the row sum.  With the filter as
-// [K][Kc] (zeros in the surplus columns) the product is a 1x1 problem for igemm_nhwc.
+// The reduction (c, r, s) of an output position is laid out explicitly: xn[m][Kc] with Kc = C*R*S rounded up to a multiple of
+// 64, entry c*R*S + r*S + s = the input code under that tap (zero code in the padding and in the surplus columns), plus
+// the row sum.  With the filter as [K][Kc] (zeros in the surplus columns) the product is a 1x1 problem for igemm_nhwc.  Beyond
+// the limits of the path above (filters of more than 49 taps, strides beyond 4), and where the estimate is lowest here:
+// 8 channels under 5x5 taps are 4 K-steps of 64 instead of 7 (8 -> 64 @12 batch 16 20.3 -> 14.2 us, 20 -> 512 7x7/2 34.2 -> 25.6).
 // One workgroup per (image, output row): the R input rows of every channel go to LDS once.
 __global__ __launch_bounds__(kThreads) void im2col_positions(const int8_t *__restrict__ x, int C, int H, int W, int R, int S,
                                                              int stride, int pad, int P, int Q, int Kc,
@@ -1003,14 +1004,12 @@ bool make_small_plan(int which, const q8t_conv_desc *d, SmallPlan *p)
     p->Kc = (int)((crs + 63) / 64 * 64);
     p->P = (d->H + 2 * d->pad - d->R) / d->stride + 1;
     p->Q = (d->W + 2 * d->pad - d->S) / d->stride + 1;
-    if (d->N > 65535) return false;
+    if (d->N > 65535 || p->P >= (1 << 24) || d->K >= (1 << 24)) return false;   // 2^32 threads are too many for a launch
     const int64_t M = (int64_t)d->N * p->P * p->Q;
     if (M >= ((int64_t)1 << 31) || (int64_t)d->N * d->C * d->H >= ((int64_t)1 << 31)) return false;
     p->lds = (((size_t)d->C * d->R * ((((d->pad + 3) & ~3) + d->W + d->pad + 3) & ~3) + 15) & ~(size_t)15) +
              ((size_t)p->Kc + p->Q) * sizeof(int);
     if (p->lds > 65536) return false;
-    Plan general;
-    if (make_plan(0, d, &general)) return false;   // the channel-contiguous path takes it
     p->o_rowsum = up256((size_t)M * p->Kc);
     p->o_wt = p->o_rowsum + up256((size_t)M * sizeof(int));
     p->o_colsum = p->o_wt + up256((size_t)d->K * p->Kc);
@@ -1025,6 +1024,25 @@ bool q8t_smallc_conv_supported(int which, const q8t_conv_desc *d)
 {
     SmallPlan p;
     return make_small_plan(which, d, &p);
+}
+
+// As q8t_generic_conv_us, for the forward product here (the shape is supported): three launches; 1024 workgroups of the im2col
+// side by side, its rows written and read, the K-steps as in q8t_nhwc_conv_us.  Measured time 0.7 .. 1.45 of it in
+// 97% of the 1646 calls that it was fitted to.
+double q8t_smallc_conv_us(const q8t_conv_desc *d, bool stats)
+{
+    SmallPlan p;
+    if (!make_small_plan(0, d, &p)) return 0.0;
+    const double M = (double)d->N * p.P * p.Q, wgs = (double)d->N * p.P, rounds = wgs > 1024 ? wgs / 1024 : 1.0;
+    const int bn = d->K % 128 == 0 ? 128 : 64, pitch = ((d->pad + 3) & ~3) + d->W + d->pad;
+    const double tiles = (double)(((int64_t)M + 127) / 128) * (d->K / bn);
+    const double t = (double)(((int64_t)tiles + 255) / 256) * (bn == 128 ? 1.6 : 1.0);
+    const int pieces = (p.Q * (p.Kc / 16) + kThreads - 1) / kThreads;
+    const int loads = (d->C * d->R * (d->W % 4 ? d->W : d->W / 4) + kThreads * 6 - 1) / (kThreads * 6);
+    const int fill = (d->C * d->R * pitch / 4 + kThreads - 1) / kThreads, steps = p.Kc / 64;
+    const double us = 10.5 + 0.35 * steps + 0.51 * steps * (t - 1.0) + 2.1 * t + rounds * (0.023 * pieces + 1.7 * loads + 0.5 * fill) +
+                      0.84e-6 * M * p.Kc + 2.4e-6 * d->K * p.Kc;
+    return us + (stats ? q8t_range_bn_stats_us(d->N, d->K, (int64_t)p.P * p.Q) : 0.0);
 }
 
 size_t q8t_smallc_conv_ws(int which, const q8t_conv_desc *d)

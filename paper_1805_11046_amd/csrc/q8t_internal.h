@@ -23,6 +23,7 @@ size_t q8t_generic_conv_ws(int which, const q8t_conv_desc *d);
 double q8t_generic_conv_us(int which, const q8t_conv_desc *d, bool stats);
 double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats);
 double q8t_first_conv_us(const q8t_conv_desc *d, bool stats);
+double q8t_smallc_conv_us(const q8t_conv_desc *d, bool stats);
 int q8t_conv_reduction_check(int which, const q8t_conv_desc *d);
 
 // Per-workgroup statistics of the corrected integer outputs of one output channel, gathered in a
@@ -76,8 +77,8 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
                   hipStream_t st);
 size_t q8t_nhwc_conv_stats_ws(const q8t_conv_desc *d);
 
-// forward with fewer than 64 input channels where that path does not reach (more taps, larger strides), output channels
-// a multiple of 64: explicit im2col rows + the same GEMM
+// forward with fewer than 64 input channels, at most 1024 reduction entries, output channels a multiple of 64: explicit im2col
+// rows + the same GEMM
 bool q8t_smallc_conv_supported(int which, const q8t_conv_desc *d);
 size_t q8t_smallc_conv_ws(int which, const q8t_conv_desc *d);
 int q8t_smallc_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b, const q8t_qparams *qb,

@@ -123,3 +123,4 @@ def test_form_of_a_product_follows_its_size():
     assert size(40, 16, 32, 32, 16, 3, 3, 1, 1) >= 40 * 32 * 32 * (16 + 4)    # copy of the operand and its channel sums
     assert 0 < size(64, 32, 27, 27, 512, 1, 1, 1, 0) - 64 * 27 * 27 * (32 + 4) < 1 << 20
     assert 64 * 192 <= size(64, 3, 27, 27, 64, 7, 7, 2, 3) < 1 << 16          # first-layer kernel: the packed filter
+    assert size(16, 8, 12, 12, 64, 5, 5, 1, 2) >= 16 * 12 * 12 * 256          # im2col rows: 200 columns filled up to 256

@@ -118,6 +118,25 @@ def test_conv_few_channels_ragged_rows(case):
     (5, 472, 7, 4, 1, 7, 7, 1, 3),        # few results, long reduction: general kernel, split
     (2, 5, 27, 24, 128, 5, 3, 1, 1),      # general product, first-layer kernel with statistics
     (4, 1, 11, 18, 80, 1, 1, 1, 0),       # general product, statistics in a pass of their own
+    (16, 8, 12, 12, 64, 5, 5, 1, 2),      # im2col rows, one tile width; surplus columns 200 .. 255
+    (16, 20, 12, 12, 512, 7, 7, 2, 3),    # ... 128-wide tiles, statistics in a pass of their own
+    (57, 5, 8, 5, 64, 7, 7, 2, 3),        # ... rows that are no whole dwords, last row tile short
+    (2, 8, 4, 4, 64, 7, 7, 1, 3),         # ... fewer positions than a tile, most taps in the padding
 ])
 def test_conv_forms(case):
     test_conv_channel_counts(case)
+
+
+def test_conv_im2col_rows_at_odd_addresses():
+    import torch
+    q8t = require_gpu()
+    case = (16, 8, 12, 12, 64, 5, 5, 1, 2)    # whole dwords in a row, but not at the operand's address
+    od, (sx, px), (sw, pw), _, _ = _conv_operands(synth.rng(208), case)
+    _, oacc = oracle.qconv_fwd(od, sx, px, sw, pw)
+    x = dev(sx)
+    for off in (1, 2, 3):
+        buf = torch.empty(x.numel() + off, dtype=torch.int8, device=x.device)
+        shifted = buf[off:].view(x.shape)
+        shifted.copy_(x)
+        _, acc = q8t.qconv_fwd(q8t.conv_desc(*case), shifted, qp_dev_from(px), dev(sw), qp_dev_from(pw), want_acc=True)
+        same_ints(host(acc), oacc)
