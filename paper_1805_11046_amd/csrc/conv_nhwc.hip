@@ -239,6 +239,7 @@ __global__ __launch_bounds__(kThreads) void repack_taps(const int8_t *__restrict
 // per step: dt taps and dc pieces, and one tap more when the pieces of a tap are used up.
 template <class C>
 struct ConvOps {
+    typedef q8t_gemm::Regs R;
     const int8_t *xin, *wt;              // wt: the thread's piece of its filter row
     const __attribute__((address_space(3))) int *stap;   // tap offsets, in LDS (3 readable entries behind the last)
     int IH, IW, Cp, CC, dt, dc, q;       // CC = Cp / 16
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
 
-    q8t_gemm::pipeline<C>(ops, wpitch >> 6, sA, sB, acc);
+    q8t_gemm::pipeline<C>(ops, wpitch >> 6, sA, sB, acc, tid);
     if (g.T == 0) __syncthreads();   // rs / roff of the other threads
 
     // ---- epilogue: zero-point correction in wrapping 32-bit arithmetic (the corrected value fits
@@ -685,8 +686,8 @@ __global__ __launch_bounds__(C::THREADS, 2) void igemm_nhwc_pair(const int8_t *_
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) accA[mt][nt] = accB[mt][nt] = (v4i){0, 0, 0, 0};
 
-    q8t_gemm::pipeline<C>(opsA, ciA[5] >> 6, sA, sB, accA);
-    q8t_gemm::pipeline<C>(opsB, ciB[5] >> 6, sA, sB, accB);
+    q8t_gemm::pipeline<C>(opsA, ciA[5] >> 6, sA, sB, accA, tid);
+    q8t_gemm::pipeline<C>(opsB, ciB[5] >> 6, sA, sB, accB, tid);
 
     // ---- epilogue: both classes corrected and dequantized, written as pairs ----
     const uint32_t kzzA = (uint32_t)(TA * g.red) * (uint32_t)za * (uint32_t)zb;

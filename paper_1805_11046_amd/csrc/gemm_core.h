@@ -18,10 +18,11 @@
 // up to an even number and the surplus step multiplies staged zeros.
 //
 // The kernel supplies an `Ops` object:
-//   void load(Regs &r, bool valid)     issue the global loads of the next K-step: a0 / a1 = chunk q of
+//   type R                             Regs, or a struct that starts with its members
+//   void load(R &r, bool valid)        issue the global loads of the next K-step: a0 / a1 = chunk q of
 //                                      tile rows ar and ar + RP, b0 / b1 likewise for the columns
 //                                      (valid == false: any readable address, no advance)
-//   void prepare(Regs &r, bool valid)  called right before the registers go to LDS: transform them
+//   void prepare(R &r, bool valid)     called right before the registers go to LDS: transform them
 //                                      in place (byte-plane split, byte sums); with !valid the B
 //                                      registers must become zero (and A too if sums are kept)
 // with ar = tid >> 2, q = tid & 3, RP = threads / 4.
@@ -104,23 +105,23 @@ __device__ __forceinline__ void compute_step(const int8_t *__restrict__ sa, cons
     }
 }
 
-// sA: 2 * BM * 64 bytes, sB: 2 * BN * 64 bytes
+// sA: 2 * BM * 64 bytes, sB: 2 * BN * 64 bytes; tid: thread among the C::THREADS of a tile (a workgroup may hold several
+// groups of them, which meet at the same barriers: as many steps in each)
 template <class C, class Ops>
 __device__ __forceinline__ void pipeline(Ops &ops, int steps, int8_t *__restrict__ sA, int8_t *__restrict__ sB,
-                                         v4i (&acc)[C::MT][C::NT])
+                                         v4i (&acc)[C::MT][C::NT], int tid)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kb = lane >> 4;
     const int rowbase = C::rowbase(wave), colbase = C::colbase(wave);
     const int ar = tid >> 2;
     const int so = ar * 64 + (((tid & 3) ^ swz(ar)) * 16);   // LDS offset of the thread's chunk in row ar
     if (steps <= 0) return;
-    Regs q0, q1;
-    q0.a0 = q0.a1 = q0.b0 = q0.b1 = make_uint4(0, 0, 0, 0);
-    q1 = q0;
-#define Q8T_GEMM_STORE(R, BUF, VALID)                                                   \
+    typedef typename Ops::R R;
+    R q0 = {}, q1 = {};
+#define Q8T_GEMM_STORE(REGS, BUF, VALID)                                                \
     {                                                                                   \
-        Regs t_ = R;                                                                    \
+        R t_ = REGS;                                                                    \
         ops.prepare(t_, VALID);                                                         \
         int8_t *a_ = sA + (BUF)*C::BM * 64 + so, *b_ = sB + (BUF)*C::BN * 64 + so;      \
         *reinterpret_cast<uint4 *>(a_) = t_.a0;                                         \
@@ -130,12 +131,12 @@ __device__ __forceinline__ void pipeline(Ops &ops, int steps, int8_t *__restrict
     }
     // one step: MFMAs on buffer S&1 while tile S+1 goes from registers to the other buffer and the
     // loads of tile S+3 are issued; everything between two barriers is one scheduling region
-#define Q8T_GEMM_STEP(R, S)                                                             \
+#define Q8T_GEMM_STEP(REGS, S)                                                          \
     {                                                                                   \
         const int buf = (S)&1;                                                          \
         compute_step<C>(sA + buf * C::BM * 64, sB + buf * C::BN * 64, rowbase, colbase, l16, kb, acc); \
-        Q8T_GEMM_STORE(R, buf ^ 1, (S) + 1 < steps)                                     \
-        ops.load(R, (S) + 3 < steps);                                                   \
+        Q8T_GEMM_STORE(REGS, buf ^ 1, (S) + 1 < steps)                                  \
+        ops.load(REGS, (S) + 3 < steps);                                                \
         q8t_lds_barrier();                                                              \
     }
     ops.load(q0, true);

@@ -6,15 +6,19 @@
 //
 //   A'[2K][Mp]   rows k      : high bytes of the stored 16-bit gradient codes of output channel k
 //                rows K + k  : their low bytes, re-centred ( s = 256*hi + lo + 128, hi and lo signed bytes )
-//   B'[CRS][Mp]  row (c,r,s) : the input code that meets gradient position m under filter tap (r,s)
-//                              (stored zero point where the tap falls into the padding)
-//   m = (n*P + p)*Q + q, padded with zero codes up to Mp (a multiple of 64).
+//   B'[CRS][Mp]  column (c,r,s) : the input code that meets gradient position m under filter tap (r,s)
 //
-// Launches: split16 (builds A'), im2col_rows (builds B'), gemm_nt (int8 MFMA, 128x128 or 128x64
-// tiles, the reduction split over blockIdx.z into slices of at most 65536 products so that the
+// B' is never written: both operands are laid out on padded planes of one pitch, where a tap is an offset into the row of
+// its input channel.
+//
+// Launches: pad_operands (A' and the padded input), gemm_nt (int8 MFMA, 256x256, 128x128 or 128x64
+// tiles, the reduction split into slices of at most 65536 products so that the
 // 32-bit accumulators cannot overflow), wgrad_finish (sums the slices in 64 bits, recombines the
 // two byte planes, applies the zero-point correction, dequantizes).  Exact for any reduction
 // length: every partial sum is an integer below 2^31 and the recombination is done in int64.
+// Whole calls, us, against byte planes + im2col rows + a GEMM without shared tiles: 96 -> 200 3x3 @27 batch 50 90 -> 55,
+// 64 -> 64 5x5 @56 batch 128 530 -> 208, 48 -> 80 3x3 @32 batch 64 50 -> 40, 112 -> 96 1x1 @56 batch 32 51 -> 34, 208 -> 160
+// 3x3/2 @14 batch 64 42 -> 32, 48 -> 64 3x3 @3 batch 300 28 -> 18, 128 -> 128 5x5 @4 batch 100 (49 positions for 16) 31 -> 28.
 #include "q8t_common.h"
 #include "q8t_internal.h"
 #include "gemm_core.h"
@@ -43,223 +47,207 @@ __device__ __forceinline__ int fdiv(int x, int d, float rd)
     return q;
 }
 
-// ---- A': byte planes of the 16-bit gradient, [2K][Mp] -----------------------------------------
-// G = codes per global load: 16 (planes of a multiple of 16 positions, 32-byte aligned rows),
-// 4 (multiple of 4, 8-byte aligned) or 1.  A group of G positions never straddles two images.
-template <int G>
-__global__ __launch_bounds__(kThreads) void split16(const int16_t *__restrict__ g16, int K, int PQ, int64_t Mtot,
-                                                    int64_t Mp, const q8t_qparams *__restrict__ qpg,
-                                                    int8_t *__restrict__ A)
-{
-    const int64_t chunks = Mp >> 4;
-    const int64_t id = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (id >= chunks * K) return;
-    const int k = (int)(id / chunks);
-    const int64_t m0 = (id - (int64_t)k * chunks) << 4;
-    const int zsg = qpg->zero_point - (1 << (qpg->bits - 1));
-    const uint32_t zz = (uint32_t)(zsg & 0xFFFF) * 0x00010001u;
-    int n = (int)(m0 / PQ), pq = (int)(m0 - (int64_t)n * PQ);
-    uint32_t d[8];   // 16 codes, two per dword
-#pragma unroll
-    for (int i = 0; i < 8; ++i) d[i] = zz;
-    if (G == 16) {
-        if (m0 < Mtot) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(g16 + ((size_t)n * K + k) * PQ + pq);
-            const uint4 u = src[0], v = src[1];
-            d[0] = u.x; d[1] = u.y; d[2] = u.z; d[3] = u.w;
-            d[4] = v.x; d[5] = v.y; d[6] = v.z; d[7] = v.w;
-        }
-    } else if (G == 4) {
-#pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-            if (m0 + grp * 4 < Mtot) {
-                const uint2 u = *reinterpret_cast<const uint2 *>(g16 + ((size_t)n * K + k) * PQ + pq);
-                d[grp * 2] = u.x;
-                d[grp * 2 + 1] = u.y;
-            }
-            pq += 4;
-            if (pq == PQ) {
-                pq = 0;
-                ++n;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (m0 + i < Mtot) {
-                const uint32_t s = (uint16_t)g16[((size_t)n * K + k) * PQ + pq];
-                d[i >> 1] = (i & 1) ? (d[i >> 1] & 0x0000FFFFu) | (s << 16) : (d[i >> 1] & 0xFFFF0000u) | s;
-            }
-            if (++pq == PQ) {
-                pq = 0;
-                ++n;
-            }
-        }
-    }
-    uint32_t hi[4], lo[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        hi[i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], 0x07050301u);
-        lo[i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], 0x06040200u) ^ 0x80808080u;
-    }
-    *reinterpret_cast<uint4 *>(A + (size_t)k * Mp + m0) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    *reinterpret_cast<uint4 *>(A + (size_t)(K + k) * Mp + m0) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-}
-
-// ---- B': one row per (c, r, s), [CRS][Mp] ------------------------------------------------------
-struct ConvG {
-    int N, C, H, W, K, R, S, stride, pad, P, Q;
+// ---- operands on padded planes --------------------------------------------------------------------
+// The gradient and the input are laid out on planes of the same pitch, so that a filter tap is a constant
+// offset into the row of its input channel and all taps of a channel share that row.  With i = r / stride, a = r % stride
+// and j = s / stride, b = s % stride, gradient position (p, q) meets plane (a, b) of the input at (p + i, q + j):
+//   A'[2K][Mp]            byte planes of the gradient at m = (n*PR + p)*PC + q, both bytes 0 at the pad positions
+//   X'[(a, b)][C][XL]     input code at (row*stride + a - pad, col*stride + b - pad) of image n, the zero code outside
+//   column (c, r, s)   =  X'[(a, b)][c] + i*PC + j, read as it lies (16-byte loads at any address)
+//   mask[Mp]              1 at the real positions: a column's byte sum may count nothing else
+// Planes share their pad columns (rows) with the next row (image) as far as both sides are padding.
+struct PadG {
+    int N, C, H, W, K, P, Q, stride, pad;
+    int ra, sa;              // input planes per channel
+    int PC, IS;              // row pitch, positions per image
+    int64_t Mp, XL;          // lengths of a row of A' and of X'
+    int chunks;              // kPadChunk positions each
+    int rows, gblocks, xblocks;   // channels per workgroup; blocks of them in the gradient, in one input plane
 };
+constexpr int kPadChunk = 4 * kThreads;   // positions per workgroup
 
-__global__ __launch_bounds__(kThreads) void im2col_rows(const int8_t *__restrict__ x, ConvG g, int64_t Mtot, int64_t Mp,
-                                                        const q8t_qparams *__restrict__ qpx, int8_t *__restrict__ B)
+// A lane owns four positions and walks the channels of its workgroup: where the codes of its positions lie inside an image is
+// the same for every channel, so the divisions are paid once and a channel costs a load, two byte permutes (one) and two
+// stores (one).  The codes are neighbours in memory except for the pads between them: one load of four codes holds them all,
+// unless the group spans two images, the plane is smaller than the load or codes are skipped (stride > 1).
+// 96 -> 200 channels @27, batch 50 (18 MB in, 20 MB out): 10 us; byte planes and im2col rows in launches of their own
+// (46 MB out) 42.5 us, one channel per workgroup 19 to 24.
+__global__ __launch_bounds__(kThreads) void pad_operands(const int16_t *__restrict__ g16, const int8_t *__restrict__ x, PadG g,
+                                                         const q8t_qparams *__restrict__ qpx, int8_t *__restrict__ A,
+                                                         int8_t *__restrict__ X, int8_t *__restrict__ mask)
 {
-    const int64_t chunks = Mp >> 4;
-    const int64_t id = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int CRS = g.C * g.R * g.S;
-    if (id >= chunks * CRS) return;
-    const int col = (int)(id / chunks);
-    const int64_t m0 = (id - (int64_t)col * chunks) << 4;
-    const int RS = g.R * g.S;
-    const int c = col / RS, t = col - c * RS, r = t / g.S, s = t - r * g.S;
-    const int zsx = qpx->zero_point - (1 << (qpx->bits - 1));
-    const int PQ = g.P * g.Q;
-    int n = (int)(m0 / PQ);
-    const int rem = (int)(m0 - (int64_t)n * PQ);
-    int p = rem / g.Q, q = rem - p * g.Q;
-    uint32_t o[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        int v = zsx;
-        if (m0 + i < Mtot) {
-            const int h = p * g.stride + r - g.pad, w = q * g.stride + s - g.pad;
-            if ((unsigned)h < (unsigned)g.H && (unsigned)w < (unsigned)g.W)
-                v = x[(((size_t)n * g.C + c) * g.H + h) * g.W + w];
-        }
-        o[i >> 2] |= (uint32_t)(v & 255) << (8 * (i & 3));
-        if (++q == g.Q) {
-            q = 0;
-            if (++p == g.P) {
-                p = 0;
-                ++n;
-            }
-        }
-    }
-    *reinterpret_cast<uint4 *>(B + (size_t)col * Mp + m0) = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// Same result through LDS: a workgroup stages the zero-padded planes of CG channels for a group of
-// NI images (NI*P*Q a multiple of 4, so that its stretch of every row starts on a dword), then
-// every thread builds, for one channel, one dword (4 consecutive positions) for each of the R*S
-// taps.  The input is read once instead of R*S times and every store is a full dword.
-// A staged plane has (H + 2*pad) rows of `pitch` bytes; the image starts at column L = pad rounded
-// up to a multiple of 4 and the pitch is a multiple of 4, so that an aligned dword of the input
-// (W % 4 == 0) is an aligned dword of the plane.
-struct PlaneG {
-    int L, pitch, PB;   // left margin, row pitch, bytes per plane (a multiple of 4)
-    int vec;            // bytes per aligned input load: 4, 2 or 1
-};
-
-__global__ __launch_bounds__(kThreads) void im2col_planes(const int8_t *__restrict__ x, ConvG g, PlaneG pg, int NI, int CG,
-                                                          int64_t Mtot, int64_t Mp, const q8t_qparams *__restrict__ qpx,
-                                                          int8_t *__restrict__ B)
-{
-    extern __shared__ __align__(16) int8_t planes[];
-    const int c0 = blockIdx.y * CG, n0 = blockIdx.x * NI;
-    const int ni = min(NI, g.N - n0), cg = min(CG, g.C - c0);
-    const int PB = pg.PB, pitch = pg.pitch;
-    const int PQ = g.P * g.Q, HW = g.H * g.W;
-    const int zsx = qpx->zero_point - (1 << (qpx->bits - 1));
-    const uint32_t zb = (uint32_t)(zsx & 255);
-    {
-        uint32_t *pw = reinterpret_cast<uint32_t *>(planes);
-        for (int i = threadIdx.x; i < (cg * NI * PB) >> 2; i += kThreads) pw[i] = zb * 0x01010101u;
-    }
-    __syncthreads();
-    // plane (cl, nl) sits at (cl*NI + nl)*PB
-    if (pg.vec == 4) {
-        const int HW4 = HW >> 2, W4 = g.W >> 2;
-        const float rHW4 = 1.0f / (float)HW4, rW4 = 1.0f / (float)W4;
-        for (int i = threadIdx.x; i < cg * ni * HW4; i += kThreads) {
-            const int pl = fdiv(i, HW4, rHW4), t = i - pl * HW4, h = fdiv(t, W4, rW4), w4 = t - h * W4;
-            const int cl = pl / ni, nl = pl - cl * ni;
-            const uint32_t v = *reinterpret_cast<const uint32_t *>(x + ((size_t)(n0 + nl) * g.C + c0 + cl) * HW + (size_t)t * 4);
-            *reinterpret_cast<uint32_t *>(planes + (cl * NI + nl) * PB + (h + g.pad) * pitch + pg.L + w4 * 4) = v;
-        }
-    } else if (pg.vec == 2) {
-        const int HW2 = HW >> 1, W2 = g.W >> 1;
-        const float rHW2 = 1.0f / (float)HW2, rW2 = 1.0f / (float)W2;
-        for (int i = threadIdx.x; i < cg * ni * HW2; i += kThreads) {
-            const int pl = fdiv(i, HW2, rHW2), t = i - pl * HW2, h = fdiv(t, W2, rW2), w2 = t - h * W2;
-            const int cl = pl / ni, nl = pl - cl * ni;
-            const uint16_t v = *reinterpret_cast<const uint16_t *>(x + ((size_t)(n0 + nl) * g.C + c0 + cl) * HW + (size_t)t * 2);
-            *reinterpret_cast<uint16_t *>(planes + (cl * NI + nl) * PB + (h + g.pad) * pitch + pg.L + w2 * 2) = v;
-        }
-    } else {
-        const float rHW = 1.0f / (float)HW, rW = 1.0f / (float)g.W;
-        for (int i = threadIdx.x; i < cg * ni * HW; i += kThreads) {
-            const int pl = fdiv(i, HW, rHW), t = i - pl * HW, h = fdiv(t, g.W, rW), w = t - h * g.W;
-            const int cl = pl / ni, nl = pl - cl * ni;
-            planes[(cl * NI + nl) * PB + (h + g.pad) * pitch + pg.L + w] = x[((size_t)(n0 + nl) * g.C + c0 + cl) * HW + t];
-        }
-    }
-    __syncthreads();
-    const float rPQ = 1.0f / (float)PQ, rQ = 1.0f / (float)g.Q;
-    const int64_t mbase = (int64_t)n0 * PQ;
-    const bool last = n0 + NI >= g.N;
-    const int64_t mend = last ? Mp : mbase + (int64_t)NI * PQ;   // the last group also writes the padding
-    const int ndw = (int)((mend - mbase) >> 2);
-    const float rndw = 1.0f / (float)ndw;
-    const int RS = g.R * g.S;
-    const int col0 = pg.L - g.pad;   // plane column of input column -pad
-    for (int it = threadIdx.x; it < cg * ndw; it += kThreads) {
-        const int cl = fdiv(it, ndw, rndw), dp = it - cl * ndw;
-        int off[4];
+    int by = blockIdx.y;
+    const bool grad = by < g.gblocks;
+    by -= grad ? 0 : g.gblocks;
+    const int cls = grad ? 0 : by / g.xblocks, a = cls / g.sa, b = cls - a * g.sa;
+    const int c0 = (by - cls * g.xblocks) * g.rows, channels = grad ? g.K : g.C, c1 = min(c0 + g.rows, channels);
+    const int h0 = grad ? 0 : a - g.pad, w0 = grad ? 0 : b - g.pad, step = grad ? 1 : g.stride;
+    const int hend = grad ? g.P : g.H, wend = grad ? g.Q : g.W, plane = hend * wend;
+    const uint32_t len = (uint32_t)(grad ? g.Mp : g.XL);
+    const int PR = g.IS / g.PC;
+    const float rIS = 1.0f / (float)g.IS, rPC = 1.0f / (float)g.PC;
+    for (uint32_t chunk = blockIdx.x; chunk < (uint32_t)g.chunks; chunk += gridDim.x) {
+        const uint32_t m0 = chunk * kPadChunk, off = threadIdx.x * 4, m = m0 + off;
+        if (m >= len) break;
+        const uint32_t n_first = m0 / (uint32_t)g.IS;   // uniform
+        const int t = (int)(m0 - n_first * (uint32_t)g.IS + off);
+        const bool small = g.IS < (1 << 22);            // the quotient by a float reciprocal is exact
+        const int dn = small ? fdiv(t, g.IS, rIS) : t / g.IS, rem = t - dn * g.IS;
+        int n = (int)n_first + dn, pr = small ? fdiv(rem, g.PC, rPC) : rem / g.PC, pc = rem - pr * g.PC;
+        const int n0 = n;
+        int place[4], image[4];
+        uint32_t real = 0;
+        bool one = step == 1 && plane >= 4;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int e = dp * 4 + j;
-            off[j] = -1;
-            if (mbase + e < Mtot) {
-                const int nl = fdiv(e, PQ, rPQ), t = e - nl * PQ, pp = fdiv(t, g.Q, rQ), qq = t - pp * g.Q;
-                off[j] = (cl * NI + nl) * PB + pp * g.stride * pitch + qq * g.stride + col0;
+            const int h = pr * step + h0, w = pc * step + w0;
+            const bool in = n < g.N && (unsigned)h < (unsigned)hend && (unsigned)w < (unsigned)wend;
+            place[j] = h * wend + w;
+            image[j] = n;
+            real |= in ? 1u << j : 0u;
+            one = one && (!in || n == n0);
+            if (++pc == g.PC) {
+                pc = 0;
+                if (++pr == PR) {
+                    pr = 0;
+                    ++n;
+                }
             }
         }
-        int8_t *dst = B + ((size_t)(c0 + cl) * RS) * Mp + mbase + (int64_t)dp * 4;
-        for (int r = 0; r < g.R; ++r)
-            for (int s = 0; s < g.S; ++s) {
-                const int o = r * pitch + s;
-                uint32_t v = 0;
+        // the load: four codes from `from` on, inside the plane; sel: which of them each position takes, 8: none
+        int from = plane - 4;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t b = off[j] >= 0 ? (uint32_t)(uint8_t)planes[off[j] + o] : zb;
-                    v |= b << (8 * j);
-                }
-                *reinterpret_cast<uint32_t *>(dst) = v;
-                dst += Mp;
+        for (int j = 3; j >= 0; --j)
+            if (real >> j & 1) from = min(place[j], plane - 4);
+        uint32_t sel[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sel[j] = real >> j & 1 ? (uint32_t)(place[j] - from) : 8u;
+        const int64_t image_step = (int64_t)channels * plane;
+        const int64_t base = real && one ? n0 * image_step + from : 0;
+        const uint32_t ones = (real & 1u) | (real & 2u) << 7 | (real & 4u) << 14 | (real & 8u) << 21;
+        if (grad) {
+            if (by == 0) *reinterpret_cast<uint32_t *>(mask + m) = ones;
+            uint32_t shi = 0, slo = 0;   // byte selectors: 2 i + 1 / 2 i of the code's pair, 0x0C: zero
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                shi |= (sel[j] < 8 ? 2 * sel[j] + 1 : 0x0Cu) << (8 * j);
+                slo |= (sel[j] < 8 ? 2 * sel[j] : 0x0Cu) << (8 * j);
             }
+            const uint32_t flip = ones << 7;
+            uint32_t *hi = reinterpret_cast<uint32_t *>(A + (size_t)c0 * g.Mp + m);
+            uint32_t *lo = reinterpret_cast<uint32_t *>(A + (size_t)(g.K + c0) * g.Mp + m);
+            if (one) {
+                const int16_t *src = g16 + base + (int64_t)c0 * plane;
+#pragma unroll 4
+                for (int c = c0; c < c1; ++c) {
+                    uint32_t w[2];
+                    __builtin_memcpy(w, src, 8);
+                    *hi = __builtin_amdgcn_perm(w[1], w[0], shi);
+                    *lo = __builtin_amdgcn_perm(w[1], w[0], slo) ^ flip;
+                    src += plane;
+                    hi += g.Mp >> 2;
+                    lo += g.Mp >> 2;
+                }
+            } else {
+                for (int c = c0; c < c1; ++c) {
+                    uint32_t h = 0, l = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (real >> j & 1) {
+                            const uint32_t v = (uint16_t)g16[image[j] * image_step + (int64_t)c * plane + place[j]];
+                            h |= (v >> 8) << (8 * j);
+                            l |= (v & 255u) << (8 * j);
+                        }
+                    *hi = h;
+                    *lo = l ^ flip;
+                    hi += g.Mp >> 2;
+                    lo += g.Mp >> 2;
+                }
+            }
+        } else {
+            const uint32_t zb = (uint32_t)(qpx->zero_point - (1 << (qpx->bits - 1))) & 255u;
+            uint32_t s = 0;   // byte selectors: 0..3 the codes, 4 the zero code
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s |= (sel[j] < 8 ? sel[j] : 4u) << (8 * j);
+            uint32_t *dst = reinterpret_cast<uint32_t *>(X + ((size_t)cls * g.C + c0) * g.XL + m);
+            if (one) {
+                const int8_t *src = x + base + (int64_t)c0 * plane;
+#pragma unroll 4
+                for (int c = c0; c < c1; ++c) {
+                    uint32_t w;
+                    __builtin_memcpy(&w, src, 4);
+                    *dst = __builtin_amdgcn_perm(zb, w, s);
+                    src += plane;
+                    dst += g.XL >> 2;
+                }
+            } else {
+#pragma unroll 2
+                for (int c = c0; c < c1; ++c) {
+                    uint32_t d = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        d |= (real >> j & 1 ? (uint32_t)(uint8_t)x[image[j] * image_step + (int64_t)c * plane + place[j]] : zb) << (8 * j);
+                    *dst = d;
+                    dst += g.XL >> 2;
+                }
+            }
+        }
     }
 }
 
 // ---- C[z][i][j] = sum over slice z of A'[i][m] * B'[j][m] ---------------------------------------
 // Also leaves the sums of the staged bytes per row (of A') and per column (row of B') and slice.
 // Staging role of a thread (see gemm_core.h): chunk q = tid & 3 of tile rows ar = tid >> 2 and ar + RP.
+// the columns of B': channels of the padded input at the offset of a tap
+struct Columns {
+    int count;                        // columns that exist
+    int RS, S, stride, sa, C, PC;
+    int64_t pitch;                    // bytes from channel to channel
+    __device__ __forceinline__ int64_t offset(int j) const
+    {
+        j = min(j, count - 1);        // surplus columns of the last tile repeat the last one
+        const int c = j / RS, t = j - c * RS, r = t / S, s = t - r * S;
+        const int i = r / stride, k = s / stride, cls = (r - i * stride) * sa + (s - k * stride);
+        return ((int64_t)cls * C + c) * pitch + i * PC + k;
+    }
+};
+
+__device__ __forceinline__ uint4 ld16(const int8_t *p)
+{
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+
+struct NtRegs {
+    uint4 a0, a1, b0, b1, ones;   // ones: which of the 16 positions are real
+};
 template <class C>
 struct NtOps {
-    const int8_t *pa, *pb, *pa0, *pb0;   // next chunk; first chunk (always readable)
-    size_t skip;                         // RP rows further
-    bool need_a, need_b;                 // this workgroup reports the row / column sums of its tiles
+    typedef NtRegs R;
+    const int8_t *pa, *pa1, *pb, *pb1, *pm;   // first step: two rows, two columns, the mask
+    int64_t at;                               // bytes to the next step
+    int stride;                               // from step to step
+    bool need_a, need_b;                      // this workgroup reports the row / column sums of its tiles
     int sa0, sa1, sb0, sb1;
-    __device__ __forceinline__ void load(q8t_gemm::Regs &r, bool valid)
+    __device__ __forceinline__ void load(R &r, bool valid)
     {
-        const int8_t *qa = valid ? pa : pa0, *qb = valid ? pb : pb0;
-        r.a0 = *reinterpret_cast<const uint4 *>(qa);
-        r.a1 = *reinterpret_cast<const uint4 *>(qa + skip);
-        r.b0 = *reinterpret_cast<const uint4 *>(qb);
-        r.b1 = C::NB == 2 ? *reinterpret_cast<const uint4 *>(qb + skip) : r.b0;
-        pa += 64;
-        pb += 64;
+        const int64_t o = valid ? at : 0;
+        r.a0 = *reinterpret_cast<const uint4 *>(pa + o);
+        r.a1 = *reinterpret_cast<const uint4 *>(pa1 + o);
+        r.b0 = ld16(pb + o);
+        r.b1 = C::NB == 2 ? ld16(pb1 + o) : r.b0;
+        r.ones = *reinterpret_cast<const uint4 *>(pm + o);
+        at += stride;
     }
-    __device__ __forceinline__ void prepare(q8t_gemm::Regs &r, bool valid)
+    __device__ __forceinline__ static int masked_sum(const uint4 &v, const uint4 &m, int s)
+    {
+        s = __builtin_amdgcn_sdot4((int)v.x, (int)m.x, s, false);
+        s = __builtin_amdgcn_sdot4((int)v.y, (int)m.y, s, false);
+        s = __builtin_amdgcn_sdot4((int)v.z, (int)m.z, s, false);
+        return __builtin_amdgcn_sdot4((int)v.w, (int)m.w, s, false);
+    }
+    __device__ __forceinline__ void prepare(R &r, bool valid)
     {
         // a surplus step stages zero B' rows, so whatever A' holds adds nothing to the products
         r.b0 = q8t_gemm::sel16(valid, r.b0);
@@ -269,8 +257,8 @@ struct NtOps {
             sa1 += valid ? bytesum16(r.a1) : 0;
         }
         if (need_b) {
-            sb0 += bytesum16(r.b0);
-            if (C::NB == 2) sb1 += bytesum16(r.b1);
+            sb0 = masked_sum(r.b0, r.ones, sb0);
+            if (C::NB == 2) sb1 = masked_sum(r.b1, r.ones, sb1);
         }
     }
 };
@@ -298,52 +286,109 @@ __device__ __forceinline__ void write_partials(int32_t *__restrict__ dst, int Rb
                 dst[(size_t)(r0 + rowbase + mt * 16 + kb * 4 + j) * Rbp + c0 + colbase + nt * 16 + l16] = acc[mt][nt][j];
 }
 
-template <class C>
-__global__ __launch_bounds__(C::THREADS, C::MINB) void gemm_nt(const int8_t *__restrict__ A, const int8_t *__restrict__ B,
-                                                                int64_t Mp, int slice, int Rap, int Rbp, int nz,
-                                                                int32_t *__restrict__ part, int *__restrict__ rsum,
-                                                                int *__restrict__ csum)
+// The KS groups of C::THREADS threads of a workgroup take every KS-th step of its slice into tiles of their own and add
+// them up through LDS: as many wavefronts in flight with 1 / KS of the partial tiles in memory.  96 -> 200 3x3 @27 batch 50,
+// 128x128 tiles: 756 workgroups of one group 34.5 us + 9.6 for wgrad_finish (50 MB of partial tiles each way), 252 of two
+// 38.5 + 5.7, 512 of two slower by a tenth for every layer with enough steps.  The main loop runs at 0.95 POP/s either way.
+template <class C, int KS>
+__global__ __launch_bounds__(C::THREADS *KS) void gemm_nt(const int8_t *__restrict__ A, const int8_t *__restrict__ B,
+                                                          const int8_t *__restrict__ mask, Columns cols, int rows, int64_t Mp,
+                                                          int slice, int Rap, int Rbp, int nz, int32_t *__restrict__ part,
+                                                          int *__restrict__ rsum, int *__restrict__ csum)
 {
-    __shared__ __align__(16) int8_t sA[2 * C::BM * 64];
-    __shared__ __align__(16) int8_t sB[2 * C::BN * 64];
+    constexpr int MT = C::MT, NT = C::NT, SHARE = NT / KS;
+    extern __shared__ __align__(16) int8_t smem[];
 
     // logical tile order: row tiles fastest (they share the B' tile), then column tiles (same A' slice)
     const int nx = Rap / C::BM, ny = Rbp / C::BN;
     const int lg = q8t_gemm::xcd_logical(blockIdx.x, nx * ny * nz);
     if (lg >= nx * ny * nz) return;
     const int bx = lg % nx, by = (lg / nx) % ny, z = lg / (nx * ny);
-    const int tid = threadIdx.x, ar = tid >> 2, q = tid & 3;
+    const int tid = threadIdx.x % C::THREADS, grp = threadIdx.x / C::THREADS, ar = tid >> 2, q = tid & 3;
+    int8_t *sA = smem + grp * C::LDS_BYTES, *sB = sA + 2 * C::BM * 64;
     const int r0 = bx * C::BM, c0 = by * C::BN;
     const int64_t mb = (int64_t)z * slice;
     const int64_t me = mb + slice < Mp ? mb + slice : Mp;
-    const int steps = (int)((me - mb) >> 6);
+    const int steps = (int)((me - mb) >> 6) / KS;   // Mp and slice are multiples of 64 * KS
 
     NtOps<C> ops;
-    ops.pa = ops.pa0 = A + (size_t)(r0 + ar) * Mp + mb + q * 16;
-    ops.pb = ops.pb0 = B + (size_t)(c0 + ar) * Mp + mb + q * 16;
-    ops.skip = (size_t)C::RP * Mp;
+    const int64_t first = mb + grp * 64 + q * 16;
+    ops.pa = A + (size_t)min(r0 + ar, rows - 1) * Mp + first;   // surplus rows of the last tile repeat the last one
+    ops.pa1 = A + (size_t)min(r0 + ar + C::RP, rows - 1) * Mp + first;
+    ops.pb = B + cols.offset(c0 + ar) + first;
+    ops.pb1 = B + cols.offset(c0 + ar + C::RP) + first;
+    ops.pm = mask + first;
+    ops.at = 0;
+    ops.stride = 64 * KS;
     ops.need_a = by == 0;
     ops.need_b = bx == 0;
     ops.sa0 = ops.sa1 = ops.sb0 = ops.sb1 = 0;
 
-    v4i acc[C::MT][C::NT];
+    v4i acc[MT][NT];
 #pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < C::NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
-    q8t_gemm::pipeline<C>(ops, steps, sA, sB, acc);
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
+    q8t_gemm::pipeline<C>(ops, steps, sA, sB, acc, tid);
 
     // byte sums of this slice: the four threads of a row hold its pieces
     const int sa0 = quad_sum(ops.sa0), sa1 = quad_sum(ops.sa1), sb0 = quad_sum(ops.sb0), sb1 = quad_sum(ops.sb1);
-    if (by == 0 && q == 0) {
-        rsum[(size_t)z * Rap + r0 + ar] = sa0;
-        rsum[(size_t)z * Rap + r0 + ar + C::RP] = sa1;
+    int *sums = reinterpret_cast<int *>(smem + KS * C::LDS_BYTES);   // [KS][BM + BN]
+    if (q == 0) {
+        int *s = sums + grp * (C::BM + C::BN);
+        s[ar] = sa0;
+        s[ar + C::RP] = sa1;
+        s[C::BM + ar] = sb0;
+        if (C::NB == 2) s[C::BM + ar + C::RP] = sb1;
     }
-    if (bx == 0 && q == 0) {
-        csum[(size_t)z * Rbp + c0 + ar] = sb0;
-        if (C::NB == 2) csum[(size_t)z * Rbp + c0 + ar + C::RP] = sb1;
+    // group o adds up column tiles o * SHARE .. of the others
+    v4i *fold = reinterpret_cast<v4i *>(smem);   // [owner][KS - 1][MT * SHARE][THREADS]
+    __syncthreads();                             // the operand tiles are no longer needed
+#pragma unroll
+    for (int o = 0; o < KS; ++o)
+        if (o != grp) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int t = 0; t < SHARE; ++t)
+                    fold[((o * (KS - 1) + (grp < o ? grp : grp - 1)) * (MT * SHARE) + mt * SHARE + t) * C::THREADS + tid] =
+                        acc[mt][o * SHARE + t];
+        }
+    __syncthreads();
+    if (grp == 0) {
+        for (int i = tid; i < C::BM + C::BN; i += C::THREADS) {
+            int s = 0;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) s += sums[k * (C::BM + C::BN) + i];
+            if (i < C::BM) {
+                if (by == 0) rsum[(size_t)z * Rap + r0 + i] = s;
+            } else if (bx == 0) {
+                csum[(size_t)z * Rbp + c0 + i - C::BM] = s;
+            }
+        }
     }
-    write_partials<C>(part + (size_t)z * Rap * Rbp, Rbp, r0, c0, acc);
+    const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kb = lane >> 4;
+    int32_t *dst = part + (size_t)z * Rap * Rbp + (size_t)(r0 + C::rowbase(wave) + kb * 4) * Rbp + c0 + C::colbase(wave) + l16;
+#pragma unroll
+    for (int o = 0; o < KS; ++o)
+        if (o == grp) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int t = 0; t < SHARE; ++t) {
+                    v4i v = acc[mt][o * SHARE + t];
+#pragma unroll
+                    for (int k = 0; k < KS - 1; ++k)
+                        v += fold[((o * (KS - 1) + k) * (MT * SHARE) + mt * SHARE + t) * C::THREADS + tid];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dst[(size_t)(mt * 16 + j) * Rbp + (o * SHARE + t) * 16] = v[j];
+                }
+        }
+}
+template <class C, int KS>
+constexpr size_t nt_lds_bytes()
+{
+    return (size_t)KS * (C::LDS_BYTES + (C::BM + C::BN) * sizeof(int));
 }
 
 // ---- 1x1, stride 1, no padding, planes of a multiple of 64 positions ---------------------------
@@ -353,6 +398,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void gemm_nt(const int8_t *__r
 // high bytes, the next RP rows the low bytes, and the slice results keep that tiled row order.
 template <class C>
 struct DirectOps {
+    typedef q8t_gemm::Regs R;
     const int16_t *g16;
     const int8_t *x;
     int K, Cin, PQ, cpi, krow, crow, q;
@@ -437,7 +483,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void gemm_direct(const int16_t
     for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < C::NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
-    q8t_gemm::pipeline<C>(ops, steps, sA, sB, acc);
+    q8t_gemm::pipeline<C>(ops, steps, sA, sB, acc, tid);
 
     const int shi = quad_sum(ops.shi), slo = quad_sum(ops.slo), sb0 = quad_sum(ops.sb0), sb1 = quad_sum(ops.sb1);
     if (by == 0 && q == 0) {
@@ -510,9 +556,10 @@ __global__ __launch_bounds__(kThreads) void wgrad_finish(const int32_t *__restri
 
 struct Plan {
     int P, Q, CRS, Rap, Rbp, nz, slice, direct;
-    int cfg;   // 2: 256x256 tiles, 1: 128x128, 0: 128x64
+    int cfg;      // 2: 256x256 tiles, 1: 128x128, 0: 128x64
+    PadG pad;
     int64_t Mtot, Mp;
-    size_t o_B, o_part, o_rsum, o_csum, total;
+    size_t o_B, o_mask, o_part, o_rsum, o_csum, total;
 };
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -765,6 +812,50 @@ bool make_fused_plan(const q8t_conv_desc *d, FusedPlan *p)
 }
 
 
+// false: more positions than 32 bits count
+bool make_padded(const q8t_conv_desc *d, int P, int Q, int64_t step, PadG *g)
+{
+    const int st = d->stride;
+    g->N = d->N;
+    g->C = d->C;
+    g->H = d->H;
+    g->W = d->W;
+    g->K = d->K;
+    g->P = P;
+    g->Q = Q;
+    g->stride = st;
+    g->pad = d->pad;
+    g->ra = d->R < st ? d->R : st;
+    g->sa = d->S < st ? d->S : st;
+    const int er = (d->R - 1) / st, es = (d->S - 1) / st;
+    // columns (rows) v of a plane are padding on the left where st*v + b < pad, on the right where st*v + b >= W + pad:
+    // the last `share` ones of a row are the first ones of the next where both hold for every plane
+    auto pitch = [&](int out, int extra, int in, int planes) {
+        int share = 0;
+        while (share < extra && (int64_t)st * share + planes - 1 < d->pad && (int64_t)st * (out + extra - share - 1) >= in + d->pad) ++share;
+        return (int64_t)out + extra - share;
+    };
+    const int64_t PC = pitch(Q, es, d->W, g->sa), PR = pitch(P, er, d->H, g->ra);
+    const int64_t len = (int64_t)d->N * PC * PR;
+    if (len + (er + 2) * PC >= ((int64_t)1 << 31) - (1 << 16)) return false;
+    g->PC = (int)PC;
+    g->IS = (int)(PC * PR);
+    g->Mp = (len + step - 1) / step * step;
+    g->XL = (g->Mp + er * PC + es + 15) & ~(int64_t)15;   // the last step reads this far under the last tap
+    const int64_t chunks = (g->XL + kPadChunk - 1) / kPadChunk, channels = d->K + (int64_t)g->ra * g->sa * d->C;
+    // channels per workgroup: the more, the less arithmetic per code, while 2048 workgroups are left; and a launch holds fewer than 2^16
+    // blocks of them
+    int64_t rows = chunks * channels / 2048;
+    rows = rows < 1 ? 1 : (rows > 16 ? 16 : rows);
+    if (rows < (channels + 32767) / 32768) rows = (channels + 32767) / 32768;
+    g->rows = (int)rows;
+    g->gblocks = (int)((d->K + rows - 1) / rows);
+    g->xblocks = (int)((d->C + rows - 1) / rows);
+    if (g->gblocks + (int64_t)g->ra * g->sa * g->xblocks > 65535) return false;
+    g->chunks = (int)chunks;
+    return true;
+}
+
 bool make_plan(const q8t_conv_desc *d, Plan *p)
 {
     if (d->N <= 0 || d->C <= 0 || d->K <= 0 || d->H <= 0 || d->W <= 0 || d->R <= 0 || d->S <= 0) return false;
@@ -778,9 +869,6 @@ bool make_plan(const q8t_conv_desc *d, Plan *p)
     p->Mtot = (int64_t)d->N * p->P * p->Q;
     if (p->Mtot >= ((int64_t)1 << 36)) return false;
     if ((int64_t)d->N * d->C >= ((int64_t)1 << 31) || (int64_t)d->N * d->K >= ((int64_t)1 << 31)) return false;
-    p->Mp = (p->Mtot + 63) & ~(int64_t)63;
-    const int64_t widest = crs > d->K ? crs : d->K;
-    if ((p->Mp >> 4) * widest / kThreads >= ((int64_t)1 << 31)) return false;   // grid of the relayout kernels
     p->Rap = (2 * d->K + BM - 1) / BM * BM;
     p->Rbp = (p->CRS + 63) / 64 * 64;
     // 1x1 / stride 1 / no padding on planes of a multiple of 64 positions: operands are used in place
@@ -789,22 +877,28 @@ bool make_plan(const q8t_conv_desc *d, Plan *p)
     p->cfg = (p->Rap % 256 == 0 && p->Rbp % 256 == 0 && (!p->direct || d->K % 128 == 0)) ? 2 : (p->Rbp % 128 == 0 ? 1 : 0);
     const int bm = p->cfg == 2 ? 256 : 128, bn = p->cfg == 2 ? 256 : (p->cfg == 1 ? 128 : 64);
     const int64_t tiles = (int64_t)(p->Rap / bm) * (p->Rbp / bn);
-    // slices: the big tile runs one workgroup per compute unit, so aim at (just under) a multiple of
-    // 256 workgroups; the small tiles at three per compute unit
-    int64_t nz = p->cfg == 2 ? (tiles >= 256 ? 1 : 256 / tiles) : (768 + tiles - 1) / tiles;
-    const int64_t most = (p->Mp + 1023) / 1024;              // but at least 16 steps per slice
+    const int64_t step = p->cfg == 2 ? 64 : (p->cfg == 1 ? 128 : 256);   // positions that the groups of a workgroup take at a time
+    if (!make_padded(d, p->P, p->Q, step, &p->pad)) return false;
+    p->Mp = p->pad.Mp;
+    // Slices.  In place: the big tile runs one workgroup per compute unit, so aim at (just under) a multiple of 256
+    // workgroups; the small tiles at three per compute unit.  Laid out: a workgroup per compute unit, whose groups of
+    // wavefronts share its steps, four steps a group or more (two and eight: within 2 us of it over 20 layers, few tiles over
+    // few positions better with four, 48 -> 96 3x3 @7 batch 200 24 against 27 us).
+    const bool dir = p->direct;
+    int64_t nz = dir && p->cfg < 2 ? (768 + tiles - 1) / tiles : (tiles >= 256 ? 1 : 256 / tiles);
+    const int64_t least = dir ? 1024 : 4 * step, most = (p->Mp + least - 1) / least;   // enough steps per slice
     if (nz > most) nz = most;
     const int64_t ovf = (p->Mp + kMaxSlice - 1) / kMaxSlice;  // 32-bit accumulator bound
     if (nz < ovf) nz = ovf;
-    int64_t slice = ((p->Mp + nz - 1) / nz + 63) & ~(int64_t)63;
+    int64_t slice = ((p->Mp + nz - 1) / nz + step - 1) / step * step;
     if (slice > kMaxSlice) slice = kMaxSlice;
     nz = (p->Mp + slice - 1) / slice;
     if (nz > 65535 || tiles * nz >= ((int64_t)1 << 30)) return false;
     p->nz = (int)nz;
     p->slice = (int)slice;
-    const size_t a_bytes = up256((size_t)p->Rap * p->Mp);
-    p->o_B = a_bytes;
-    p->o_part = p->o_B + up256((size_t)p->Rbp * p->Mp);
+    p->o_B = up256((size_t)2 * d->K * p->Mp);
+    p->o_mask = p->o_B + up256((size_t)p->pad.ra * p->pad.sa * d->C * p->pad.XL);
+    p->o_part = p->o_mask + up256((size_t)p->Mp);
     p->o_rsum = p->o_part + up256((size_t)p->nz * p->Rap * p->Rbp * sizeof(int32_t));
     p->o_csum = p->o_rsum + up256((size_t)p->nz * p->Rap * sizeof(int));
     p->total = p->o_csum + up256((size_t)p->nz * p->Rbp * sizeof(int));
@@ -866,7 +960,8 @@ int q8t_gemm_wgrad(const q8t_conv_desc *d, const int16_t *g16, const q8t_qparams
     int32_t *part = (int32_t *)((char *)ws + p.o_part);
     int *rsum = (int *)((char *)ws + p.o_rsum);
     int *csum = (int *)((char *)ws + p.o_csum);
-    const int64_t chunks = p.Mp >> 4;
+    int8_t *mask = (int8_t *)ws + p.o_mask;
+    const Columns cols = {p.CRS, d->R * d->S, d->S, d->stride, p.pad.sa, d->C, p.pad.PC, p.pad.XL};
     const int direct = p.direct && q8t_aligned(g16, 16) && q8t_aligned(x, 16);
     if (direct) {
         const int steps_total = (int)(p.Mtot >> 6), steps_slice = p.slice >> 6;
@@ -880,47 +975,22 @@ int q8t_gemm_wgrad(const q8t_conv_desc *d, const int16_t *g16, const q8t_qparams
 #undef Q8T_GO
         Q8T_LAUNCH_CHECK();
     } else {
-    {
-        const int64_t blocks = (chunks * d->K + kThreads - 1) / kThreads;
-        const int PQ = p.P * p.Q;
-        if (PQ % 16 == 0 && q8t_aligned(g16, 16))
-            hipLaunchKernelGGL(split16<16>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g16, d->K, PQ, p.Mtot, p.Mp, qg, A);
-        else if (PQ % 4 == 0 && q8t_aligned(g16, 8))
-            hipLaunchKernelGGL(split16<4>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g16, d->K, PQ, p.Mtot, p.Mp, qg, A);
-        else
-            hipLaunchKernelGGL(split16<1>, dim3((unsigned)blocks), dim3(kThreads), 0, st, g16, d->K, PQ, p.Mtot, p.Mp, qg, A);
+        const unsigned gy = (unsigned)(p.pad.gblocks + p.pad.ra * p.pad.sa * p.pad.xblocks);
+        const unsigned gx = (unsigned)p.pad.chunks < (1u << 23) / gy ? (unsigned)p.pad.chunks : (1u << 23) / gy;
+        hipLaunchKernelGGL(pad_operands, dim3(gx, gy), dim3(kThreads), 0, st, g16, x, p.pad, qx, A, B, mask);
         Q8T_LAUNCH_CHECK();
+#define Q8T_GO(CFG, KS)                                                                                               \
+    {                                                                                                                 \
+        static Q8tLdsOptIn optin;                                                                                     \
+        constexpr size_t lds = nt_lds_bytes<CFG, KS>();                                                               \
+        if (lds > 65536 && q8t_allow_lds(optin, (const void *)gemm_nt<CFG, KS>, lds) != Q8T_OK) return Q8T_ERR_HIP;    \
+        hipLaunchKernelGGL((gemm_nt<CFG, KS>), dim3(q8t_gemm::xcd_grid((int64_t)(p.Rap / CFG::BM) * (p.Rbp / CFG::BN) * p.nz)), \
+                           dim3(CFG::THREADS * KS), lds, st, A, B, mask, cols, 2 * d->K, p.Mp, p.slice, p.Rap, p.Rbp, p.nz, \
+                           part, rsum, csum);                                                                         \
     }
-    {
-        ConvG g = {d->N, d->C, d->H, d->W, d->K, d->R, d->S, d->stride, d->pad, p.P, p.Q};
-        const int64_t blocks = (chunks * p.CRS + kThreads - 1) / kThreads;
-        const int PQ = p.P * p.Q;
-        const int NI = PQ % 4 == 0 ? 1 : (PQ % 2 == 0 ? 2 : 4);
-        PlaneG pg;
-        pg.L = (d->pad + 3) & ~3;
-        pg.pitch = (pg.L + d->W + d->pad + 3) & ~3;
-        pg.PB = (d->H + 2 * d->pad) * pg.pitch;
-        pg.vec = d->W % 4 == 0 && q8t_aligned(x, 4) ? 4 : (d->W % 2 == 0 && q8t_aligned(x, 2) ? 2 : 1);
-        const size_t lds1 = (size_t)NI * pg.PB;
-        // channels per workgroup: about 1024 dwords of work per tap, within 32 KB of LDS
-        int CG = (int)(4096 / ((int64_t)NI * PQ) > 0 ? 4096 / ((int64_t)NI * PQ) : 1);
-        if (lds1 * CG > 32768) CG = (int)(32768 / lds1 > 0 ? 32768 / lds1 : 1);
-        if (CG > d->C) CG = d->C;
-        const size_t lds = lds1 * CG;
-        if (lds <= 65536 && (int64_t)CG * (NI * (int64_t)PQ + 64) < (1 << 24) && (int64_t)CG * NI * d->H * d->W < (1 << 24) &&
-            (d->C + CG - 1) / CG <= 65535)
-            hipLaunchKernelGGL(im2col_planes, dim3((unsigned)((d->N + NI - 1) / NI), (unsigned)((d->C + CG - 1) / CG)),
-                               dim3(kThreads), lds, st, x, g, pg, NI, CG, p.Mtot, p.Mp, qx, B);
-        else
-            hipLaunchKernelGGL(im2col_rows, dim3((unsigned)blocks), dim3(kThreads), 0, st, x, g, p.Mtot, p.Mp, qx, B);
-        Q8T_LAUNCH_CHECK();
-    }
-#define Q8T_GO(CFG)                                                                                                   \
-    hipLaunchKernelGGL(gemm_nt<CFG>, dim3(q8t_gemm::xcd_grid((int64_t)(p.Rap / CFG::BM) * (p.Rbp / CFG::BN) * p.nz)), \
-                       dim3(CFG::THREADS), 0, st, A, B, p.Mp, p.slice, p.Rap, p.Rbp, p.nz, part, rsum, csum)
-    if (p.cfg == 2) Q8T_GO(q8t_gemm::Big);
-    else if (p.cfg == 1) Q8T_GO(q8t_gemm::Mid);
-    else Q8T_GO(q8t_gemm::Small);
+    if (p.cfg == 2) Q8T_GO(q8t_gemm::Big, 1)
+    else if (p.cfg == 1) Q8T_GO(q8t_gemm::Mid, 2)
+    else Q8T_GO(q8t_gemm::Small, 4)
 #undef Q8T_GO
     Q8T_LAUNCH_CHECK();
     }
@@ -929,7 +999,7 @@ int q8t_gemm_wgrad(const q8t_conv_desc *d, const int16_t *g16, const q8t_qparams
         const int zgn = p.nz >= 64 ? 16 : (p.nz >= 8 ? 4 : 1);   // lanes sharing the slices of one output
         const int per = kThreads / zgn;
         hipLaunchKernelGGL(wgrad_finish, dim3((unsigned)((count + per - 1) / per)), dim3(kThreads), 0, st,
-                           part, rsum, csum, p.nz, d->K, p.CRS, p.Rap, p.Rbp, p.Mp, qg, qx, dw, acc_out, zgn,
+                           part, rsum, csum, p.nz, d->K, p.CRS, p.Rap, p.Rbp, p.Mtot, qg, qx, dw, acc_out, zgn,
                            direct ? (p.cfg == 2 ? 128 : 64) : 0, 1, 0);
         Q8T_LAUNCH_CHECK();
     }
