@@ -5,7 +5,7 @@
 //
 // GEMM view: rows = flattened (image, y, x) positions, cols = output channels, reduction = (64
 // input channels, tap).  A workgroup of 4 wavefronts owns 128 rows x 256 output channels (128 where the
-// layer has no multiple of 256); every wavefront multiplies all 128 rows against its own 64 (32) output
+// layer has no multiple of 256; 64 or 32 rows x 128 where there are few rows, see tile_rows); every wavefront multiplies all 128 rows against its own 64 (32) output
 // channels (eight or four 32x32 accumulators, v_mfma_i32_32x32x32_i8).  What this buys over a 64-channel output tile:
 //  * the activations of a 64-channel chunk (128 rows + halo) are staged ONCE and serve 9 taps x 256
 //    output channels: they sit in LDS in padded coordinates (a zero-point row after every image row
@@ -33,7 +33,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
-constexpr int BM = 128, CH = 64;   // rows per workgroup, channels per chunk; columns per workgroup: 128 or 256
+constexpr int CH = 64;   // channels per chunk
 constexpr int ROWB = 80;
 constexpr int MARG = 8;          // spare LDS rows on either side of an activation buffer (pieces that hang over)
 constexpr int MAXR = 256;        // rows of one activation buffer (one thread per row sums it)
@@ -51,7 +51,16 @@ struct WideGeom {
     int nslot;           // staging iterations per thread (<= MAXSLOT)
     int igroups;         // unaligned planes: position groups per image, ceil(PQ / 4)
     int last_dword;      // index of the last aligned dword of the operand
+    int bm;              // rows per workgroup: 128, 64 or 32
+    int lb;              // columns per block of the packed filter: 256, or 128
 };
+
+// LDS in front of the row sums: two activation buffers, which later hold the tiles that the wavefronts turn round
+__host__ __device__ __forceinline__ int front_bytes(const WideGeom &g)
+{
+    const int act = 2 * (g.maxr + 2 * MARG) * ROWB, turn = g.PQ % 4 ? (kThreads / 64) * 32 * 36 * 4 : 0;
+    return act > turn ? act : turn;
+}
 
 // Packed filter (layout and body: repack.h, q8t_repack_wide)
 __global__ __launch_bounds__(kRepackThreads) void repack_wide(const int8_t *__restrict__ w, int Kf, int Cf, int dgrad, int BN,
@@ -75,9 +84,9 @@ __device__ __forceinline__ void transpose4x4(const uint32_t in[4], uint32_t out[
 }
 
 // AL: the plane size is a multiple of 4 (aligned dwords per channel).  NS: staging pieces per thread.
-// NTW: 32-column tiles per wavefront (2: 256 output channels per workgroup, 1: 128).
-template <bool AL, int NS, bool STATS, int NTW>
-__global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const int8_t *__restrict__ x,
+// NTW: 32-column tiles per wavefront (2: 256 output channels per workgroup, 1: 128).  MT: 32-row groups per workgroup.
+template <bool AL, int NS, bool STATS, int NTW, int MT>
+__global__ __launch_bounds__(kThreads, AL || MT == 1 ? 2 : 1) void conv_wide_kernel(const int8_t *__restrict__ x,
                                                                         const int8_t *__restrict__ wpk,
                                                                         const int *__restrict__ colsum,
                                                                         const q8t_qparams *__restrict__ qpa,
@@ -86,11 +95,11 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
                                                                         int32_t *__restrict__ acc_out,
                                                                         Q8tConvStat *__restrict__ bnpart)
 {
-    constexpr int BN = 128 * NTW, WN = 32 * NTW;   // columns of the workgroup, of a wavefront
+    constexpr int BM = 32 * MT, BN = 128 * NTW, WN = 32 * NTW;   // rows, columns of the workgroup, columns of a wavefront
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int A_BYTES = (g.maxr + 2 * MARG) * ROWB;   // one activation buffer with its spare rows
     uint8_t *As = smem + MARG * ROWB;                  // buffer b at As + b * A_BYTES
-    int *Srow = reinterpret_cast<int *>(smem + 2 * A_BYTES);   // [maxr] byte sums of the staged rows over all channels
+    int *Srow = reinterpret_cast<int *>(smem + front_bytes(g));   // [maxr] byte sums of the staged rows over all channels
     int *RS = Srow + MAXR;                             // [BM] row sums over the taps
     int *OOFF = RS + BM;                               // [BM] offset of the row's position in the result (channel 0)
 
@@ -210,13 +219,14 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
     // ---- weights: a wavefront's 64 output channels are its own, so their fragments go from memory straight to
     // registers; block (chunk, tap) holds, per wavefront, four 1 KB fragments (column tile, K half) in lane order ----
     const int nsteps = CC * 9;
-    const int8_t *wsrc = wpk + (size_t)blockIdx.y * CC * 9 * BN * CH + wave * (2048 * NTW) + lane * 16;
+    const int lb = NTW == 2 ? BN : g.lb;   // the layout of the filter is the layer's, not the tile's
+    const int8_t *wsrc = wpk + (size_t)(n0 / lb) * CC * 9 * lb * CH + ((n0 % lb) / 32 + wave * NTW) * 2048 + lane * 16;
     struct BFrag {
         v4i n0k0, n0k1, n1k0, n1k1;   // named members: the sets stay in registers
     };
     auto load_b = [&](int q) -> BFrag {
         const int qc = min(q, nsteps - 1);   // past the end: the last block again, never used
-        const int8_t *src = wsrc + (size_t)qc * (BN * CH);
+        const int8_t *src = wsrc + (size_t)qc * (lb * CH);
         BFrag f;
         f.n0k0 = *reinterpret_cast<const v4i *>(src);
         f.n0k1 = *reinterpret_cast<const v4i *>(src + 1024);
@@ -231,17 +241,17 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
     };
 
     // fragment addresses: lane -> row l32 of a 32-row tile, 16-byte group hk (+2 for the second K half)
-    int arow[4];
+    int arow[MT];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
         int gr = g0 + mt * 32 + l32;
         if (gr >= g.M) gr = g0;
         arow[mt] = (apad(gr) - a0 - (W1 + 1)) * ROWB + hk * 16;   // row of the tap (0, 0); tap (dr, ds) adds dr * W1 + ds
     }
 
-    v16i acc[4][NTW];
+    v16i acc[MT][NTW];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
@@ -250,12 +260,15 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
 
     // Operands are fetched ahead of their use so that no MFMA waits: the activation fragments of the next
     // 32-row group one group ahead (LDS), the weight fragments two steps ahead (three register sets, used in
-    // turn: 9 steps per chunk keep set = tap % 3).
+    // turn: 9 steps per chunk keep set = tap % 3).  With fewer than 128 rows a step is a quarter or an eighth of that and
+    // covers no latency: there the activations go one step ahead and the weights a whole chunk (nine register sets).
     struct AFrag {
         v4i k0, k1;
     };
     AFrag af0, af1;
+    AFrag as0[MT], as1[MT];
     BFrag bf0, bf1, bf2;
+    BFrag bs[MT == 4 ? 1 : 9];
     auto read_a = [&](int buf, int tap, int mt) -> AFrag {
         const uint8_t *p = As + buf * A_BYTES + ((tap / 3) * W1 + (tap % 3)) * ROWB + arow[mt];
         AFrag f;
@@ -271,8 +284,13 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
     };
 
     load_a(0);
-    bf0 = load_b(0);
-    bf1 = load_b(1);
+    if (MT == 4) {
+        bf0 = load_b(0);
+        bf1 = load_b(1);
+    } else {
+#pragma unroll
+        for (int t = 0; t < (MT == 4 ? 1 : 9); ++t) bs[t] = load_b(t);
+    }
     __syncthreads();          // the fill above is complete
     commit_a(0, 0);
 
@@ -282,26 +300,42 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
     auto step = [&](auto tap_c, int cc) {
         constexpr int T = decltype(tap_c)::value;
         const int s = cc * 9 + T, buf = cc & 1;
+        if constexpr (MT < 4) {
+            AFrag(&cur_a)[MT] = T % 2 == 0 ? as0 : as1;
+            AFrag(&nxt_a)[MT] = T % 2 == 0 ? as1 : as0;
+            if (T < 8) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) nxt_a[mt] = read_a(buf, T + 1, mt);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) mma(mt, cur_a[mt], bs[T]);
+            bs[T] = load_b(s + 9);
+            if (T < 8) __builtin_amdgcn_sched_group_barrier(0x100, 2 * MT, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2 * MT * NTW, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, 2 * NTW, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            return;
+        } else {
         const BFrag &cur = T % 3 == 0 ? bf0 : (T % 3 == 1 ? bf1 : bf2);
         const BFrag nxt = load_b(s + 2);
         constexpr int NM = 2 * NTW;   // MFMAs per 32-row group
-        af1 = read_a(buf, T, 1);
+        af1 = read_a(buf, T, 1 % MT);
         mma(0, af0, cur);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
-        af0 = read_a(buf, T, 2);
-        mma(1, af1, cur);
+        af0 = read_a(buf, T, 2 % MT);
+        mma(1 % MT, af1, cur);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         if (NTW == 2) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
-        af1 = read_a(buf, T, 3);
-        mma(2, af0, cur);
+        af1 = read_a(buf, T, 3 % MT);
+        mma(2 % MT, af0, cur);
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
         if (T < 8) af0 = read_a(buf, T + 1, 0);   // the next chunk's activations may not be in LDS yet
-        mma(3, af1, cur);
+        mma(3 % MT, af1, cur);
         if (T < 8) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         if (NTW == 2) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
@@ -309,12 +343,18 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
         if (T % 3 == 0) bf2 = nxt;        // set (T + 2) % 3 was last used in the previous step
         else if (T % 3 == 1) bf0 = nxt;
         else bf1 = nxt;
+        }
     };
     for (int cc = 0; cc < CC; ++cc) {
         const int buf = cc & 1;
         // chunk cc is complete in buffer buf, and every wavefront is past its reads of the other buffer
         q8t_lds_barrier();
-        af0 = read_a(buf, 0, 0);
+        if (MT == 4) {
+            af0 = read_a(buf, 0, 0);
+        } else {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) as0[mt] = read_a(buf, 0, mt);
+        }
         // byte sum of this thread's LDS row over the chunk's 64 channels
         if (tid < g.maxr) {
             const uint8_t *row = As + buf * A_BYTES + tid * ROWB;
@@ -368,7 +408,7 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
         long long st_s = 0;
         int st_mn = 2147483647, st_mx = -2147483647 - 1;
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) {
+        for (int mt = 0; mt < MT; ++mt) {
             if (g0 + mt * 32 >= g1) continue;   // uniform
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -449,7 +489,8 @@ __global__ __launch_bounds__(kThreads, AL ? 2 : 1) void conv_wide_kernel(const i
     }
 }
 
-bool make_geom(int which, const q8t_conv_desc *d, WideGeom *g)
+// rows: per workgroup, 128 unless a smaller tile is asked for
+bool make_geom(int which, const q8t_conv_desc *d, WideGeom *g, int BM = 128)
 {
     if (which > 1 || d->R != 3 || d->S != 3 || d->stride != 1 || d->pad != 1) return false;
     g->N = d->N;
@@ -467,6 +508,8 @@ bool make_geom(int which, const q8t_conv_desc *d, WideGeom *g)
     g->IMG = (d->H + 1) * g->W1;
     // padded coordinates a tile of BM positions can span, plus the halo rows on either side
     const int row_ends = (BM + d->W - 2) / d->W + 1, img_ends = (BM + g->PQ - 2) / g->PQ + 1;
+    g->bm = BM;
+    g->lb = g->K % 256 == 0 ? 256 : 128;
     g->maxr = BM + row_ends + img_ends * g->W1 + 2 * (g->W1 + 1) + 1;
     if (g->maxr > MAXR) return false;
     g->halo = (d->W + 1 + 3) & ~3;
@@ -486,21 +529,34 @@ bool make_geom(int which, const q8t_conv_desc *d, WideGeom *g)
 
 size_t lds_bytes(const WideGeom &g)
 {
-    return (size_t)2 * (g.maxr + 2 * MARG) * ROWB + (size_t)(MAXR + 2 * BM) * sizeof(int);
+    return (size_t)front_bytes(g) + (size_t)(MAXR + 2 * g.bm) * sizeof(int);
 }
 
-template <bool AL, int NS, bool STATS, int NTW>
+template <bool AL, int NS, bool STATS, int NTW, int MT>
 int launch(const WideGeom &g, hipStream_t st, const int8_t *a, const int8_t *wpk, const int *colsum, const q8t_qparams *qa,
            const q8t_qparams *qb, float *out_f, int32_t *out_acc, Q8tConvStat *bnpart)
 {
     static Q8tLdsOptIn optin;
     const size_t lds = lds_bytes(g);
-    if (q8t_allow_lds(optin, (const void *)conv_wide_kernel<AL, NS, STATS, NTW>, 96 * 1024) != Q8T_OK) return Q8T_ERR_HIP;
+    if (q8t_allow_lds(optin, (const void *)conv_wide_kernel<AL, NS, STATS, NTW, MT>, 96 * 1024) != Q8T_OK) return Q8T_ERR_HIP;
     const dim3 grid((unsigned)((g.nbx + 7) / 8 * 8), (unsigned)(g.K / (128 * NTW)));
-    hipLaunchKernelGGL((conv_wide_kernel<AL, NS, STATS, NTW>), grid, dim3(kThreads), lds, st, a, wpk, colsum, qa, qb, g, out_f,
+    hipLaunchKernelGGL((conv_wide_kernel<AL, NS, STATS, NTW, MT>), grid, dim3(kThreads), lds, st, a, wpk, colsum, qa, qb, g, out_f,
                        out_acc, bnpart);
     Q8T_LAUNCH_CHECK();
     return Q8T_OK;
+}
+
+// The tile of a launch: 128 rows x 256 columns (128 x 128 without a multiple of 256 output channels), or 64 (32) x 128 where
+// those are too few for the chip: a tile streams the filter of its columns at what one compute unit gets from the L2 (512
+// channels: 590 KB, 13 us), however many stand idle beside it.  Whole calls with statistics, 128 / 64 / 32 rows, us:
+//   256 -> 256 @14  batch 8 31 / 19 / 16   32 32 / 20 / 21   64 34 / 26 / 32   96 35 / 36 / 39   128 37 / 41 / 49
+//   512 -> 512 @7   batch 8 62 / 36 / 32   32 62 / 37 / 31   48 63 / 37 / 40  128 65 / 50 / 62   192 66 / 68 / 79
+//   128 -> 384 @9   batch 24 26 / 21 / 18  32 26 / 22 / 21   64 27 / 25 / 23  128 33 / 29 / 36   192 35 / 41 / 48
+// The lines lie at one tile of 128x128 per compute unit and a bit over a quarter of that.
+int tile_rows(const WideGeom &g)
+{
+    const int64_t tiles = (int64_t)g.nbx * (g.K / 128);
+    return tiles >= 256 ? 128 : (tiles >= 72 ? 64 : 32);
 }
 
 }  // namespace
@@ -530,7 +586,7 @@ size_t q8t_wide_conv_ws(int which, const q8t_conv_desc *d)
     if (!make_geom(which, d, &g)) return 0;
     const size_t wbytes = (size_t)d->K * d->C * 9;
     return ((wbytes + 255) & ~(size_t)255) + (((size_t)g.K * sizeof(int) + 255) & ~(size_t)255) +
-           (size_t)g.K * g.nbx * sizeof(Q8tConvStat);
+           (size_t)g.K * ((g.M + tile_rows(g) - 1) / tile_rows(g)) * sizeof(Q8tConvStat);
 }
 
 int q8t_wide_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qparams *qa, const void *b,
@@ -541,6 +597,8 @@ int q8t_wide_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
     if (!make_geom(which, d, &g)) return Q8T_ERR_SHAPE;
     if (!ws || !q8t_aligned(ws, 16)) return Q8T_ERR_WORKSPACE;
     if (packed && !q8t_aligned(packed, 16)) return Q8T_ERR_WORKSPACE;
+    const int rows = tile_rows(g);
+    if (rows < 128 && !make_geom(which, d, &g, rows)) return Q8T_ERR_SHAPE;   // a smaller tile needs less of everything
     if (lds_bytes(g) > 96 * 1024) return Q8T_ERR_SHAPE;
     const size_t wbytes = (size_t)d->K * d->C * 9;
     // the packed filter and its column sums: made here in the workspace, or handed in (q8t_qconv_pack_multi)
@@ -559,10 +617,12 @@ int q8t_wide_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
     int32_t *pacc = (int32_t *)out_acc;
     const bool al = g.PQ % 4 == 0;
     int rc;
-#define Q8T_WIDE2(ALV, NSV, NT)                                                                                     \
-    (bnpart ? launch<ALV, NSV, true, NT>(g, st, pa, wpk, colsum, qa, qb, out_f, pacc, bnpart)                       \
-            : launch<ALV, NSV, false, NT>(g, st, pa, wpk, colsum, qa, qb, out_f, pacc, bnpart))
-#define Q8T_WIDE(ALV, NSV) (ntw == 2 ? Q8T_WIDE2(ALV, NSV, 2) : Q8T_WIDE2(ALV, NSV, 1))
+#define Q8T_WIDE2(ALV, NSV, NT, MTV)                                                                                \
+    (bnpart ? launch<ALV, NSV, true, NT, MTV>(g, st, pa, wpk, colsum, qa, qb, out_f, pacc, bnpart)                  \
+            : launch<ALV, NSV, false, NT, MTV>(g, st, pa, wpk, colsum, qa, qb, out_f, pacc, bnpart))
+#define Q8T_WIDE(ALV, NSV)                                                                                          \
+    (rows == 32 ? Q8T_WIDE2(ALV, NSV, 1, 1) : rows == 64 ? Q8T_WIDE2(ALV, NSV, 1, 2)                                \
+                                            : (ntw == 2 ? Q8T_WIDE2(ALV, NSV, 2, 4) : Q8T_WIDE2(ALV, NSV, 1, 4)))
     if (al)
         rc = g.nslot <= 3 ? Q8T_WIDE(true, 3) : Q8T_WIDE(true, 5);
     else
