@@ -371,30 +371,39 @@ def qconv_pack_size(d, which):
     return int(_lib.q8t_qconv_pack_size(C.byref(d), int(which)))
 
 
+class PackPlan:
+    """The shapes of a list of filters to pack ahead, [(desc, which)]: sizes and the tables of the call, made once."""
+
+    def __init__(self, jobs):
+        self.n = len(jobs)
+        self.shapes = [(d.K, d.C, d.R, d.S) for d, _ in jobs]
+        self.descs = (ConvDesc * self.n)(*[d for d, _ in jobs])
+        self.which = (C.c_int * self.n)(*[int(w) for _, w in jobs])
+        self.sizes = [qconv_pack_size(d, w) for d, w in jobs]
+
+    def run(self, qws, out=None):
+        """qws: the codes, one per job.  Returns one buffer per job, None where the shape packs nothing ahead."""
+        for t, shape in zip(qws, self.shapes):
+            _dev(t)
+            assert tuple(t.shape) == shape and t.dtype == torch.int8
+        # one allocation for all of them (their sizes are multiples of 256)
+        kept = out if out is not None else [None] * self.n
+        sizes = [0 if b is not None else s for s, b in zip(self.sizes, kept)]
+        fresh = torch.empty(sum(sizes), dtype=torch.uint8, device=qws[0].device).split_with_sizes(sizes)
+        assert all(b is None or (b.numel() >= s and b.dtype == torch.uint8) for s, b in zip(self.sizes, kept))
+        bufs = [None if s == 0 else (b if b is not None else f) for s, b, f in zip(self.sizes, kept, fresh)]
+        ptrs = (C.c_void_p * self.n)(*[_ptr(t) for t in qws])
+        pks = (C.c_void_p * self.n)(*[_ptr(b) for b in bufs])
+        _check(_lib.q8t_qconv_pack_multi(self.n, self.descs, self.which, ptrs, pks, _stream()), "q8t_qconv_pack_multi")
+        return bufs
+
+
 def qconv_pack_multi(jobs, out=None):
     """jobs: list of (desc, which, qw).  Packs the filters of all of them in one launch and returns one buffer per job
     (None where the shape packs nothing ahead) for the packed= argument of the products.  out: buffers to reuse."""
-    n = len(jobs)
-    if n == 0:
+    if len(jobs) == 0:
         return []
-    descs = (ConvDesc * n)(*[j[0] for j in jobs])
-    which = (C.c_int * n)(*[int(j[1]) for j in jobs])
-    bufs = []
-    for i, (d, w, qw) in enumerate(jobs):
-        _dev(qw)
-        assert tuple(qw.shape) == (d.K, d.C, d.R, d.S) and qw.dtype == torch.int8
-        size = qconv_pack_size(d, w)
-        if size == 0:
-            bufs.append(None)
-        elif out is not None and out[i] is not None:
-            assert out[i].numel() >= size and out[i].dtype == torch.uint8
-            bufs.append(out[i])
-        else:
-            bufs.append(torch.empty(size, dtype=torch.uint8, device=qw.device))
-    qws = (C.c_void_p * n)(*[_ptr(j[2]) for j in jobs])
-    pks = (C.c_void_p * n)(*[_ptr(b) for b in bufs])
-    _check(_lib.q8t_qconv_pack_multi(n, descs, which, qws, pks, _stream()), "q8t_qconv_pack_multi")
-    return bufs
+    return PackPlan([j[:2] for j in jobs]).run([j[2] for j in jobs], out)
 
 
 def qconv_fwd_bn_stats(d, qx, px, qw, pw, want_acc=False, out=None, stats_out=None, ws=None, packed=None):

@@ -81,8 +81,9 @@ __global__ __launch_bounds__(kRepackThreads) void repack_weights(const int8_t *_
                                                            int S, int dgrad, int8_t *__restrict__ out,
                                                            int *__restrict__ colsum)
 {
-    __shared__ int red[kRepackThreads / 64];
-    q8t_repack_tile64(w, Kf, Cf, R, S, dgrad, out, colsum, (int)blockIdx.x, red);
+    __shared__ __align__(16) uint8_t lds[kRepackLds];
+    __shared__ int red[64];
+    q8t_repack(w, Kf, Cf, R * S, dgrad, 0, out, colsum, (int)blockIdx.x * kRepackCols, lds, red);
 }
 
 // 4x4 byte transpose: in[j] = 4 consecutive positions of channel j; out[i] = 4 channels of position i
@@ -646,7 +647,7 @@ int q8t_fast_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
     g.dW1 = mkdiv(W1);
     g.dIMG = mkdiv(taps == 9 ? (d->H + 1) * W1 : g.PQ);
     if (!packed) {
-        hipLaunchKernelGGL(repack_weights, dim3(g.K), dim3(kRepackThreads), 0, st, (const int8_t *)b, d->K, d->C, d->R, d->S,
+        hipLaunchKernelGGL(repack_weights, dim3(g.K / kRepackCols), dim3(kRepackThreads), 0, st, (const int8_t *)b, d->K, d->C, d->R, d->S,
                            which, wpk, colsum);
         Q8T_LAUNCH_CHECK();
     }

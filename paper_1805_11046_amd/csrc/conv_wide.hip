@@ -62,12 +62,13 @@ __host__ __device__ __forceinline__ int front_bytes(const WideGeom &g)
     return act > turn ? act : turn;
 }
 
-// Packed filter (layout and body: repack.h, q8t_repack_wide)
+// Packed filter (layout and body: repack.h)
 __global__ __launch_bounds__(kRepackThreads) void repack_wide(const int8_t *__restrict__ w, int Kf, int Cf, int dgrad, int BN,
                                                               int8_t *__restrict__ out, int *__restrict__ colsum)
 {
-    __shared__ int red[kRepackThreads / 64];
-    q8t_repack_wide(w, Kf, Cf, dgrad, BN, out, colsum, (int)blockIdx.x, red);
+    __shared__ __align__(16) uint8_t lds[kRepackLds];
+    __shared__ int red[64];
+    q8t_repack(w, Kf, Cf, 9, dgrad, BN, out, colsum, (int)blockIdx.x * kRepackCols, lds, red);
 }
 
 // in[j] = 4 consecutive positions of channel j; out[i] = 4 channels of position i
@@ -609,7 +610,7 @@ int q8t_wide_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
                                    : (Q8tConvStat *)nullptr;
     const int ntw = g.K % 256 == 0 ? 2 : 1;
     if (!packed) {
-        hipLaunchKernelGGL(repack_wide, dim3((unsigned)g.K), dim3(kRepackThreads), 0, st, (const int8_t *)b, d->K, d->C, which,
+        hipLaunchKernelGGL(repack_wide, dim3((unsigned)(g.K / kRepackCols)), dim3(kRepackThreads), 0, st, (const int8_t *)b, d->K, d->C, which,
                            128 * ntw, wpk, colsum);
         Q8T_LAUNCH_CHECK();
     }

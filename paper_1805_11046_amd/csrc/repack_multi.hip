@@ -15,17 +15,15 @@ struct PackTable {
 
 __global__ __launch_bounds__(kRepackThreads) void repack_multi(const PackTable t)
 {
-    __shared__ int red[kRepackThreads / 64];
+    __shared__ __align__(16) uint8_t lds[kRepackLds];
+    __shared__ int red[64];
     // the job whose run of blocks holds this one (jobs are few: a uniform scan)
     int j = 0;
     for (int i = 1; i < t.n; ++i)
         if ((int)blockIdx.x >= t.job[i].first_block) j = i;
     const Q8tPackJob &b = t.job[j];
-    const int oc = (int)blockIdx.x - b.first_block;
-    if (b.layout == Q8T_PACK_TILE64)
-        q8t_repack_tile64(b.w, b.Kf, b.Cf, b.R, b.S, b.dgrad, b.out, b.colsum, oc, red);
-    else
-        q8t_repack_wide(b.w, b.Kf, b.Cf, b.dgrad, b.layout == Q8T_PACK_WIDE256 ? 256 : 128, b.out, b.colsum, oc, red);
+    q8t_repack(b.w, b.Kf, b.Cf, b.R * b.S, b.dgrad, b.layout == Q8T_PACK_TILE64 ? 0 : (b.layout == Q8T_PACK_WIDE256 ? 256 : 128), b.out,
+               b.colsum, ((int)blockIdx.x - b.first_block) * kRepackCols, lds, red);
 }
 
 }  // namespace
@@ -39,7 +37,7 @@ int q8t_pack_launch(const Q8tPackJob *jobs, int n, hipStream_t st)
         for (int i = 0; i < t.n; ++i) {
             t.job[i] = jobs[at + i];
             t.job[i].first_block = blocks;
-            blocks += jobs[at + i].dgrad ? jobs[at + i].Cf : jobs[at + i].Kf;   // one workgroup per output channel of the product
+            blocks += (jobs[at + i].dgrad ? jobs[at + i].Cf : jobs[at + i].Kf) / kRepackCols;   // output channels of the product
         }
         if (blocks == 0) continue;
         hipLaunchKernelGGL(repack_multi, dim3((unsigned)blocks), dim3(kRepackThreads), 0, st, t);

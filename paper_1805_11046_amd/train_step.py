@@ -22,6 +22,7 @@ per second of the streaming calls.  Needs a GPU.
 """
 import argparse
 import collections
+import functools
 import time
 
 import torch
@@ -76,17 +77,18 @@ def _angle(kind, t, q, qp):
 
 
 _qcache = {}   # data_ptr of an activation -> (codes, parameters) left behind by the kernel that wrote it
-_pcache = {}   # (data_ptr of a layer's weight codes, 0 forward / 1 layer gradient) -> its packed filter for this step
-_pbufs = {}    # the same keys by weight tensor: buffers kept from step to step
+# (data_ptr of a layer's weight codes, 0 forward / 1 layer gradient) -> (its packed filter for this step, the codes: while they
+# are held here no other tensor has their address); None once the step is over
+_pcache = {}
 # Pack all filters in one launch after the weights are quantized (off: every product packs its own, a small launch in
-# front of each).  Off: the best runs gain 0.06 ms of 8.5 with it, but the timed single-stream loop came out 0.3 - 1.5
-# ms slower in most trials (first processes on a fresh machine above all), with unchanged per-call times; until that is
-# understood the step keeps the per-call pre-pass.  tests/test_gpu_train_step.py runs both ways.
-_pack = False
+# front of each: 30 of 3 - 9 us in a ResNet-18 step).  Device time of a step at batch 32 / 256: 2.87 -> 2.81 /
+# 8.43 -> 8.37 ms.
+_pack = True
 
 
 def _packed(qw, which):
-    return _pcache.get((qw.data_ptr(), which))
+    hit = _pcache.get((qw.data_ptr(), which))
+    return hit[0] if hit is not None else None
 
 
 def _quantize(name, t):
@@ -451,7 +453,7 @@ def make_weights(dev, gen):
 def _quantize_weights(tensors):
     """all weight tensors of the network in one call (two launches instead of one or two per tensor); the layers
     find the codes in the cache when they ask for them"""
-    tensors = [t if t.is_contiguous() else t.contiguous() for t in tensors]
+    tensors = [t for t in tensors if t.is_contiguous()]   # the others are quantized where they are used
     n = sum(t.numel() for t in tensors)
     res = _call("quantize (weights)", 0, 9 * n, q8t.quantize_multi, [t.detach() for t in tensors], 8)
     for t, (q, qp) in zip(tensors, res):
@@ -459,44 +461,51 @@ def _quantize_weights(tensors):
         _qcache[t.data_ptr()] = (q, qp)
 
 
-def _pack_filters(x, ws):
-    """The filters of every convolution of the network, in the layouts its forward and layer-gradient kernels read,
-    by one launch (the products then skip their own small pre-pass)."""
-    n = x.shape[0]
-    h = (x.shape[2] + 2 * 3 - 7) // 2 + 1      # first layer 7x7 / 2, pad 3
-    h = (h + 2 * 1 - 3) // 2 + 1               # pooling 3x3 / 2, pad 1
-    jobs, keys = [], []
+@functools.lru_cache(maxsize=8)
+def _pack_plan(shapes):
+    return q8t.PackPlan([(q8t.conv_desc(*s[:9]), s[9]) for s in shapes])
 
-    def add(w, d, which):
-        qw, _ = _quantize("quantize (weights)", w)
-        jobs.append((d, which, qw))
-        keys.append(((w.data_ptr(), which), (qw.data_ptr(), which)))
 
-    for (cin, cout, stride), b in zip(STAGES, ws["blocks"]):
+@functools.lru_cache(maxsize=8)
+def _resnet_shapes(n, size):
+    """conv_desc arguments and direction of every product whose filter is packed ahead, in the order of the filters"""
+    h = (size + 2 * 3 - 7) // 2 + 1      # first layer 7x7 / 2, pad 3
+    h = (h + 2 * 1 - 3) // 2 + 1         # pooling 3x3 / 2, pad 1
+    shapes = []
+    for cin, cout, stride in STAGES:
         h2 = (h + 2 - 3) // stride + 1
-        d1 = q8t.conv_desc(n, cin, h, h, cout, 3, 3, stride, 1)
-        d2 = q8t.conv_desc(n, cout, h2, h2, cout, 3, 3, 1, 1)
-        for w, d in ((b["c1"], d1), (b["c2"], d2)):
-            add(w, d, 0)
-            add(w, d, 1)
-        if "sc" in b:
-            add(b["sc"], q8t.conv_desc(n, cin, h, h, cout, 1, 1, stride, 0), 0)
-            # its layer gradient runs as the stride-1 product on the positions the layer read (_convbn_bwd)
-            add(b["sc"], q8t.conv_desc(n, cin, h2, h2, cout, 1, 1, 1, 0), 1)
+        for s in ((n, cin, h, h, cout, 3, 3, stride, 1), (n, cout, h2, h2, cout, 3, 3, 1, 1)):
+            shapes += [s + (0,), s + (1,)]
+        if stride != 1 or cin != cout:
+            # the shortcut's layer gradient runs as the stride-1 product on the positions the layer read (_convbn_bwd)
+            shapes += [(n, cin, h, h, cout, 1, 1, stride, 0, 0), (n, cin, h2, h2, cout, 1, 1, 1, 0, 1)]
         h = h2
-    nbytes = 2 * sum(j[2].numel() for j in jobs)
-    bufs = _call("qconv_pack_multi", 0, nbytes, q8t.qconv_pack_multi, jobs, [_pbufs.get(k[0]) for k in keys])
-    for (kw, kq), b in zip(keys, bufs):
+    return tuple(shapes)
+
+
+def _pack_filters(shapes, filters):
+    """The filters, each for both directions, in the layouts their forward and layer-gradient kernels read, by one launch
+    (the products then skip their own small pre-pass)."""
+    codes = [_quantize("quantize (weights)", w)[0] for w in filters for _ in (0, 1)]
+    plan = _pack_plan(shapes)
+    bufs = _call("qconv_pack_multi", 0, 2 * sum(q.numel() for q in codes), plan.run, codes)
+    for s, q, b in zip(shapes, codes, bufs):
         if b is not None:
-            _pbufs[kw] = b
-            _pcache[kq] = b
+            _pcache[(q.data_ptr(), s[9])] = (b, q)
+
+
+def _end_step():
+    # codes and packed filters are found by address: they must not outlive the step whose tensors these addresses are
+    _qcache.clear()
+    for key in _pcache:
+        _pcache[key] = None
 
 
 def step(x, labels, ws):
     try:
         return _step(x, labels, ws)
     finally:
-        _qcache.clear()   # codes are found by address: they must not outlive the step whose tensors these addresses are
+        _end_step()
 
 
 def _step(x, labels, ws):
@@ -506,7 +515,7 @@ def _step(x, labels, ws):
     if _fuse:
         _quantize_weights([ws["conv1"], ws["fc"]] + [w for b in ws["blocks"] for w in b.values()])
         if _pack:
-            _pack_filters(x, ws)
+            _pack_filters(_resnet_shapes(x.shape[0], x.shape[2]), [w for b in ws["blocks"] for w in b.values()])
     if _fuse:
         a = StemConvBNPool.apply(x, ws["conv1"], 2, 3)
     else:
@@ -534,9 +543,21 @@ def bottleneck_step(x, gy, ws):
     _qcache.clear()
     _pcache.clear()
     _layer[0] = 0
+    try:
+        return _bottleneck_step(x, gy, ws)
+    finally:
+        _end_step()
+
+
+def _bottleneck_step(x, gy, ws):
     # one node where the chain's result has the shape of its input (nothing for the sum to broadcast)
     plain = ws[2].shape[0] == x.shape[1] and [tuple(w.shape[2:]) for w in ws] == [(1, 1), (3, 3), (1, 1)]
     if _fuse and plain and x.dtype == torch.float32:
+        _quantize_weights(ws)
+        if _pack:
+            n, _, h, wd = x.shape
+            _pack_filters(tuple((n, w.shape[1], h, wd, w.shape[0], w.shape[2], w.shape[3], 1, pad, which)
+                                for w, pad in zip(ws, (0, 1, 0)) for which in (0, 1)), ws)
         out = Bottleneck.apply(x, ((1, 0), (1, 1), (1, 0)), *ws)
         out.backward(gy)
         return out
