@@ -1,5 +1,6 @@
-"""Thin ctypes binding over libq8t.so (the C ABI declared in include/q8t.h).
+"""Thin binding over libq8t.so (the C ABI declared in include/q8t.h).
 
+The calls of a training step go through _q8t_calls.so (csrc/python_calls.cpp), the others through ctypes.
 Argument marshalling only: torch supplies device memory and the current stream, every step of
 the method runs in the library's HIP kernels.  There is no CPU fallback: if the library is not
 built the import fails.
@@ -12,12 +13,13 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libq8t.so")
 
-if not os.path.exists(LIB_PATH):
+if not (os.path.exists(LIB_PATH) and os.path.exists(os.path.join(_HERE, "_q8t_calls.so"))):
     raise ImportError(
-        "libq8t.so is not built (%s): run `python -c 'import __graft_entry__ as g; g.build()'` "
+        "libq8t.so or _q8t_calls.so is not built (%s): run `python -c 'import __graft_entry__ as g; g.build()'` "
         "or `python paper_1805_11046_amd/build.py`" % LIB_PATH)
 
 _lib = C.CDLL(LIB_PATH)
+from . import _q8t_calls as _calls  # noqa: E402  (linked against the library)
 
 ERRORS = {-1: "Q8T_ERR_NULL", -2: "Q8T_ERR_SHAPE", -3: "Q8T_ERR_BITS", -4: "Q8T_ERR_OVERFLOW",
           -5: "Q8T_ERR_WORKSPACE", -6: "Q8T_ERR_HIP"}
@@ -173,6 +175,9 @@ def workspace(nbytes, device):
     return buf
 
 
+_calls.setup(workspace, _ws_cache, Q8TError)
+
+
 def new_qparams(device):
     """Device-resident q8t_qparams (24 bytes) as an int32[6] tensor."""
     return torch.empty(6, dtype=torch.int32, device=device)
@@ -200,15 +205,7 @@ def range_bn_scale(n):
 
 # ------------------------------------------------------------------ quantization
 def quantize(x, bits=8, stochastic=False, seed=0, q_out=None, qp_out=None, ws=None):
-    _dev(x)
-    n = x.numel()
-    q = q_out if q_out is not None else torch.empty(x.shape, dtype=torch.int8 if bits <= 8 else torch.int16,
-                                                     device=x.device)
-    qp = qp_out if qp_out is not None else new_qparams(x.device)
-    ws = ws if ws is not None else workspace(_lib.q8t_quantize_workspace_size(n), x.device)
-    _check(_lib.q8t_quantize(_ptr(x), n, bits, int(bool(stochastic)), int(seed) & (2 ** 64 - 1), _ptr(q),
-                             _ptr(qp), _ptr(ws), _stream()), "q8t_quantize")
-    return q, qp
+    return _calls.quantize(x, bits, stochastic, seed, q_out, qp_out, ws)
 
 
 def quantize_multi(tensors, bits=8):
@@ -244,30 +241,11 @@ def quantize_noalloc(x, q_out, qp_out, bits=8, stochastic=False, seed=0):
 
 
 def quantize_with_range(x, vmin_vmax, bits=8, stochastic=False, seed=0, q_out=None, qp_out=None):
-    _dev(x)
-    _dev(vmin_vmax)
-    n = x.numel()
-    q = q_out if q_out is not None else torch.empty(x.shape, dtype=torch.int8 if bits <= 8 else torch.int16,
-                                                     device=x.device)
-    qp = qp_out if qp_out is not None else new_qparams(x.device)
-    _check(_lib.q8t_quantize_with_range(_ptr(x), n, bits, int(bool(stochastic)), int(seed) & (2 ** 64 - 1),
-                                        _ptr(vmin_vmax), _ptr(q), _ptr(qp), _stream()),
-           "q8t_quantize_with_range")
-    return q, qp
+    return _calls.quantize_with_range(x, vmin_vmax, bits, stochastic, seed, q_out, qp_out)
 
 
 def quantize_bifurcate(g, seed8=0, seed16=1, q8_out=None, qp8_out=None, q16_out=None, qp16_out=None, ws=None):
-    _dev(g)
-    n = g.numel()
-    q8 = q8_out if q8_out is not None else torch.empty(g.shape, dtype=torch.int8, device=g.device)
-    q16 = q16_out if q16_out is not None else torch.empty(g.shape, dtype=torch.int16, device=g.device)
-    qp8 = qp8_out if qp8_out is not None else new_qparams(g.device)
-    qp16 = qp16_out if qp16_out is not None else new_qparams(g.device)
-    ws = ws if ws is not None else workspace(_lib.q8t_quantize_workspace_size(n), g.device)
-    _check(_lib.q8t_quantize_bifurcate(_ptr(g), n, int(seed8) & (2 ** 64 - 1), int(seed16) & (2 ** 64 - 1),
-                                       _ptr(q8), _ptr(qp8), _ptr(q16), _ptr(qp16), _ptr(ws), _stream()),
-           "q8t_quantize_bifurcate")
-    return q8, qp8, q16, qp16
+    return _calls.quantize_bifurcate(g, seed8, seed16, q8_out, qp8_out, q16_out, qp16_out, ws)
 
 
 def dequantize(q, qp, out=None):
@@ -278,55 +256,24 @@ def dequantize(q, qp, out=None):
 
 
 # ------------------------------------------------------------------ FC products
-def _fc(fn, name, a, pa, b, pb, M, N, K, out_shape, which, acc_dtype, want_acc, out, ws):
-    dev = a.device
-    y = out if out is not None else torch.empty(out_shape, dtype=torch.float32, device=dev)
-    acc = torch.empty(out_shape, dtype=acc_dtype, device=dev) if want_acc else None
-    if ws is None:
-        need = _lib.q8t_qgemm_workspace_size(M, N, K, which)
-        ws = workspace(need, dev) if need else None
-    _check(fn(_ptr(a), _ptr(pa), _ptr(b), _ptr(pb), M, N, K, _ptr(y), _ptr(acc), _ptr(ws), _stream()), name)
-    return y, acc
-
-
 def qgemm_fwd(qx, px, qw, pw, want_acc=False, out=None, ws=None):
     """Y[M,N] = X[M,K] W[K,N]"""
-    _dev(qx), _dev(qw)
-    M, K = qx.shape
-    K2, N = qw.shape
-    assert K == K2
-    return _fc(_lib.q8t_qgemm_fwd, "q8t_qgemm_fwd", qx, px, qw, pw, M, N, K, (M, N), 0, torch.int32, want_acc,
-               out, ws)
+    return _calls.qgemm_fwd(qx, px, qw, pw, want_acc, out, ws)
 
 
 def qgemm_dgrad(qdy, pg, qw, pw, want_acc=False, out=None, ws=None):
     """dX[M,K] = dY[M,N] W[K,N]^T"""
-    _dev(qdy), _dev(qw)
-    M, N = qdy.shape
-    K, N2 = qw.shape
-    assert N == N2
-    return _fc(_lib.q8t_qgemm_dgrad, "q8t_qgemm_dgrad", qdy, pg, qw, pw, M, N, K, (M, K), 1, torch.int32,
-               want_acc, out, ws)
+    return _calls.qgemm_dgrad(qdy, pg, qw, pw, want_acc, out, ws)
 
 
 def qgemm_wgrad(qx, px, qdy16, pg16, want_acc=False, out=None, ws=None):
     """dW[K,N] = X[M,K]^T dY16[M,N]"""
-    _dev(qx), _dev(qdy16)
-    M, K = qx.shape
-    M2, N = qdy16.shape
-    assert M == M2 and qdy16.dtype == torch.int16
-    return _fc(_lib.q8t_qgemm_wgrad, "q8t_qgemm_wgrad", qx, px, qdy16, pg16, M, N, K, (K, N), 2, torch.int64,
-               want_acc, out, ws)
+    return _calls.qgemm_wgrad(qx, px, qdy16, pg16, want_acc, out, ws)
 
 
 def chunk_range(x, K, ws=None):
     """Clamping range averaged over K contiguous chunks (App. B).  Returns a device tensor {vmin, vmax}."""
-    _dev(x)
-    n = x.numel()
-    out = torch.empty(2, dtype=torch.float32, device=x.device)
-    ws = ws if ws is not None else workspace(_lib.q8t_chunk_range_workspace_size(n, int(K)), x.device)
-    _check(_lib.q8t_chunk_range(_ptr(x), n, int(K), _ptr(out), _ptr(ws), _stream()), "q8t_chunk_range")
-    return out
+    return _calls.chunk_range(x, K, ws)
 
 
 def quant_angle(x, q, qp, ws=None):
@@ -345,25 +292,13 @@ def conv_desc(N, Cin, H, W, K, R, S, stride, pad):
     return ConvDesc(N, Cin, H, W, K, R, S, stride, pad)
 
 
-def _conv(fn, name, d, a, pa, b, pb, out_shape, which, acc_dtype, want_acc, out, ws):
-    dev = a.device
-    y = out if out is not None else torch.empty(out_shape, dtype=torch.float32, device=dev)
-    acc = torch.empty(out_shape, dtype=acc_dtype, device=dev) if want_acc else None
-    ws = ws if ws is not None else workspace(_lib.q8t_qconv_workspace_size(C.byref(d), which), dev)
-    _check(fn(C.byref(d), _ptr(a), _ptr(pa), _ptr(b), _ptr(pb), _ptr(y), _ptr(acc), _ptr(ws), _stream()), name)
-    return y, acc
-
-
 def qconv_workspace_size(d, which):
     """Bytes of workspace q8t_qconv_fwd (0) / dgrad (1) / wgrad (2) need for this layer."""
     return int(_lib.q8t_qconv_workspace_size(C.byref(d), int(which)))
 
 
 def qconv_fwd(d, qx, px, qw, pw, want_acc=False, out=None, ws=None):
-    _dev(qx), _dev(qw)
-    assert tuple(qx.shape) == (d.N, d.C, d.H, d.W) and tuple(qw.shape) == (d.K, d.C, d.R, d.S)
-    return _conv(_lib.q8t_qconv_fwd, "q8t_qconv_fwd", d, qx, px, qw, pw, (d.N, d.K, d.P, d.Q), 0, torch.int32,
-                 want_acc, out, ws)
+    return _calls.qconv_fwd(d, qx, px, qw, pw, want_acc, out, ws, None)
 
 
 def qconv_pack_size(d, which):
@@ -409,146 +344,54 @@ def qconv_pack_multi(jobs, out=None):
 def qconv_fwd_bn_stats(d, qx, px, qw, pw, want_acc=False, out=None, stats_out=None, ws=None, packed=None):
     """Forward convolution + Range BN statistics of its result.  Returns (y, acc or None, stats[3,K]).
     packed: the layer's filter from qconv_pack_multi (same desc, which = 0, same codes)."""
-    _dev(qx), _dev(qw)
-    assert tuple(qx.shape) == (d.N, d.C, d.H, d.W) and tuple(qw.shape) == (d.K, d.C, d.R, d.S)
-    dev = qx.device
-    shape = (d.N, d.K, d.P, d.Q)
-    y = out if out is not None else torch.empty(shape, dtype=torch.float32, device=dev)
-    acc = torch.empty(shape, dtype=torch.int32, device=dev) if want_acc else None
-    stats = stats_out if stats_out is not None else torch.empty((3, d.K), dtype=torch.float32, device=dev)
-    ws = ws if ws is not None else workspace(_lib.q8t_qconv_fwd_bn_stats_workspace_size(C.byref(d)), dev)
-    if packed is not None:
-        _check(_lib.q8t_qconv_fwd_bn_stats_packed(C.byref(d), _ptr(qx), _ptr(px), _ptr(qw), _ptr(pw), _ptr(packed), _ptr(y),
-                                                  _ptr(acc), _ptr(stats), _ptr(ws), _stream()), "q8t_qconv_fwd_bn_stats_packed")
-    else:
-        _check(_lib.q8t_qconv_fwd_bn_stats(C.byref(d), _ptr(qx), _ptr(px), _ptr(qw), _ptr(pw), _ptr(y), _ptr(acc),
-                                           _ptr(stats), _ptr(ws), _stream()), "q8t_qconv_fwd_bn_stats")
-    return y, acc, stats
+    return _calls.qconv_fwd_bn_stats(d, qx, px, qw, pw, want_acc, out, stats_out, ws, packed)
 
 
 def qconv_dgrad(d, qdy, pg, qw, pw, want_acc=False, out=None, ws=None, packed=None):
     """packed: the layer's filter from qconv_pack_multi (same desc, which = 1, same codes)."""
-    _dev(qdy), _dev(qw)
-    assert tuple(qdy.shape) == (d.N, d.K, d.P, d.Q) and tuple(qw.shape) == (d.K, d.C, d.R, d.S)
-    if packed is not None:
-        dev = qdy.device
-        shape = (d.N, d.C, d.H, d.W)
-        dx = out if out is not None else torch.empty(shape, dtype=torch.float32, device=dev)
-        acc = torch.empty(shape, dtype=torch.int32, device=dev) if want_acc else None
-        ws = ws if ws is not None else workspace(_lib.q8t_qconv_workspace_size(C.byref(d), 1), dev)
-        _check(_lib.q8t_qconv_dgrad_packed(C.byref(d), _ptr(qdy), _ptr(pg), _ptr(qw), _ptr(pw), _ptr(packed), _ptr(dx), _ptr(acc),
-                                           _ptr(ws), _stream()), "q8t_qconv_dgrad_packed")
-        return dx, acc
-    return _conv(_lib.q8t_qconv_dgrad, "q8t_qconv_dgrad", d, qdy, pg, qw, pw, (d.N, d.C, d.H, d.W), 1,
-                 torch.int32, want_acc, out, ws)
+    return _calls.qconv_dgrad(d, qdy, pg, qw, pw, want_acc, out, ws, packed)
 
 
 def qconv_dgrad_relu_sum(d, qdy, pg, qw, pw, other, act, out=None, ws=None, packed=None):
     """act > 0 ? dgrad + other : 0 (other may be None): the layer gradient of a residual block's first convolution
     with the end of the block's backward pass in its epilogue.  Returns dx."""
-    _dev(qdy), _dev(qw), _dev(act)
-    shape = (d.N, d.C, d.H, d.W)
-    assert tuple(qdy.shape) == (d.N, d.K, d.P, d.Q) and tuple(qw.shape) == (d.K, d.C, d.R, d.S)
-    assert tuple(act.shape) == shape and act.dtype == torch.float32 and act.is_contiguous()
-    if other is not None:
-        _dev(other)
-        assert tuple(other.shape) == shape and other.dtype == torch.float32 and other.is_contiguous()
-    dx = out if out is not None else torch.empty(shape, dtype=torch.float32, device=qdy.device)
-    ws = ws if ws is not None else workspace(_lib.q8t_qconv_workspace_size(C.byref(d), 1), qdy.device)
-    if packed is not None:
-        _check(_lib.q8t_qconv_dgrad_relu_sum_packed(C.byref(d), _ptr(qdy), _ptr(pg), _ptr(qw), _ptr(pw), _ptr(packed), _ptr(other),
-                                                    _ptr(act), _ptr(dx), _ptr(ws), _stream()), "q8t_qconv_dgrad_relu_sum_packed")
-    else:
-        _check(_lib.q8t_qconv_dgrad_relu_sum(C.byref(d), _ptr(qdy), _ptr(pg), _ptr(qw), _ptr(pw), _ptr(other), _ptr(act), _ptr(dx),
-                                             _ptr(ws), _stream()), "q8t_qconv_dgrad_relu_sum")
-    return dx
+    _dev(act)
+    return _calls.qconv_dgrad_sum(d, qdy, pg, qw, pw, other, act, out, ws, packed)
 
 
 def qconv_dgrad_sum(d, qdy, pg, qw, pw, other, out=None, ws=None, packed=None):
     """dgrad + other: the layer gradient of a residual block's first convolution with the gradient of the shortcut
     added in its epilogue.  Returns dx."""
-    _dev(qdy), _dev(qw), _dev(other)
-    shape = (d.N, d.C, d.H, d.W)
-    assert tuple(qdy.shape) == (d.N, d.K, d.P, d.Q) and tuple(qw.shape) == (d.K, d.C, d.R, d.S)
-    assert tuple(other.shape) == shape and other.dtype == torch.float32 and other.is_contiguous()
-    dx = out if out is not None else torch.empty(shape, dtype=torch.float32, device=qdy.device)
-    ws = ws if ws is not None else workspace(_lib.q8t_qconv_workspace_size(C.byref(d), 1), qdy.device)
-    _check(_lib.q8t_qconv_dgrad_sum(C.byref(d), _ptr(qdy), _ptr(pg), _ptr(qw), _ptr(pw), _ptr(packed), _ptr(other), _ptr(dx),
-                                    _ptr(ws), _stream()), "q8t_qconv_dgrad_sum")
-    return dx
+    _dev(other)
+    return _calls.qconv_dgrad_sum(d, qdy, pg, qw, pw, other, None, out, ws, packed)
 
 
 def qconv_wgrad(d, qx, px, qdy16, pg16, want_acc=False, out=None, ws=None):
-    _dev(qx), _dev(qdy16)
-    assert tuple(qx.shape) == (d.N, d.C, d.H, d.W) and tuple(qdy16.shape) == (d.N, d.K, d.P, d.Q)
-    assert qdy16.dtype == torch.int16
-    return _conv(_lib.q8t_qconv_wgrad, "q8t_qconv_wgrad", d, qx, px, qdy16, pg16, (d.K, d.C, d.R, d.S), 2,
-                 torch.int64, want_acc, out, ws)
+    return _calls.qconv_wgrad(d, qx, px, qdy16, pg16, want_acc, out, ws, None)
 
 
 # ------------------------------------------------------------------ Range BN
 def range_bn_fwd(x, gamma=None, beta=None, eps=0.0, quantized=False, want_y=True, y_out=None, stats_out=None,
                  q_out=None, qp_out=None, ws=None):
     """Returns (y or None, stats[3,C], q or None, qp or None)."""
-    _dev(x)
-    N, Cc, H, W = x.shape
-    dev = x.device
-    y = y_out if y_out is not None else (torch.empty_like(x) if want_y else None)
-    stats = stats_out if stats_out is not None else torch.empty((3, Cc), dtype=torch.float32, device=dev)
-    q = qp = None
-    if quantized:
-        q = q_out if q_out is not None else torch.empty(x.shape, dtype=torch.int8, device=dev)
-        qp = qp_out if qp_out is not None else new_qparams(dev)
-    ws = ws if ws is not None else workspace(_lib.q8t_range_bn_workspace_size(N, Cc, H, W), dev)
-    _check(_lib.q8t_range_bn_fwd(_ptr(x), N, Cc, H, W, _ptr(gamma), _ptr(beta), float(eps), _ptr(y), _ptr(stats),
-                                 _ptr(q), _ptr(qp), _ptr(ws), _stream()), "q8t_range_bn_fwd")
-    return y, stats, q, qp
+    return _calls.range_bn_fwd(x, gamma, beta, eps, quantized, want_y, y_out, stats_out, q_out, qp_out, ws)
 
 
 def range_bn_fwd_apply(x, stats, gamma=None, beta=None, eps=0.0, quantized=False, want_y=True, y_out=None, q_out=None,
                        qp_out=None):
     """Range BN forward from given statistics.  Returns (y or None, q or None, qp or None)."""
-    _dev(x), _dev(stats)
-    N, Cc, H, W = x.shape
-    dev = x.device
-    y = y_out if y_out is not None else (torch.empty_like(x) if want_y else None)
-    q = qp = None
-    if quantized:
-        q = q_out if q_out is not None else torch.empty(x.shape, dtype=torch.int8, device=dev)
-        qp = qp_out if qp_out is not None else new_qparams(dev)
-    _check(_lib.q8t_range_bn_fwd_apply(_ptr(x), N, Cc, H, W, _ptr(gamma), _ptr(beta), float(eps), _ptr(stats), _ptr(y),
-                                       _ptr(q), _ptr(qp), _stream()), "q8t_range_bn_fwd_apply")
-    return y, q, qp
+    return _calls.range_bn_fwd_apply(x, stats, gamma, beta, eps, quantized, want_y, y_out, q_out, qp_out)
 
 
 def range_bn_relu_fwd_apply(x, stats, gamma=None, beta=None, eps=0.0, quantized=False, want_y=True, y_out=None,
                             q_out=None, qp_out=None):
     """Range BN + ReLU forward from given statistics.  Returns (y or None, q or None, qp or None)."""
-    _dev(x), _dev(stats)
-    N, Cc, H, W = x.shape
-    dev = x.device
-    y = y_out if y_out is not None else (torch.empty_like(x) if want_y else None)
-    q = qp = None
-    if quantized:
-        q = q_out if q_out is not None else torch.empty(x.shape, dtype=torch.int8, device=dev)
-        qp = qp_out if qp_out is not None else new_qparams(dev)
-    _check(_lib.q8t_range_bn_relu_fwd_apply(_ptr(x), N, Cc, H, W, _ptr(gamma), _ptr(beta), float(eps), _ptr(stats),
-                                            _ptr(y), _ptr(q), _ptr(qp), _stream()), "q8t_range_bn_relu_fwd_apply")
-    return y, q, qp
+    return _calls.range_bn_relu_fwd_apply(x, stats, gamma, beta, eps, quantized, want_y, y_out, q_out, qp_out)
 
 
 def range_bn_bwd(x, dy, stats, gamma=None, eps=0.0, dx_out=None, ws=None):
     """Returns (dx, dgamma, dbeta)."""
-    _dev(x), _dev(dy), _dev(stats)
-    N, Cc, H, W = x.shape
-    dev = x.device
-    dx = dx_out if dx_out is not None else torch.empty_like(x)
-    dgamma = torch.empty(Cc, dtype=torch.float32, device=dev)
-    dbeta = torch.empty(Cc, dtype=torch.float32, device=dev)
-    ws = ws if ws is not None else workspace(_lib.q8t_range_bn_workspace_size(N, Cc, H, W), dev)
-    _check(_lib.q8t_range_bn_bwd(_ptr(x), _ptr(dy), _ptr(stats), N, Cc, H, W, _ptr(gamma), float(eps), _ptr(dx),
-                                 _ptr(dgamma), _ptr(dbeta), _ptr(ws), _stream()), "q8t_range_bn_bwd")
-    return dx, dgamma, dbeta
+    return _calls.range_bn_bwd(x, dy, stats, gamma, eps, dx_out, ws)
 
 
 def _bn_bwd_bifurcate_buffers(x, dx_out, q8_out, qp8_out, q16_out, qp16_out, ws, want_dx, want_q8=True, ws_size=None):
@@ -573,46 +416,24 @@ def range_bn_relu_bwd_bifurcate(x, dy, stats, gamma=None, beta=None, eps=0.0, se
                                 q8_out=None, qp8_out=None, q16_out=None, qp16_out=None, ws=None, want_dx=True):
     """Backward of Range BN + ReLU + bifurcated quantization of dx in one call.
     Returns (dx or None, dgamma, dbeta, q8, qp8, q16, qp16)."""
-    _dev(x), _dev(dy), _dev(stats)
-    N, Cc, H, W = x.shape
-    dx, dgamma, dbeta, q8, qp8, q16, qp16, ws = _bn_bwd_bifurcate_buffers(x, dx_out, q8_out, qp8_out, q16_out, qp16_out,
-                                                                          ws, want_dx)
-    _check(_lib.q8t_range_bn_relu_bwd_bifurcate(_ptr(x), _ptr(dy), _ptr(stats), N, Cc, H, W, _ptr(gamma), _ptr(beta),
-                                                float(eps), _ptr(dx), _ptr(dgamma), _ptr(dbeta),
-                                                int(seed8) & (2 ** 64 - 1), int(seed16) & (2 ** 64 - 1), _ptr(q8),
-                                                _ptr(qp8), _ptr(q16), _ptr(qp16), _ptr(ws), _stream()),
-           "q8t_range_bn_relu_bwd_bifurcate")
-    return dx, dgamma, dbeta, q8, qp8, q16, qp16
+    return _calls.range_bn_relu_bwd_bifurcate(x, dy, stats, gamma, beta, eps, seed8, seed16, dx_out, q8_out, qp8_out, q16_out,
+                                              qp16_out, ws, want_dx, True, None)
 
 
 def range_bn_bwd_bifurcate(x, dy, stats, gamma=None, eps=0.0, seed8=0, seed16=1, dx_out=None, q8_out=None,
                            qp8_out=None, q16_out=None, qp16_out=None, ws=None, want_dx=True, want_q8=True):
     """Range BN backward + bifurcated quantization of dx in one call.
     Returns (dx or None, dgamma, dbeta, q8, qp8, q16, qp16); want_q8=False leaves q8 = qp8 = None."""
-    _dev(x), _dev(dy), _dev(stats)
-    N, Cc, H, W = x.shape
-    dx, dgamma, dbeta, q8, qp8, q16, qp16, ws = _bn_bwd_bifurcate_buffers(x, dx_out, q8_out, qp8_out, q16_out, qp16_out,
-                                                                          ws, want_dx, want_q8)
-    _check(_lib.q8t_range_bn_bwd_bifurcate(_ptr(x), _ptr(dy), _ptr(stats), N, Cc, H, W, _ptr(gamma), float(eps),
-                                           _ptr(dx), _ptr(dgamma), _ptr(dbeta), int(seed8) & (2 ** 64 - 1),
-                                           int(seed16) & (2 ** 64 - 1), _ptr(q8), _ptr(qp8), _ptr(q16), _ptr(qp16),
-                                           _ptr(ws), _stream()), "q8t_range_bn_bwd_bifurcate")
-    return dx, dgamma, dbeta, q8, qp8, q16, qp16
+    return _calls.range_bn_bwd_bifurcate(x, dy, stats, gamma, None, eps, seed8, seed16, dx_out, q8_out, qp8_out, q16_out, qp16_out,
+                                         ws, want_dx, want_q8, None)
 
 
 def range_bn_bwd_bifurcate_masked(x, dy, act, stats, gamma=None, eps=0.0, seed8=0, seed16=1):
     """range_bn_bwd_bifurcate with the gradient dy masked by the rectifier whose result is act.
     Returns (masked dy, dgamma, dbeta, q8, qp8, q16, qp16)."""
-    _dev(x), _dev(dy), _dev(act), _dev(stats)
-    N, Cc, H, W = x.shape
-    assert dy.shape == x.shape and act.shape == x.shape and dy.dtype == torch.float32 and act.dtype == torch.float32
-    gm = torch.empty_like(x)
-    _, dgamma, dbeta, q8, qp8, q16, qp16, ws = _bn_bwd_bifurcate_buffers(x, None, None, None, None, None, None, False)
-    _check(_lib.q8t_range_bn_bwd_bifurcate_masked(_ptr(x), _ptr(dy), _ptr(act), _ptr(stats), N, Cc, H, W, _ptr(gamma), float(eps),
-                                                  _ptr(gm), _ptr(dgamma), _ptr(dbeta), int(seed8) & (2 ** 64 - 1),
-                                                  int(seed16) & (2 ** 64 - 1), _ptr(q8), _ptr(qp8), _ptr(q16), _ptr(qp16),
-                                                  _ptr(ws), _stream()), "q8t_range_bn_bwd_bifurcate_masked")
-    return gm, dgamma, dbeta, q8, qp8, q16, qp16
+    _dev(act)
+    return _calls.range_bn_bwd_bifurcate(x, dy, stats, gamma, None, eps, seed8, seed16, None, None, None, None, None, None, False,
+                                         True, act)
 
 
 # ------------------------------------------------------------------ ternarized back-propagation
@@ -725,16 +546,7 @@ def range_bn_add_relu_quantize(x, stats, other, gamma=None, beta=None, other_sta
                                other_beta=None, eps=0.0, quantized=True):
     """relu(bn(x; stats) + o), o = other or bn(other; other_stats), and the 8-bit codes of the result.
     Returns (out, codes or None, qparams or None)."""
-    _dev(x), _dev(other), _dev(stats)
-    N, Cc, H, W = x.shape
-    out = torch.empty_like(x)
-    q = torch.empty(x.shape, dtype=torch.int8, device=x.device) if quantized else None
-    qp = new_qparams(x.device) if quantized else None
-    ws = workspace(_lib.q8t_add_relu_quantize_workspace_size(x.numel()), x.device)
-    _check(_lib.q8t_range_bn_add_relu_quantize(_ptr(x), _ptr(stats), _ptr(gamma), _ptr(beta), _ptr(other), _ptr(other_stats),
-                                               _ptr(other_gamma), _ptr(other_beta), N, Cc, H, W, float(eps), _ptr(out),
-                                               _ptr(q), _ptr(qp), _ptr(ws), _stream()), "q8t_range_bn_add_relu_quantize")
-    return out, q, qp
+    return _calls.range_bn_add_relu_quantize(x, stats, other, gamma, beta, other_stats, other_gamma, other_beta, eps, quantized)
 
 
 def range_bn_add_relu(x, stats, other, gamma=None, beta=None, eps=0.0):
