@@ -17,20 +17,18 @@
 // both operands.  With masked entries zero, sum (a-za)(b-zb) = sum ab - zb sum a - za sum b + red za zb holds
 // for the real reduction length.
 //
-// Two kernels (times: back to back on one MI355X, M x N x K, against the general kernel that served every FC call before):
+// Three kernels (times: back to back on one MI355X, M x N x K, against the general kernel that served every FC call before):
 //   fc_direct  operands go from memory to registers, no LDS in the main loop; the wavefronts of a workgroup share a
 //              tile of 32x64 (wgrad 64x64) results and split its reduction, or own a tile each.  Bound by latency
 //              (launch, one or two dependent loads, the fold through LDS): 64x128x256 takes 3.9 / 3.9 / 6.0 us for
 //              forward / dgrad / wgrad (18.7 / 12.2 / 8.0 before), 256x1000x512 4.7 / 5.2 / 6.8 (23.9 / 15.8 / 19.7), the
 //              forward and dgrad of 512x2048x2048 10.7 and 15.0.  Few results and a long reduction: slices of it in
 //              workgroups of their own and fc_fold behind them.
-//   fc_tile    128x128 tiles, K-steps of 64 through double-buffered LDS with two register sets of prefetch.  65 / 59 / 112 us
-//              at 2048x4096x4096 (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s; 512x2048x2048's wgrad 19.  The wavefronts wait
-//              for issue (37 - 43% of their cycles) more than for data (23 - 28%): 4 - 6 vector instructions per MFMA, MFMA pipe
-//              20 - 26% busy, L2 hits 88 - 92% at 170 - 305 clocks a read, LDS active a quarter of the time.
+//   fc_dma     matrices of aligned rows, many tiles: operands go to LDS without registers (see there).
+//   fc_tile    the same sizes at any address and pitch: 128x128 tiles, K-steps of 64 through double-buffered LDS with two
+//              register sets of prefetch.  65 / 59 / 112 us at 2048x4096x4096 (1002 / 1777 / 473 before), 1.0 - 1.2 POP/s.
 // Measured and dropped: prefetching the next K-step in fc_direct (more registers, fewer wavefronts: 7.5 -> 8.4 us at
-// 1024^3), RS operands through LDS and the transposing reads ds_read_b64_tr_b8 / _b16 with 32x32x32 MFMAs (half the
-// instructions, same time), K-steps of 128 in fc_tile with one or two register sets (whole 128-byte lines per row: 68 / 61 and
+// 1024^3), K-steps of 128 in fc_tile with one or two register sets (whole 128-byte lines per row: 68 / 61 and
 // 68 / 65 us against 70 / 64 on the same box, 3000x333x2777 30 -> 38).
 #include "q8t_common.h"
 #include "q8t_internal.h"
@@ -721,6 +719,252 @@ __global__ __launch_bounds__(TT, 2) void fc_tile(const FcArgs p)
         }
 }
 
+// ---- large products of aligned matrices: tiles that go to LDS without registers -----------------------------------
+// 128 rows x 128 byte columns a workgroup (weight gradient: 64 columns, the two bytes of a 16-bit code are neighbouring byte
+// columns), K-steps of 128 in two LDS buffers.  A tile of either operand is 128 LDS rows of 128 bytes, eight 16-byte pieces
+// each, which global_load_lds writes as 64 lanes x 16 bytes in a row; so the permutation that keeps the fragment reads free
+// of bank conflicts is applied to the addresses in memory: piece s of LDS row r holds the operand's piece s ^ perm(r).
+//   RF operand: LDS row = row of the operand, pieces along the reduction; a fragment is one ds_read_b128
+//   RS operand: LDS row = reduction index, pieces along the columns; a fragment is two ds_read_b64_tr_b8, in which 16 lanes
+//               read 8 rows x 16 bytes and lane i receives the 8 bytes of column i
+// Nothing is transposed or split on the way.  2048x4096x4096, us, against fc_tile: forward 69 / 45, layer gradient 60 / 46, weight
+// gradient 111 / 101; 2048^3 31 / 19, 26 / 19, 43 / 31; 1.9 POP/s of the main loop.  Whole lines (K-steps of 128: of 64 the
+// same loop takes 47 us for 37 here), no registers between memory and LDS and the second workgroup of a compute unit are what
+// it lives on: tiles of 128x256 and three or four buffers, one workgroup a unit, take as long; 32x32x32 products are slower (43).
+constexpr int DT = 512, DK = 128, DTILE = 128 * DK;   // threads, reduction indices a step, bytes of an operand's tile
+
+__device__ __constant__ __align__(16) int8_t fc_zeros[16] = {};   // what pieces outside an operand read
+
+// 16 bytes per lane from memory to `lds` + 16 * lane (`lds` uniform in the wavefront).  Nothing is returned to registers; the
+// wavefront's vmcnt counts the transfer.  The LDS address goes through m0, which nothing else here uses.
+__device__ __forceinline__ void copy16_to_lds(const int8_t *g, int8_t *lds)
+{
+    const uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)lds);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(o), "v"(g) : "memory");
+}
+
+// One operand's share of the staging: two pieces per thread and step.
+template <bool RS>
+struct DmaStage {
+    const int8_t *src[2];
+    size_t step[2];      // bytes from step to step
+    int at[2];           // reduction index of the piece in step 0
+    __device__ __forceinline__ static int perm(int r)
+    {
+        // RS: eight neighbouring reduction indices on four pieces, indices 16 apart on others
+        return RS ? ((r >> 1) & 3) | ((r >> 2) & 4) : (r >> 1) & 7;
+    }
+    // first / count: rows (RF) or byte columns (RS) of the operand; ld in bytes
+    __device__ __forceinline__ void init(const void *base, int64_t ld, int first, int count)
+    {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int p = u * DT + (int)threadIdx.x, r = p >> 3, q = (p & 7) ^ perm(r);
+            if (RS) {
+                const bool in = first + q * 16 < count;   // the columns of the piece exist
+                at[u] = r;
+                src[u] = in ? (const int8_t *)base + r * ld + first + q * 16 : fc_zeros;
+                step[u] = in ? (size_t)DK * ld : 0;
+            } else {
+                at[u] = q * 16;
+                src[u] = (const int8_t *)base + min(first + r, count - 1) * ld + q * 16;
+                step[u] = DK;
+            }
+        }
+    }
+    // left: reduction indices from this step on
+    __device__ __forceinline__ void issue(int8_t *lds, int left)
+    {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int8_t *g = src[u];
+            if (left < DK && at[u] >= left) g = fc_zeros;
+            copy16_to_lds(g, lds + (u * DT + wave * 64) * 16);
+            src[u] += step[u];
+        }
+    }
+    // the 16 reduction indices h * 64 + 16 * kb .. of row / byte column `c16` * 16 + l16
+    __device__ __forceinline__ static v4i fragment(const int8_t *lds, int c16, int h, int l16, int kb)
+    {
+        if (!RS) {
+            const int r = c16 * 16 + l16;
+            return *reinterpret_cast<const v4i *>(lds + r * DK + (((h * 4 + kb) ^ perm(r)) * 16));
+        }
+        typedef int v2i __attribute__((ext_vector_type(2)));
+        v2i t[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int k = h * 64 + kb * 16 + e * 8 + (l16 >> 1);
+            const int8_t *a = lds + k * DK + ((c16 ^ perm(k)) * 16) + (l16 & 1) * 8;
+            t[e] = __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i *)(int8_t *)a);
+        }
+        return (v4i){t[0][0], t[0][1], t[1][0], t[1][1]};
+    }
+};
+
+template <int WHICH>
+__global__ __launch_bounds__(DT, 4) void fc_dma(const FcArgs p)
+{
+    constexpr bool RSA = WHICH == WGRAD, RSB = WHICH != DGRAD;
+    constexpr int WR = 2, WC = 4, MT = 4, NT = 2;   // wavefronts down and across, 16x16 tiles of a wavefront
+    constexpr int CB = WHICH == WGRAD ? 2 : 1;      // byte columns per column
+    constexpr int COLS = 128 / CB, STAGE = 2 * DTILE;
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];   // two buffers of A and B tiles
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kb = lane >> 4;
+    const int lg = q8t_gemm::xcd_logical(blockIdx.x, p.tiles);
+    if (lg >= p.tiles) return;
+    // tiles in blocks of 8 rows of tiles: the tiles an XCD works on at a time share both operands
+    const int tm = p.tiles / p.tn, per = 8 * p.tn, blk = lg / per, in = lg - blk * per;
+    const int bh = min(8, tm - blk * 8);
+    const int m0 = (blk * 8 + in % bh) * 128, n0 = (in / bh) * COLS;   // rows, columns
+    const int wr = wave % WR, wc = wave / WR;
+
+    DmaStage<RSA> sta;
+    DmaStage<RSB> stb;
+    sta.init(p.a, p.lda, m0, p.rows);
+    stb.init(p.b, (int64_t)p.ldb * CB, n0 * CB, p.cols * CB);
+    auto issue = [&](int s, int8_t *to) {
+        sta.issue(to, p.red - s * DK);
+        stb.issue(to + DTILE, p.red - s * DK);
+    };
+
+    v4i acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = (v4i){0, 0, 0, 0};
+    // Byte sums, as products with ones (forward, us: without sums 43, as v_dot4 on the fragments 48 to 51, so 46): the
+    // wavefronts that share rows (columns) take a row tile (column tile) each, the first one they multiply: a wavefront goes
+    // round its tiles from there.
+    static_assert(MT == WC && NT == WR, "a tile per wavefront");
+    const v4i ones = (v4i){0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    v4i rsum = (v4i){0, 0, 0, 0}, csum = (v4i){0, 0, 0, 0};
+    auto row_tile = [&](int i) { return wr * MT + ((i + wc) & (MT - 1)); };
+    auto col_tile = [&](int j) { return wc * NT + ((j + wr) & (NT - 1)); };
+    const uint32_t flip = WHICH == WGRAD && !(l16 & 1) ? 0x80808080u : 0u;   // low bytes are re-centred
+
+    const int steps = (p.red + DK - 1) / DK;
+    issue(0, smem);
+    v4i af[2][MT], bf[2][NT];
+    auto read = [&](const int8_t *a, int h) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) bf[h][j] = DmaStage<RSB>::fragment(a + DTILE, col_tile(j), h, l16, kb);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) af[h][i] = DmaStage<RSA>::fragment(a, row_tile(i), h, l16, kb);
+    };
+    auto multiply = [&](int h) {
+        if (WHICH == WGRAD) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) bf[h][j][d] ^= (int)flip;
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[h][i], bf[h][j], acc[i][j], 0, 0, 0);
+        rsum = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[h][0], ones, rsum, 0, 0, 0);
+        csum = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, bf[h][0], csum, 0, 0, 0);
+    };
+    auto step = [&](int s, const int8_t *cur, int8_t *nxt) {
+        // the tiles of this step are there, and every wavefront is past its reads of the other buffer
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (s + 1 < steps) issue(s + 1, nxt);
+        read(cur, 0);
+        read(cur, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);   // a wavefront that multiplies goes before the ones that read (46 -> 45 us)
+        multiply(0);
+        multiply(1);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    for (int s = 0; s < steps; s += 2) {
+        step(s, smem, smem + STAGE);
+        if (s + 1 < steps) step(s + 1, smem + STAGE, smem);
+    }
+    __syncthreads();
+    int *s_rs = reinterpret_cast<int *>(smem), *s_cs = s_rs + 128;   // [128] each
+    if (l16 == 0) *reinterpret_cast<v4i *>(&s_rs[row_tile(0) * 16 + kb * 4]) = rsum;   // every column holds the sums
+    // every row does; the zeros behind the reduction went in as low bytes of -128
+    if (kb == 0) s_cs[col_tile(0) * 16 + l16] = csum[0] + (flip ? 128 * (steps * DK - p.red) : 0);
+    __syncthreads();
+
+    const Zero z = zero_points(p);
+    if (WHICH != WGRAD) {
+        const uint32_t kzz = (uint32_t)p.red * (uint32_t)z.za * (uint32_t)z.zb;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int lc = col_tile(j) * 16 + l16, col = n0 + lc;
+            const uint32_t cs = (uint32_t)z.za * (uint32_t)s_cs[lc];
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int lr = row_tile(i) * 16 + kb * 4 + r, row = m0 + lr;
+                    const int c = (int)((uint32_t)acc[i][j][r] + kzz - (uint32_t)z.zb * (uint32_t)s_rs[lr] - cs);   // fits by contract
+                    if (row < p.rows && col < p.cols) {
+                        const int64_t o = (int64_t)row * p.cols + col;
+                        if (p.acc) ((int32_t *)p.acc)[o] = c;
+                        if (p.out) p.out[o] = z.sc * (float)c;
+                    }
+                }
+        }
+    } else {
+        // a lane pair holds the low and the high byte products of a column: the even lane finishes rows 0, 1 of the four, the
+        // odd one rows 2, 3; results go through LDS so that they leave in whole lines
+        // The sums are integers below 2^53 in magnitude (65536 products of 255 * 65535): in double they and the correction are exact
+        // and take a fifth of the instructions of 64-bit integers (16.8 M results: 20 us of vector instructions before).
+        constexpr int TP = COLS + 4;
+        float *turn = reinterpret_cast<float *>(smem + 4096);            // [128][TP]
+        double *s_t = reinterpret_cast<double *>(smem + 2048);           // the rows' share of the correction
+        if (tid < 128)
+            s_t[tid] = (double)(128 - z.zb) * (double)s_rs[tid] + (double)p.red * (double)z.za * (double)(z.zb - 128);
+        __syncthreads();
+        const bool odd = l16 & 1;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int lb = col_tile(j) * 16 + l16, lc = lb >> 1, col = n0 + lc;
+            const double cs = (double)z.za * (256.0 * (double)s_cs[lb | 1] + (double)s_cs[lb & ~1]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                int other[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) other[r] = __builtin_amdgcn_mov_dpp(acc[i][j][r], 0xB1, 0xF, 0xF, true);   // lane ^ 1
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int hi = odd ? acc[i][j][2 + k] : other[k], lo = odd ? other[2 + k] : acc[i][j][k];
+                    const int lr = row_tile(i) * 16 + kb * 4 + (odd ? 2 : 0) + k, row = m0 + lr;
+                    const double c = (256.0 * (double)hi + (double)lo) + (s_t[lr] - cs);
+                    turn[lr * TP + lc] = (float)(c * (double)z.sc);
+                    if (p.acc && row < p.rows && col < p.cols) ((int64_t *)p.acc)[(int64_t)row * p.cols + col] = (int64_t)c;
+                }
+            }
+        }
+        __syncthreads();
+        if (p.out) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = u * DT + tid, lr = e / (COLS / 4), lc = e % (COLS / 4) * 4, row = m0 + lr, col = n0 + lc;   // cols is a multiple of 8
+                if (row < p.rows && col < p.cols) {
+                    const float4 v = *reinterpret_cast<const float4 *>(&turn[lr * TP + lc]);
+                    float *d = p.out + (int64_t)row * p.cols + col;
+                    if (p.vec) {
+                        *reinterpret_cast<float4 *>(d) = v;
+                    } else {
+                        d[0] = v.x;
+                        d[1] = v.y;
+                        d[2] = v.z;
+                        d[3] = v.w;
+                    }
+                }
+            }
+        }
+    }
+}
+
 constexpr int kMaxRed = 65536;   // |a*b| <= 2^14 per product of two signed bytes: partial sums stay below 2^31
 
 struct Plan {
@@ -774,6 +1018,21 @@ Plan plan_for(int which, int M, int N, int K)
     return p;
 }
 
+// fc_dma: 16-byte pieces that lie whole inside or outside of the operands, at 16-byte addresses, and tiles for half the compute
+// units.  us, fc_dma / the kernel that plan_for names: forward, 104 tiles over 2816 21.4 / 28.8, 114 over 576 10.5 / 10.9, 80 over
+// 2528 19.8 / 24.2, 68 over 3248 27.9 / 29.0, 90 over 128 7.9 / 7.3, 63 over 544 9.9 / 7.2; layer gradient 96 over 688 10.9 / 10.3, 100
+// over 1936 17.3 / 20.1; weight gradient (tiles of 64 columns) 130 over 1584 15.8 / 24.8, 118 over 1328 14.1 / 15.0, 65 over 1136
+// 12.5 / 11.3.  Results narrower than three quarters of a tile stay away: they would multiply zeros.
+bool dma_wanted(int which, const FcArgs &p)
+{
+    const int bytes = which == 2 ? 2 : 1, cols = 128 / bytes;
+    if (!(q8t_aligned(p.a, 16) && q8t_aligned(p.b, 16) && p.lda % 16 == 0 && p.ldb * bytes % 16 == 0)) return false;
+    if (p.red < 64 || p.rows < 96 || p.cols < cols * 3 / 4) return false;
+    const int64_t tiles = (int64_t)((p.rows + 127) / 128) * ((p.cols + cols - 1) / cols);
+    if (tiles >= (1 << 24)) return false;   // a launch holds fewer than 2^32 threads
+    return which == 2 ? tiles >= 112 : tiles >= 128 || (tiles >= 80 && p.red >= 1024);
+}
+
 }  // namespace
 
 // sizes the kernels above take: whole groups of four columns (rows) and one 16-entry piece of the reduction exist
@@ -817,6 +1076,18 @@ int q8t_fc(int which, const void *a, const q8t_qparams *qa, const void *b, const
     p.vec = p.cols % 4 == 0 && q8t_aligned(out_f, 16);
     p.tn = pl.tn;
     p.tiles = (int)pl.tiles;
+    if (dma_wanted(which, p)) {
+        const int cols = which == 2 ? 64 : 128;
+        p.tn = (p.cols + cols - 1) / cols;
+        p.tiles = (p.rows + 127) / 128 * p.tn;
+        const dim3 grid(q8t_gemm::xcd_grid(p.tiles));
+        constexpr size_t lds = 4 * DTILE;
+        if (which == 0) hipLaunchKernelGGL(fc_dma<FWD>, grid, dim3(DT), lds, st, p);
+        else if (which == 1) hipLaunchKernelGGL(fc_dma<DGRAD>, grid, dim3(DT), lds, st, p);
+        else hipLaunchKernelGGL(fc_dma<WGRAD>, grid, dim3(DT), lds, st, p);
+        Q8T_LAUNCH_CHECK();
+        return Q8T_OK;
+    }
     if (pl.tile) {
         const dim3 grid(q8t_gemm::xcd_grid(pl.tiles));
         if (which == 0) hipLaunchKernelGGL(fc_tile<FWD>, grid, dim3(TT), 0, st, p);

@@ -101,3 +101,32 @@ def test_fc_split_needs_its_workspace():
         q8t.binding._check(q8t.binding._lib.q8t_qgemm_fwd(x.data_ptr(), px.data_ptr(), w.data_ptr(), px.data_ptr(), 8, 8, 8192,
                                                           x.data_ptr(), None, None, 0), "q8t_qgemm_fwd")
     assert e.value.code == -5
+
+
+# tiles that go to LDS without registers: rows of whole 16-byte pieces, many tiles; the reduction in one step, in whole steps,
+# with a tail of one or several pieces (forward: of both operands; otherwise any length along slow indices), rows and columns
+# that end inside a tile, the first sizes that go this way, and neighbours that do not
+@pytest.mark.parametrize("which,R,Cc,red", [
+    ("fwd", 1409, 1424, 80), ("fwd", 1409, 1424, 128), ("fwd", 1537, 1296, 144), ("fwd", 1409, 1424, 1040), ("fwd", 4000, 400, 272),
+    ("fwd", 1025, 1152, 1024), ("fwd", 1025, 1152, 1008), ("fwd", 16384, 96, 64), ("fwd", 16384, 80, 64),
+    ("dgrad", 1409, 1413, 80), ("dgrad", 1537, 1283, 256), ("dgrad", 1409, 1411, 400), ("dgrad", 100, 16390, 64), ("dgrad", 129, 8193, 1040),
+    ("wgrad", 1424, 1000, 64), ("wgrad", 1040, 808, 127), ("wgrad", 1040, 808, 128), ("wgrad", 1536, 776, 129), ("wgrad", 1424, 584, 300),
+    ("wgrad", 112, 7168, 1027), ("wgrad", 16400, 48, 65),
+])
+def test_fc_copied_tiles(which, R, Cc, red):
+    q8t = require_gpu()
+    g = synth.rng(R + 3 * Cc + red)
+    M, N, K = {"fwd": (R, Cc, red), "dgrad": (R, red, Cc), "wgrad": (red, Cc, R)}[which]
+    if which == "fwd":
+        (sa, pa), (sb, pb) = _rand_q(g, (M, K)), _rand_q(g, (K, N))
+        out, want = q8t.qgemm_fwd, oracle.qgemm_fwd
+    elif which == "dgrad":
+        (sa, pa), (sb, pb) = _rand_q(g, (M, N)), _rand_q(g, (K, N))
+        out, want = q8t.qgemm_dgrad, oracle.qgemm_dgrad
+    else:
+        (sa, pa), (sb, pb) = _rand_q(g, (M, K)), _rand_q(g, (M, N), bits=16)
+        out, want = q8t.qgemm_wgrad, oracle.qgemm_wgrad
+    y, acc = out(dev(sa), qp_dev_from(pa), dev(sb), qp_dev_from(pb), want_acc=True)
+    oy, oacc = want(sa, pa, sb, pb)
+    same_ints(host(acc), oacc)
+    same_ints(host(y), oy)
