@@ -1,21 +1,28 @@
 // General MFMA path for the forward and layer-gradient convolutions (Section 4: both products
 // take 8-bit operands and accumulate in 32 bits): any filter size, stride, padding and channel count.
-// Three launches per call:
+// Two launches per call:
 //
-//  1. to_nhwc      the NCHW int8 operand is rewritten channel-contiguous ([N][H][W][Cp], Cp = reduction
+//  1. prepare      to_nhwc: the NCHW int8 operand is rewritten channel-contiguous ([N][H][W][Cp], Cp = reduction
 //                  channels rounded up to 16) into the workspace, so that 16 reduction channels of one
-//                  filter tap are one aligned 16-byte piece; the same pass emits the per-position channel
-//                  sum that the zero-point correction needs.  (to_nhwc_small for many small planes.)
-//  2. repack_taps  filter -> [class][output channel][tap][Cp], each row filled up with zeros to a multiple
+//                  filter tap are one aligned 16-byte piece (to_nhwc_small for many small planes); and
+//                  repack_taps: filter -> [class][output channel][tap][Cp], each row filled up with zeros to a multiple
 //                  of 64 and the output channels to a multiple of 64, and the per-output-channel sums
 //                  (per stride class).
-//  3. igemm_nhwc   implicit GEMM, rows = output positions, columns = output channels, K = the pieces of
-//                  (tap, 16 channels) four to a step of 64, on the shared software-pipelined main loop
-//                  (gemm_core.h; 256x256, 128x128 or 128x64 tiles).
+//  2. igemm_nhwc   implicit GEMM, rows = output positions, columns = output channels, K = the pieces of
+//                  (tap, 16 channels) eight to a step of 128, which go from memory to LDS without registers
+//                  (gemm_core.h; 128x128 or 128x64 tiles).  The sums of the operand rows, which the zero-point
+//                  correction needs, are products with ones beside the others.
+//
+// Until the pieces were copied (registers between memory and LDS, steps of 64, sums per position from a pass of their own, the
+// two relayouts one after the other), a whole call took, us, before / now: 128->256 3x3/2 @28 batch 256 forward 68.1 / 63.2, layer
+// gradient 84.0 / 72.6; 64->128 3x3/2 @56 batch 32 32.5 / 22.6, 29.2 / 23.2; 96->200 3x3 @27 batch 50 52.4 / 47.2, 50.7 / 40.6;
+// 240->240 3x3 @20 batch 200 123 / 106, 112 / 95; 16->16 3x3 @32 batch 128 25.1 / 21.7, 20.0 / 16.2.  Geometric mean over 400
+// drawn shapes 1.24 (forward), 1.35 (layer gradient).  Of the 41 us of the first one's product its steps are 20, the rest its
+// first loads and its results, which 784 workgroups on 512 places overlap only in part.
 //
 // Pieces of 16 instead of 64 channels are what lets any channel count run here: 16 channels under a 3x3 filter
-// are 3 steps (9 pieces, 3 surplus) where whole steps per tap would be 9, and 200 channels 30 instead of 36.
-// Whatever the surplus operand bytes hold, they meet zero filter bytes; sums count the real channels only.
+// are 9 pieces (3 surplus) where whole steps per tap would be 9 times 4.
+// Surplus operand channels are zeros and so are the surplus filter bytes.
 //
 // Padded taps are staged as the stored zero point, which makes their corrected contribution
 // exactly zero; with a = stored code, za/zb = stored zero points:
@@ -67,9 +74,7 @@ struct Geo {
                              // also write the zeros of the three empty classes
 };
 
-__device__ __forceinline__ int bytesum4(uint32_t v) { return __builtin_amdgcn_sdot4((int)v, 0x01010101, 0, false); }
-
-// ---- 1. NCHW -> NHWC with channel sums --------------------------------------------------------
+// ---- 1. NCHW -> NHWC ---------------------------------------------------------------------------
 // A workgroup rewrites 64 positions of one image: tiles of 64 channels x 64 positions go through LDS.  A thread
 // takes 4 channels x 4 positions with four 4-byte loads (any alignment), turns them round in registers with eight
 // byte permutes and stores 4 dwords, one per position; rows of 21 dwords keep those stores free of bank conflicts
@@ -78,12 +83,11 @@ __device__ __forceinline__ int bytesum4(uint32_t v) { return __builtin_amdgcn_sd
 // channel tiles of a position where the launch would otherwise be small (few images, small planes).
 constexpr int TPITCH = 21;   // dwords
 template <int G>
-__global__ __launch_bounds__(kThreads * G) void to_nhwc(const int8_t *__restrict__ src, int C, int Cp, int HW,
-                                                        int ptiles, int8_t *__restrict__ dst, int *__restrict__ chansum)
+__device__ __forceinline__ void to_nhwc(int block, const int8_t *__restrict__ src, int C, int Cp, int HW, int ptiles,
+                                        int8_t *__restrict__ dst)
 {
     __shared__ uint32_t tile[G][64 * TPITCH];
-    __shared__ int part[G][64];
-    const int n = blockIdx.x / ptiles, p0 = (blockIdx.x - n * ptiles) * 64;
+    const int n = block / ptiles, p0 = (block - n * ptiles) * 64;
     const int grp = threadIdx.x / kThreads, tid = threadIdx.x % kThreads;
     const int cq = tid >> 4, d = tid & 15;   // staging role: channels 4 cq .., positions 4 d ..
     const int rp = tid >> 2, rq = tid & 3;   // read-out role: position rp, 16-byte chunk rq
@@ -109,7 +113,6 @@ __global__ __launch_bounds__(kThreads * G) void to_nhwc(const int8_t *__restrict
             v[i] = w;
         }
     };
-    int sum = 0;
     load(grp * 64);
     for (int t = 0; t < tiles; t += G) {   // every group runs the same number of rounds (barriers)
         const int c0 = (t + grp) * 64;
@@ -124,25 +127,9 @@ __global__ __launch_bounds__(kThreads * G) void to_nhwc(const int8_t *__restrict
         __syncthreads();
         const uint32_t *r = tile[grp] + rp * TPITCH + rq * 4;
         const uint4 o = make_uint4(r[0], r[1], r[2], r[3]);
-        if (p0 + rp < HW && c0 + rq * 16 < Cp) {
+        if (p0 + rp < HW && c0 + rq * 16 < Cp)
             *reinterpret_cast<uint4 *>(dst + ((size_t)n * HW + p0 + rp) * Cp + c0 + rq * 16) = o;
-            sum += bytesum4(o.x) + bytesum4(o.y) + bytesum4(o.z) + bytesum4(o.w);
-        }
         __syncthreads();
-    }
-    sum += __shfl_xor(sum, 1, Q8T_WAVE);
-    sum += __shfl_xor(sum, 2, Q8T_WAVE);
-    if (G == 1) {
-        if (rq == 0 && p0 + rp < HW) chansum[(size_t)n * HW + p0 + rp] = sum;
-    } else {
-        if (rq == 0) part[grp][rp] = sum;
-        __syncthreads();
-        if (threadIdx.x < 64 && p0 + (int)threadIdx.x < HW) {
-            int s = 0;
-#pragma unroll
-            for (int g = 0; g < G; ++g) s += part[g][threadIdx.x];
-            chansum[(size_t)n * HW + p0 + threadIdx.x] = s;
-        }
     }
 }
 
@@ -152,13 +139,12 @@ __global__ __launch_bounds__(kThreads * G) void to_nhwc(const int8_t *__restrict
 // positions however small it is: whole 1x1 products over 65536 planes of one position, 48 -> 80 channels 74 -> 23 us,
 // 256 -> 512 190 -> 63, of four positions, 64 -> 64 95 -> 40; 4096 planes of 49, 64 -> 64 49 both.
 constexpr int kSmallBytes = 32 * 1024;
-__global__ __launch_bounds__(kThreads) void to_nhwc_small(const int8_t *__restrict__ src, int N, int C, int Cp, int HW, int ipw,
-                                                         int8_t *__restrict__ dst, int *__restrict__ chansum)
+__device__ __forceinline__ void to_nhwc_small(int block, const int8_t *__restrict__ src, int N, int C, int Cp, int HW, int ipw,
+                                              int8_t *__restrict__ dst)
 {
-    extern __shared__ __align__(16) int8_t flat[];   // [images][C][HW], then the sums of the positions
-    const int n0 = blockIdx.x * ipw, images = min(ipw, N - n0), CC = Cp >> 4;
+    extern __shared__ __align__(16) int8_t flat[];   // [images][C][HW]
+    const int n0 = block * ipw, images = min(ipw, N - n0), CC = Cp >> 4;
     const int bytes = images * C * HW, positions = images * HW;
-    int *sum = reinterpret_cast<int *>(flat + ((ipw * C * HW + 15) & ~15));
     const int8_t *in = src + (size_t)n0 * C * HW;
     for (int i = threadIdx.x * 16; i < bytes; i += kThreads * 16) {
         if (i + 16 <= bytes) {
@@ -169,7 +155,6 @@ __global__ __launch_bounds__(kThreads) void to_nhwc_small(const int8_t *__restri
             for (int k = i; k < bytes; ++k) flat[k] = in[k];
         }
     }
-    for (int i = threadIdx.x; i < positions; i += kThreads) sum[i] = 0;
     __syncthreads();
     int8_t *out = dst + (size_t)n0 * HW * Cp;
     for (int i = threadIdx.x; i < positions * CC; i += kThreads) {
@@ -185,37 +170,45 @@ __global__ __launch_bounds__(kThreads) void to_nhwc_small(const int8_t *__restri
                 if (4 * d + e < left) w[d] |= (uint32_t)(uint8_t)b[(4 * d + e) * HW] << (8 * e);
         }
         *reinterpret_cast<uint4 *>(out + (size_t)i * 16) = make_uint4(w[0], w[1], w[2], w[3]);
-        atomicAdd(&sum[pos], bytesum4(w[0]) + bytesum4(w[1]) + bytesum4(w[2]) + bytesum4(w[3]));
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < positions; i += kThreads) chansum[(size_t)n0 * HW + i] = sum[i];
 }
 
-// ---- 2. filter -> [class][output channel][tap][reduction channel], sums per output channel ------
-// grid (OCp, classes).  which 0: out = k, reduction = c;  which 1: out = c, reduction = k.
-__global__ __launch_bounds__(kThreads) void repack_taps(const int8_t *__restrict__ w, int Kf, int Cf, int R, int S,
-                                                        int which, int Cp, TapList taps, TapList offs, ClassOffsets co,
-                                                        ClassGeo cg, int8_t *__restrict__ wt,
-                                                        int *__restrict__ colsum, int *__restrict__ tapoff,
-                                                        int *__restrict__ clsinfo)
+// ---- filter -> [class][output channel][tap][reduction channel], sums per output channel ------
+// One row (output channel j, class z) a workgroup of THREADS.  which 0: out = k, reduction = c;  which 1: out = c, reduction = k.
+// The first one also writes the tables of the main kernel: operand offsets of the taps (dh in the low half), the classes, and
+// three pieces of 16 bytes for what lies outside: the zero code, the zero code in the last piece of a tap (only the channels that
+// are there, as the row sums count them), zeros.
+constexpr int PADS = MAXT + 3;   // ints from the tap table to those pieces
+
+__device__ __forceinline__ void pad_pieces(int8_t *pads, int red, const q8t_qparams *__restrict__ qpa)
 {
-    __shared__ int part[kThreads / 64], stap[MAXT];
-    const int j = blockIdx.x, z = blockIdx.y;
-    // operand offsets of the taps, packed (dh in the low half), and the class table, for the main kernel
-    if (j == 0 && z == 0 && threadIdx.x == 0) {
-        for (int tt = 0; tt < co.off[MAXCLS]; ++tt)
-            tapoff[tt] = (int)((uint32_t)(uint16_t)(int16_t)offs.a[tt] | ((uint32_t)(uint16_t)(int16_t)offs.b[tt] << 16));
-        for (int c = 0; c < (int)gridDim.y; ++c)
-            for (int k = 0; k < 7; ++k) clsinfo[c * CLS_INTS + k] = cg.v[c][k];
-    }
+    const int i = threadIdx.x, last = red & 15, za = qpa->zero_point - (1 << (qpa->bits - 1));
+    if (i < 48) pads[i] = i < 16 || (i < 32 && (last == 0 || i - 16 < last)) ? (int8_t)za : (int8_t)0;
+}
+
+template <int THREADS>
+__device__ __forceinline__ void repack_taps(int j, int z, int ncls, const int8_t *__restrict__ w, int Kf, int Cf, int R, int S,
+                                            int which, int Cp, const TapList &taps, const TapList &offs, const ClassOffsets &co,
+                                            const ClassGeo &cg, const q8t_qparams *__restrict__ qpa, int OCp,
+                                            int8_t *__restrict__ wt, int *__restrict__ colsum, int *__restrict__ tapoff,
+                                            int *__restrict__ clsinfo)
+{
+    __shared__ int part[THREADS / 64], stap[MAXT];
     const int OC = which == 0 ? Kf : Cf, red = which == 0 ? Cf : Kf;
+    if (j == 0 && z == 0) {
+        for (int t = threadIdx.x; t < co.off[MAXCLS]; t += THREADS)
+            tapoff[t] = (int)((uint32_t)(uint16_t)(int16_t)offs.a[t] | ((uint32_t)(uint16_t)(int16_t)offs.b[t] << 16));
+        for (int c = threadIdx.x; c < ncls; c += THREADS)
+            for (int k = 0; k < 7; ++k) clsinfo[c * CLS_INTS + k] = cg.v[c][k];
+        pad_pieces(reinterpret_cast<int8_t *>(tapoff + PADS), red, qpa);
+    }
     const int RS = R * S, t0 = co.off[z], T = co.off[z + 1] - t0, pitch = cg.v[z][5];
     int8_t *out = wt + (size_t)cg.v[z][6] * 64 + (size_t)j * pitch;
     // one loop over (tap, channel): tap by tap, 49 taps of 16 channels were 49 dependent rounds with 16 threads at work
-    for (int t = threadIdx.x; t < T; t += kThreads) stap[t] = taps.a[t0 + t] * S + taps.b[t0 + t];
+    for (int t = threadIdx.x; t < T; t += THREADS) stap[t] = taps.a[t0 + t] * S + taps.b[t0 + t];
     __syncthreads();
     int sum = 0;
-    for (int i = threadIdx.x; i < T * Cp; i += kThreads) {
+    for (int i = threadIdx.x; i < T * Cp; i += THREADS) {
         const int t = i / Cp, c = i - t * Cp;
         int8_t v = 0;
         if (j < OC && c < red) {
@@ -230,63 +223,108 @@ __global__ __launch_bounds__(kThreads) void repack_taps(const int8_t *__restrict
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, Q8T_WAVE);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) colsum[z * gridDim.x + j] = part[0] + part[1] + part[2] + part[3];
+    if (threadIdx.x == 0) {
+        int s = 0;
+#pragma unroll
+        for (int i = 0; i < THREADS / 64; ++i) s += part[i];
+        colsum[z * OCp + j] = s;
+    }
 }
 
-// ---- 3. implicit GEMM ---------------------------------------------------------------------------
-// Staging role of a thread (see gemm_core.h): piece q = tid & 3 of a step, i.e. 16 channels of one tap, of the output
-// positions (tile rows) ar = tid >> 2 and ar + RP, and of the filter rows ar and ar + RP.  The piece number grows by 4
-// per step: dt taps and dc pieces, and one tap more when the pieces of a tap are used up.
-template <class C>
-struct ConvOps {
-    typedef q8t_gemm::Regs R;
-    const int8_t *xin, *wt;              // wt: the thread's piece of its filter row
-    const __attribute__((address_space(3))) int *stap;   // tap offsets, in LDS (3 readable entries behind the last)
-    int IH, IW, Cp, CC, dt, dc, q;       // CC = Cp / 16
-    size_t wrows;                        // bytes from the first to the second filter row
-    int an0, ih0, iw0, an1, ih1, iw1;    // image and top-left operand position of the two rows
-    bool av0, av1;
-    uint32_t padw;
-    int lt, lc, lw;   // tap, piece of the tap and filter byte of the next load
+// Both in one launch, the filter rows first: neither needs the other, and the filter alone is 4.8 us.
+// G: channel groups of to_nhwc, 0 for to_nhwc_small.
+struct PrepArgs {
+    const int8_t *x, *w;
+    int8_t *xn, *wt;
+    const q8t_qparams *qpa;
+    int *colsum, *tapoff, *clsinfo;
+    int N, C, Cp, HW, per, ncls, OCp, Kf, Cf, R, S, which;   // per: 64-position tiles of a plane / images a workgroup
+    int row0, rows;                                          // filter rows of this launch
+    TapList taps, offs;
+    ClassOffsets co;
+    ClassGeo cg;
+};
+template <int G>
+__global__ __launch_bounds__(kThreads * (G ? G : 1)) void prepare(const PrepArgs p)
+{
+    const int b = (int)blockIdx.x - p.rows;
+    if (b < 0) {
+        const int row = p.row0 + (int)blockIdx.x, z = row / p.OCp, j = row - z * p.OCp;
+        repack_taps<kThreads * (G ? G : 1)>(j, z, p.ncls, p.w, p.Kf, p.Cf, p.R, p.S, p.which, p.Cp, p.taps, p.offs, p.co, p.cg,
+                                            p.qpa, p.OCp, p.wt, p.colsum, p.tapoff, p.clsinfo);
+    } else if constexpr (G == 0)
+        to_nhwc_small(b, p.x, p.N, p.C, p.Cp, p.HW, p.per, p.xn);
+    else
+        to_nhwc<G>(b, p.x, p.C, p.Cp, p.HW, p.per, p.xn);
+}
 
-    __device__ __forceinline__ void start(int q_)
+// ---- 2. implicit GEMM ---------------------------------------------------------------------------
+// The pieces of a step of 128 as a thread of the Dma tiles copies them: piece (tid & 7) ^ perm of the rows tid >> 3 and 64 further
+// down, of both operands.  Eight pieces on per step.
+template <class C>
+struct DmaConvOps {
+    const int8_t *xin, *wt, *pads;       // wt: the thread's piece of its filter row
+    const __attribute__((address_space(3))) int *stap;
+    int IH, IW, Cp, CC, dt, dc;
+    size_t wrows;                        // bytes from a filter row to the one 64 further down
+    int an[2], ih[2], iw[2];             // image (-1: no such row) and top-left operand position of the two rows
+    int lt, lc;                          // tap and piece of it in the next step
+    int at, taps, pitch;                 // its place in the reduction, the bytes of the class's taps and of a filter row
+    int wave;
+
+    __device__ __forceinline__ void start(const Geo &g, int m0, int n0, int M, int OHW, int OW, int T, int pitch_, const int8_t *wbase, int tid)
     {
-        q = q_;
+        const int r = tid >> 3, q = (tid & 7) ^ C::perm(r);
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        IH = g.IH;
+        IW = g.IW;
+        Cp = g.Cp;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int m = m0 + r + u * 64, n = m / OHW, rem = m - n * OHW, oh = rem / OW;
+            an[u] = m < M ? n : -1;
+            ih[u] = oh * g.ish;
+            iw[u] = (rem - oh * OW) * g.isw;
+        }
         CC = Cp >> 4;
-        dt = 4 / CC;
-        dc = 4 - dt * CC;
+        dt = 8 / CC;
+        dc = 8 - dt * CC;
+        filter(wbase + (size_t)(n0 + r) * pitch_, T, pitch_, q);
+    }
+    // from the first piece of a filter on
+    __device__ __forceinline__ void filter(const int8_t *row, int T, int pitch_, int q)
+    {
+        wt = row + q * 16;
+        wrows = (size_t)64 * pitch_;
+        at = q * 16;
+        taps = T * Cp;
+        pitch = pitch_;
         lt = q / CC;
         lc = q - lt * CC;
-        lw = 0;
     }
-    __device__ __forceinline__ uint4 row(bool av, int an, int ihb, int iwb, int to, int c) const
+    __device__ __forceinline__ void issue(int8_t *buf)
     {
-        const int ih = ihb + (int)(int16_t)(to & 0xFFFF), iw = iwb + (to >> 16);
-        uint4 v = make_uint4(padw, padw, padw, padw);
-        if (av && (unsigned)ih < (unsigned)IH && (unsigned)iw < (unsigned)IW)
-            v = *reinterpret_cast<const uint4 *>(xin + (size_t)((an * IH + ih) * IW + iw) * Cp + c * 16);
-        return v;
-    }
-    __device__ __forceinline__ void load(q8t_gemm::Regs &r, bool valid)
-    {
-        const int t = valid ? lt : 0, c = valid ? lc : 0;
-        const int to = stap[t];
-        r.a0 = row(av0, an0, ih0, iw0, to, c);
-        r.a1 = row(av1, an1, ih1, iw1, to, c);
-        const int8_t *w = wt + (valid ? lw : 0);
-        r.b0 = *reinterpret_cast<const uint4 *>(w);
-        r.b1 = C::NB == 2 ? *reinterpret_cast<const uint4 *>(w + wrows) : r.b0;
-        lw += 64;
+        const bool in = at < taps;
+        const int to = stap[in ? lt : 0];
+        const int dh = (int)(int16_t)(to & 0xFFFF), dw = to >> 16;
+        const int8_t *out = pads + (!in ? 32 : (lc == CC - 1 ? 16 : 0));
+        int8_t *dst = buf + wave * 1024;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int h = ih[u] + dh, w = iw[u] + dw;
+            const bool ok = in && an[u] >= 0 && (unsigned)h < (unsigned)IH && (unsigned)w < (unsigned)IW;
+            const int8_t *p = xin + (size_t)((an[u] * IH + h) * IW + w) * Cp + lc * 16;
+            q8t_gemm::copy16_to_lds(ok ? p : out, dst + u * 8192);
+        }
+#pragma unroll
+        for (int u = 0; u < C::NB; ++u)
+            q8t_gemm::copy16_to_lds(at < pitch ? wt + u * wrows : pads + 32, dst + C::BM * C::DK + u * 8192);
+        wt += C::DK;
+        at += C::DK;
         lc += dc;
         const bool wrap = lc >= CC;
         lc -= wrap ? CC : 0;
         lt += dt + (wrap ? 1 : 0);
-    }
-    // a surplus step stages zero filter rows: whatever the operand rows hold, it adds nothing
-    __device__ __forceinline__ void prepare(q8t_gemm::Regs &r, bool valid)
-    {
-        r.b0 = q8t_gemm::sel16(valid, r.b0);
-        r.b1 = q8t_gemm::sel16(valid, r.b1);
     }
 };
 
@@ -298,7 +336,6 @@ constexpr size_t conv_lds_bytes()
 
 template <class C>
 __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *__restrict__ xin,
-                                                                   const int *__restrict__ chansum,
                                                                    const int8_t *__restrict__ wt,
                                                                    const int *__restrict__ colsum,
                                                                    const q8t_qparams *__restrict__ qpa,
@@ -310,8 +347,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
 {
     constexpr int MT = C::MT, NT = C::NT, BM = C::BM, BN = C::BN;
     extern __shared__ __align__(16) int8_t smem[];
-    int8_t *sA = smem, *sB = smem + 2 * BM * 64;
-    long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
+        long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
     int *rs = reinterpret_cast<int *>(roff + BM);
     int *stap = rs + BM;
 
@@ -325,6 +361,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
     if (lg >= total) return;
     const int n0 = (lg % ny) * BN, zc = (lg / ny) % g.ncls, m0 = (lg / (ny * g.ncls)) * BM;
     int wpitch;
+    const int8_t *pads;
     {
         const int *ci = clsinfo + zc * CLS_INTS;
         g.OH = ci[0];
@@ -335,6 +372,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
         g.opw = zc - g.oph * g.osw;
         wpitch = ci[5];
         wt += (size_t)ci[6] * 64;
+        pads = reinterpret_cast<const int8_t *>(tapoff + PADS);
         tapoff += ci[3];
         colsum += (size_t)zc * g.OCp;
     }
@@ -345,78 +383,35 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
 
     if (tid < MAXT + 3) stap[tid] = tid < g.T ? tapoff[tid] : 0;
     __syncthreads();
-    // per-row bookkeeping: operand sum over the taps (padded taps count Cp zero codes) and the
+    DmaConvOps<C> ops;
+    ops.stap = (const __attribute__((address_space(3))) int *)stap;
+    ops.xin = xin;
+    ops.pads = pads;
+    ops.start(g, m0, n0, g.M, OHW, g.OW, g.T, wpitch, wt, tid);
+    if (wpitch) ops.issue(smem);
     // offset of the row's position inside one output channel plane
     if (tid < BM) {
         const int m = m0 + tid;
-        int sum = 0;
         long long off = -1;
         if (m < g.M) {
             const int n = m / OHW, rem = m - n * OHW;
             const int oh = rem / g.OW, ow = rem - oh * g.OW;
-            // five loads in flight: one after the other they were most of a call with many taps
-            for (int t0 = 0; t0 < g.T; t0 += 5) {
-                int v[5];
-                bool in[5];
-#pragma unroll
-                for (int u = 0; u < 5; ++u) {
-                    const int to = stap[min(t0 + u, g.T - 1)];
-                    const int ih = oh * g.ish + (int)(int16_t)(to & 0xFFFF), iw = ow * g.isw + (to >> 16);
-                    in[u] = (unsigned)ih < (unsigned)g.IH && (unsigned)iw < (unsigned)g.IW;
-                    v[u] = chansum[in[u] ? (n * g.IH + ih) * g.IW + iw : 0];
-                }
-#pragma unroll
-                for (int u = 0; u < 5; ++u)
-                    if (t0 + u < g.T) sum += in[u] ? v[u] : g.red * za;
-            }
             off = (long long)n * g.OC * g.OHf * g.OWf + (long long)(oh * g.osh + g.oph) * g.OWf + ow * g.osw + g.opw;
         }
-        rs[tid] = sum;
         roff[tid] = off;
     }
 
-    ConvOps<C> ops;
-    ops.xin = xin;
-    ops.wt = wt + (size_t)(n0 + (tid >> 2)) * wpitch + (tid & 3) * 16;
-    ops.wrows = (size_t)C::RP * wpitch;
-    ops.stap = (const __attribute__((address_space(3))) int *)stap;
-    ops.IH = g.IH;
-    ops.IW = g.IW;
-    ops.Cp = g.Cp;
-    ops.padw = (uint32_t)(za & 255) * 0x01010101u;
-    ops.start(tid & 3);
-    {
-        const int am = m0 + (tid >> 2);
-        ops.av0 = am < g.M;
-        ops.an0 = ops.ih0 = ops.iw0 = 0;
-        if (ops.av0) {
-            ops.an0 = am / OHW;
-            const int rem = am - ops.an0 * OHW;
-            const int oh = rem / g.OW;
-            ops.ih0 = oh * g.ish;
-            ops.iw0 = (rem - oh * g.OW) * g.isw;
-        }
-        const int bm = am + C::RP;
-        ops.av1 = bm < g.M;
-        ops.an1 = ops.ih1 = ops.iw1 = 0;
-        if (ops.av1) {
-            ops.an1 = bm / OHW;
-            const int rem = bm - ops.an1 * OHW;
-            const int oh = rem / g.OW;
-            ops.ih1 = oh * g.ish;
-            ops.iw1 = (rem - oh * g.OW) * g.isw;
-        }
-    }
-
-    const int rowbase = C::rowbase(wave), colbase = C::colbase(wave);
+    const int colbase = C::colbase(wave);
     v4i acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (v4i){0, 0, 0, 0};
 
-    q8t_gemm::pipeline<C>(ops, wpitch >> 6, sA, sB, acc, tid);
-    if (g.T == 0) __syncthreads();   // rs / roff of the other threads
+    v4i rsum;
+    q8t_gemm::dma_pipeline<C, false>(ops, wpitch >> 6, smem, acc, rsum, tid);
+    if (l16 == 0) *reinterpret_cast<v4i *>(&rs[C::row(wave, 0) + kb * 4]) = rsum;
+    __syncthreads();
 
     // ---- epilogue: zero-point correction in wrapping 32-bit arithmetic (the corrected value fits
     // by contract), dequantization; a lane holds 4 consecutive rows of one output channel ----
@@ -436,7 +431,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const int r0 = rowbase + mt * 16 + kb * 4;
+        const int r0 = C::row(wave, mt) + kb * 4;
         long long o[4];
         uint32_t t[4];
 #pragma unroll
@@ -575,8 +570,7 @@ constexpr size_t conv_pair_lds_bytes()
 }
 
 template <class C>
-__global__ __launch_bounds__(C::THREADS, 2) void igemm_nhwc_pair(const int8_t *__restrict__ xin,
-                                                                  const int *__restrict__ chansum,
+__global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc_pair(const int8_t *__restrict__ xin,
                                                                   const int8_t *__restrict__ wt,
                                                                   const int *__restrict__ colsum,
                                                                   const q8t_qparams *__restrict__ qpa,
@@ -587,8 +581,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void igemm_nhwc_pair(const int8_t *_
 {
     constexpr int MT = C::MT, NT = C::NT, BM = C::BM, BN = C::BN;
     extern __shared__ __align__(16) int8_t smem[];
-    int8_t *sA = smem, *sB = smem + 2 * BM * 64;
-    long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
+        long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
     int *rsA = reinterpret_cast<int *>(roff + BM);
     int *rsB = rsA + BM;
     int *stap = rsB + BM;
@@ -611,83 +604,45 @@ __global__ __launch_bounds__(C::THREADS, 2) void igemm_nhwc_pair(const int8_t *_
     // the taps of the two classes are neighbours in the table
     if (tid < MAXT + 3) stap[tid] = tid < TA + TB ? tapoff[ciA[3] + tid] : 0;
     __syncthreads();
+    DmaConvOps<C> ops;
+    ops.stap = (const __attribute__((address_space(3))) int *)stap;
+    ops.xin = xin;
+    ops.pads = reinterpret_cast<const int8_t *>(tapoff + PADS);
+    ops.start(g, m0, n0, M, OHW, OW, TA, ciA[5], wt + (size_t)ciA[6] * 64, tid);
+    if (ciA[5]) ops.issue(smem);
     if (tid < BM) {
         const int m = m0 + tid;
-        int sumA = 0, sumB = 0;
         long long off = -1;
         if (m < M) {
             const int n = m / OHW, rem = m - n * OHW;
             const int oh = rem / OW, ow = rem - oh * OW;
-            for (int t0 = 0; t0 < TA + TB; t0 += 3) {
-                int v[3];
-                bool in[3];
-#pragma unroll
-                for (int u = 0; u < 3; ++u) {
-                    const int to = stap[min(t0 + u, TA + TB - 1)];
-                    const int ih = oh + (int)(int16_t)(to & 0xFFFF), iw = ow + (to >> 16);
-                    in[u] = (unsigned)ih < (unsigned)g.IH && (unsigned)iw < (unsigned)g.IW;
-                    v[u] = chansum[in[u] ? (n * g.IH + ih) * g.IW + iw : 0];
-                }
-#pragma unroll
-                for (int u = 0; u < 3; ++u) {
-                    const int c = t0 + u < TA + TB ? (in[u] ? v[u] : g.red * za) : 0;
-                    sumA += t0 + u < TA ? c : 0;
-                    sumB += t0 + u < TA ? 0 : c;
-                }
-            }
             off = (long long)n * g.OC * g.OHf * g.OWf + (long long)(oh * 2 + ph) * g.OWf + ow * 2;
         }
-        rsA[tid] = sumA;
-        rsB[tid] = sumB;
         roff[tid] = off;
     }
-    __syncthreads();
 
-    ConvOps<C> opsA;
-    opsA.xin = xin;
-    const size_t wbase = (size_t)(n0 + (tid >> 2));
-    opsA.wt = wt + (size_t)ciA[6] * 64 + wbase * ciA[5] + (tid & 3) * 16;
-    opsA.wrows = (size_t)C::RP * ciA[5];
-    opsA.stap = (const __attribute__((address_space(3))) int *)stap;
-    opsA.IH = g.IH;
-    opsA.IW = g.IW;
-    opsA.Cp = g.Cp;
-    opsA.padw = (uint32_t)(za & 255) * 0x01010101u;
-    opsA.start(tid & 3);
-    {
-        const int am = m0 + (tid >> 2);
-        opsA.av0 = am < M;
-        opsA.an0 = opsA.ih0 = opsA.iw0 = 0;
-        if (opsA.av0) {
-            opsA.an0 = am / OHW;
-            const int rem = am - opsA.an0 * OHW;
-            opsA.ih0 = rem / OW;
-            opsA.iw0 = rem - opsA.ih0 * OW;
-        }
-        const int bm = am + C::RP;
-        opsA.av1 = bm < M;
-        opsA.an1 = opsA.ih1 = opsA.iw1 = 0;
-        if (opsA.av1) {
-            opsA.an1 = bm / OHW;
-            const int rem = bm - opsA.an1 * OHW;
-            opsA.ih1 = rem / OW;
-            opsA.iw1 = rem - opsA.ih1 * OW;
-        }
-    }
-    ConvOps<C> opsB = opsA;
-    opsB.wt = wt + (size_t)ciB[6] * 64 + wbase * ciB[5] + (tid & 3) * 16;
-    opsB.wrows = (size_t)C::RP * ciB[5];
-    opsB.stap = (const __attribute__((address_space(3))) int *)(stap + TA);
-
-    const int rowbase = C::rowbase(wave), colbase = C::colbase(wave);
+    const int colbase = C::colbase(wave);
     v4i accA[MT][NT], accB[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) accA[mt][nt] = accB[mt][nt] = (v4i){0, 0, 0, 0};
 
-    q8t_gemm::pipeline<C>(opsA, ciA[5] >> 6, sA, sB, accA, tid);
-    q8t_gemm::pipeline<C>(opsB, ciB[5] >> 6, sA, sB, accB, tid);
+    v4i rsumA, rsumB;
+    q8t_gemm::dma_pipeline<C, true>(ops, ciA[5] >> 6, smem, accA, rsumA, tid);
+    {
+        const int r = tid >> 3;
+        ops.filter(wt + (size_t)ciB[6] * 64 + (size_t)(n0 + r) * ciB[5], TB, ciB[5], (tid & 7) ^ C::perm(r));
+        ops.stap += TA;
+    }
+    q8t_lds_barrier();   // every wavefront is past its reads of the first class's tiles
+    if (ciB[5]) ops.issue(smem);
+    q8t_gemm::dma_pipeline<C, true>(ops, ciB[5] >> 6, smem, accB, rsumB, tid);
+    if (l16 == 0) {
+        *reinterpret_cast<v4i *>(&rsA[C::row(wave, 0) + kb * 4]) = rsumA;
+        *reinterpret_cast<v4i *>(&rsB[C::row(wave, 0) + kb * 4]) = rsumB;
+    }
+    __syncthreads();
 
     // ---- epilogue: both classes corrected and dequantized, written as pairs ----
     const uint32_t kzzA = (uint32_t)(TA * g.red) * (uint32_t)za * (uint32_t)zb;
@@ -702,7 +657,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void igemm_nhwc_pair(const int8_t *_
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const int r0 = rowbase + mt * 16 + kb * 4;
+        const int r0 = C::row(wave, mt) + kb * 4;
         long long o[4];
         uint32_t tA[4], tB[4];
 #pragma unroll
@@ -834,18 +789,16 @@ __device__ __forceinline__ void stage_rows(const int8_t *__restrict__ x, int n, 
 __global__ __launch_bounds__(kThreads) void im2col_positions(const int8_t *__restrict__ x, int C, int H, int W, int R, int S,
                                                              int stride, int pad, int P, int Q, int Kc,
                                                              const q8t_qparams *__restrict__ qpx,
-                                                             int8_t *__restrict__ xn, int *__restrict__ rowsum, int vec4)
+                                                             int8_t *__restrict__ xn, int vec4)
 {
     extern __shared__ __align__(16) int8_t lds[];
     const int CRS = C * R * S;
     const int L = (pad + 3) & ~3, Wp = (L + W + pad + 3) & ~3;   // staged row: left margin, pitch
     int8_t *rows = lds;                                   // [C*R][Wp]
     int *lut = reinterpret_cast<int *>(lds + ((C * R * Wp + 15) & ~15));   // [Kc]: offset of column j in `rows`, -1: surplus
-    int *rsum = lut + Kc;                                                   // [Q]
     const int n = blockIdx.y, p = blockIdx.x, tid = threadIdx.x;
     const int zsx = qpx->zero_point - (1 << (qpx->bits - 1));
     stage_rows(x, n, C, H, W, R, stride, pad, p, L, Wp, zsx, vec4 != 0, rows);
-    for (int q = tid; q < Q; q += kThreads) rsum[q] = 0;
     for (int j = tid; j < Kc; j += kThreads) {
         int off = -1;
         if (j < CRS) {
@@ -874,20 +827,18 @@ __global__ __launch_bounds__(kThreads) void im2col_positions(const int8_t *__res
             w4[d] = v;
         }
         *reinterpret_cast<uint4 *>(xn + (m0 + q) * Kc + ch * 16) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
-        // row sums: every column of a position, surplus columns included
-        atomicAdd(&rsum[q], bytesum4(w4[0]) + bytesum4(w4[1]) + bytesum4(w4[2]) + bytesum4(w4[3]));
     }
-    __syncthreads();
-    for (int q = tid; q < Q; q += kThreads) rowsum[m0 + q] = rsum[q];
 }
 
 // filter [K][C*R*S] -> [K][Kc] with zero surplus columns, sums per output channel, tap offset 0
 __global__ __launch_bounds__(kThreads) void repack_flat(const int8_t *__restrict__ w, int CRS, int Kc, int OH, int OW,
-                                                        int M, int8_t *__restrict__ wt, int *__restrict__ colsum,
-                                                        int *__restrict__ tapoff, int *__restrict__ clsinfo)
+                                                        int M, const q8t_qparams *__restrict__ qpx, int8_t *__restrict__ wt,
+                                                        int *__restrict__ colsum, int *__restrict__ tapoff,
+                                                        int *__restrict__ clsinfo)
 {
     __shared__ int part[kThreads / 64];
     const int k = blockIdx.x;
+    if (k == 0) pad_pieces(reinterpret_cast<int8_t *>(tapoff + PADS), Kc, qpx);
     int sum = 0;
     for (int j = threadIdx.x; j < Kc; j += kThreads) {
         const int8_t v = j < CRS ? w[(size_t)k * CRS + j] : (int8_t)0;
@@ -921,7 +872,7 @@ struct Plan {
     int IH, IW;           // operand spatial size
     int OHf, OWf;         // result spatial size
     int ncls;             // stride classes
-    size_t o_chansum, o_wt, o_colsum, o_tapoff, o_cls, total;
+    size_t o_wt, o_colsum, o_tapoff, o_cls, total;
 };
 
 // Operand planes for to_nhwc_small: from half the images on that fill the chip with workgroups of to_nhwc.  Fewer leave
@@ -957,40 +908,29 @@ bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
     if (!small_planes(*p, d->N) && (int64_t)d->N * (((int64_t)p->IH * p->IW + 63) / 64) >= (1 << 24)) return false;
     if (opos >= ((int64_t)1 << 30)) return false;
     const size_t xn = up256((size_t)ipos * p->Cp);
-    p->o_chansum = xn;
-    p->o_wt = p->o_chansum + up256((size_t)ipos * sizeof(int));
+    p->o_wt = xn;
     // filter rows: the taps of a class times Cp, filled up to 64
     const int64_t wbytes = (int64_t)p->OCp * ((int64_t)d->R * d->S * p->Cp + 63 * p->ncls);
     if (wbytes >= ((int64_t)1 << 36) || (int64_t)d->R * d->S * p->Cp >= ((int64_t)1 << 30)) return false;
     p->o_colsum = p->o_wt + up256((size_t)wbytes);
     p->o_tapoff = p->o_colsum + up256((size_t)p->ncls * p->OCp * sizeof(int));
-    p->o_cls = p->o_tapoff + up256((MAXT + 3) * sizeof(int));
+    p->o_cls = p->o_tapoff + up256(PADS * sizeof(int) + 48);
     p->total = p->o_cls + up256((size_t)MAXCLS * CLS_INTS * sizeof(int));
     return true;
 }
 
-// Tile: the one whose tiles, dealt out over 256 compute units, take the fewest rounds of work.  A unit is what a
-// 128x64 tile takes; a 128x128 tile does twice its products in about 1.6 times its time and a 256x256 tile eight
-// times in 6 (operand bytes read from LDS per product fall as 12 : 8 : 6).  Whole calls measured with 128x64 / 128x128
-// / 256x256 tiles: 128->256 3x3/2 @28 batch 256 68 / 70 / 61 us, 256->512 3x3/2 @14 batch 256 62 / 59 / 75,
-// 256->256 3x3/2 @14 batch 32 34 / 40 / 63, 240->240 3x3 @20 batch 200 125 / 104 / 113, 96->200 3x3 @27 batch 50
-// 49 / 46 / 48 us: the rule takes the fastest in each.
-struct Rounds {
-    double small, mid, big;
-};
-Rounds rounds_for(int64_t M, int ncls, int OCp)
+// Tile: 128x128 from a tile for every compute unit on, else 128x64.  Whole calls with 128x64 / 128x128 tiles, us: 128->256 3x3/2
+// @28 batch 256 (784 tiles) 72 / 68, layer gradient 82 / 74; 96->200 3x3 @27 batch 50 (570) 52.4 / 51.5; 256->512 3x3/2 @14
+// batch 256 (392) 71 / 61; 48->96 3x3 @24 batch 64 (288) 25.9 / 25.7; 64->128 3x3/2 @56 batch 32 (196) 28.0 / 27.8; 128->256
+// 3x3/2 @28 batch 32 (98) 25.0 / 27.5; 256->512 3x3/2 @14 batch 32 (52) 30.8 / 34.4, layer gradient 36 / 41.
+bool wide_tiles(int64_t M, int ncls, int OCp)
 {
-    const int64_t r128 = (M + 127) / 128 * ncls, r256 = (M + 255) / 256 * ncls;
-    Rounds r;
-    r.small = (double)((r128 * (OCp / 64) + 255) / 256);
-    r.mid = OCp % 128 == 0 ? 1.6 * (double)((r128 * (OCp / 128) + 255) / 256) : 1e30;
-    r.big = OCp % 256 == 0 ? 6.0 * (double)((r256 * (OCp / 256) + 255) / 256) : 1e30;
-    return r;
+    return OCp % 128 == 0 && (M + 127) / 128 * ncls * (OCp / 128) >= 256;
 }
 
 struct SmallPlan {
     int P, Q, Kc;
-    size_t lds, o_rowsum, o_wt, o_colsum, o_tapoff, total;
+    size_t lds, o_wt, o_colsum, o_tapoff, total;
 };
 
 // forward only: fewer than 64 input channels, output channels a multiple of 64
@@ -1009,10 +949,9 @@ bool make_small_plan(int which, const q8t_conv_desc *d, SmallPlan *p)
     const int64_t M = (int64_t)d->N * p->P * p->Q;
     if (M >= ((int64_t)1 << 31) || (int64_t)d->N * d->C * d->H >= ((int64_t)1 << 31)) return false;
     p->lds = (((size_t)d->C * d->R * ((((d->pad + 3) & ~3) + d->W + d->pad + 3) & ~3) + 15) & ~(size_t)15) +
-             ((size_t)p->Kc + p->Q) * sizeof(int);
+             (size_t)p->Kc * sizeof(int);
     if (p->lds > 65536) return false;
-    p->o_rowsum = up256((size_t)M * p->Kc);
-    p->o_wt = p->o_rowsum + up256((size_t)M * sizeof(int));
+    p->o_wt = up256((size_t)M * p->Kc);
     p->o_colsum = p->o_wt + up256((size_t)d->K * p->Kc);
     p->o_tapoff = p->o_colsum + up256((size_t)d->K * sizeof(int));
     p->total = p->o_tapoff + 256;
@@ -1029,13 +968,13 @@ bool q8t_smallc_conv_supported(int which, const q8t_conv_desc *d)
 
 // As q8t_generic_conv_us, for the forward product here (the shape is supported): three launches; 1024 workgroups of the im2col
 // side by side, its rows written and read, the K-steps as in q8t_nhwc_conv_us.  Measured time 0.7 .. 1.45 of it in
-// 97% of the 1646 calls that it was fitted to.
+// 97% of the 1646 calls that it was fitted to, before the product's pieces were copied to LDS (1 to 4 us less).
 double q8t_smallc_conv_us(const q8t_conv_desc *d, bool stats)
 {
     SmallPlan p;
     if (!make_small_plan(0, d, &p)) return 0.0;
     const double M = (double)d->N * p.P * p.Q, wgs = (double)d->N * p.P, rounds = wgs > 1024 ? wgs / 1024 : 1.0;
-    const int bn = d->K % 128 == 0 ? 128 : 64, pitch = ((d->pad + 3) & ~3) + d->W + d->pad;
+    const int bn = wide_tiles((int64_t)M, 1, d->K) ? 128 : 64, pitch = ((d->pad + 3) & ~3) + d->W + d->pad;
     const double tiles = (double)(((int64_t)M + 127) / 128) * (d->K / bn);
     const double t = (double)(((int64_t)tiles + 255) / 256) * (bn == 128 ? 1.6 : 1.0);
     const int pieces = (p.Q * (p.Kc / 16) + kThreads - 1) / kThreads;
@@ -1059,17 +998,16 @@ int q8t_smallc_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa
     if (!make_small_plan(0, d, &p)) return Q8T_ERR_SHAPE;
     if (!ws || !q8t_aligned(ws, 16)) return Q8T_ERR_WORKSPACE;
     int8_t *xn = (int8_t *)ws;
-    int *rowsum = (int *)((char *)ws + p.o_rowsum);
     int8_t *wt = (int8_t *)ws + p.o_wt;
     int *colsum = (int *)((char *)ws + p.o_colsum);
     int *tapoff = (int *)((char *)ws + p.o_tapoff);
     const int vec4 = d->W % 4 == 0 && q8t_aligned(a, 4);
     int *clsinfo = tapoff + 8;   // the tap table of this path has one entry
     hipLaunchKernelGGL(repack_flat, dim3((unsigned)d->K), dim3(kThreads), 0, st, (const int8_t *)b, d->C * d->R * d->S, p.Kc,
-                       p.P, p.Q, d->N * p.P * p.Q, wt, colsum, tapoff, clsinfo);
+                       p.P, p.Q, d->N * p.P * p.Q, qa, wt, colsum, tapoff, clsinfo);
     Q8T_LAUNCH_CHECK();
     hipLaunchKernelGGL(im2col_positions, dim3((unsigned)p.P, (unsigned)d->N), dim3(kThreads), p.lds, st, (const int8_t *)a,
-                       d->C, d->H, d->W, d->R, d->S, d->stride, d->pad, p.P, p.Q, p.Kc, qa, xn, rowsum, vec4);
+                       d->C, d->H, d->W, d->R, d->S, d->stride, d->pad, p.P, p.Q, p.Kc, qa, xn, vec4);
     Q8T_LAUNCH_CHECK();
     Geo g;
     g.N = d->N;
@@ -1091,14 +1029,18 @@ int q8t_smallc_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa
     g.fill = 0;
 #define Q8T_GO(CFG)                                                                                                   \
     {                                                                                                                 \
+        static Q8tLdsOptIn optin;                                                                                     \
+        if (conv_lds_bytes<CFG>() > 65536 &&                                                                          \
+            q8t_allow_lds(optin, (const void *)igemm_nhwc<CFG>, conv_lds_bytes<CFG>()) != Q8T_OK)                      \
+            return Q8T_ERR_HIP;                                                                                       \
         g.mtiles = (g.M + CFG::BM - 1) / CFG::BM;                                                                     \
         const int64_t tiles = (int64_t)g.mtiles * (d->K / CFG::BN);                                                   \
         hipLaunchKernelGGL(igemm_nhwc<CFG>, dim3(q8t_gemm::xcd_grid(tiles)), dim3(CFG::THREADS), conv_lds_bytes<CFG>(), \
-                           st, xn, rowsum, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, (int32_t *)out_acc,         \
+                           st, xn, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, (int32_t *)out_acc,         \
                            (Q8tConvStat *)nullptr);                                                                \
     }
-    if (d->K % 128 == 0) Q8T_GO(q8t_gemm::Mid)
-    else Q8T_GO(q8t_gemm::Small)
+    if (wide_tiles(g.M, 1, d->K)) Q8T_GO(q8t_gemm::Dma<128>)
+    else Q8T_GO(q8t_gemm::Dma<64>)
 #undef Q8T_GO
     Q8T_LAUNCH_CHECK();
     return Q8T_OK;
@@ -1116,21 +1058,22 @@ size_t q8t_nhwc_conv_ws(int which, const q8t_conv_desc *d)
     return make_plan(which, d, &p) ? p.total : 0;
 }
 
-// As q8t_generic_conv_us, for the product here (the shape is supported): three launches, the copy, the filter, then the longest
+// As q8t_generic_conv_us, for the product here (the shape is supported): two launches, the copy, the filter, then the longest
 // class's K-steps, the first round of them at the price of its latency.  Isolated results of strides beyond 2 cost their
-// lines several times.  0.8 .. 1.3 in 96% of the calls.
+// lines several times.  0.8 .. 1.3 in 97% of the 1200 calls that it was fitted to (0.85 .. 1.2 in 94%).
 double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats)
 {
     Plan p;
     if (!make_plan(which, d, &p)) return 0.0;
     const int st = which == 0 ? 1 : d->stride;
     const int64_t opos = (int64_t)d->N * p.OHf * p.OWf;
-    const Rounds rd = rounds_for((opos + p.ncls - 1) / p.ncls, p.ncls, p.OCp);
-    const double t = fmin(rd.small, fmin(rd.mid, rd.big)), results = 1e-6 * opos * p.oc;
+    const int64_t M = (opos + p.ncls - 1) / p.ncls;
+    const int bn = wide_tiles(M, p.ncls, p.OCp) ? 128 : 64;
+    const double t = (double)(((M + 127) / 128 * p.ncls * (p.OCp / bn) + 255) / 256) * (bn == 128 ? 1.6 : 1.0), results = 1e-6 * opos * p.oc;
     const int taps = d->R * d->S, steps = (((d->R + st - 1) / st) * ((d->S + st - 1) / st) * p.Cp + 63) / 64;
-    double us = 10.3 + 0.44 * steps + 0.19 * steps * (t - 1.0) + t + 0.23 * taps + 0.67e-6 * d->N * p.IH * p.IW * p.Cp +
-                3.7e-6 * taps * p.OCp * p.Cp + (st > 2 ? 4.6 : (st == 2 && taps > 3 ? 1.3 : 0.8)) * results;
-    return us + (stats ? 3.2 + 0.4 * results : 0.0);
+    const double us = 8.2 + 0.28 * steps + 0.16 * steps * (t - 1.0) + 0.75 * t + 0.65e-6 * d->N * p.IH * p.IW * p.Cp +
+                      4.7e-6 * taps * p.OCp * p.Cp + (st > 2 ? 4.1 : (st == 2 && taps > 3 ? 1.6 : 1.1)) * results;
+    return us + (stats ? 2.9 + 0.54 * results : 0.0);
 }
 
 size_t q8t_nhwc_conv_stats_ws(const q8t_conv_desc *d)
@@ -1152,37 +1095,11 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
     if (bn_stats && (which != 0 || !stats_ws || !q8t_aligned(stats_ws, 16))) return Q8T_ERR_WORKSPACE;
     Q8tConvStat *bnp = bn_stats ? (Q8tConvStat *)stats_ws : (Q8tConvStat *)nullptr;
     int8_t *xn = (int8_t *)ws;
-    int *chansum = (int *)((char *)ws + p.o_chansum);
     int8_t *wt = (int8_t *)ws + p.o_wt;
     int *colsum = (int *)((char *)ws + p.o_colsum);
     int *tapoff = (int *)((char *)ws + p.o_tapoff);
 
-    // 1. operand relayout
-    {
-        const int HW = p.IH * p.IW;
-        const int ptiles = (HW + 63) / 64;
-        const dim3 grid((unsigned)(ptiles * d->N));   // below 2^31: so is the number of positions
-        // four channel groups per position tile where single ones would leave wavefront slots empty (256 compute
-        // units hold 2048 workgroups of 256 threads)
-        if (small_planes(p, d->N)) {
-            // images per workgroup: a piece of 16 bytes for every thread, more of them while the launch stays large
-            const int plane = p.red * HW, pieces = HW * (p.Cp >> 4);
-            int64_t ipw = (kThreads + pieces - 1) / pieces;
-            while (d->N / ipw > 2048) ipw *= 2;
-            if (ipw > kSmallBytes / plane) ipw = kSmallBytes / plane;   // LDS
-            if (ipw > 2048 / HW) ipw = 2048 / HW;
-            const size_t lds = ((size_t)(ipw * plane + 15) & ~(size_t)15) + (size_t)ipw * HW * sizeof(int);
-            hipLaunchKernelGGL(to_nhwc_small, dim3((unsigned)((d->N + ipw - 1) / ipw)), dim3(kThreads), lds, st, (const int8_t *)a,
-                               d->N, p.red, p.Cp, HW, (int)ipw, xn, chansum);
-        } else if (p.Cp > 64 && grid.x < 1024)
-            hipLaunchKernelGGL(to_nhwc<4>, grid, dim3(kThreads * 4), 0, st, (const int8_t *)a, p.red, p.Cp, HW, ptiles, xn,
-                               chansum);
-        else
-            hipLaunchKernelGGL(to_nhwc<1>, grid, dim3(kThreads), 0, st, (const int8_t *)a, p.red, p.Cp, HW, ptiles, xn, chansum);
-        Q8T_LAUNCH_CHECK();
-    }
-
-    // 2. taps of every class.  forward: one class with all taps, operand offset (r - pad, s - pad).
+    // 1. taps of every class.  forward: one class with all taps, operand offset (r - pad, s - pad).
     // layer gradient: class (ph, pw) keeps the taps with (ph + pad - r) and (pw + pad - s) divisible
     // by the stride; the operand (output-gradient) offset is that quotient.
     TapList rs_list = {}, off_list = {};
@@ -1241,8 +1158,70 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
     const int ncls = fill ? 1 : p.ncls;
     if (fill) maxM = cg.v[0][2];
     int *clsinfo = (int *)((char *)ws + p.o_cls);
-    hipLaunchKernelGGL(repack_taps, dim3((unsigned)p.OCp, (unsigned)p.ncls), dim3(kThreads), 0, st, (const int8_t *)b,
-                       d->K, d->C, d->R, d->S, which, p.Cp, rs_list, off_list, co, cg, wt, colsum, tapoff, clsinfo);
+
+    // 2. operand and filter relayout
+    const int HW = p.IH * p.IW, ptiles = (HW + 63) / 64;
+    PrepArgs pa = {};
+    pa.x = (const int8_t *)a;
+    pa.w = (const int8_t *)b;
+    pa.xn = xn;
+    pa.wt = wt;
+    pa.qpa = qa;
+    pa.colsum = colsum;
+    pa.tapoff = tapoff;
+    pa.clsinfo = clsinfo;
+    pa.N = d->N;
+    pa.C = p.red;
+    pa.Cp = p.Cp;
+    pa.HW = HW;
+    pa.per = ptiles;
+    pa.ncls = p.ncls;
+    pa.OCp = p.OCp;
+    pa.Kf = d->K;
+    pa.Cf = d->C;
+    pa.R = d->R;
+    pa.S = d->S;
+    pa.which = which;
+    pa.taps = rs_list;
+    pa.offs = off_list;
+    pa.co = co;
+    pa.cg = cg;
+    int64_t blocks = (int64_t)ptiles * d->N;   // of the operand; below 2^31: so is the number of positions
+    const bool small = small_planes(p, d->N);
+    size_t lds = 0;
+    if (small) {
+        // images per workgroup: a piece of 16 bytes for every thread, more of them while the launch stays large
+        const int plane = p.red * HW, pieces = HW * (p.Cp >> 4);
+        int64_t ipw = (kThreads + pieces - 1) / pieces;
+        while (d->N / ipw > 2048) ipw *= 2;
+        if (ipw > kSmallBytes / plane) ipw = kSmallBytes / plane;   // LDS
+        if (ipw > 2048 / HW) ipw = 2048 / HW;
+        lds = (size_t)(ipw * plane + 15) & ~(size_t)15;
+        pa.per = (int)ipw;
+        blocks = (d->N + ipw - 1) / ipw;
+    }
+    // a launch holds fewer than 2^32 threads: very many filter rows go ahead in launches of their own
+    const int64_t rows = (int64_t)p.OCp * p.ncls, room = 1 << 21;
+    pa.rows = (int)(rows < room ? rows : room);
+    for (; pa.row0 + room < rows; pa.row0 += (int)room) {
+        hipLaunchKernelGGL(prepare<0>, dim3((unsigned)room), dim3(kThreads), 0, st, pa);
+        Q8T_LAUNCH_CHECK();
+    }
+    pa.rows = (int)(rows - pa.row0);
+    if (blocks + pa.rows >= (1 << 24)) {
+        hipLaunchKernelGGL(prepare<0>, dim3((unsigned)pa.rows), dim3(kThreads), 0, st, pa);
+        Q8T_LAUNCH_CHECK();
+        pa.rows = 0;
+    }
+    const dim3 grid((unsigned)(blocks + pa.rows));
+    // four channel groups per position tile where single ones would leave wavefront slots empty (256 compute
+    // units hold 2048 workgroups of 256 threads)
+    if (small)
+        hipLaunchKernelGGL(prepare<0>, grid, dim3(kThreads), lds, st, pa);
+    else if (p.Cp > 64 && blocks < 1024)
+        hipLaunchKernelGGL(prepare<4>, grid, dim3(kThreads * 4), 0, st, pa);
+    else
+        hipLaunchKernelGGL(prepare<1>, grid, dim3(kThreads), 0, st, pa);
     Q8T_LAUNCH_CHECK();
 
     // 3. one launch over all classes (the kernel picks its class from the tile index)
@@ -1274,16 +1253,15 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
         g.mtiles = (pairM + CFG::BM - 1) / CFG::BM;                                                                  \
         const int64_t tiles = (int64_t)g.mtiles * 2 * (p.OCp / CFG::BN);                                              \
         hipLaunchKernelGGL(igemm_nhwc_pair<CFG>, dim3(q8t_gemm::xcd_grid(tiles)), dim3(CFG::THREADS),                \
-                           conv_pair_lds_bytes<CFG>(), st, xn, chansum, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
+                           conv_pair_lds_bytes<CFG>(), st, xn, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
                            (int32_t *)out_acc);                                                                      \
     }
-        if (p.OCp % 128 == 0) Q8T_GOP(q8t_gemm::Mid)
-        else Q8T_GOP(q8t_gemm::Small)
+        if (wide_tiles(pairM, 2, p.OCp)) Q8T_GOP(q8t_gemm::Dma<128>)
+        else Q8T_GOP(q8t_gemm::Dma<64>)
 #undef Q8T_GOP
         Q8T_LAUNCH_CHECK();
         return Q8T_OK;
     }
-    const Rounds rd = rounds_for(maxM, ncls, p.OCp);
 #define Q8T_GO(CFG)                                                                                                  \
     {                                                                                                                \
         static Q8tLdsOptIn optin;                                                                                    \
@@ -1293,12 +1271,11 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
         const int64_t tiles = (int64_t)g.mtiles * ncls * (p.OCp / CFG::BN);                                         \
         if (tiles > 0)                                                                                               \
             hipLaunchKernelGGL(igemm_nhwc<CFG>, dim3(q8t_gemm::xcd_grid(tiles)), dim3(CFG::THREADS),                 \
-                               conv_lds_bytes<CFG>(), st, xn, chansum, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
+                               conv_lds_bytes<CFG>(), st, xn, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
                                (int32_t *)out_acc, bnp);                                                             \
     }
-    if (rd.big <= rd.mid && rd.big <= rd.small) Q8T_GO(q8t_gemm::Big)
-    else if (rd.mid <= rd.small) Q8T_GO(q8t_gemm::Mid)
-    else Q8T_GO(q8t_gemm::Small)
+    if (wide_tiles(maxM, ncls, p.OCp)) Q8T_GO(q8t_gemm::Dma<128>)
+    else Q8T_GO(q8t_gemm::Dma<64>)
 #undef Q8T_GO
     Q8T_LAUNCH_CHECK();
     if (bnp)   // forward: one class, every row tile wrote its partial

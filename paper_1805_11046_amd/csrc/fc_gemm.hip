@@ -735,14 +735,6 @@ constexpr int DT = 512, DK = 128, DTILE = 128 * DK;   // threads, reduction indi
 
 __device__ __constant__ __align__(16) int8_t fc_zeros[16] = {};   // what pieces outside an operand read
 
-// 16 bytes per lane from memory to `lds` + 16 * lane (`lds` uniform in the wavefront).  Nothing is returned to registers; the
-// wavefront's vmcnt counts the transfer.  The LDS address goes through m0, which nothing else here uses.
-__device__ __forceinline__ void copy16_to_lds(const int8_t *g, int8_t *lds)
-{
-    const uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)lds);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(o), "v"(g) : "memory");
-}
-
 // One operand's share of the staging: two pieces per thread and step.
 template <bool RS>
 struct DmaStage {
@@ -780,7 +772,7 @@ struct DmaStage {
         for (int u = 0; u < 2; ++u) {
             const int8_t *g = src[u];
             if (left < DK && at[u] >= left) g = fc_zeros;
-            copy16_to_lds(g, lds + (u * DT + wave * 64) * 16);
+            q8t_gemm::copy16_to_lds(g, lds + (u * DT + wave * 64) * 16);
             src[u] += step[u];
         }
     }

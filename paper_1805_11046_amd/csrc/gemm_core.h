@@ -1,6 +1,6 @@
-// Shared main loop of the int8 MFMA GEMM kernels (conv_nhwc.hip, wgrad_gemm.hip).
+// Main loops of the int8 MFMA GEMM kernels: through registers (wgrad_gemm.hip), and copied to LDS (conv_nhwc.hip, below).
 //
-// Three tile configurations (rows x columns of the workgroup tile, K-step 64):
+// Through registers, three tile configurations (rows x columns of the workgroup tile, K-step 64):
 //   Big    256 x 256, 8 wavefronts of 128 x 64   (one workgroup per compute unit)
 //   Mid    128 x 128, 4 wavefronts of  64 x 64   (three workgroups per compute unit)
 //   Small  128 x  64, 4 wavefronts of  32 x 64
@@ -150,6 +150,93 @@ __device__ __forceinline__ void pipeline(Ops &ops, int steps, int8_t *__restrict
     }
 #undef Q8T_GEMM_STEP
 #undef Q8T_GEMM_STORE
+}
+
+// ---- tiles that go to LDS without registers ----------------------------------------------------------------------
+// 16 bytes per lane from memory to `lds` + 16 * lane (`lds` uniform in the wavefront).  Nothing is returned to registers; the
+// wavefront's vmcnt counts the transfer.  The LDS address goes through m0, which nothing else here uses.
+__device__ __forceinline__ void copy16_to_lds(const int8_t *g, int8_t *lds)
+{
+    const uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)lds);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(o), "v"(g) : "memory");
+}
+
+// 128 x 128 (eight wavefronts of 64 x 32) or 128 x 64 (of 32 x 32), K-steps of 128 in two buffers, two workgroups per compute
+// unit.  An operand tile is LDS rows of 128 bytes, eight 16-byte pieces each, which a copy writes as 64 lanes x 16 bytes in a
+// row; so the permutation that keeps the fragment reads free of bank conflicts is applied to the addresses in memory: piece s
+// of LDS row r holds piece s ^ perm(r) of the step.
+template <int BN_>
+struct Dma {
+    static constexpr int BM = 128, BN = BN_, THREADS = 512, DK = 128;
+    static constexpr int WR = BN == 128 ? 2 : 4, MT = 8 / WR, NT = 2;
+    static constexpr int NB = BN / 64;                          // pieces of the B tile a thread copies per step (A: 2)
+    static constexpr int BUF = (BM + BN) * DK, LDS_BYTES = 2 * BUF;
+    static constexpr int MINB = 4;                              // wavefronts per SIMD
+    static_assert(8 / WR == MT, "the wavefronts that share rows take a row tile's sums each");
+    // first row of the wavefront's row tile i: a wavefront goes round its row tiles from the one whose sums it takes
+    __device__ static __forceinline__ int row(int wave, int i) { return ((wave % WR) * MT + ((i + wave / WR) & (MT - 1))) * 16; }
+    __device__ static __forceinline__ int colbase(int wave) { return (wave / WR) * 32; }
+    __device__ static __forceinline__ int perm(int r) { return (r >> 1) & 7; }
+};
+
+// The steps of a tile.  Ops: void issue(int8_t *buf), which copies the thread's pieces of the next step (the first 64 of its reduction
+// indices only, where no more are left) and moves on; the kernel has called it once, for buffer 0.  halves: the reduction in units of 64.
+// rsum: sums over the reduction of the four rows row(wave, 0) + 4 * (lane / 16) .., in every lane of the 16.  They are products with
+// ones: an eighth (a quarter) more products, where sums of the operand bytes in the vector unit cost more.
+template <class C, bool TIGHT, class Ops>
+__device__ __forceinline__ void dma_pipeline(Ops &ops, int halves, int8_t *__restrict__ smem, v4i (&acc)[C::MT][C::NT],
+                                             v4i &rsum, int tid)
+{
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kb = lane >> 4;
+    const int rb = C::colbase(wave) + l16;
+    const v4i ones = (v4i){0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    rsum = (v4i){0, 0, 0, 0};
+    constexpr int H1 = TIGHT ? 0 : 1;   // fragments of the second half
+    v4i af[1 + H1][C::MT], bf[1 + H1][C::NT];
+    auto read = [&](const int8_t *a, int h) {
+#pragma unroll
+        for (int j = 0; j < C::NT; ++j) {
+            const int r = rb + j * 16;
+            bf[h * H1][j] = *reinterpret_cast<const v4i *>(a + C::BM * C::DK + r * C::DK + (((h * 4 + kb) ^ C::perm(r)) * 16));
+        }
+#pragma unroll
+        for (int i = 0; i < C::MT; ++i) {
+            const int r = C::row(wave, i) + l16;
+            af[h * H1][i] = *reinterpret_cast<const v4i *>(a + r * C::DK + (((h * 4 + kb) ^ C::perm(r)) * 16));
+        }
+    };
+    auto multiply = [&](int h) {
+#pragma unroll
+        for (int i = 0; i < C::MT; ++i)
+#pragma unroll
+            for (int j = 0; j < C::NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[h * H1][i], bf[h * H1][j], acc[i][j], 0, 0, 0);
+        rsum = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[h * H1][0], ones, rsum, 0, 0, 0);
+    };
+    for (int s = 0; 2 * s < halves; ++s) {
+        int8_t *cur = smem + (s & 1) * C::BUF, *nxt = smem + ((s & 1) ^ 1) * C::BUF;
+        // the tiles of this step are there, and every wavefront is past its reads of the other buffer
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (2 * s + 2 < halves) ops.issue(nxt);
+        read(cur, 0);
+        if (TIGHT) {
+            multiply(0);
+            if (2 * s + 1 < halves) {
+                read(cur, 1);
+                multiply(1);
+            }
+        } else if (2 * s + 1 < halves) {
+            read(cur, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);   // a wavefront that multiplies goes before the ones that read
+            multiply(0);
+            multiply(1);
+        } else {
+            __builtin_amdgcn_s_setprio(1);
+            multiply(0);
+        }
+        __builtin_amdgcn_s_setprio(0);
+    }
 }
 
 }  // namespace q8t_gemm

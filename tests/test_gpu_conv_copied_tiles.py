@@ -1,0 +1,45 @@
+"""GPU parity of the general convolution where its pieces are copied to LDS: reductions that end in the first or the second half
+of a step, one step and several, taps that begin inside a step, padded taps with a last piece of few channels, 128x128 tiles
+(256 of them and more) beside 128x64 ones, class pairs.  Accumulators and float results bit-exact."""
+import pytest
+
+import oracle
+import synth
+from gpu_util import dev, host, qp_dev_from, require_gpu, same_ints
+from test_gpu_products import _conv_operands
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # N, C, H, W, K, R, S, stride, pad
+    (8, 16, 12, 12, 64, 2, 2, 1, 1),       # one half of a step
+    (8, 32, 12, 12, 64, 2, 2, 1, 1),       # a whole step
+    (8, 48, 12, 12, 80, 2, 2, 1, 1),       # a step and a half; taps of three pieces
+    (8, 33, 11, 13, 70, 3, 3, 1, 2),       # one channel in the last piece, two rows of padding
+    (4, 31, 9, 9, 129, 5, 5, 1, 4),        # padding beyond the picture on every side
+    (16, 64, 46, 46, 128, 3, 3, 2, 1),     # 67 tiles of 128x128: 128x64 instead
+    (127, 72, 16, 16, 136, 3, 3, 1, 1),    # 254 row tiles, two columns of 128: 508 tiles, the last of 8 channels
+    (64, 100, 22, 22, 100, 3, 3, 1, 1),    # 242 tiles of 128: not enough
+    (67, 100, 22, 22, 100, 3, 3, 1, 1),    # 254
+    (68, 100, 22, 22, 100, 3, 3, 1, 1),    # 258
+    (90, 128, 28, 28, 136, 3, 3, 2, 1),    # class pairs in 128x128 tiles
+    (2, 20, 27, 30, 24, 4, 3, 2, 0),       # pairs of classes with unlike numbers of taps
+    (3, 18, 12, 14, 40, 2, 1, 2, 0),       # ... none in some
+    (2050, 24, 3, 3, 40, 3, 3, 1, 1),      # many small planes
+]
+
+
+@pytest.mark.parametrize("case", SHAPES)
+def test_copied_tiles(case):
+    q8t = require_gpu()
+    od, (sx, px), (sw, pw), (sg, pg), _ = _conv_operands(synth.rng(sum(case)), case)
+    d = q8t.conv_desc(*case)
+    dpx, dpw, dpg = (qp_dev_from(p) for p in (px, pw, pg))
+    oy, oacc = oracle.qconv_fwd(od, sx, px, sw, pw)
+    y, acc = q8t.qconv_fwd(d, dev(sx), dpx, dev(sw), dpw, want_acc=True)
+    same_ints(host(acc), oacc)
+    same_ints(host(y), oy)
+    odx, oacc = oracle.qconv_dgrad(od, sg, pg, sw, pw)
+    dx, acc = q8t.qconv_dgrad(d, dev(sg), dpg, dev(sw), dpw, want_acc=True)
+    same_ints(host(acc), oacc)
+    same_ints(host(dx), odx)
