@@ -908,7 +908,7 @@ bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
     if (!small_planes(*p, d->N) && (int64_t)d->N * (((int64_t)p->IH * p->IW + 63) / 64) >= (1 << 24)) return false;
     if (opos >= ((int64_t)1 << 30)) return false;
     const size_t xn = up256((size_t)ipos * p->Cp);
-    p->o_wt = xn;
+    p->o_wt = xn + up256((size_t)ipos * sizeof(int));   // 4 bytes a position are unused: the size is what it was with sums of positions
     // filter rows: the taps of a class times Cp, filled up to 64
     const int64_t wbytes = (int64_t)p->OCp * ((int64_t)d->R * d->S * p->Cp + 63 * p->ncls);
     if (wbytes >= ((int64_t)1 << 36) || (int64_t)d->R * d->S * p->Cp >= ((int64_t)1 << 30)) return false;
@@ -951,7 +951,7 @@ bool make_small_plan(int which, const q8t_conv_desc *d, SmallPlan *p)
     p->lds = (((size_t)d->C * d->R * ((((d->pad + 3) & ~3) + d->W + d->pad + 3) & ~3) + 15) & ~(size_t)15) +
              (size_t)p->Kc * sizeof(int);
     if (p->lds > 65536) return false;
-    p->o_wt = up256((size_t)M * p->Kc);
+    p->o_wt = up256((size_t)M * p->Kc) + up256((size_t)M * sizeof(int));   // as in make_plan
     p->o_colsum = p->o_wt + up256((size_t)d->K * p->Kc);
     p->o_tapoff = p->o_colsum + up256((size_t)d->K * sizeof(int));
     p->total = p->o_tapoff + 256;
@@ -967,8 +967,8 @@ bool q8t_smallc_conv_supported(int which, const q8t_conv_desc *d)
 }
 
 // As q8t_generic_conv_us, for the forward product here (the shape is supported): three launches; 1024 workgroups of the im2col
-// side by side, its rows written and read, the K-steps as in q8t_nhwc_conv_us.  Measured time 0.7 .. 1.45 of it in
-// 97% of the 1646 calls that it was fitted to, before the product's pieces were copied to LDS (1 to 4 us less).
+// side by side, its rows written and read, the K-steps as in q8t_nhwc_conv_us.  Measured time 0.84 .. 1.3 of it in
+// 96% of the 200 calls that it was fitted to.
 double q8t_smallc_conv_us(const q8t_conv_desc *d, bool stats)
 {
     SmallPlan p;
@@ -980,8 +980,8 @@ double q8t_smallc_conv_us(const q8t_conv_desc *d, bool stats)
     const int pieces = (p.Q * (p.Kc / 16) + kThreads - 1) / kThreads;
     const int loads = (d->C * d->R * (d->W % 4 ? d->W : d->W / 4) + kThreads * 6 - 1) / (kThreads * 6);
     const int fill = (d->C * d->R * pitch / 4 + kThreads - 1) / kThreads, steps = p.Kc / 64;
-    const double us = 10.5 + 0.35 * steps + 0.51 * steps * (t - 1.0) + 2.1 * t + rounds * (0.023 * pieces + 1.7 * loads + 0.5 * fill) +
-                      0.84e-6 * M * p.Kc + 2.4e-6 * d->K * p.Kc;
+    const double us = 7.6 + 0.33 * steps + 0.28 * steps * (t - 1.0) + 2.6 * t + rounds * (0.1 * pieces + 1.05 * loads + 0.8 * fill) +
+                      1.1e-6 * M * p.Kc + 4.4e-6 * d->K * p.Kc;
     return us + (stats ? q8t_range_bn_stats_us(d->N, d->K, (int64_t)p.P * p.Q) : 0.0);
 }
 
