@@ -298,6 +298,11 @@ int q8t_range_bn_bwd_bifurcate_masked(const float *x, const float *dy, const flo
                                       int W, const float *gamma, float eps, float *dy_masked, float *dgamma, float *dbeta,
                                       uint64_t seed8, uint64_t seed16, int8_t *q8_out, q8t_qparams *qp8_out, int16_t *q16_out,
                                       q8t_qparams *qp16_out, void *ws, void *stream);
+/* The same with the bits of q8t_range_bn_add_relu_pass in place of act (N*C*H*W a multiple of 4). */
+int q8t_range_bn_bwd_bifurcate_pass(const float *x, const float *dy, const uint8_t *pass, const float *stats, int N, int C, int H,
+                                    int W, const float *gamma, float eps, float *dy_masked, float *dgamma, float *dbeta,
+                                    uint64_t seed8, uint64_t seed16, int8_t *q8_out, q8t_qparams *qp8_out, int16_t *q16_out,
+                                    q8t_qparams *qp16_out, void *ws, void *stream);
 
 /* Range BN followed by ReLU in one pass (eq. (range) of Section 3, then max(., 0); the 8-bit
  * output follows Section 4's remark that the normalizer already knows the extrema: the range of
@@ -400,6 +405,8 @@ int q8t_tern_wgrad_multi(const float *g, const int8_t *a_codes, int M, int N, in
  *   written: 12 (+5 for the codes) bytes per element instead of 20 (+5).  ws: q8t_add_relu_quantize_workspace_size.
  * q8t_range_bn_add_relu: the same out = relu(bn(x) + other) for a block whose result is not quantized here: no codes,
  *   no workspace; a NaN in the sum stays a NaN.
+ * q8t_range_bn_add_relu_pass: the same, and where the gradient of out passes (out is not <= 0): bit k of byte i of pass for
+ *   element 4 i + k.  pass (N*C*H*W / 4 bytes) nullable; with it H*W is a multiple of 4 and x, other, out are 16-byte aligned.
  * q8t_relu_bwd_add: res = (out > 0 ? g : 0) + other (other nullable: nothing added).
  * q8t_relu_bwd_sum: the gradient that reaches a rectified tensor `out` from its two consumers (a residual
  *   block's convolutions and its shortcut): res = out > 0 ? g1 + g2 : 0 in one pass, instead of a sum and a
@@ -422,6 +429,8 @@ int q8t_range_bn_add_relu_quantize(const float *x, const float *stats, const flo
                                    q8t_qparams *qp_out, void *ws, void *stream);
 int q8t_range_bn_add_relu(const float *x, const float *stats, const float *gamma, const float *beta, const float *other, int N,
                           int C, int H, int W, float eps, float *out, void *stream);
+int q8t_range_bn_add_relu_pass(const float *x, const float *stats, const float *gamma, const float *beta, const float *other, int N,
+                               int C, int H, int W, float eps, float *out, uint8_t *pass, void *stream);
 int q8t_relu_bwd_add(const float *g, const float *out, const float *other, int64_t n, float *res, void *stream);
 int q8t_relu_bwd_sum(const float *g1, const float *g2, const float *out, int64_t n, float *res, void *stream);
 int q8t_relu_bwd_sum_lattice(const float *g1, const float *g2s, const float *out, int N, int C, int H, int W, int stride,

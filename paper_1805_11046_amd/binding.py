@@ -92,6 +92,7 @@ _SIGS = {
     "q8t_qconv_dgrad_sum": (_i, [C.POINTER(ConvDesc), _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "q8t_maxpool_relu_bwd": (_i, [_vp, _vp, _i, _i, _i, _i, _vp, _vp]),
     "q8t_range_bn_bwd_bifurcate_masked": (_i, [_vp] * 4 + [_i, _i, _i, _i, _vp, _f, _vp, _vp, _vp, _u64, _u64] + [_vp] * 6),
+    "q8t_range_bn_bwd_bifurcate_pass": (_i, [_vp] * 4 + [_i, _i, _i, _i, _vp, _f, _vp, _vp, _vp, _u64, _u64] + [_vp] * 6),
     "q8t_maxpool_range_bn_bwd_bifurcate_workspace_size": (_sz, [_i, _i, _i, _i]),
     "q8t_maxpool_range_bn_bwd_bifurcate": (_i, [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _f, _vp, _vp, _u64, _u64, _vp, _vp,
                                                 _vp, _vp, _vp, _vp]),
@@ -99,6 +100,7 @@ _SIGS = {
     "q8t_add_relu_quantize": (_i, [_vp, _vp, _i64, _vp, _vp, _vp, _vp, _vp]),
     "q8t_range_bn_add_relu_quantize": (_i, [_vp] * 8 + [_i, _i, _i, _i, _f, _vp, _vp, _vp, _vp, _vp]),
     "q8t_range_bn_add_relu": (_i, [_vp] * 5 + [_i, _i, _i, _i, _f, _vp, _vp]),
+    "q8t_range_bn_add_relu_pass": (_i, [_vp] * 5 + [_i, _i, _i, _i, _f, _vp, _vp, _vp]),
     "q8t_relu_bwd_add": (_i, [_vp, _vp, _vp, _i64, _vp, _vp]),
     "q8t_relu_bwd_sum": (_i, [_vp, _vp, _vp, _i64, _vp, _vp]),
     "q8t_relu_bwd_sum_lattice": (_i, [_vp, _vp, _vp, _i, _i, _i, _i, _i, _vp, _vp]),
@@ -432,8 +434,17 @@ def range_bn_bwd_bifurcate_masked(x, dy, act, stats, gamma=None, eps=0.0, seed8=
     """range_bn_bwd_bifurcate with the gradient dy masked by the rectifier whose result is act.
     Returns (masked dy, dgamma, dbeta, q8, qp8, q16, qp16)."""
     _dev(act)
+    assert act.dtype == torch.float32
     return _calls.range_bn_bwd_bifurcate(x, dy, stats, gamma, None, eps, seed8, seed16, None, None, None, None, None, None, False,
                                          True, act)
+
+
+def range_bn_bwd_bifurcate_pass(x, dy, bits, stats, gamma=None, eps=0.0, seed8=0, seed16=1):
+    """range_bn_bwd_bifurcate_masked with the bits of range_bn_add_relu_pass in place of act."""
+    _dev(bits)
+    assert bits.dtype == torch.uint8
+    return _calls.range_bn_bwd_bifurcate(x, dy, stats, gamma, None, eps, seed8, seed16, None, None, None, None, None, None, False,
+                                         True, bits)
 
 
 # ------------------------------------------------------------------ ternarized back-propagation
@@ -558,6 +569,20 @@ def range_bn_add_relu(x, stats, other, gamma=None, beta=None, eps=0.0):
     _check(_lib.q8t_range_bn_add_relu(_ptr(x), _ptr(stats), _ptr(gamma), _ptr(beta), _ptr(other), N, Cc, H, W, eps, _ptr(out),
                                       _stream()), "q8t_range_bn_add_relu")
     return out
+
+
+def range_bn_add_relu_pass(x, stats, other, gamma=None, beta=None, eps=0.0):
+    """range_bn_add_relu that also leaves where the gradient of its result passes, four elements to a byte.
+    Returns (out, bits); bits None where H*W is no multiple of 4 or an operand is not 16-byte aligned."""
+    _dev(x), _dev(stats), _dev(other)
+    N, Cc, H, W = x.shape
+    assert x.dtype == torch.float32 and other.dtype == torch.float32 and other.shape == x.shape
+    out, bits = torch.empty_like(x), None
+    if H * W % 4 == 0 and x.numel() < 2 ** 34 and (x.data_ptr() | other.data_ptr() | out.data_ptr()) % 16 == 0:
+        bits = torch.empty(x.numel() // 4, dtype=torch.uint8, device=x.device)
+    _check(_lib.q8t_range_bn_add_relu_pass(_ptr(x), _ptr(stats), _ptr(gamma), _ptr(beta), _ptr(other), N, Cc, H, W, eps, _ptr(out),
+                                           _ptr(bits), _stream()), "q8t_range_bn_add_relu_pass")
+    return out, bits
 
 
 def relu_bwd_sum(g1, g2=None, out=None):

@@ -230,7 +230,8 @@ __device__ __forceinline__ void tail_consts(const TailBN &t, int c, int C, float
 template <bool VEC, bool PLAIN>
 __global__ __launch_bounds__(kThreads) void bn_add_relu_fwd(const float *__restrict__ x, TailBN bx, const float *__restrict__ other,
                                                             TailBN bo, int64_t n, int C, int HW, float cn, float eps,
-                                                            float *__restrict__ out, float2 *__restrict__ partials)
+                                                            float *__restrict__ out, float2 *__restrict__ partials,
+                                                            uint8_t *__restrict__ pass)
 {
     __shared__ float smem[kThreads / 64];
     float mx = 0.0f;
@@ -260,6 +261,8 @@ __global__ __launch_bounds__(kThreads) void bn_add_relu_fwd(const float *__restr
             r.x = rectify<PLAIN>(r.x); r.y = rectify<PLAIN>(r.y);
             r.z = rectify<PLAIN>(r.z); r.w = rectify<PLAIN>(r.w);
             r4[i] = r;
+            if (PLAIN && pass)
+                pass[i] = (uint8_t)((r.x <= 0.0f ? 0u : 1u) | (r.y <= 0.0f ? 0u : 2u) | (r.z <= 0.0f ? 0u : 4u) | (r.w <= 0.0f ? 0u : 8u));
             if (!PLAIN) mx = fmaxf(fmaxf(mx, r.x), fmaxf(r.y, fmaxf(r.z, r.w)));
         }
     } else {
@@ -555,10 +558,10 @@ int q8t_range_bn_add_relu_quantize(const float *x, const float *stats, const flo
     const TailBN bx = {stats, gamma, beta}, bo = {other_stats, other_gamma, other_beta};
     if (vec)
         hipLaunchKernelGGL((bn_add_relu_fwd<true, false>), dim3(grid), dim3(kThreads), 0, st, x, bx, other, bo, n, C, HW, cn, eps, out,
-                           (float2 *)ws);
+                           (float2 *)ws, (uint8_t *)nullptr);
     else
         hipLaunchKernelGGL((bn_add_relu_fwd<false, false>), dim3(grid), dim3(kThreads), 0, st, x, bx, other, bo, n, C, HW, cn, eps, out,
-                           (float2 *)ws);
+                           (float2 *)ws, (uint8_t *)nullptr);
     Q8T_LAUNCH_CHECK();
     if (!q_out) return Q8T_OK;
     return q8t_quantize8_from_partials(out, n, ws, grid, q_out, qp_out, st);
@@ -566,6 +569,12 @@ int q8t_range_bn_add_relu_quantize(const float *x, const float *stats, const flo
 
 int q8t_range_bn_add_relu(const float *x, const float *stats, const float *gamma, const float *beta, const float *other, int N,
                           int C, int H, int W, float eps, float *out, void *stream)
+{
+    return q8t_range_bn_add_relu_pass(x, stats, gamma, beta, other, N, C, H, W, eps, out, nullptr, stream);
+}
+
+int q8t_range_bn_add_relu_pass(const float *x, const float *stats, const float *gamma, const float *beta, const float *other, int N,
+                               int C, int H, int W, float eps, float *out, uint8_t *pass, void *stream)
 {
     if (N <= 0 || C <= 0 || H <= 0 || W <= 0 || (int64_t)N * H * W < 2) return Q8T_ERR_SHAPE;
     const int64_t n = (int64_t)N * C * H * W;
@@ -575,14 +584,15 @@ int q8t_range_bn_add_relu(const float *x, const float *stats, const float *gamma
     const float cn = (float)q8t_range_bn_scale((int64_t)N * HW);
     const bool vec = HW % 4 == 0 && (n >> 2) < ((int64_t)1 << 32) && q8t_aligned(x, 16) && q8t_aligned(other, 16) &&
                      q8t_aligned(out, 16);
+    if (pass && !vec) return Q8T_ERR_SHAPE;
     const int grid = grid_for(vec ? (n >> 2) : n, 4, kMaxPartials);
     const TailBN bx = {stats, gamma, beta}, bo = {nullptr, nullptr, nullptr};
     if (vec)
         hipLaunchKernelGGL((bn_add_relu_fwd<true, true>), dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, x, bx, other, bo, n, C,
-                           HW, cn, eps, out, (float2 *)nullptr);
+                           HW, cn, eps, out, (float2 *)nullptr, pass);
     else
         hipLaunchKernelGGL((bn_add_relu_fwd<false, true>), dim3(grid), dim3(kThreads), 0, (hipStream_t)stream, x, bx, other, bo, n, C,
-                           HW, cn, eps, out, (float2 *)nullptr);
+                           HW, cn, eps, out, (float2 *)nullptr, (uint8_t *)nullptr);
     Q8T_LAUNCH_CHECK();
     return Q8T_OK;
 }

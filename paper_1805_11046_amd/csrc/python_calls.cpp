@@ -483,7 +483,8 @@ PyObject *range_bn_bwd(Argv a)
 }
 
 // x, dy, stats, gamma, beta, eps, seed8, seed16, dx_out, q8_out, qp8_out, q16_out, qp16_out, ws, want_dx, want_q8, act;
-// act: the gradient is masked where it is not positive and the masked gradient takes the place of dx in the results
+// act: the gradient is masked where it is not positive (or, bytes: where the bits of q8t_range_bn_add_relu_pass say so) and the
+// masked gradient takes the place of dx in the results
 template <bool RELU>
 PyObject *range_bn_bwd_bifurcate(Argv a)
 {
@@ -493,11 +494,17 @@ PyObject *range_bn_bwd_bifurcate(Argv a)
     const uint64_t s8 = seed(a[6]), s16 = seed(a[7]);
     const bool masked = !RELU && a[16] != Py_None, want_q8 = truth(a[15]);
     const float *act = nullptr;
+    const uint8_t *pass = nullptr;
     if (masked) {
         const at::Tensor &t = dev(a[16]);
-        require(dy.sizes().equals(x.sizes()) && t.sizes().equals(x.sizes()) && dy.scalar_type() == at::kFloat &&
-                t.scalar_type() == at::kFloat);
-        act = ptr<float>(t);
+        require(dy.sizes().equals(x.sizes()) && dy.scalar_type() == at::kFloat);
+        if (t.scalar_type() == at::kByte) {
+            require(t.numel() * 4 == x.numel());
+            pass = ptr<uint8_t>(t);
+        } else {
+            require(t.sizes().equals(x.sizes()) && t.scalar_type() == at::kFloat);
+            act = ptr<float>(t);
+        }
     }
     at::Tensor dx, q8, p8;
     if (a[8] != Py_None || truth(a[14]) || masked) dx = given(a[8], [&] { return same(x); });
@@ -510,7 +517,7 @@ PyObject *range_bn_bwd_bifurcate(Argv a)
     const at::Tensor p16 = given(a[12], [&] { return make_params(x); });
     const Scratch ws(a[13], q8t_range_bn_bwd_bifurcate_workspace_size(s.N, s.C, s.H, s.W), a[0]);
     const float *gamma = ptr<float>(a[3]), *beta = ptr<float>(a[4]);
-    run(RELU ? "q8t_range_bn_relu_bwd_bifurcate" : (masked ? "q8t_range_bn_bwd_bifurcate_masked" : "q8t_range_bn_bwd_bifurcate"),
+    run(RELU ? "q8t_range_bn_relu_bwd_bifurcate" : (pass ? "q8t_range_bn_bwd_bifurcate_pass" : (masked ? "q8t_range_bn_bwd_bifurcate_masked" : "q8t_range_bn_bwd_bifurcate")),
         [&, w = ws.get()](void *stream) {
             const float *px = ptr<float>(x), *pdy = ptr<float>(dy), *pst = ptr<float>(stats);
             float *dg = ptr<float>(dgamma), *db = ptr<float>(dbeta);
@@ -519,6 +526,9 @@ PyObject *range_bn_bwd_bifurcate(Argv a)
             q8t_qparams *r8 = ptr<q8t_qparams>(p8), *r16 = ptr<q8t_qparams>(p16);
             if (RELU)
                 return q8t_range_bn_relu_bwd_bifurcate(px, pdy, pst, s.N, s.C, s.H, s.W, gamma, beta, eps, ptr<float>(dx), dg, db, s8,
+                                                       s16, o8, r8, o16, r16, w, stream);
+            if (pass)
+                return q8t_range_bn_bwd_bifurcate_pass(px, pdy, pass, pst, s.N, s.C, s.H, s.W, gamma, eps, ptr<float>(dx), dg, db, s8,
                                                        s16, o8, r8, o16, r16, w, stream);
             if (masked)
                 return q8t_range_bn_bwd_bifurcate_masked(px, pdy, act, pst, s.N, s.C, s.H, s.W, gamma, eps, ptr<float>(dx), dg, db, s8,

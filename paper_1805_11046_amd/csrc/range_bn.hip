@@ -674,21 +674,30 @@ __device__ __forceinline__ float4 pool_grad4(const PoolSrc &ps, const uint8_t *l
 // passes, as in a rectifier's own backward); `gm` receives the masked gradient for pass 2 and the shortcut.
 struct MaskSrc {
     const float *act;
+    const uint8_t *pass;   // or what the pass that wrote act left: bit k of byte i for element 4 i + k
     float *gm;
 };
+constexpr int kMaskAct = 1, kMaskBits = 2;
 __device__ __forceinline__ float mask_grad(float g, float a) { return a <= 0.0f ? 0.0f : g; }
+template <int MASK>
 __device__ __forceinline__ float4 mask_grad4(const MaskSrc &ms, int64_t i4, float4 g)
 {
-    const float4 a = q8t_ld_last(reinterpret_cast<const float4 *>(ms.act) + i4);
-    g.x = mask_grad(g.x, a.x); g.y = mask_grad(g.y, a.y);
-    g.z = mask_grad(g.z, a.z); g.w = mask_grad(g.w, a.w);
+    if (MASK == kMaskBits) {
+        const uint32_t m = ms.pass[i4];
+        g.x = (m & 1u) ? g.x : 0.0f; g.y = (m & 2u) ? g.y : 0.0f;
+        g.z = (m & 4u) ? g.z : 0.0f; g.w = (m & 8u) ? g.w : 0.0f;
+    } else {
+        const float4 a = q8t_ld_last(reinterpret_cast<const float4 *>(ms.act) + i4);
+        g.x = mask_grad(g.x, a.x); g.y = mask_grad(g.y, a.y);
+        g.z = mask_grad(g.z, a.z); g.w = mask_grad(g.w, a.w);
+    }
     reinterpret_cast<float4 *>(ms.gm)[i4] = g;
     return g;
 }
 
 // MASK: the masking pass in front of this one happens on the way (1.65 GB at 128x256x56x56 against 1.23 + 0.82 in two
 // passes of 214 + 165 us): bound by memory; a whole bottleneck block of that size takes 1936 instead of 1967 us.
-template <bool VEC, bool POOL = false, bool MASK = false>
+template <bool VEC, bool POOL = false, int MASK = 0>
 __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restrict__ x, const float *__restrict__ dy,
                                                             const float *__restrict__ stats, int N, int C, int HW, int NB,
                                                             float cn, float eps, const float *__restrict__ gamma,
@@ -756,7 +765,7 @@ __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restr
                 for (int i = threadIdx.x; i < hw4; i += kThreads) {
                     const float4 v = q8t_ld_first(px + i);
                     float4 g = POOL ? pool_grad4(pool, pool_lds, i) : q8t_ld_first(pg + i);
-                    if (MASK) g = mask_grad4(mask, (base >> 2) + i, g);
+                    if (MASK) g = mask_grad4<MASK>(mask, (base >> 2) + i, g);
                     const uint32_t m = one(v.x, g.x, b, 4 * i) | (one(v.y, g.y, b, 4 * i + 1) << 1) |
                                        (one(v.z, g.z, b, 4 * i + 2) << 2) | (one(v.w, g.w, b, 4 * i + 3) << 3);
                     if (flags) flags[(base >> 2) + i] = (uint8_t)m;
@@ -771,7 +780,7 @@ __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restr
                 const int64_t base = ((int64_t)(b0 + bl) * C + c) * HW;
                 const float4 v = q8t_ld_first(reinterpret_cast<const float4 *>(x + base) + i);
                 float4 g = q8t_ld_first(reinterpret_cast<const float4 *>(dy + base) + i);
-                if (MASK) g = mask_grad4(mask, (base >> 2) + i, g);
+                if (MASK) g = mask_grad4<MASK>(mask, (base >> 2) + i, g);
                 const uint32_t m = one(v.x, g.x, b0 + bl, 4 * i) | (one(v.y, g.y, b0 + bl, 4 * i + 1) << 1) |
                                    (one(v.z, g.z, b0 + bl, 4 * i + 2) << 2) | (one(v.w, g.w, b0 + bl, 4 * i + 3) << 3);
                 if (flags) flags[(base >> 2) + i] = (uint8_t)m;
@@ -784,7 +793,7 @@ __global__ __launch_bounds__(kThreads) void bn_bwdq_partial(const float *__restr
             const int64_t j = ((int64_t)b * C + c) * HW + i;
             float d = dy[j];
             if (MASK) {
-                d = mask_grad(d, mask.act[j]);
+                d = MASK == kMaskBits ? ((mask.pass[j >> 2] >> (j & 3)) & 1 ? d : 0.0f) : mask_grad(d, mask.act[j]);
                 mask.gm[j] = d;
             }
             one(x[j], d, b, i);
@@ -1452,7 +1461,7 @@ static int range_bn_bwd_bifurcate_impl(const float *x, const float *dy, const fl
                                        float *dgamma, float *dbeta, uint64_t seed8, uint64_t seed16, int8_t *q8_out,
                                        q8t_qparams *qp8_out, int16_t *q16_out, q8t_qparams *qp16_out, void *ws,
                                        void *stream, const float *gpool = nullptr, const uint8_t *idx = nullptr,
-                                       const float *act = nullptr, float *gm = nullptr)
+                                       const float *act = nullptr, float *gm = nullptr, const uint8_t *pass = nullptr)
 {
     const int rc = check_shape(N, C, H, W);
     if (rc) return rc;
@@ -1471,7 +1480,7 @@ static int range_bn_bwd_bifurcate_impl(const float *x, const float *dy, const fl
                      q8t_aligned(q8_out, 4) && q8t_aligned(q16_out, 8) && q8t_aligned(act, 16) && q8t_aligned(gm, 16);
     if (pooled && !(vec && !relu && pooled_direct(H, W) && q8t_aligned(gpool, 16) && q8t_aligned(idx, 16))) return Q8T_ERR_SHAPE;
     PoolSrc pool = {gpool, idx, W >> 2, (H - 1) / 2 + 1, (W - 1) / 2 + 1, 1.0f / (float)(W >> 2 ? W >> 2 : 1)};
-    const MaskSrc mask = {act, gm};
+    const MaskSrc mask = {act, pass, gm};
     const size_t pool_lds = pooled ? q8t_pool::lds_bytes(pool.P * pool.Q) : 0;
     // Without the rectifier (and with float4 access) pass 2 leaves x alone: 15 instead of 19 bytes per element.
     // Measured: -6% only, the pass is as much bound by the ~45 vector operations per element of the two hashed
@@ -1488,12 +1497,11 @@ static int range_bn_bwd_bifurcate_impl(const float *x, const float *dy, const fl
         hipLaunchKernelGGL((bn_bwdq_partial<true, true>), dim3(C, nsplit), dim3(kThreads), pool_lds, st, x, dy, stats, N, C, HW, NB,
                            cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask);
     else if (gm) {
-        if (vec)
-            hipLaunchKernelGGL((bn_bwdq_partial<true, false, true>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C, HW,
-                               NB, cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask);
-        else
-            hipLaunchKernelGGL((bn_bwdq_partial<false, false, true>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C,
-                               HW, NB, cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask);
+#define Q8T_GO(V, M) \
+    hipLaunchKernelGGL((bn_bwdq_partial<V, false, M>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C, HW, NB, cn, eps, gamma, beta, relu, parts, lists, flags, pool, mask)
+        if (vec) { if (pass) Q8T_GO(true, kMaskBits); else Q8T_GO(true, kMaskAct); }
+        else     { if (pass) Q8T_GO(false, kMaskBits); else Q8T_GO(false, kMaskAct); }
+#undef Q8T_GO
         dy = gm;
     } else if (vec)
         hipLaunchKernelGGL((bn_bwdq_partial<true, false>), dim3(C, nsplit), dim3(kThreads), 0, st, x, dy, stats, N, C, HW, NB, cn,
@@ -1575,6 +1583,19 @@ int q8t_range_bn_bwd_bifurcate_masked(const float *x, const float *dy, const flo
     if (!act || !dy_masked) return Q8T_ERR_NULL;
     return range_bn_bwd_bifurcate_impl(x, dy, stats, N, C, H, W, gamma, nullptr, 0, eps, nullptr, dgamma, dbeta, seed8, seed16,
                                        q8_out, qp8_out, q16_out, qp16_out, ws, stream, nullptr, nullptr, act, dy_masked);
+}
+
+int q8t_range_bn_bwd_bifurcate_pass(const float *x, const float *dy, const uint8_t *pass, const float *stats, int N, int C, int H,
+                                    int W, const float *gamma, float eps, float *dy_masked, float *dgamma, float *dbeta,
+                                    uint64_t seed8, uint64_t seed16, int8_t *q8_out, q8t_qparams *qp8_out, int16_t *q16_out,
+                                    q8t_qparams *qp16_out, void *ws, void *stream)
+{
+    const int rc = check_shape(N, C, H, W);
+    if (rc) return rc;
+    if ((int64_t)N * C * H * W % 4) return Q8T_ERR_SHAPE;
+    if (!pass || !dy_masked) return Q8T_ERR_NULL;
+    return range_bn_bwd_bifurcate_impl(x, dy, stats, N, C, H, W, gamma, nullptr, 0, eps, nullptr, dgamma, dbeta, seed8, seed16,
+                                       q8_out, qp8_out, q16_out, qp16_out, ws, stream, nullptr, nullptr, nullptr, dy_masked, pass);
 }
 
 int q8t_range_bn_relu_bwd_bifurcate(const float *x, const float *dy, const float *stats, int N, int C, int H, int W,

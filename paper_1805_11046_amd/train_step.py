@@ -284,19 +284,19 @@ def _chain_fwd(a, specs, ws, apply_last=True):
     return out, saved
 
 
-def _chain_bwd(saved, g, need_dx, block_end=None, out=None):
+def _chain_bwd(saved, g, need_dx, block_end=None, out=None, bits=None):
     """backward of _chain_fwd: the ReLU mask is recomputed inside the Range BN backward.  block_end = (other, act):
     the chain is the main branch of a residual block; the layer gradient of its first convolution then also adds
     the other branch's gradient and applies the mask of the block's input (act > 0; None: nothing to mask) in its
     epilogue.  out: the rectified result of the block; g is then the gradient of that result, masked on the way into the
-    chain, and the masked gradient takes the place of `other`."""
+    chain, and the masked gradient takes the place of `other`; bits: where it passes, if the pass that wrote out left them."""
     g = g.contiguous()
     dws = [None] * len(saved)
     for i in range(len(saved) - 1, -1, -1):
         d, qa, pa, qw, pw, y, stats, ops, nx, ny, lid = saved[i]
         if i + 1 == len(saved) and out is not None and _angles is None:
-            r = _call("range_bn_bwd_bifurcate", 0, 23 * ny, q8t.range_bn_bwd_bifurcate_masked, y, g, out, stats, None, 1e-5,
-                      2 * lid + 1, 2 * lid + 2)
+            masked, by = (q8t.range_bn_bwd_bifurcate_masked, out) if bits is None else (q8t.range_bn_bwd_bifurcate_pass, bits)
+            r = _call("range_bn_bwd_bifurcate", 0, 23 * ny, masked, y, g, by, stats, None, 1e-5, 2 * lid + 1, 2 * lid + 2)
             block_end = (r[0], block_end[1])
         elif i + 1 == len(saved):
             if out is not None:
@@ -396,14 +396,15 @@ class Bottleneck(torch.autograd.Function):
     def forward(ctx, x, specs, *ws):
         x = x.contiguous()
         (y, stats), ctx.chain = _chain_fwd(x, specs, ws, apply_last=False)
-        out = _call("range_bn_add_relu", 0, 12 * y.numel(), q8t.range_bn_add_relu, y, stats, x, eps=1e-5)
+        out, bits = _call("range_bn_add_relu", 0, 12 * y.numel(), q8t.range_bn_add_relu_pass, y, stats, x, eps=1e-5)
+        ctx.bits = bits   # the backward pass reads these instead of out (a sixteenth of the bytes)
         ctx.save_for_backward(out)
         return out
 
     @staticmethod
     def backward(ctx, g):
         out, = ctx.saved_tensors
-        gx, dws = _chain_bwd(ctx.chain, g, True, (None, None), out)
+        gx, dws = _chain_bwd(ctx.chain, g, True, (None, None), out, ctx.bits)
         return (gx, None, *dws)
 
 
