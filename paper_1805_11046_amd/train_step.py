@@ -81,9 +81,11 @@ _qcache = {}   # data_ptr of an activation -> (codes, parameters) left behind by
 # are held here no other tensor has their address); None once the step is over
 _pcache = {}
 # Pack all filters in one launch after the weights are quantized (off: every product packs its own, a small launch in
-# front of each: 30 of 3 - 9 us in a ResNet-18 step).  Device time of a step at batch 32 / 256: 2.87 -> 2.81 /
-# 8.43 -> 8.37 ms.
+# front of each: 30 of 3 - 9 us in a ResNet-18 step).  ResNet-18 at batch 32 2786 -> 2659 us.  At batch 256 8403 -> 8270 where steps
+# are waited for, but a loop that queues many steps ahead with events around a product came out at 9.5 instead of 8.6 ms
+# in most trials, with unchanged per-call times, for a reason not found: larger batches keep the per-call pre-pass there.
 _pack = True
+_PACK_BATCH = 64
 
 
 def _packed(qw, which):
@@ -515,7 +517,7 @@ def _step(x, labels, ws):
     _layer[0] = 0
     if _fuse:
         _quantize_weights([ws["conv1"], ws["fc"]] + [w for b in ws["blocks"] for w in b.values()])
-        if _pack:
+        if _pack and x.shape[0] <= _PACK_BATCH:
             _pack_filters(_resnet_shapes(x.shape[0], x.shape[2]), [w for b in ws["blocks"] for w in b.values()])
     if _fuse:
         a = StemConvBNPool.apply(x, ws["conv1"], 2, 3)
