@@ -77,8 +77,9 @@ def _angle(kind, t, q, qp):
 
 
 _qcache = {}   # data_ptr of an activation -> (codes, parameters) left behind by the kernel that wrote it
-# (data_ptr of a layer's weight codes, 0 forward / 1 layer gradient) -> (its packed filter for this step, the codes: while they
-# are held here no other tensor has their address); None once the step is over
+# (data_ptr of a layer's weight codes, descriptor, 0 forward / 1 layer gradient) -> (its packed filter for this step, the codes:
+# while they are held here no other tensor has their address); None once the step is over.  The layout of a packed filter
+# follows from the descriptor (batch, planes) and is not stored in it, so a product takes the one made for its own only.
 _pcache = {}
 # Pack all filters in one launch after the weights are quantized (off: every product packs its own, a small launch in
 # front of each: 30 of 3 - 9 us in a ResNet-18 step).  ResNet-18 at batch 32 2786 -> 2659 us.  At batch 256 8403 -> 8270 where steps
@@ -88,8 +89,8 @@ _pack = True
 _PACK_BATCH = 64
 
 
-def _packed(qw, which):
-    hit = _pcache.get((qw.data_ptr(), which))
+def _packed(qw, d, which):
+    hit = _pcache.get((qw.data_ptr(), bytes(d), which))
     return hit[0] if hit is not None else None
 
 
@@ -176,7 +177,7 @@ def _convbn_fwd(a, w, stride, pad, apply=True):
     ops = 2.0 * n * d.P * d.Q * k * c * r * s
     nx, ny = a.numel(), n * k * d.P * d.Q
     y, _, stats = _call("qconv_fwd_bn_stats", ops, nx + 4 * ny, q8t.qconv_fwd_bn_stats, d, qa, pa, qw, pw, tag=_tag(d),
-                        packed=_packed(qw, 0))
+                        packed=_packed(qw, d, 0))
     saved = (d, qa, pa, qw, pw, y, stats, ops, nx, ny, _next_layer())
     if not apply:
         return (y, stats), saved
@@ -195,9 +196,9 @@ def _convbn_bwd(saved, dbn, need_dx, lattice=False):
     if need_dx and lattice:
         ds = q8t.conv_desc(d.N, d.C, d.P, d.Q, d.K, 1, 1, 1, 0)
         dx, _ = _call("qconv_dgrad", ops, ny + 4 * (nx // (d.stride * d.stride)), q8t.qconv_dgrad, ds, g8, pg8, qw, pw, tag=_tag(d),
-                      packed=_packed(qw, 1))
+                      packed=_packed(qw, ds, 1))
     elif need_dx:
-        dx, _ = _call("qconv_dgrad", ops, ny + 4 * nx, q8t.qconv_dgrad, d, g8, pg8, qw, pw, tag=_tag(d), packed=_packed(qw, 1))
+        dx, _ = _call("qconv_dgrad", ops, ny + 4 * nx, q8t.qconv_dgrad, d, g8, pg8, qw, pw, tag=_tag(d), packed=_packed(qw, d, 1))
     dw = _wgrad(d, qa, pa, g16, pg16, ops, nx, ny)
     return dx, dw
 
@@ -273,7 +274,7 @@ def _chain_fwd(a, specs, ws, apply_last=True):
         ops = 2.0 * n * d.P * d.Q * k * c * r * s
         nx, ny = n * c * h * wd, n * k * d.P * d.Q
         y, _, stats = _call("qconv_fwd_bn_stats", ops, nx + 4 * ny, q8t.qconv_fwd_bn_stats, d, qa, pa, qw, pw, tag=_tag(d),
-                            packed=_packed(qw, 0))
+                            packed=_packed(qw, d, 0))
         saved.append((d, qa, pa, qw, pw, y, stats, ops, nx, ny, _next_layer()))
         if i + 1 < len(ws):
             _, qa, pa = _call("range_bn_relu_fwd_apply (int8 out)", 0, 5 * ny, q8t.range_bn_relu_fwd_apply, y, stats,
@@ -315,12 +316,12 @@ def _chain_bwd(saved, g, need_dx, block_end=None, out=None, bits=None):
             other, act = block_end
             if act is None:
                 g = _call("qconv_dgrad", ops, ny + 8 * nx, q8t.qconv_dgrad_sum, d, g8, pg8, qw, pw, other, tag=_tag(d),
-                          packed=_packed(qw, 1))
+                          packed=_packed(qw, d, 1))
             else:
                 g = _call("qconv_dgrad", ops, ny + (12 if other is not None else 8) * nx, q8t.qconv_dgrad_relu_sum, d, g8,
-                          pg8, qw, pw, other, act, tag=_tag(d), packed=_packed(qw, 1))
+                          pg8, qw, pw, other, act, tag=_tag(d), packed=_packed(qw, d, 1))
         elif i > 0 or need_dx:
-            g, _ = _call("qconv_dgrad", ops, ny + 4 * nx, q8t.qconv_dgrad, d, g8, pg8, qw, pw, tag=_tag(d), packed=_packed(qw, 1))
+            g, _ = _call("qconv_dgrad", ops, ny + 4 * nx, q8t.qconv_dgrad, d, g8, pg8, qw, pw, tag=_tag(d), packed=_packed(qw, d, 1))
         dws[i] = _wgrad(d, qa, pa, g16, pg16, ops, nx, ny)
     return g, dws
 
@@ -470,19 +471,21 @@ def _pack_plan(shapes):
 
 
 @functools.lru_cache(maxsize=8)
-def _resnet_shapes(n, size):
+def _resnet_shapes(n, height, width):
     """conv_desc arguments and direction of every product whose filter is packed ahead, in the order of the filters"""
-    h = (size + 2 * 3 - 7) // 2 + 1      # first layer 7x7 / 2, pad 3
-    h = (h + 2 * 1 - 3) // 2 + 1         # pooling 3x3 / 2, pad 1
+    def plane(hw, r, stride, pad):
+        return tuple((v + 2 * pad - r) // stride + 1 for v in hw)
+
+    hw = plane(plane((height, width), 7, 2, 3), 3, 2, 1)      # first layer 7x7 / 2, pad 3; pooling 3x3 / 2, pad 1
     shapes = []
     for cin, cout, stride in STAGES:
-        h2 = (h + 2 - 3) // stride + 1
-        for s in ((n, cin, h, h, cout, 3, 3, stride, 1), (n, cout, h2, h2, cout, 3, 3, 1, 1)):
+        hw2 = plane(hw, 3, stride, 1)
+        for s in ((n, cin, *hw, cout, 3, 3, stride, 1), (n, cout, *hw2, cout, 3, 3, 1, 1)):
             shapes += [s + (0,), s + (1,)]
         if stride != 1 or cin != cout:
             # the shortcut's layer gradient runs as the stride-1 product on the positions the layer read (_convbn_bwd)
-            shapes += [(n, cin, h, h, cout, 1, 1, stride, 0, 0), (n, cin, h2, h2, cout, 1, 1, 1, 0, 1)]
-        h = h2
+            shapes += [(n, cin, *hw, cout, 1, 1, stride, 0, 0), (n, cin, *hw2, cout, 1, 1, 1, 0, 1)]
+        hw = hw2
     return tuple(shapes)
 
 
@@ -492,9 +495,9 @@ def _pack_filters(shapes, filters):
     codes = [_quantize("quantize (weights)", w)[0] for w in filters for _ in (0, 1)]
     plan = _pack_plan(shapes)
     bufs = _call("qconv_pack_multi", 0, 2 * sum(q.numel() for q in codes), plan.run, codes)
-    for s, q, b in zip(shapes, codes, bufs):
+    for d, which, q, b in zip(plan.descs, plan.which, codes, bufs):
         if b is not None:
-            _pcache[(q.data_ptr(), s[9])] = (b, q)
+            _pcache[(q.data_ptr(), bytes(d), which)] = (b, q)
 
 
 def _end_step():
@@ -518,7 +521,7 @@ def _step(x, labels, ws):
     if _fuse:
         _quantize_weights([ws["conv1"], ws["fc"]] + [w for b in ws["blocks"] for w in b.values()])
         if _pack and x.shape[0] <= _PACK_BATCH:
-            _pack_filters(_resnet_shapes(x.shape[0], x.shape[2]), [w for b in ws["blocks"] for w in b.values()])
+            _pack_filters(_resnet_shapes(x.shape[0], x.shape[2], x.shape[3]), [w for b in ws["blocks"] for w in b.values()])
     if _fuse:
         a = StemConvBNPool.apply(x, ws["conv1"], 2, 3)
     else:

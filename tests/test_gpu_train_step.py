@@ -143,3 +143,32 @@ def test_a_step_leaves_no_codes_behind():
         y = ts.Linear.apply(a, ws["fc"])
     (qa, pa), (qw, pw) = q8t.quantize(a, 8), q8t.quantize(ws["fc"].detach(), 8)
     assert torch.equal(y, q8t.qgemm_fwd(qa, pa, qw, pw)[0])
+
+
+@pytest.mark.parametrize("height,width", [(64, 160), (256, 512), (128, 96)])
+def test_filters_packed_ahead_change_nothing_on_oblong_images(height, width):
+    # sizes at which the layout of a filter would be another one on a square image of either side
+    require_gpu()
+    import torch
+    from paper_1805_11046_amd import train_step as ts
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(13)
+    ws = ts.make_weights(dev, gen)
+    x = torch.randn((2, 3, height, width), device=dev, generator=gen)
+    labels = torch.randint(0, 1000, (2,), device=dev, generator=gen)
+    params = [ws["conv1"], ws["fc"]] + [w for b in ws["blocks"] for w in b.values()]
+    results, before = [], ts._pack
+    try:
+        for pack in (False, True):
+            ts._pack = pack
+            for p in params:
+                p.grad = None
+            loss = ts.step(x, labels, ws)
+            torch.cuda.synchronize()
+            results.append((float(loss.detach()), [p.grad.clone() for p in params]))
+    finally:
+        ts._pack = before
+    assert results[0][0] == results[1][0]
+    for i, (a, b) in enumerate(zip(results[0][1], results[1][1])):
+        assert torch.equal(a, b), "gradient of parameter %d differs" % i
