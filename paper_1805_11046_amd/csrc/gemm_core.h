@@ -154,12 +154,16 @@ __device__ __forceinline__ void pipeline(Ops &ops, int steps, int8_t *__restrict
 
 // ---- tiles that go to LDS without registers ----------------------------------------------------------------------
 // 16 bytes per lane from memory to `lds` + 16 * lane (`lds` uniform in the wavefront).  Nothing is returned to registers; the
-// wavefront's vmcnt counts the transfer.  The LDS address goes through m0, which nothing else here uses.
+// wavefront's vmcnt counts the transfer.  The LDS address goes through m0, a register that the compiler reserves for such uses and
+// warns about; it is named as overwritten so that no value of its own is expected there afterwards.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy16_to_lds(const int8_t *g, int8_t *lds)
 {
     const uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)lds);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(o), "v"(g) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(o), "v"(g) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // 128 x 128 (eight wavefronts of 64 x 32) or 128 x 64 (of 32 x 32), K-steps of 128 in two buffers, two workgroups per compute
 // unit.  An operand tile is LDS rows of 128 bytes, eight 16-byte pieces each, which a copy writes as 64 lanes x 16 bytes in a
