@@ -78,7 +78,7 @@ def _angle(kind, t, q, qp):
 
 _qcache = {}   # data_ptr of an activation -> (codes, parameters) left behind by the kernel that wrote it
 # (data_ptr of a layer's weight codes, descriptor, 0 forward / 1 layer gradient) -> (its packed filter for this step, the codes:
-# while they are held here no other tensor has their address); None once the step is over.  The layout of a packed filter
+# while they are held here no other tensor has their address).  The layout of a packed filter
 # follows from the descriptor (batch, planes) and is not stored in it, so a product takes the one made for its own only.
 _pcache = {}
 # Pack all filters in one launch after the weights are quantized (off: every product packs its own, a small launch in
@@ -90,8 +90,7 @@ _PACK_BATCH = 64
 
 
 def _packed(qw, d, which):
-    hit = _pcache.get((qw.data_ptr(), bytes(d), which))
-    return hit[0] if hit is not None else None
+    return _pcache.get((qw.data_ptr(), bytes(d), which), (None,))[0]
 
 
 def _quantize(name, t):
@@ -503,8 +502,7 @@ def _pack_filters(shapes, filters):
 def _end_step():
     # codes and packed filters are found by address: they must not outlive the step whose tensors these addresses are
     _qcache.clear()
-    for key in _pcache:
-        _pcache[key] = None
+    _pcache.clear()
 
 
 def step(x, labels, ws):

@@ -105,21 +105,38 @@ def test_filters_packed_in_one_launch_change_nothing():
     x = torch.randn((4, 3, 224, 224), device=dev, generator=gen)
     labels = torch.randint(0, 1000, (4,), device=dev, generator=gen)
     params = [ws["conv1"], ws["fc"]] + [w for b in ws["blocks"] for w in b.values()]
-    results = []
+    results, before, lookup = [], ts._pack, ts._packed
+
+    def counted(*a):
+        b = lookup(*a)
+        used.append(b is not None)
+        return b
+
+    ts._packed = counted
     try:
         for pack in (False, True, True):
-            ts._pack = pack
+            ts._pack, used = pack, []
             for p in params:
                 p.grad = None
             loss = ts.step(x, labels, ws)
             torch.cuda.synchronize()
             results.append((float(loss.detach()), [p.grad.clone() for p in params]))
-            if pack:
-                assert len(ts._pcache) >= 30      # most layers have a packed form in both directions
-            else:
-                assert len(ts._pcache) == 0
+            assert len(used) == 38 and sum(used) == (30 if pack else 0)      # the products that have a packed form
+            assert not ts._pcache
+        with torch.no_grad():      # a weight that changes in place between two steps is packed anew
+            ws["blocks"][4]["c2"].neg_()
+        changed = []
+        for pack in (False, True):
+            ts._pack, used = pack, []
+            for p in params:
+                p.grad = None
+            ts.step(x, labels, ws)
+            torch.cuda.synchronize()
+            changed.append([p.grad.clone() for p in params])
     finally:
-        ts._pack = False
+        ts._pack, ts._packed = before, lookup
+    assert not all(torch.equal(a, b) for a, b in zip(results[0][1], changed[0]))
+    assert all(torch.equal(a, b) for a, b in zip(*changed))
     for lo, go in results[1:]:
         assert lo == results[0][0]
         for i, (a, b) in enumerate(zip(results[0][1], go)):
