@@ -82,11 +82,9 @@ _qcache = {}   # data_ptr of an activation -> (codes, parameters) left behind by
 # follows from the descriptor (batch, planes) and is not stored in it, so a product takes the one made for its own only.
 _pcache = {}
 # Pack all filters in one launch after the weights are quantized (off: every product packs its own, a small launch in
-# front of each: 30 of 3 - 9 us in a ResNet-18 step).  ResNet-18 at batch 32 2786 -> 2659 us.  At batch 256 8403 -> 8270 where steps
-# are waited for, but a loop that queues many steps ahead with events around a product came out at 9.5 instead of 8.6 ms
-# in most trials, with unchanged per-call times, for a reason not found: larger batches keep the per-call pre-pass there.
+# front of each: 30 of 3 - 9 us in a ResNet-18 step).  us a step over 30 queued ones, off / on: batch 256 8530 / 8410, 128
+# 5300 / 5190, 64 3750 / 3600, 32 2990 / 2860; waited for one by one at 256 8630 / 8550.
 _pack = True
-_PACK_BATCH = 64
 
 
 def _packed(qw, d, which):
@@ -518,7 +516,7 @@ def _step(x, labels, ws):
     _layer[0] = 0
     if _fuse:
         _quantize_weights([ws["conv1"], ws["fc"]] + [w for b in ws["blocks"] for w in b.values()])
-        if _pack and x.shape[0] <= _PACK_BATCH:
+        if _pack:
             _pack_filters(_resnet_shapes(x.shape[0], x.shape[2], x.shape[3]), [w for b in ws["blocks"] for w in b.values()])
     if _fuse:
         a = StemConvBNPool.apply(x, ws["conv1"], 2, 3)

@@ -75,11 +75,12 @@ def step(monkeypatch):
     ts._pack_plan.cache_clear()
 
 
-@pytest.mark.parametrize("height,width", [(64, 64), (64, 160), (160, 64), (128, 96), (96, 352), (65, 131)])
-def test_resnet18_products_take_filters_packed_for_their_own_descriptor(step, height, width):
+@pytest.mark.parametrize("batch,height,width", [(2, 64, 64), (2, 64, 160), (2, 160, 64), (2, 128, 96), (2, 96, 352),
+                                                (2, 65, 131), (65, 32, 64), (300, 32, 32)])
+def test_resnet18_products_take_filters_packed_for_their_own_descriptor(step, batch, height, width):
     ts, products = step
     ws = ts.make_weights(torch.device("cpu"), torch.Generator().manual_seed(0))
-    ts.step(torch.zeros(2, 3, height, width), torch.zeros(2, dtype=torch.long), ws)
+    ts.step(torch.zeros(batch, 3, height, width), torch.zeros(batch, dtype=torch.long), ws)
     assert len(products) == 2 * 19 and sum(products) >= 12
 
 
