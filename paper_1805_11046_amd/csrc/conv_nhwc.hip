@@ -347,7 +347,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
 {
     constexpr int MT = C::MT, NT = C::NT, BM = C::BM, BN = C::BN;
     extern __shared__ __align__(16) int8_t smem[];
-        long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
+    long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
     int *rs = reinterpret_cast<int *>(roff + BM);
     int *stap = rs + BM;
 
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc(const int8_t *
     // classes of one row tile: they write interleaved elements of the same result lines, and run
     // back to back on one XCD so that its L2 merges them before they go to memory
     const int ny = g.OCp / BN, total = g.mtiles * g.ncls * ny;
-    const int lg = q8t_gemm::xcd_logical(blockIdx.x, total);
+    const int lg = q8t_gemm::xcd_logical(total);
     if (lg >= total) return;
     const int n0 = (lg % ny) * BN, zc = (lg / ny) % g.ncls, m0 = (lg / (ny * g.ncls)) * BM;
     int wpitch;
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc_pair(const int
 {
     constexpr int MT = C::MT, NT = C::NT, BM = C::BM, BN = C::BN;
     extern __shared__ __align__(16) int8_t smem[];
-        long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
+    long long *roff = reinterpret_cast<long long *>(smem + C::LDS_BYTES);
     int *rsA = reinterpret_cast<int *>(roff + BM);
     int *rsB = rsA + BM;
     int *stap = rsB + BM;
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(C::THREADS, C::MINB) void igemm_nhwc_pair(const int
     const int l16 = lane & 15, kb = lane >> 4;
     // logical tile order: output-channel tiles fastest, then the two row parities of one row tile
     const int ny = g.OCp / BN, total = g.mtiles * 2 * ny;
-    const int lg = q8t_gemm::xcd_logical(blockIdx.x, total);
+    const int lg = q8t_gemm::xcd_logical(total);
     if (lg >= total) return;
     const int n0 = (lg % ny) * BN, ph = (lg / ny) & 1, m0 = (lg / (ny * 2)) * BM;
     const int *ciA = clsinfo + (ph * 2) * CLS_INTS, *ciB = ciA + CLS_INTS;
@@ -904,7 +904,7 @@ bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
     const int64_t ipos = (int64_t)d->N * p->IH * p->IW, opos = (int64_t)d->N * p->OHf * p->OWf;
     if (ipos >= ((int64_t)1 << 31) || opos >= ((int64_t)1 << 31)) return false;
     if ((int64_t)d->N * (which == 0 ? d->C : d->K) >= ((int64_t)1 << 31)) return false;
-    // a launch holds fewer than 2^32 threads: 256 for 64 positions of a plane (to_nhwc), 256 for 128 result positions
+    // a launch holds fewer than 2^32 threads: 256 for 64 positions of a plane (to_nhwc)
     if (!small_planes(*p, d->N) && (int64_t)d->N * (((int64_t)p->IH * p->IW + 63) / 64) >= (1 << 24)) return false;
     if (opos >= ((int64_t)1 << 30)) return false;
     const size_t xn = up256((size_t)ipos * p->Cp);
@@ -1035,7 +1035,7 @@ int q8t_smallc_conv(const q8t_conv_desc *d, const void *a, const q8t_qparams *qa
             return Q8T_ERR_HIP;                                                                                       \
         g.mtiles = (g.M + CFG::BM - 1) / CFG::BM;                                                                     \
         const int64_t tiles = (int64_t)g.mtiles * (d->K / CFG::BN);                                                   \
-        hipLaunchKernelGGL(igemm_nhwc<CFG>, dim3(q8t_gemm::xcd_grid(tiles)), dim3(CFG::THREADS), conv_lds_bytes<CFG>(), \
+        hipLaunchKernelGGL(igemm_nhwc<CFG>, q8t_gemm::xcd_rows(tiles), dim3(CFG::THREADS), conv_lds_bytes<CFG>(), \
                            st, xn, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, (int32_t *)out_acc,         \
                            (Q8tConvStat *)nullptr);                                                                \
     }
@@ -1252,7 +1252,7 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
             return Q8T_ERR_HIP;                                                                                      \
         g.mtiles = (pairM + CFG::BM - 1) / CFG::BM;                                                                  \
         const int64_t tiles = (int64_t)g.mtiles * 2 * (p.OCp / CFG::BN);                                              \
-        hipLaunchKernelGGL(igemm_nhwc_pair<CFG>, dim3(q8t_gemm::xcd_grid(tiles)), dim3(CFG::THREADS),                \
+        hipLaunchKernelGGL(igemm_nhwc_pair<CFG>, q8t_gemm::xcd_rows(tiles), dim3(CFG::THREADS),                \
                            conv_pair_lds_bytes<CFG>(), st, xn, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
                            (int32_t *)out_acc);                                                                      \
     }
@@ -1270,7 +1270,7 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
         g.mtiles = (maxM + CFG::BM - 1) / CFG::BM;                                                                   \
         const int64_t tiles = (int64_t)g.mtiles * ncls * (p.OCp / CFG::BN);                                         \
         if (tiles > 0)                                                                                               \
-            hipLaunchKernelGGL(igemm_nhwc<CFG>, dim3(q8t_gemm::xcd_grid(tiles)), dim3(CFG::THREADS),                 \
+            hipLaunchKernelGGL(igemm_nhwc<CFG>, q8t_gemm::xcd_rows(tiles), dim3(CFG::THREADS),                 \
                                conv_lds_bytes<CFG>(), st, xn, wt, colsum, qa, qb, g, tapoff, clsinfo, out_f, \
                                (int32_t *)out_acc, bnp);                                                             \
     }

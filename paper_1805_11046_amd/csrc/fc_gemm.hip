@@ -1020,8 +1020,7 @@ bool dma_wanted(int which, const FcArgs &p)
     const int bytes = which == 2 ? 2 : 1, cols = 128 / bytes;
     if (!(q8t_aligned(p.a, 16) && q8t_aligned(p.b, 16) && p.lda % 16 == 0 && p.ldb * bytes % 16 == 0)) return false;
     if (p.red < 64 || p.rows < 96 || p.cols < cols * 3 / 4) return false;
-    const int64_t tiles = (int64_t)((p.rows + 127) / 128) * ((p.cols + cols - 1) / cols);
-    if (tiles >= (1 << 24)) return false;   // a launch holds fewer than 2^32 threads
+    const int64_t tiles = (int64_t)((p.rows + 127) / 128) * ((p.cols + cols - 1) / cols);   // below 2^20: a matrix has fewer than 2^31 entries
     return which == 2 ? tiles >= 112 : tiles >= 128 || (tiles >= 80 && p.red >= 1024);
 }
 

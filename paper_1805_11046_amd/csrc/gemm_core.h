@@ -37,7 +37,7 @@ namespace q8t_gemm {
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin by linear index.  The
-// kernels are launched on a 1-D grid of 8*ceil(total/8) workgroups and run logical tile
+// kernels are launched on a grid of 8*ceil(total/8) workgroups and run logical tile
 // xcd_logical(blockIdx.x, total): consecutive logical tiles, which share an operand tile, then
 // execute back to back on one XCD and find it in that XCD's L2.  A result >= total means "exit".
 __device__ __forceinline__ int xcd_logical(int linear, int total)
@@ -46,6 +46,19 @@ __device__ __forceinline__ int xcd_logical(int linear, int total)
     return (linear & 7) * per + (linear >> 3);
 }
 inline unsigned xcd_grid(int64_t total) { return (unsigned)(((total + 7) >> 3) << 3); }
+// Where that may be more workgroups than one dimension of a launch holds (fewer than 2^32 threads, 2^22 workgroups of 1024): rows
+// of 2^kRowBits of them, of which the kernel runs tile xcd_logical(total).
+constexpr int kRowBits = 21;
+__device__ __forceinline__ int xcd_logical(int total)
+{
+    const int linear = (int)(blockIdx.y << kRowBits | blockIdx.x);
+    return linear >> 3 < (total + 7) >> 3 ? xcd_logical(linear, total) : total;   // the last row is not full
+}
+inline dim3 xcd_rows(int64_t total)
+{
+    const int64_t n = ((total + 7) >> 3) << 3, row = (int64_t)1 << kRowBits;
+    return n <= row ? dim3((unsigned)n) : dim3((unsigned)row, (unsigned)((n + row - 1) / row));
+}
 
 struct Regs {
     uint4 a0, a1, b0, b1;

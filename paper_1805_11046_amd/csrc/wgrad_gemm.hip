@@ -301,7 +301,7 @@ __global__ __launch_bounds__(C::THREADS *KS) void gemm_nt(const int8_t *__restri
 
     // logical tile order: row tiles fastest (they share the B' tile), then column tiles (same A' slice)
     const int nx = Rap / C::BM, ny = Rbp / C::BN;
-    const int lg = q8t_gemm::xcd_logical(blockIdx.x, nx * ny * nz);
+    const int lg = q8t_gemm::xcd_logical(nx * ny * nz);
     if (lg >= nx * ny * nz) return;
     const int bx = lg % nx, by = (lg / nx) % ny, z = lg / (nx * ny);
     const int tid = threadIdx.x % C::THREADS, grp = threadIdx.x / C::THREADS, ar = tid >> 2, q = tid & 3;
@@ -984,7 +984,7 @@ int q8t_gemm_wgrad(const q8t_conv_desc *d, const int16_t *g16, const q8t_qparams
         static Q8tLdsOptIn optin;                                                                                     \
         constexpr size_t lds = nt_lds_bytes<CFG, KS>();                                                               \
         if (lds > 65536 && q8t_allow_lds(optin, (const void *)gemm_nt<CFG, KS>, lds) != Q8T_OK) return Q8T_ERR_HIP;    \
-        hipLaunchKernelGGL((gemm_nt<CFG, KS>), dim3(q8t_gemm::xcd_grid((int64_t)(p.Rap / CFG::BM) * (p.Rbp / CFG::BN) * p.nz)), \
+        hipLaunchKernelGGL((gemm_nt<CFG, KS>), q8t_gemm::xcd_rows((int64_t)(p.Rap / CFG::BM) * (p.Rbp / CFG::BN) * p.nz), \
                            dim3(CFG::THREADS * KS), lds, st, A, B, mask, cols, 2 * d->K, p.Mp, p.slice, p.Rap, p.Rbp, p.nz, \
                            part, rsum, csum);                                                                         \
     }

@@ -43,3 +43,21 @@ def test_copied_tiles(case):
     dx, acc = q8t.qconv_dgrad(d, dev(sg), dpg, dev(sw), dpw, want_acc=True)
     same_ints(host(acc), oacc)
     same_ints(host(dx), odx)
+
+
+def test_more_workgroups_than_one_dimension_of_a_launch_holds():
+    # 16 stride classes of 2^26 planes of one position: 2^23 + 16 tiles of 512 threads, 2^32 threads and more
+    import torch
+    q8t = require_gpu()
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    N = (1 << 26) + 3
+    d = q8t.conv_desc(N, 1, 1, 1, 1, 1, 1, 4, 0)
+    assert q8t.qconv_workspace_size(d, 1) >= 16 * N      # the form with the channel-contiguous copy
+    qg, pg = q8t.quantize(torch.randn((N, 1, 1, 1), device="cuda:0", generator=gen), 8)
+    qw, pw = q8t.quantize(torch.full((1, 1, 1, 1), -0.7, device="cuda:0"), 8)
+    dx, acc = q8t.qconv_dgrad(d, qg, pg, qw, pw, want_acc=True)
+    zero = [int(p[4]) - 128 for p in (pg, pw)]
+    want = (qg.int() - zero[0]) * (int(qw) - zero[1])
+    assert torch.equal(acc, want)
+    scale = torch.stack([p.view(torch.float32)[2] for p in (pg, pw)]).prod()
+    assert torch.equal(dx, want.float() * scale)
