@@ -124,3 +124,13 @@ def test_form_of_a_product_follows_its_size():
     assert 0 < size(64, 32, 27, 27, 512, 1, 1, 1, 0) - 64 * 27 * 27 * (32 + 4) < 1 << 20
     assert 64 * 192 <= size(64, 3, 27, 27, 64, 7, 7, 2, 3) < 1 << 16          # first-layer kernel: the packed filter
     assert size(16, 8, 12, 12, 64, 5, 5, 1, 2) >= 16 * 12 * 12 * 256          # im2col rows: 200 columns filled up to 256
+
+
+def test_weight_gradient_of_a_filter_as_large_as_the_plane_lays_out_no_padding():
+    # one result a plane: 1024 positions of the gradient's byte planes and the codes once, beside the partial tiles
+    _lib_path()
+    from paper_1805_11046_amd import binding
+    K, crs, positions = 512, 512 * 49, 1024
+    size = binding.qconv_workspace_size(binding.conv_desc(positions, 512, 7, 7, K, 7, 7, 1, 0), 2)
+    tiles = 2 * K * crs * 4
+    assert tiles < size < tiles + (2 * K + crs) * positions + (4 << 20)
