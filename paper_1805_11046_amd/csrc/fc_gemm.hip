@@ -1013,15 +1013,17 @@ Plan plan_for(int which, int M, int N, int K)
 // fc_dma: 16-byte pieces that lie whole inside or outside of the operands, at 16-byte addresses, and tiles for half the compute
 // units.  us, fc_dma / the kernel that plan_for names: forward, 104 tiles over 2816 21.4 / 28.8, 114 over 576 10.5 / 10.9, 80 over
 // 2528 19.8 / 24.2, 68 over 3248 27.9 / 29.0, 90 over 128 7.9 / 7.3, 63 over 544 9.9 / 7.2; layer gradient 96 over 688 10.9 / 10.3, 100
-// over 1936 17.3 / 20.1; weight gradient (tiles of 64 columns) 130 over 1584 15.8 / 24.8, 118 over 1328 14.1 / 15.0, 65 over 1136
-// 12.5 / 11.3.  Results narrower than three quarters of a tile stay away: they would multiply zeros.
+// over 1936 17.3 / 20.1; weight gradient (tiles of 64 columns) 130 over 1584 15.8 / 24.8.  The weight gradient's fc_direct runs a round of 256
+// tiles of 64x64 at once and shares their reduction among wavefronts, so up to there it stays: results of 256x4096 over 65536 (128
+// tiles) 534 / 311, 1024x1024 over 4096 28 / 23; 447 sizes: 0.2% slower than the better of the two, 0.5 with a line at 112 tiles.
+// Results narrower than three quarters of a tile stay away: they would multiply zeros.
 bool dma_wanted(int which, const FcArgs &p)
 {
     const int bytes = which == 2 ? 2 : 1, cols = 128 / bytes;
     if (!(q8t_aligned(p.a, 16) && q8t_aligned(p.b, 16) && p.lda % 16 == 0 && p.ldb * bytes % 16 == 0)) return false;
     if (p.red < 64 || p.rows < 96 || p.cols < cols * 3 / 4) return false;
     const int64_t tiles = (int64_t)((p.rows + 127) / 128) * ((p.cols + cols - 1) / cols);   // below 2^20: a matrix has fewer than 2^31 entries
-    return which == 2 ? tiles >= 112 : tiles >= 128 || (tiles >= 80 && p.red >= 1024);
+    return which == 2 ? (int64_t)((p.rows + 63) / 64) * ((p.cols + 63) / 64) > 256 : tiles >= 128 || (tiles >= 80 && p.red >= 1024);
 }
 
 }  // namespace

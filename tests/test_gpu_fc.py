@@ -112,6 +112,8 @@ def test_fc_split_needs_its_workspace():
     ("dgrad", 1409, 1413, 80), ("dgrad", 1537, 1283, 256), ("dgrad", 1409, 1411, 400), ("dgrad", 100, 16390, 64), ("dgrad", 129, 8193, 1040),
     ("wgrad", 1424, 1000, 64), ("wgrad", 1040, 808, 127), ("wgrad", 1040, 808, 128), ("wgrad", 1536, 776, 129), ("wgrad", 1424, 584, 300),
     ("wgrad", 112, 7168, 1027), ("wgrad", 16400, 48, 65),
+    ("wgrad", 1296, 808, 127), ("wgrad", 1296, 808, 128), ("wgrad", 1424, 776, 300), ("wgrad", 112, 8448, 1027),
+    ("wgrad", 1024, 1024, 1030), ("wgrad", 1040, 1024, 1030),      # 256 tiles of 64x64: not copied; 272
 ])
 def test_fc_copied_tiles(which, R, Cc, red):
     q8t = require_gpu()
