@@ -907,8 +907,7 @@ bool make_plan(int which, const q8t_conv_desc *d, Plan *p)
     // a launch holds fewer than 2^32 threads: 256 for 64 positions of a plane (to_nhwc)
     if (!small_planes(*p, d->N) && (int64_t)d->N * (((int64_t)p->IH * p->IW + 63) / 64) >= (1 << 24)) return false;
     if (opos >= ((int64_t)1 << 30)) return false;
-    const size_t xn = up256((size_t)ipos * p->Cp);
-    p->o_wt = xn + up256((size_t)ipos * sizeof(int));   // 4 bytes a position are unused: the size is what it was with sums of positions
+    p->o_wt = up256((size_t)ipos * p->Cp);
     // filter rows: the taps of a class times Cp, filled up to 64
     const int64_t wbytes = (int64_t)p->OCp * ((int64_t)d->R * d->S * p->Cp + 63 * p->ncls);
     if (wbytes >= ((int64_t)1 << 36) || (int64_t)d->R * d->S * p->Cp >= ((int64_t)1 << 30)) return false;
@@ -951,7 +950,7 @@ bool make_small_plan(int which, const q8t_conv_desc *d, SmallPlan *p)
     p->lds = (((size_t)d->C * d->R * ((((d->pad + 3) & ~3) + d->W + d->pad + 3) & ~3) + 15) & ~(size_t)15) +
              (size_t)p->Kc * sizeof(int);
     if (p->lds > 65536) return false;
-    p->o_wt = up256((size_t)M * p->Kc) + up256((size_t)M * sizeof(int));   // as in make_plan
+    p->o_wt = up256((size_t)M * p->Kc);
     p->o_colsum = p->o_wt + up256((size_t)d->K * p->Kc);
     p->o_tapoff = p->o_colsum + up256((size_t)d->K * sizeof(int));
     p->total = p->o_tapoff + 256;
