@@ -38,11 +38,9 @@ bool wgrad_wants_gemm(const q8t_conv_desc *d) { return q8t_gemm_wgrad_supported(
 // a filter row to eight taps, im2col rows pad nothing but multiply the operand.  Measured, us a call, general / channel-contiguous / first-layer form:
 //   472 -> 1 7x7 @7x4 batch 5   46 / 202 / -       16 -> 64 3x3 @32 batch 128 54 / 24 / -       4 -> 32 3x3 @27 batch 64 12.5 / 17.2 / -
 //   32 -> 512 1x1 @27 batch 64 65 / 59 / 104       3 -> 64 7x7/2 @27 batch 64 21 / 29 / 14       3 -> 64 1x1 @7 batch 56 8 / 14 / 12
-// Over 3700 calls (channels 1 .. 600, filters up to 7x7, strides 1 .. 3, planes 1 .. 224, batches 1 .. 65536, with and without
-// statistics) the form taken is 0.5% slower than the best of the first three in the mean, more than 7% in 140 of them, 1.6 times
-// at most; over the 1646 calls with few channels that the estimate of im2col rows was fitted to 0.7%, 61 and 1.5 times
-// (without them 4.1%, 247 and 1.9).  Since the second form copies its tiles to LDS (its times above are from before) it is chosen more
-// often: 400 drawn calls are 2.3% (forward; with statistics and backward 0.8%) slower than the better of the form taken and it.  Under 1x1 filters they are only a second copy: 32 -> 512 @27 batch 64 63 us, 59 without.
+// Over 8340 calls (channels 1 .. 600, filters up to 7x7, strides 1 .. 3, planes 1 .. 224, batches 1 .. 65536) the form taken is 2.5%
+// (forward; with statistics 0.6, layer gradient 0.5) slower than the best of the four in the mean, and 1.9 times at most.  Under 1x1
+// filters im2col rows are only a second copy: 32 -> 512 @27 batch 64 63 us, 59 without.
 enum Form { FIRST, NHWC, SMALLC, GENERAL };
 Form conv_form(int which, const q8t_conv_desc *d, bool stats)
 {
@@ -56,19 +54,9 @@ Form conv_form(int which, const q8t_conv_desc *d, bool stats)
             best = us;
         }
     };
-    const bool rows = nhwc && d->R * d->S > 1 && q8t_smallc_conv_supported(which, d);
-    const double first_us = first ? q8t_first_conv_us(d, stats) : 0.0, rows_us = rows ? q8t_smallc_conv_us(d, stats) : 0.0;
-    if (nhwc) {
-        // The first layer's form needs the packed filter as workspace, 13 KB where the copy of the operand is 1 MB (3 -> 64 7x7/2 @27
-        // batch 64, 14.7 against 13.0 us): it stays unless the copy, or the rows, are a fifth faster (@96 batch 8 18.7 against 13.2).  Up to 8
-        // channels under 25 taps and more the copy pads every tap to 16 and is as fast as im2col rows (these take 0.81 .. 1.35 of
-        // its time, median 1.06, 61 calls): they stay unless it is a quarter faster.
-        const double us = q8t_nhwc_conv_us(which, d, stats);
-        const bool stays = first && d->R * d->S > 1 ? us > 0.8 * first_us : (rows && d->C <= 8 && d->R * d->S >= 25 && us > 0.75 * rows_us);
-        if (!stays) consider(NHWC, us);
-    }
-    if (rows && !(first && rows_us > 0.8 * first_us)) consider(SMALLC, rows_us);
-    if (first) consider(FIRST, first_us);
+    if (nhwc) consider(NHWC, q8t_nhwc_conv_us(which, d, stats));
+    if (nhwc && d->R * d->S > 1 && q8t_smallc_conv_supported(which, d)) consider(SMALLC, q8t_smallc_conv_us(d, stats));
+    if (first) consider(FIRST, q8t_first_conv_us(d, stats));
     return !nhwc && f == GENERAL && smallc_wanted(which, d) ? SMALLC : f;   // beyond 49 taps or strides of 4
 }
 

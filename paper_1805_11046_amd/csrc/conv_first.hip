@@ -300,7 +300,8 @@ bool q8t_first_conv_supported(const q8t_conv_desc *d)
 }
 
 // As q8t_generic_conv_us, for the forward product here (the shape is supported): 1024 workgroups side by side, each stages its
-// band (a round of loads per 32 rows) and takes its tasks four at a time.  0.67 .. 1.5 in 96% of 490 calls.
+// band (a round of loads per 32 rows) and takes its tasks four at a time; the fourth K-step costs more than its share.  0.67 .. 1.5
+// in 96% of 490 calls.
 double q8t_first_conv_us(const q8t_conv_desc *d, bool stats)
 {
     FirstGeom g;
@@ -309,7 +310,7 @@ double q8t_first_conv_us(const q8t_conv_desc *d, bool stats)
     const double results = 1e-6 * g.N * d->K * g.P * g.Q;
     const int rows_round = kStageU * (kThreads / 64), stage = (g.C * g.NR + rows_round - 1) / rows_round * ((g.W + 255) / 256);
     const int tasks = (g.P < kRPB ? g.P : kRPB) * ((g.mtiles + 1) / 2), turns = (tasks + 3) / 4;
-    double us = 4.6 + rounds * (0.75 + 1.3 * stage + turns * (1.3 + 0.78 * ksteps(g))) + 0.06 * g.KB + (g.Q % 4 ? 1.5 : 0.9) * results;
+    double us = 4.6 + rounds * (0.75 + 1.3 * stage + turns * (1.3 + 0.78 * ksteps(g) + (ksteps(g) > 3 ? 1.4 : 0.0))) + 0.06 * g.KB + (g.Q % 4 ? 1.5 : 0.9) * results;
     return us + (stats ? 2.4 + 4.2 * wgs / 1024 : 0.0);
 }
 

@@ -1058,20 +1058,24 @@ size_t q8t_nhwc_conv_ws(int which, const q8t_conv_desc *d)
 }
 
 // As q8t_generic_conv_us, for the product here (the shape is supported): two launches, the copy, the filter, then the longest
-// class's K-steps, the first round of them at the price of its latency.  Isolated results of strides beyond 2 cost their
-// lines several times.  0.8 .. 1.3 in 97% of the 1200 calls that it was fitted to (0.85 .. 1.2 in 94%).
+// class's K-steps (two classes one after the other where a workgroup has both), the first round of them at the price of its latency.
+// Isolated results of strides beyond 2 cost their lines several times; under 1x1 filters those of narrow or odd rows cost a
+// workgroup's end more.  0.8 .. 1.2 in 90% of the 8340 calls it was checked on.
 double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats)
 {
     Plan p;
     if (!make_plan(which, d, &p)) return 0.0;
-    const int st = which == 0 ? 1 : d->stride;
-    const int64_t opos = (int64_t)d->N * p.OHf * p.OWf;
-    const int64_t M = (opos + p.ncls - 1) / p.ncls;
-    const int bn = wide_tiles(M, p.ncls, p.OCp) ? 128 : 64;
-    const double t = (double)(((M + 127) / 128 * p.ncls * (p.OCp / bn) + 255) / 256) * (bn == 128 ? 1.6 : 1.0), results = 1e-6 * opos * p.oc;
-    const int taps = d->R * d->S, steps = (((d->R + st - 1) / st) * ((d->S + st - 1) / st) * p.Cp + 63) / 64;
-    const double us = 8.2 + 0.28 * steps + 0.16 * steps * (t - 1.0) + 0.75 * t + 0.65e-6 * d->N * p.IH * p.IW * p.Cp +
-                      4.7e-6 * taps * p.OCp * p.Cp + (st > 2 ? 4.1 : (st == 2 && taps > 3 ? 1.6 : 1.1)) * results;
+    const int st = which == 0 ? 1 : d->stride, taps = d->R * d->S, Q = (d->W + st - 1) / st;
+    const bool fill = st == 2 && taps == 1 && d->pad == 0 && d->H % 2 == 0 && d->W % 2 == 0;
+    const bool pair = st == 2 && !fill && d->W % 2 == 0;
+    const int launched = fill ? 1 : (pair ? 2 : p.ncls);
+    const int64_t opos = (int64_t)d->N * p.OHf * p.OWf, M = (opos + p.ncls - 1) / p.ncls;
+    const int bn = wide_tiles(M, launched, p.OCp) ? 128 : 64;
+    const double t = (double)(((M + 127) / 128 * launched * (p.OCp / bn) + 255) / 256) * (bn == 128 ? 1.6 : 1.0), results = 1e-6 * opos * p.oc;
+    const int steps = (((d->R + st - 1) / st) * (pair ? d->S : (d->S + st - 1) / st) * p.Cp + 63) / 64;
+    double us = 8.2 + 0.28 * steps + 0.16 * steps * (t - 1.0) + 0.75 * t + 0.65e-6 * d->N * p.IH * p.IW * p.Cp +
+                4.7e-6 * taps * p.OCp * p.Cp + (st > 2 ? 4.1 : (st == 2 && taps > 3 ? 1.6 : 1.1)) * results;
+    if (st > 1 && taps == 1 && Q > 1 && results >= 0.05 && (Q % 4 || (!fill && (d->W % 2 || st > 2)))) us += d->C < 192 ? d->C / 38.0 : 5.0;
     return us + (stats ? 2.9 + 0.54 * results : 0.0);
 }
 
