@@ -454,7 +454,6 @@ def make_weights(dev, gen):
 def _quantize_weights(tensors):
     """all weight tensors of the network in one call (two launches instead of one or two per tensor); the layers
     find the codes in the cache when they ask for them"""
-    tensors = [t for t in tensors if t.is_contiguous()]   # the others are quantized where they are used
     n = sum(t.numel() for t in tensors)
     res = _call("quantize (weights)", 0, 9 * n, q8t.quantize_multi, [t.detach() for t in tensors], 8)
     for t, (q, qp) in zip(tensors, res):

@@ -92,3 +92,18 @@ def test_bottleneck_products_take_filters_packed_for_their_own_descriptor(step, 
     x = torch.zeros(2, 256, height, width, requires_grad=True)
     ts.bottleneck_step(x, torch.zeros(2, 256, height, width), ws)
     assert len(products) == 6
+
+
+def test_weights_that_are_not_contiguous_are_refused_as_such(step, monkeypatch):
+    from paper_1805_11046_amd import binding
+    ts, _ = step
+
+    def contiguous_only(t):
+        if not t.is_contiguous():
+            raise ValueError("q8t needs contiguous tensors")
+
+    monkeypatch.undo()     # the calls check their own arguments, of CPU tensors too
+    monkeypatch.setattr(binding, "_dev", contiguous_only)
+    ws = [torch.zeros(c, k, r, r).transpose(0, 1) for k, c, r in ((64, 256, 1), (64, 64, 3), (256, 64, 1))]
+    with pytest.raises(ValueError, match="contiguous"):
+        ts.bottleneck_step(torch.zeros(2, 256, 14, 14, requires_grad=True), torch.zeros(2, 256, 14, 14), ws)
