@@ -295,8 +295,10 @@ def _chain_bwd(saved, g, need_dx, block_end=None, out=None, bits=None):
     for i in range(len(saved) - 1, -1, -1):
         d, qa, pa, qw, pw, y, stats, ops, nx, ny, lid = saved[i]
         if i + 1 == len(saved) and out is not None and _angles is None:
-            masked, by = (q8t.range_bn_bwd_bifurcate_masked, out) if bits is None else (q8t.range_bn_bwd_bifurcate_pass, bits)
-            r = _call("range_bn_bwd_bifurcate", 0, 23 * ny, masked, y, g, by, stats, None, 1e-5, 2 * lid + 1, 2 * lid + 2)
+            # bytes as in _bn_bwd, the masked gradient written and `by` (fp32, or four elements to a byte) read
+            masked, by, per = ((q8t.range_bn_bwd_bifurcate_masked, out, 23) if bits is None
+                               else (q8t.range_bn_bwd_bifurcate_pass, bits, 19.25))
+            r = _call("range_bn_bwd_bifurcate", 0, per * ny, masked, y, g, by, stats, None, 1e-5, 2 * lid + 1, 2 * lid + 2)
             block_end = (r[0], block_end[1])
         elif i + 1 == len(saved):
             if out is not None:

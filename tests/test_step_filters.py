@@ -107,3 +107,28 @@ def test_weights_that_are_not_contiguous_are_refused_as_such(step, monkeypatch):
     ws = [torch.zeros(c, k, r, r).transpose(0, 1) for k, c, r in ((64, 256, 1), (64, 64, 3), (256, 64, 1))]
     with pytest.raises(ValueError, match="contiguous"):
         ts.bottleneck_step(torch.zeros(2, 256, 14, 14, requires_grad=True), torch.zeros(2, 256, 14, 14), ws)
+
+
+@pytest.mark.parametrize("bits", [False, True])
+def test_bytes_booked_for_the_masked_backward_pass_are_those_it_moves(step, monkeypatch, bits):
+    from paper_1805_11046_amd import binding
+    ts, _ = step
+    n, booked, call = 2 * 256 * 14 * 14, [], ts._call
+
+    def note(name, ops, nbytes, fn, *a, **k):
+        if fn in (binding.range_bn_bwd_bifurcate_masked, binding.range_bn_bwd_bifurcate_pass):
+            booked.append((nbytes, a[2].numel() * a[2].element_size()))
+        return call(name, ops, nbytes, fn, *a, **k)
+
+    monkeypatch.setattr(ts, "_call", note)
+    if bits:
+        monkeypatch.setattr(binding, "range_bn_bwd_bifurcate_masked", None)
+        monkeypatch.setattr(binding, "range_bn_add_relu_pass",
+                            lambda x, *a, **k: (torch.zeros_like(x), torch.zeros(x.numel() // 4, dtype=torch.uint8)))
+    else:
+        monkeypatch.setattr(binding, "range_bn_bwd_bifurcate_pass", None)
+    gen = torch.Generator().manual_seed(0)
+    ws = [ts._he("cpu", gen, 64, 256, 1), ts._he("cpu", gen, 64, 64, 3), ts._he("cpu", gen, 256, 64, 1)]
+    ts.bottleneck_step(torch.zeros(2, 256, 14, 14, requires_grad=True), torch.zeros(2, 256, 14, 14), ws)
+    # x and dy read, the masked gradient written and read, the two copies written; and what the mask comes from, once
+    assert [nbytes for nbytes, _ in booked] == [(8 + 8 + 3) * n + by for _, by in booked] and len(booked) == 1
