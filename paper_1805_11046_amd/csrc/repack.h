@@ -38,6 +38,7 @@ __device__ __forceinline__ void q8t_repack(const int8_t *__restrict__ w, int Kf,
         uint4 v[kRepackTaps];
 #pragma unroll
         for (int u = 0; u < kRepackTaps; ++u) {
+            if (u == 1 && pieces <= kRepackThreads) break;   // 1x1: one piece a thread
             const int p = min(tid + u * kRepackThreads, pieces - 1), row = p / run, at = p - row * run;
             const size_t first = dgrad ? ((size_t)(ch0 + row) * Cf + oc0) * taps : ((size_t)(oc0 + row) * Cf + ch0) * taps;
             __builtin_memcpy(&v[u], w + first + at * 16, 16);
