@@ -82,7 +82,7 @@ __global__ __launch_bounds__(kRepackThreads) void repack_weights(const int8_t *_
                                                            int *__restrict__ colsum)
 {
     __shared__ __align__(16) uint8_t lds[kRepackLds];
-    __shared__ int red[64];
+    __shared__ int red[kRepackRed];
     q8t_repack(w, Kf, Cf, R * S, dgrad, 0, out, colsum, (int)blockIdx.x * kRepackCols, lds, red);
 }
 

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kRepackThreads) void repack_wide(const int8_t *__re
                                                               int8_t *__restrict__ out, int *__restrict__ colsum)
 {
     __shared__ __align__(16) uint8_t lds[kRepackLds];
-    __shared__ int red[64];
+    __shared__ int red[kRepackRed];
     q8t_repack(w, Kf, Cf, 9, dgrad, BN, out, colsum, (int)blockIdx.x * kRepackCols, lds, red);
 }
 

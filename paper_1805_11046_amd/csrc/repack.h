@@ -5,10 +5,11 @@
 #pragma once
 #include "q8t_common.h"
 
-constexpr int kRepackThreads = 256;
+constexpr int kRepackThreads = 512;
 constexpr int kRepackCols = 16;    // output channels per workgroup
 constexpr int kRepackChan = 256;   // reduction channels per round
 constexpr int kRepackTaps = 9;     // at most
+constexpr int kRepackRed = kRepackThreads / 64 * 16;
 constexpr int kRepackLds = kRepackChan * (kRepackCols * kRepackTaps + 4);   // bytes; the larger of the two row forms below
 
 // Layouts:
@@ -20,32 +21,40 @@ constexpr int kRepackLds = kRepackChan * (kRepackCols * kRepackTaps + 4);   // b
 //   MFMA operand of a wavefront is one 16-byte load per lane, 1 KB contiguous per instruction.
 // colsum[oc] = sum of W'(oc,.,.).  Output and reduction channels are multiples of 64, at most kRepackTaps taps.
 //
-// One workgroup of kRepackThreads per 16 output channels, red: 4 * 16 ints, lds: kRepackLds bytes, 4-byte aligned.  The filter
+// One workgroup of kRepackThreads per 16 output channels, red: kRepackRed ints, lds: kRepackLds bytes, 4-byte aligned.  The filter
 // comes in runs that lie together (an output channel's taps of all channels forward, a reduction channel's taps of 16 output
 // channels backward), 16 bytes a load, and is picked apart in LDS: byte loads from memory, one line for each in the layer
-// gradient, took 9 us for 512 -> 512 3x3 and 56 for the filters of a ResNet-18 in both directions; now 5 and 23.
-__device__ __forceinline__ void q8t_repack(const int8_t *__restrict__ w, int Kf, int Cf, int taps, int dgrad, int wide_bn,
-                                           int8_t *__restrict__ out, int *__restrict__ colsum, int oc0, uint8_t *lds, int *red)
+// gradient, took 56 us for the filters of a ResNet-18 in both directions.  A filter on its own is a few workgroups, each bound by the
+// latency of its loads and LDS reads: 512 threads (of 256, or of 1024), the next round's loads in flight across the LDS barriers and
+// constant distances in LDS.  us a launch, back to back, 256 threads without these / now: 512 -> 512 3x3 10.9 / 6.7, 256 -> 256
+// 6.25 / 4.1, 64 -> 64 3.7 / 2.9, 1x1 3.0 / 2.1; whole forward calls, byte loads / 256 threads / now: 512 -> 512 @7 batch 256 65.0 / 68.3 /
+// 65.8, 256 -> 256 @14 44.6 / 47.9 / 45.2, 64 -> 64 @56 batch 8 11.3 / 11.0 / 10.2, 512 -> 64 1x1 @8 11.9 / 13.6 / 11.8.
+template <int taps, bool dgrad>
+__device__ __forceinline__ void q8t_repack_taps(const int8_t *__restrict__ w, int Kf, int Cf, int wide_bn,
+                                                int8_t *__restrict__ out, int *__restrict__ colsum, int oc0, uint8_t *lds, int *red)
 {
     const int CHN = dgrad ? Kf : Cf, CC = CHN / 64, tid = threadIdx.x;
     const int oc = oc0 + (tid & 15);   // of the thread's pieces
     int sum = 0;
-    for (int ch0 = 0; ch0 < CHN; ch0 += kRepackChan) {
-        const int nch = min(kRepackChan, CHN - ch0), pieces = taps * nch;
-        // rows in LDS: forward [output channel][nch * taps], layer gradient [reduction channel][16 * taps]; 4 bytes between them
-        // keep the rows of neighbouring output channels on different banks
-        const int run = dgrad ? taps : pieces / 16, pitch = run * 16 + 4;
-        uint4 v[kRepackTaps];
+    constexpr int U = (taps * kRepackChan + kRepackThreads - 1) / kRepackThreads;
+    uint4 v[U];
+    // rows in LDS: forward [output channel][channels * taps], layer gradient [reduction channel][16 * taps], `run` pieces each; 4 bytes
+    // between them keep the rows of neighbouring output channels on different banks
+    auto load = [&](int ch0) {
+        const int pieces = taps * min(kRepackChan, CHN - ch0), run = dgrad ? taps : pieces / 16;
 #pragma unroll
-        for (int u = 0; u < kRepackTaps; ++u) {
-            if (u == 1 && pieces <= kRepackThreads) break;   // 1x1: one piece a thread
+        for (int u = 0; u < U; ++u) {
             const int p = min(tid + u * kRepackThreads, pieces - 1), row = p / run, at = p - row * run;
             const size_t first = dgrad ? ((size_t)(ch0 + row) * Cf + oc0) * taps : ((size_t)(oc0 + row) * Cf + ch0) * taps;
             __builtin_memcpy(&v[u], w + first + at * 16, 16);
         }
-        if (ch0) __syncthreads();   // the previous round's pieces are out
+    };
+    load(0);
+    for (int ch0 = 0; ch0 < CHN; ch0 += kRepackChan) {
+        const int pieces = taps * min(kRepackChan, CHN - ch0), run = dgrad ? taps : pieces / 16, pitch = run * 16 + 4;
+        if (ch0) q8t_lds_barrier();   // the previous round's pieces are out
 #pragma unroll
-        for (int u = 0; u < kRepackTaps; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int p = tid + u * kRepackThreads, row = p / run, at = p - row * run;
             if (p < pieces) {
                 uint32_t *d = reinterpret_cast<uint32_t *>(lds + row * pitch + at * 16);
@@ -55,7 +64,8 @@ __device__ __forceinline__ void q8t_repack(const int8_t *__restrict__ w, int Kf,
                 d[3] = v[u].w;
             }
         }
-        __syncthreads();
+        if (ch0 + kRepackChan < CHN) load(ch0 + kRepackChan);
+        q8t_lds_barrier();
         for (int p = tid; p < pieces; p += kRepackThreads) {
             const int e = p >> 4, tap = e % taps, c16 = e / taps;   // 16 reduction channels of one tap
             const uint8_t *src = dgrad ? lds + c16 * 16 * pitch + (tid & 15) * taps + (taps - 1 - tap)
@@ -85,7 +95,22 @@ __device__ __forceinline__ void q8t_repack(const int8_t *__restrict__ w, int Kf,
     sum += __shfl_xor(sum, 32, Q8T_WAVE);
     if ((tid & 63) < 16) red[(tid >> 6) * 16 + tid % 16] = sum;
     __syncthreads();
-    if (tid < 16) colsum[oc0 + tid] = red[tid] + red[16 + tid] + red[32 + tid] + red[48 + tid];
+    if (tid < 16) {
+        int t = 0;
+#pragma unroll
+        for (int i = 0; i < kRepackThreads / 64; ++i) t += red[i * 16 + tid];
+        colsum[oc0 + tid] = t;
+    }
+}
+
+// taps: 9 or 1
+__device__ __forceinline__ void q8t_repack(const int8_t *__restrict__ w, int Kf, int Cf, int taps, int dgrad, int wide_bn,
+                                           int8_t *__restrict__ out, int *__restrict__ colsum, int oc0, uint8_t *lds, int *red)
+{
+    if (taps == 1 && dgrad) q8t_repack_taps<1, true>(w, Kf, Cf, wide_bn, out, colsum, oc0, lds, red);
+    else if (taps == 1) q8t_repack_taps<1, false>(w, Kf, Cf, wide_bn, out, colsum, oc0, lds, red);
+    else if (dgrad) q8t_repack_taps<kRepackTaps, true>(w, Kf, Cf, wide_bn, out, colsum, oc0, lds, red);
+    else q8t_repack_taps<kRepackTaps, false>(w, Kf, Cf, wide_bn, out, colsum, oc0, lds, red);
 }
 
 // Filters packed ahead of the products (q8t_qconv_pack): which layout a (shape, product) pair takes

@@ -16,7 +16,7 @@ struct PackTable {
 __global__ __launch_bounds__(kRepackThreads) void repack_multi(const PackTable t)
 {
     __shared__ __align__(16) uint8_t lds[kRepackLds];
-    __shared__ int red[64];
+    __shared__ int red[kRepackRed];
     // the job whose run of blocks holds this one (jobs are few: a uniform scan)
     int j = 0;
     for (int i = 1; i < t.n; ++i)
