@@ -728,7 +728,7 @@ __global__ __launch_bounds__(TT, 2) void fc_tile(const FcArgs p)
 //   RS operand: LDS row = reduction index, pieces along the columns; a fragment is two ds_read_b64_tr_b8, in which 16 lanes
 //               read 8 rows x 16 bytes and lane i receives the 8 bytes of column i
 // Nothing is transposed or split on the way.  2048x4096x4096, us, against fc_tile: forward 69 / 45, layer gradient 60 / 46, weight
-// gradient 111 / 101; 2048^3 31 / 19, 26 / 19, 43 / 31; 1.9 POP/s of the main loop.  Whole lines (K-steps of 128: of 64 the
+// gradient 111 / 101; 2048^3 31 / 19, 26 / 19, 43 / 31; matrix units 42, 43 and 40% busy (fc_tile 20, 23, 26).  Whole lines (K-steps of 128: of 64 the
 // same loop takes 47 us for 37 here), no registers between memory and LDS and the second workgroup of a compute unit are what
 // it lives on: tiles of 128x256 and three or four buffers, one workgroup a unit, take as long; 32x32x32 products are slower (43).
 constexpr int DT = 512, DK = 128, DTILE = 128 * DK;   // threads, reduction indices a step, bytes of an operand's tile
