@@ -174,41 +174,41 @@ __device__ __forceinline__ void to_nhwc_small(int block, const int8_t *__restric
 }
 
 // ---- filter -> [class][output channel][tap][reduction channel], sums per output channel ------
-// One row (output channel j, class z) a workgroup of THREADS.  which 0: out = k, reduction = c;  which 1: out = c, reduction = k.
+// One row (output channel j, class z) by THREADS threads; tid: the thread among them, part [THREADS / 64] and stap [MAXT]: their LDS.
+// which 0: out = k, reduction = c;  which 1: out = c, reduction = k.
 // The first one also writes the tables of the main kernel: operand offsets of the taps (dh in the low half), the classes, and
 // three pieces of 16 bytes for what lies outside: the zero code, the zero code in the last piece of a tap (only the channels that
 // are there, as the row sums count them), zeros.
 constexpr int PADS = MAXT + 3;   // ints from the tap table to those pieces
 
-__device__ __forceinline__ void pad_pieces(int8_t *pads, int red, const q8t_qparams *__restrict__ qpa)
+__device__ __forceinline__ void pad_pieces(int tid, int8_t *pads, int red, const q8t_qparams *__restrict__ qpa)
 {
-    const int i = threadIdx.x, last = red & 15, za = qpa->zero_point - (1 << (qpa->bits - 1));
+    const int i = tid, last = red & 15, za = qpa->zero_point - (1 << (qpa->bits - 1));
     if (i < 48) pads[i] = i < 16 || (i < 32 && (last == 0 || i - 16 < last)) ? (int8_t)za : (int8_t)0;
 }
 
 template <int THREADS>
-__device__ __forceinline__ void repack_taps(int j, int z, int ncls, const int8_t *__restrict__ w, int Kf, int Cf, int R, int S,
-                                            int which, int Cp, const TapList &taps, const TapList &offs, const ClassOffsets &co,
+__device__ __forceinline__ void repack_taps(int tid, int *part, int *stap, int j, int z, int ncls, const int8_t *__restrict__ w,
+                                            int Kf, int Cf, int R, int S, int which, int Cp, const TapList &taps, const TapList &offs, const ClassOffsets &co,
                                             const ClassGeo &cg, const q8t_qparams *__restrict__ qpa, int OCp,
                                             int8_t *__restrict__ wt, int *__restrict__ colsum, int *__restrict__ tapoff,
                                             int *__restrict__ clsinfo)
 {
-    __shared__ int part[THREADS / 64], stap[MAXT];
     const int OC = which == 0 ? Kf : Cf, red = which == 0 ? Cf : Kf;
     if (j == 0 && z == 0) {
-        for (int t = threadIdx.x; t < co.off[MAXCLS]; t += THREADS)
+        for (int t = tid; t < co.off[MAXCLS]; t += THREADS)
             tapoff[t] = (int)((uint32_t)(uint16_t)(int16_t)offs.a[t] | ((uint32_t)(uint16_t)(int16_t)offs.b[t] << 16));
-        for (int c = threadIdx.x; c < ncls; c += THREADS)
+        for (int c = tid; c < ncls; c += THREADS)
             for (int k = 0; k < 7; ++k) clsinfo[c * CLS_INTS + k] = cg.v[c][k];
-        pad_pieces(reinterpret_cast<int8_t *>(tapoff + PADS), red, qpa);
+        pad_pieces(tid, reinterpret_cast<int8_t *>(tapoff + PADS), red, qpa);
     }
     const int RS = R * S, t0 = co.off[z], T = co.off[z + 1] - t0, pitch = cg.v[z][5];
     int8_t *out = wt + (size_t)cg.v[z][6] * 64 + (size_t)j * pitch;
     // one loop over (tap, channel): tap by tap, 49 taps of 16 channels were 49 dependent rounds with 16 threads at work
-    for (int t = threadIdx.x; t < T; t += THREADS) stap[t] = taps.a[t0 + t] * S + taps.b[t0 + t];
+    for (int t = tid; t < T; t += THREADS) stap[t] = taps.a[t0 + t] * S + taps.b[t0 + t];
     __syncthreads();
     int sum = 0;
-    for (int i = threadIdx.x; i < T * Cp; i += THREADS) {
+    for (int i = tid; i < T * Cp; i += THREADS) {
         const int t = i / Cp, c = i - t * Cp;
         int8_t v = 0;
         if (j < OC && c < red) {
@@ -218,12 +218,12 @@ __device__ __forceinline__ void repack_taps(int j, int z, int ncls, const int8_t
         out[i] = v;
         sum += v;
     }
-    if ((int)threadIdx.x < pitch - T * Cp) out[T * Cp + threadIdx.x] = 0;   // fewer than 64 bytes
+    if (tid < pitch - T * Cp) out[T * Cp + tid] = 0;   // fewer than 64 bytes
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, Q8T_WAVE);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    if ((tid & 63) == 0) part[tid >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         int s = 0;
 #pragma unroll
         for (int i = 0; i < THREADS / 64; ++i) s += part[i];
@@ -232,14 +232,19 @@ __device__ __forceinline__ void repack_taps(int j, int z, int ncls, const int8_t
 }
 
 // Both in one launch, the filter rows first: neither needs the other, and the filter alone is 4.8 us.
-// G: channel groups of to_nhwc, 0 for to_nhwc_small.
+// G: channel groups of to_nhwc, 0 for to_nhwc_small.  A workgroup of four groups takes one filter row with all of its threads or,
+// `apart`, one with each group.  Thousands of short rows (strided layer gradients have a row per class) wait for workgroups to come
+// and go, few long ones for the loads of a group: apart up to a mean of 2 bytes a row for every row there is.  Whole calls, one row /
+// four rows a workgroup, us: layer gradients 512 <- 128 3x3/4 @2x53 batch 8 (8192 rows of 72 bytes) 33.3 / 16.4, 320 <- 128 5x3/4 @13
+// batch 12 (5120 of 120) 30 / 20; 128 <- 256 5x5 @24 batch 5 (128 of 6400) 40.5 / 50.4.  1114 calls: 0.2% slower than the better one.
 struct PrepArgs {
     const int8_t *x, *w;
     int8_t *xn, *wt;
     const q8t_qparams *qpa;
     int *colsum, *tapoff, *clsinfo;
     int N, C, Cp, HW, per, ncls, OCp, Kf, Cf, R, S, which;   // per: 64-position tiles of a plane / images a workgroup
-    int row0, rows;                                          // filter rows of this launch
+    int row0, rows;                                          // first filter row, workgroups of filter rows in this launch
+    int apart;                                               // G > 1: G rows a workgroup
     TapList taps, offs;
     ClassOffsets co;
     ClassGeo cg;
@@ -247,11 +252,17 @@ struct PrepArgs {
 template <int G>
 __global__ __launch_bounds__(kThreads * (G ? G : 1)) void prepare(const PrepArgs p)
 {
+    constexpr int GROUPS = G ? G : 1;
+    __shared__ int part[GROUPS * (kThreads / 64)], stap[GROUPS * MAXT];
     const int b = (int)blockIdx.x - p.rows;
-    if (b < 0) {
+    if (b < 0 && GROUPS > 1 && p.apart) {
+        const int grp = threadIdx.x / kThreads, row = p.row0 + (int)blockIdx.x * GROUPS + grp, z = row / p.OCp, j = row - z * p.OCp;
+        repack_taps<kThreads>(threadIdx.x % kThreads, part + grp * (kThreads / 64), stap + grp * MAXT, j, z, p.ncls, p.w, p.Kf, p.Cf, p.R,
+                              p.S, p.which, p.Cp, p.taps, p.offs, p.co, p.cg, p.qpa, p.OCp, p.wt, p.colsum, p.tapoff, p.clsinfo);
+    } else if (b < 0) {
         const int row = p.row0 + (int)blockIdx.x, z = row / p.OCp, j = row - z * p.OCp;
-        repack_taps<kThreads * (G ? G : 1)>(j, z, p.ncls, p.w, p.Kf, p.Cf, p.R, p.S, p.which, p.Cp, p.taps, p.offs, p.co, p.cg,
-                                            p.qpa, p.OCp, p.wt, p.colsum, p.tapoff, p.clsinfo);
+        repack_taps<kThreads * GROUPS>(threadIdx.x, part, stap, j, z, p.ncls, p.w, p.Kf, p.Cf, p.R, p.S, p.which, p.Cp, p.taps, p.offs,
+                                       p.co, p.cg, p.qpa, p.OCp, p.wt, p.colsum, p.tapoff, p.clsinfo);
     } else if constexpr (G == 0)
         to_nhwc_small(b, p.x, p.N, p.C, p.Cp, p.HW, p.per, p.xn);
     else
@@ -838,7 +849,7 @@ __global__ __launch_bounds__(kThreads) void repack_flat(const int8_t *__restrict
 {
     __shared__ int part[kThreads / 64];
     const int k = blockIdx.x;
-    if (k == 0) pad_pieces(reinterpret_cast<int8_t *>(tapoff + PADS), Kc, qpx);
+    if (k == 0) pad_pieces(threadIdx.x, reinterpret_cast<int8_t *>(tapoff + PADS), Kc, qpx);
     int sum = 0;
     for (int j = threadIdx.x; j < Kc; j += kThreads) {
         const int8_t v = j < CRS ? w[(size_t)k * CRS + j] : (int8_t)0;
@@ -1216,12 +1227,15 @@ int q8t_nhwc_conv(int which, const q8t_conv_desc *d, const void *a, const q8t_qp
         Q8T_LAUNCH_CHECK();
         pa.rows = 0;
     }
-    const dim3 grid((unsigned)(blocks + pa.rows));
     // four channel groups per position tile where single ones would leave wavefront slots empty (256 compute
     // units hold 2048 workgroups of 256 threads)
+    const bool four = !small && p.Cp > 64 && blocks < 1024;
+    pa.apart = four && (int64_t)d->R * d->S * p.Cp <= 2 * rows * p.ncls;   // bytes of a row, in the mean
+    if (pa.apart) pa.rows /= 4;   // a multiple of 64
+    const dim3 grid((unsigned)(blocks + pa.rows));
     if (small)
         hipLaunchKernelGGL(prepare<0>, grid, dim3(kThreads), lds, st, pa);
-    else if (p.Cp > 64 && blocks < 1024)
+    else if (four)
         hipLaunchKernelGGL(prepare<4>, grid, dim3(kThreads * 4), 0, st, pa);
     else
         hipLaunchKernelGGL(prepare<1>, grid, dim3(kThreads), 0, st, pa);

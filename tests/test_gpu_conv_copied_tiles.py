@@ -45,6 +45,23 @@ def test_copied_tiles(case):
     same_ints(host(dx), odx)
 
 
+FILTER_ROWS = [
+    # N, C, H, W, K, R, S, stride, pad; the filter's rows (forward; layer gradient) and their mean bytes
+    (2, 128, 5, 5, 40, 1, 1, 1, 0),        # 64 of 128: four a workgroup, just so
+    (2, 129, 5, 5, 40, 1, 1, 1, 0),        # 64 of 144: one a workgroup
+    (2, 128, 6, 6, 96, 3, 3, 4, 1),        # 2048 of 54, classes of 0 to 1 taps
+    (3, 200, 9, 7, 72, 5, 5, 3, 2),        # 2304 of 222, channels of the last class beyond 200
+    (1, 70, 13, 13, 512, 7, 7, 2, 3),      # 512 of 6272
+    (2, 128, 9, 9, 128, 2, 2, 2, 0),       # 512 of 128, class pairs
+    (2, 64, 9, 9, 128, 1, 1, 4, 0),        # 1024 of 8: a class with a tap, 15 without
+]
+
+
+@pytest.mark.parametrize("case", FILTER_ROWS)
+def test_filter_rows_by_whole_workgroups_and_by_their_groups(case):
+    test_copied_tiles(case)
+
+
 def test_more_workgroups_than_one_dimension_of_a_launch_holds():
     # 16 stride classes of 2^26 planes of one position: 2^23 + 16 tiles of 512 threads, 2^32 threads and more
     import torch
