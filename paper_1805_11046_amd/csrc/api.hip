@@ -38,9 +38,9 @@ bool wgrad_wants_gemm(const q8t_conv_desc *d) { return q8t_gemm_wgrad_supported(
 // a filter row to eight taps, im2col rows pad nothing but multiply the operand.  Measured, us a call, general / channel-contiguous / first-layer form:
 //   472 -> 1 7x7 @7x4 batch 5   46 / 202 / -       16 -> 64 3x3 @32 batch 128 54 / 24 / -       4 -> 32 3x3 @27 batch 64 12.5 / 17.2 / -
 //   32 -> 512 1x1 @27 batch 64 65 / 59 / 104       3 -> 64 7x7/2 @27 batch 64 21 / 29 / 14       3 -> 64 1x1 @7 batch 56 8 / 14 / 12
-// Over 8340 calls (channels 1 .. 600, filters up to 7x7, strides 1 .. 3, planes 1 .. 224, batches 1 .. 65536) the form taken is 2.5%
-// (forward; with statistics 0.6, layer gradient 0.5) slower than the best of the four in the mean, and 1.9 times at most.  Under 1x1
-// filters im2col rows are only a second copy: 32 -> 512 @27 batch 64 63 us, 59 without.
+// Over 23000 calls (channels 1 .. 600, in half of them at most 24 to reduce; filters up to 7x7, strides 1 .. 4, planes 1 .. 160, batches
+// 1 .. 65536) the form taken is 0.9% (forward; with statistics 0.6, layer gradient 0.9) slower than the best of the four in the mean,
+// more than 15% in 1.5 / 0.9 / 2.0 of a hundred.  Under 1x1 filters im2col rows are only a second copy: 32 -> 512 @27 batch 64 63 us, 59 without.
 enum Form { FIRST, NHWC, SMALLC, GENERAL };
 Form conv_form(int which, const q8t_conv_desc *d, bool stats)
 {

@@ -1070,8 +1070,9 @@ size_t q8t_nhwc_conv_ws(int which, const q8t_conv_desc *d)
 
 // As q8t_generic_conv_us, for the product here (the shape is supported): two launches, the copy, the filter, then the longest
 // class's K-steps (two classes one after the other where a workgroup has both), the first round of them at the price of its latency.
-// Isolated results of strides beyond 2 cost their lines several times; under 1x1 filters those of narrow or odd rows cost a
-// workgroup's end more.  0.8 .. 1.2 in 90% of the 8340 calls it was checked on.
+// Isolated results (strides beyond 2; stride 2 on rows of odd length, which have no pairs) cost their lines several times, the more the
+// shorter the rows are (256 <- 7 1x1/2 @5 batch 3510 7 us a million, @160 2.5); under 1x1 filters those of narrow or odd rows cost a
+// workgroup's end more.  Fitted to half of 20000 layer gradients with a stride, 0.75 .. 1.3 in 90% of the others.
 double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats)
 {
     Plan p;
@@ -1084,8 +1085,9 @@ double q8t_nhwc_conv_us(int which, const q8t_conv_desc *d, bool stats)
     const int bn = wide_tiles(M, launched, p.OCp) ? 128 : 64;
     const double t = (double)(((M + 127) / 128 * launched * (p.OCp / bn) + 255) / 256) * (bn == 128 ? 1.6 : 1.0), results = 1e-6 * opos * p.oc;
     const int steps = (((d->R + st - 1) / st) * (pair ? d->S : (d->S + st - 1) / st) * p.Cp + 63) / 64;
+    const double scatter = st > 2 ? 4.1 : (d->W % 2 ? 2.4 : 0.7) + (taps > 3 ? 0.6 : 0.0), line = st > 2 ? 7.6 : (d->W % 2 ? 11.4 : 7.1);
     double us = 8.2 + 0.28 * steps + 0.16 * steps * (t - 1.0) + 0.75 * t + 0.65e-6 * d->N * p.IH * p.IW * p.Cp +
-                4.7e-6 * taps * p.OCp * p.Cp + (st > 2 ? 4.1 : (st == 2 && taps > 3 ? 1.6 : 1.1)) * results;
+                4.7e-6 * taps * p.OCp * p.Cp + (st == 1 ? 1.1 : scatter + line / (d->W + 2)) * results;
     if (st > 1 && taps == 1 && Q > 1 && results >= 0.05 && (Q % 4 || (!fill && (d->W % 2 || st > 2)))) us += d->C < 192 ? d->C / 38.0 : 5.0;
     return us + (stats ? 2.9 + 0.54 * results : 0.0);
 }

@@ -533,9 +533,11 @@ size_t q8t_generic_conv_ws(int which, const q8t_conv_desc *d)
 }
 
 // Microseconds that a forward (which = 0) or layer-gradient (1) product takes here, back to back on one MI355X, for the
-// choice between the forms of api.hip: a K-step of a workgroup costs what gathering its operands byte by byte does, 1024
-// workgroups run side by side, slices are written, read and added up behind.  The constants are fitted to the 3700 calls
-// described there; measured over estimated 0.7 .. 1.4 in 95% of 5390 calls, above 1.2 mostly between 1024 and 2048 workgroups.
+// choice between the forms of api.hip: a K-step of a workgroup costs what gathering its operands byte by byte does, a thread up to
+// 16 of them one after the other, so that a step of 1 to 16 elements costs less (4 channels under a 1x1 filter 0.7 of a whole one);
+// 1024 workgroups run side by side, slices are written, read and added up behind.  Fitted to half of 41000 calls (channels 1 .. 600,
+// every second reduction below 25 of them); measured over estimated 0.75 .. 1.45 in 96% of the others, above 1.2 mostly between 1024 and
+// 2048 workgroups.
 double q8t_generic_conv_us(int which, const q8t_conv_desc *d, bool stats)
 {
     ConvGeom g;
@@ -544,10 +546,15 @@ double q8t_generic_conv_us(int which, const q8t_conv_desc *d, bool stats)
     const int64_t red = (int64_t)(which == 0 ? g.C : g.K) * g.R * g.S;
     const Plan p = plan_for(rows, cols, red);
     if ((cols + BN - 1) / BN > 65535 || p.splits > 65535) return 1e30;   // refused here
-    const double steps = (double)(((red < p.slice_k ? red : p.slice_k) + BK - 1) / BK);
+    const int64_t len = red < p.slice_k ? red : p.slice_k;
+    auto step = [&](int64_t k) {
+        const double in_turn = k < 16 ? k / 16.0 : 1.0, beside = k > 16 ? (k - 16) / 48.0 : 0.0;
+        return which == 0 ? 2.8 + 2.0 * in_turn + 0.2 * beside : 3.2 + 3.2 * in_turn + 0.5 * beside;
+    };
+    const double steps = (double)(len / BK) * step(BK) + (len % BK ? step(len % BK) : 0.0);
     const double wgs = (double)((rows + BM - 1) / BM) * (double)((cols + BN - 1) / BN) * p.splits, results = 1e-6 * rows * cols;
-    double us = 3.0 + (which == 0 ? 5.4 : 7.7) * steps * (wgs > 1024 ? wgs / 1024 : 1.0) + 1.4 * results;
-    if (p.splits > 1) us += p.splits * (0.23 + 5.7 * results);
+    double us = 3.5 + steps * (wgs > 1024 ? wgs / 1024 : 1.0) + 2.2 * results;
+    if (p.splits > 1) us += p.splits * (0.23 + 7.4 * results);
     return us + (stats ? q8t_range_bn_stats_us(g.N, g.K, (int64_t)g.P * g.Q) : 0.0);
 }
 

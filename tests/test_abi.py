@@ -3,6 +3,8 @@ import ctypes
 import os
 import re
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -125,6 +127,14 @@ def test_form_of_a_product_follows_its_size():
     assert 0 < size(64, 3, 27, 27, 64, 7, 7, 2, 3) - 64 * 27 * 27 * 16 < 1 << 17   # 13.0 us; first-layer kernel 14.7
     assert 64 * 64 <= size(128, 1, 56, 56, 64, 5, 5, 1, 2) < 1 << 16          # first-layer kernel (28 us; copy 56): the packed filter
     assert 0 < size(256, 3, 28, 28, 512, 7, 7, 2, 3) - 256 * 14 * 14 * 192 < 1 << 18   # im2col rows: 147 columns filled up to 192
+
+
+@pytest.mark.parametrize("case", [(6, 496, 27, 4, 4, 1, 1, 4, 0), (111, 42, 17, 17, 3, 1, 1, 2, 0),    # 8.6 us, copied 14.1; 9.9, 15.8
+                                  (367, 56, 9, 9, 4, 2, 2, 2, 1), (3510, 256, 5, 5, 7, 1, 1, 2, 0)])   # 13.3, 21.4; 64, 157
+def test_layer_gradients_of_few_channels_to_scattered_results_need_no_copy(case):
+    _lib_path()
+    from paper_1805_11046_amd import binding
+    assert binding.qconv_workspace_size(binding.conv_desc(*case), 1) == 0     # general kernel
 
 
 def test_weight_gradient_of_a_filter_as_large_as_the_plane_lays_out_no_padding():
